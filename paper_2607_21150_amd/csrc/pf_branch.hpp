@@ -2,7 +2,7 @@
 // branches of a phase add their degraded Kirchhoff stresses to the block's and their
 // psi^+ to its psi^+, and the history switch and the local phase-field residual are
 // taken from the total (eq:history-field-linearization, eq:L-viscous). Each branch
-// has its own state Cin^-1 (so its own principal frame) and its own Amor split; a
+// has its own state Cin^-1 (so its own trial strain) and its own Amor split; a
 // Maxwell branch relaxes with the degraded modulus (eq:principal-directions-format-1).
 // The FP64 operator kernels call these helpers after the block's own point state.
 #pragma once
@@ -30,9 +30,9 @@ struct Slot9 {
 // Point state of extra branch j of the phase (Box 1 steps 1-3 with the branch's
 // material); a Hooke branch reads no state (Cin^-1 = I), and neither does a lane
 // without a point (valid = false: gq may lie past the state arrays).
-template <bool VOCE>
+template <bool TAN, bool VOCE>
 __device__ inline void xbranch_state(const OpArgs& a, const XBranch& b, int j, int64_t gq, bool valid,
-                                     const double* G, double phi, QPState<double>& s) {
+                                     const double* G, double phi, TState& s) {
   double st[8];
   if (b.kind == XB_HOOKE || !valid) {
 #pragma unroll
@@ -42,7 +42,7 @@ __device__ inline void xbranch_state(const OpArgs& a, const XBranch& b, int j, i
     for (int k = 0; k < 7; ++k) st[k] = a.xstate[(int64_t)(7 * j + k) * a.n_q + gq];
     st[7] = 0.0;
   }
-  qp_state<double, VOCE, true>(b.m, a.fr, G, phi, phi, st, s);
+  ts_state<TAN, VOCE, true>(b.m, a.fr, G, phi, phi, st, s);
 }
 
 // History field and the local phase-field residual and its phi-derivative at fixed
@@ -68,13 +68,13 @@ __device__ inline double mb_residual(const OpArgs& a, const MatParams<double>& m
   for (int j = 0; j < a.n_extra; ++j) {
     const XBranch& b = a.xb[pid * a.n_extra + j];
     if (b.kind == XB_NONE) continue;
-    QPState<double> s;
+    TState s;
     double G[9];
     sG.get(G);
-    xbranch_state<VOCE>(a, b, j, gq, valid, G, phi, s);
+    xbranch_state<false, VOCE>(a, b, j, gq, valid, G, phi, s);
     bad |= s.bad;
     double Pj[9];
-    piola<double>(s, Pj);
+    ts_piola(b.m, s, Pj);
 #pragma unroll
     for (int k = 0; k < 9; ++k) P[k] += Pj[k];
     psi += s.psi;
@@ -88,27 +88,27 @@ __device__ inline double mb_residual(const OpArgs& a, const MatParams<double>& m
 // Jacobian action: dP = sum of the branches' dP, dL = dLcoef dphi + g' dH with
 // dH = sum of the branches' dpsi^+ when the total switch is on. Returns dL.
 template <bool VOCE>
-__device__ inline double mb_jacobian(const OpArgs& a, const MatParams<double>& m0, const QPState<double>& s0,
+__device__ inline double mb_jacobian(const OpArgs& a, const MatParams<double>& m0, const TState& s0,
                                      int pid, int64_t gq, bool valid, Slot9 sG, double phi, double phin,
                                      double Hn, const double* W, Slot9 sW, double wphi, double* dP, bool& bad) {
   double dpsi;
-  qp_tangent_psi<double>(m0, s0, W, wphi, dP, dpsi);
+  ts_tangent_psi(m0, s0, W, wphi, dP, dpsi);
   double psi = s0.psi;
   const double gp = s0.gp;
 #pragma unroll 1
   for (int j = 0; j < a.n_extra; ++j) {
     const XBranch& b = a.xb[pid * a.n_extra + j];
     if (b.kind == XB_NONE) continue;
-    QPState<double> s;
+    TState s;
     {
       double G[9];
       sG.get(G);
-      xbranch_state<VOCE>(a, b, j, gq, valid, G, phi, s);
+      xbranch_state<true, VOCE>(a, b, j, gq, valid, G, phi, s);
     }
     bad |= s.bad;
     double dPj[9], dpj, Wj[9];
     sW.get(Wj);
-    qp_tangent_psi<double>(b.m, s, Wj, wphi, dPj, dpj);
+    ts_tangent_psi(b.m, s, Wj, wphi, dPj, dpj);
 #pragma unroll
     for (int k = 0; k < 9; ++k) dP[k] += dPj[k];
     dpsi += dpj;
@@ -130,10 +130,10 @@ __device__ inline double mb_psi_extra(const OpArgs& a, int pid, int64_t gq, bool
   for (int j = 0; j < a.n_extra; ++j) {
     const XBranch& b = a.xb[pid * a.n_extra + j];
     if (b.kind == XB_NONE) continue;
-    QPState<double> s;
+    TState s;
     double G[9];
     sG.get(G);
-    xbranch_state<VOCE>(a, b, j, gq, valid, G, phi, s);
+    xbranch_state<false, VOCE>(a, b, j, gq, valid, G, phi, s);
     bad |= s.bad;
     psi += s.psi;
   }
@@ -143,14 +143,14 @@ __device__ inline double mb_psi_extra(const OpArgs& a, int pid, int64_t gq, bool
 // Adjoint, block part: Gb and phib of the block with the total switch; returns the
 // psi^+ cotangent Hb (g' Lb when the switch is on, else 0) for the extra branches and
 // the parameter partials.
-__device__ inline double mb_adjoint_block(const OpArgs& a, const MatParams<double>& m0, const QPState<double>& s0,
+__device__ inline double mb_adjoint_block(const OpArgs& a, const MatParams<double>& m0, const TState& s0,
                                           double psi_x, double phi, double phin, double Hn, const double* Pb,
-                                          double Lb, double* Gb, double& phib, double* Xd) {
+                                          double Lb, double* Gb, double& phib, double& xe) {
   bool hact;
   double L, dLcoef;
   mb_fracture(a, m0, phi, phin, Hn, s0.psi + psi_x, s0.gp, hact, L, dLcoef);
   const double Hb = hact ? s0.gp * Lb : 0.0;
-  qp_tangent_T_psi<double>(m0, s0, Pb, Hb, dLcoef * Lb, Gb, phib, Xd);
+  ts_tangent_T_psi(m0, s0, Pb, Hb, dLcoef * Lb, Gb, phib, xe);
   return Hb;
 }
 
@@ -162,15 +162,15 @@ __device__ inline void mb_adjoint_extra(const OpArgs& a, int pid, int64_t gq, bo
   for (int j = 0; j < a.n_extra; ++j) {
     const XBranch& b = a.xb[pid * a.n_extra + j];
     if (b.kind == XB_NONE) continue;
-    QPState<double> s;
+    TState s;
     {
       double G[9];
       sG.get(G);
-      xbranch_state<VOCE>(a, b, j, gq, valid, G, phi, s);
+      xbranch_state<true, VOCE>(a, b, j, gq, valid, G, phi, s);
     }
-    double Gj[9], pj, Xj[3], Pb[9];
+    double Gj[9], pj, xj, Pb[9];
     sPb.get(Pb);
-    qp_tangent_T_psi<double>(b.m, s, Pb, Hb, 0.0, Gj, pj, Xj);
+    ts_tangent_T_psi(b.m, s, Pb, Hb, 0.0, Gj, pj, xj);
 #pragma unroll
     for (int k = 0; k < 9; ++k) Gb[k] += Gj[k];
     phib += pj;

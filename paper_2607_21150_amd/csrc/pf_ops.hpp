@@ -1,7 +1,7 @@
 // FP64 operator kernels: residual, Jacobian action and adjoint (device side).
 #pragma once
 #include "pf_brick.hpp"
-#include "pf_qf.hpp"
+#include "pf_tensor.hpp"
 
 namespace pfmf {
 
@@ -181,13 +181,13 @@ __global__ __launch_bounds__(NT, P >= 5 ? 1 : 2) void k_op64(OpArgs a, int colou
       const int pid = a.phase[gq];
       bad_pid |= pid >= a.nph;  // an id outside the phase table raises the phase flag
       const MatParams<double> mp = a.mats[pid < a.nph ? pid : 0];
-      QPState<double> s;
-      qp_state<double>(mp, a.fr, G, phi, phin, st, s);
+      TState s;
+      ts_state<MODE != M_RES, true>(mp, a.fr, G, phi, phin, st, s);
       any_bad |= s.bad;
       const double wdet = wq[qx] * wq[qy] * wq[qz] * jdet;
       const double kfg = a.fr.kf * mp.Gc;
       if (MODE == M_RES) {
-        piola<double>(s, Fu);
+        ts_piola(mp, s, Fu);
         f0 = a.fr.s_phi * s.L;
 #pragma unroll
         for (int J = 0; J < 3; ++J) f1[J] = kfg * gphi[J];
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(NT, P >= 5 ? 1 : 2) void k_op64(OpArgs a, int colou
         for (int J = 0; J < 3; ++J) f1[J] *= wdet;
       } else if (MODE == M_JAC) {
         double dL;
-        qp_tangent<double>(mp, s, W, wphi, Fu, dL);
+        ts_tangent(mp, s, W, wphi, Fu, dL);
 #pragma unroll
         for (int k = 0; k < 9; ++k) Fu[k] *= wdet;
         f0 = wdet * a.fr.s_phi * dL;
@@ -211,8 +211,8 @@ __global__ __launch_bounds__(NT, P >= 5 ? 1 : 2) void k_op64(OpArgs a, int colou
         for (int k = 0; k < 9; ++k) Pb[k] = wdet * W[k];
         const double f0b = wdet * wphi;
         const double Lb = a.fr.s_phi * f0b;
-        double phib, Xd[3];
-        qp_tangent_T<double>(mp, s, Pb, Lb, Fu, phib, Xd);
+        double phib, xe;
+        ts_tangent_T(mp, s, Pb, Lb, Fu, phib, xe);
         f0 = phib;
 #pragma unroll
         for (int J = 0; J < 3; ++J) f1[J] = kfg * wdet * gwphi[J];
@@ -222,12 +222,10 @@ __global__ __launch_bounds__(NT, P >= 5 ? 1 : 2) void k_op64(OpArgs a, int colou
                                 a.fr.kf / a.fr.s_phi * (gphi[0] * wdet * gwphi[0] + gphi[1] * wdet * gwphi[1] +
                                                         gphi[2] * wdet * gwphi[2]));
         if (s.plastic) {
-          const double ee = s.e[0] * s.e[0] + s.e[1] * s.e[1] + s.e[2] * s.e[2];
-          const double q = 2.0 * mp.mu * sqrt(1.5 * ee);
+          const double q = 2.0 * mp.mu * sqrt(1.5 * s.ee);
           const double w3q = 3.0 * mp.mu / q;
-          const double xe = Xd[0] * s.e[0] + Xd[1] * s.e[1] + Xd[2] * s.e[2];
           // d(c e)_i = -w3q ddg e_i ; d tau^d_i = g 2 mu d(ce)_i ; dH = 2 mu c e.d(ce)
-          const double base = s.g * 2.0 * mp.mu * xe + (s.hactive ? Lb * s.gp * 2.0 * mp.mu * s.c * ee : 0.0);
+          const double base = s.g * 2.0 * mp.mu * xe + (s.hactive ? Lb * s.gp * 2.0 * mp.mu * s.c * s.ee : 0.0);
           gsum[1] = -w3q * s.ddg_s0 * base;
           gsum[2] = -w3q * s.ddg_visc * base;
         } else {

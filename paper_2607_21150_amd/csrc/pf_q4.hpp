@@ -24,7 +24,7 @@
 #include "pf_ops.hpp"
 #include "pf_branch.hpp"
 #include "pf_geom.hpp"
-#include "pf_qf.hpp"
+#include "pf_tensor.hpp"
 #include "pf_mfma.hpp"
 
 namespace pfmf {
@@ -488,8 +488,8 @@ __global__ __launch_bounds__(NT5, 2) void k_op64_q4(OpArgs a, int colour, DevTab
   double psi_x = 0.0;
   if (MB) sG.put(G);
   if (MB && MODE == M_ADJ) psi_x = mb_psi_extra<VOCE>(a, pidc, gq, pt, sG, phi, xbad);
-  QPState<double> s;
-  qp_state<double, VOCE>(mp, a.fr, G, phi, phin, st, s);
+  TState s;
+  ts_state<MODE != M_RES, VOCE>(mp, a.fr, G, phi, phin, st, s);
   bool bad = pt && s.bad;
   const bool bad_pid = pt && pid >= a.nph;  // an id outside the phase table raises the phase flag
   double W[9], wphi = 0.0, gw[3] = {0.0, 0.0, 0.0};
@@ -509,7 +509,7 @@ __global__ __launch_bounds__(NT5, 2) void k_op64_q4(OpArgs a, int colour, DevTab
   double Fu[9], f0, f1[3];
   double gsum[3] = {0.0, 0.0, 0.0};
   if (MODE == M_RES) {
-    piola<double>(s, Fu);
+    ts_piola(mp, s, Fu);
     double Lr = s.L;
     if (MB) Lr = mb_residual<VOCE>(a, mp, pidc, gq, pt, sG, phi, phin, st[7], s.psi, s.gp, Fu, xbad);
 #pragma unroll
@@ -523,7 +523,7 @@ __global__ __launch_bounds__(NT5, 2) void k_op64_q4(OpArgs a, int colour, DevTab
       sW.put(W);
       dL = mb_jacobian<VOCE>(a, mp, s, pidc, gq, pt, sG, phi, phi, st[7], W, sW, wphi, Fu, xbad);
     } else
-      qp_tangent<double>(mp, s, W, wphi, Fu, dL);
+      ts_tangent(mp, s, W, wphi, Fu, dL);
 #pragma unroll
     for (int k = 0; k < 9; ++k) Fu[k] *= wdet;
     f0 = wdet * a.fr.s_phi * dL;
@@ -535,21 +535,19 @@ __global__ __launch_bounds__(NT5, 2) void k_op64_q4(OpArgs a, int colour, DevTab
     for (int k = 0; k < 9; ++k) Pb[k] = wdet * W[k];
     const double f0b = wdet * wphi;
     const double Lb = a.fr.s_phi * f0b;
-    double phib, Xd[3], Hb = 0.0;
+    double phib, xe, Hb = 0.0;
     if (MB)
-      Hb = mb_adjoint_block(a, mp, s, psi_x, phi, phi, st[7], Pb, Lb, Fu, phib, Xd);
+      Hb = mb_adjoint_block(a, mp, s, psi_x, phi, phi, st[7], Pb, Lb, Fu, phib, xe);
     else
-      qp_tangent_T<double>(mp, s, Pb, Lb, Fu, phib, Xd);
+      ts_tangent_T(mp, s, Pb, Lb, Fu, phib, xe);
 #pragma unroll
     for (int J = 0; J < 3; ++J) f1[J] = kfg * wdet * gw[J];
     const double alpha_p = (a.fr.at == 2) ? 2.0 * phi : 1.0;
     gsum[0] = alpha_p * a.fr.inv_c0l0 * Lb + a.fr.kf * wdet * (gphi[0] * gw[0] + gphi[1] * gw[1] + gphi[2] * gw[2]);
     if (s.plastic) {
-      const double ee = s.e[0] * s.e[0] + s.e[1] * s.e[1] + s.e[2] * s.e[2];
-      const double q = 2.0 * mp.mu * sqrt(1.5 * ee);
+      const double q = 2.0 * mp.mu * sqrt(1.5 * s.ee);
       const double w3q = 3.0 * mp.mu / q;
-      const double xe = Xd[0] * s.e[0] + Xd[1] * s.e[1] + Xd[2] * s.e[2];
-      const double hterm = MB ? Hb * 2.0 * mp.mu * s.c * ee : (s.hactive ? Lb * s.gp * 2.0 * mp.mu * s.c * ee : 0.0);
+      const double hterm = MB ? Hb * 2.0 * mp.mu * s.c * s.ee : (s.hactive ? Lb * s.gp * 2.0 * mp.mu * s.c * s.ee : 0.0);
       const double base = s.g * 2.0 * mp.mu * xe + hterm;
       gsum[1] = -w3q * s.ddg_s0 * base;
       gsum[2] = -w3q * s.ddg_visc * base;
@@ -882,8 +880,8 @@ __global__ __launch_bounds__(NT, 2) void k_op64_q2r(OpArgs a, DevTables* __restr
   const bool bad_pid = pt && pid >= a.nph;  // an id outside the phase table raises the phase flag
   const int pidc = pid < a.nph ? pid : 0;
   const MatParams<double> mp = a.mats[pidc];
-  QPState<double> s;
-  qp_state<double, VOCE>(mp, a.fr, G, phi, phin, st, s);
+  TState s;
+  ts_state<MODE != M_RES, VOCE>(mp, a.fr, G, phi, phin, st, s);
   const bool bad = pt && s.bad;
   double W[9], wphi = 0.0, gw[3] = {0.0, 0.0, 0.0};
   if (MODE != M_RES) {
@@ -907,7 +905,7 @@ __global__ __launch_bounds__(NT, 2) void k_op64_q2r(OpArgs a, DevTables* __restr
   double Fu[9], f0, f1[3];
   double gsum[3] = {0.0, 0.0, 0.0};
   if (MODE == M_RES) {
-    piola<double>(s, Fu);
+    ts_piola(mp, s, Fu);
 #pragma unroll
     for (int k = 0; k < 9; ++k) Fu[k] *= wdet;
     f0 = wdet * a.fr.s_phi * s.L;
@@ -915,7 +913,7 @@ __global__ __launch_bounds__(NT, 2) void k_op64_q2r(OpArgs a, DevTables* __restr
     for (int J = 0; J < 3; ++J) f1[J] = wdet * kfg * gphi[J];
   } else if (MODE == M_JAC) {
     double dL;
-    qp_tangent<double>(mp, s, W, wphi, Fu, dL);
+    ts_tangent(mp, s, W, wphi, Fu, dL);
 #pragma unroll
     for (int k = 0; k < 9; ++k) Fu[k] *= wdet;
     f0 = wdet * a.fr.s_phi * dL;
@@ -927,18 +925,16 @@ __global__ __launch_bounds__(NT, 2) void k_op64_q2r(OpArgs a, DevTables* __restr
     for (int k = 0; k < 9; ++k) Pb[k] = wdet * W[k];
     const double f0b = wdet * wphi;
     const double Lb = a.fr.s_phi * f0b;
-    double phib, Xd[3];
-    qp_tangent_T<double>(mp, s, Pb, Lb, Fu, phib, Xd);
+    double phib, xe;
+    ts_tangent_T(mp, s, Pb, Lb, Fu, phib, xe);
 #pragma unroll
     for (int J = 0; J < 3; ++J) f1[J] = kfg * wdet * gw[J];
     const double alpha_p = (a.fr.at == 2) ? 2.0 * phi : 1.0;
     gsum[0] = alpha_p * a.fr.inv_c0l0 * Lb + a.fr.kf * wdet * (gphi[0] * gw[0] + gphi[1] * gw[1] + gphi[2] * gw[2]);
     if (s.plastic) {
-      const double ee = s.e[0] * s.e[0] + s.e[1] * s.e[1] + s.e[2] * s.e[2];
-      const double qv = 2.0 * mp.mu * sqrt(1.5 * ee);
+      const double qv = 2.0 * mp.mu * sqrt(1.5 * s.ee);
       const double w3q = 3.0 * mp.mu / qv;
-      const double xe = Xd[0] * s.e[0] + Xd[1] * s.e[1] + Xd[2] * s.e[2];
-      const double hterm = s.hactive ? Lb * s.gp * 2.0 * mp.mu * s.c * ee : 0.0;
+      const double hterm = s.hactive ? Lb * s.gp * 2.0 * mp.mu * s.c * s.ee : 0.0;
       const double base = s.g * 2.0 * mp.mu * xe + hterm;
       gsum[1] = -w3q * s.ddg_s0 * base;
       gsum[2] = -w3q * s.ddg_visc * base;

@@ -296,19 +296,14 @@ __device__ inline T log_divdiff(T beta_i, T beta_j, T eps_i, T eps_j, T ib_j) {
 // Everything the tangent needs at one point (residual pass output).
 template <typename T> struct QPState {
   T Fi[9];      // F^-1
-  T b[6];       // b_tr = I + A
   T N[9];       // eigenvectors of b_tr (columns)
   T bd[3];      // principal values b_i of b_tr
-  T hinv[3];    // 1 / (2 b_i)
   T e[3];       // deviatoric principal trial log strain
   T theta;      // tr eps
   T g, gp;      // degradation and its derivative
   T c;          // radial-return factor
   T kq, kphi;   // plastic tangent: d(c e)_i = c de_i + e_i (kq e.de + kphi dphi)
-  T taub[3];    // block principal Kirchhoff stress (undegraded)
-  T taud[3];    // degraded principal Kirchhoff stress
   T coef[3];    // off-diagonal tangent factors for pairs (1,2), (0,2), (0,1)
-  T tau[6];     // degraded Kirchhoff stress tau_degr
   T psi, H, L;  // psi^+, max(H_n, psi^+), local phase-field residual
   T dLcoef;     // dL / dphi at fixed history
   T ddg_s0, ddg_visc;  // d dgamma / d sigma0, d dgamma / d visc (0 when elastic)
@@ -316,32 +311,34 @@ template <typename T> struct QPState {
   bool tension, hactive, plastic, bad;
 };
 
-// Kinematics at one point (Box 1 step 1, Appendix A): F^-1, b_tr, principal frame,
-// principal log strains. G: grad_X u (row-major), st: D[6] (Voigt).
-// Returns beta_i and eps_i for the divided differences.
+// Inverse (by cofactors) and determinant of a row-major 3x3.
 template <typename T>
-__device__ inline void qp_kin(const T* G, const T* st, QPState<T>& s, T* beta, T* eps) {
-  // F = I + G and its inverse
-  T F[9];
-#pragma unroll
-  for (int k = 0; k < 9; ++k) F[k] = G[k] + ((k % 4 == 0) ? T(1) : T(0));
+__device__ inline T inverse33(const T* F, T* Fi) {
   const T c00 = F[4] * F[8] - F[5] * F[7];
   const T c01 = F[5] * F[6] - F[3] * F[8];
   const T c02 = F[3] * F[7] - F[4] * F[6];
   const T det = F[0] * c00 + F[1] * c01 + F[2] * c02;
   const T idet = frcp(det);
-  s.Fi[0] = c00 * idet;
-  s.Fi[3] = c01 * idet;
-  s.Fi[6] = c02 * idet;
-  s.Fi[1] = (F[2] * F[7] - F[1] * F[8]) * idet;
-  s.Fi[4] = (F[0] * F[8] - F[2] * F[6]) * idet;
-  s.Fi[7] = (F[1] * F[6] - F[0] * F[7]) * idet;
-  s.Fi[2] = (F[1] * F[5] - F[2] * F[4]) * idet;
-  s.Fi[5] = (F[2] * F[3] - F[0] * F[5]) * idet;
-  s.Fi[8] = (F[0] * F[4] - F[1] * F[3]) * idet;
+  Fi[0] = c00 * idet;
+  Fi[3] = c01 * idet;
+  Fi[6] = c02 * idet;
+  Fi[1] = (F[2] * F[7] - F[1] * F[8]) * idet;
+  Fi[4] = (F[0] * F[8] - F[2] * F[6]) * idet;
+  Fi[7] = (F[1] * F[6] - F[0] * F[7]) * idet;
+  Fi[2] = (F[1] * F[5] - F[2] * F[4]) * idet;
+  Fi[5] = (F[2] * F[3] - F[0] * F[5]) * idet;
+  Fi[8] = (F[0] * F[4] - F[1] * F[3]) * idet;
+  return det;
+}
 
-  // A = b_tr - I = G + G^T + G G^T + F D F^T  (eq:inelasticity-be-update, Cin^-1 = I + D)
-  T A[6];
+// F^-1, A = b_tr - I (Voigt) and det F from G = grad_X u (row-major) and D = st[0..5] (Voigt):
+// A = G + G^T + G G^T + F D F^T (eq:inelasticity-be-update, Cin^-1 = I + D).
+template <typename T>
+__device__ inline T kinematics(const T* G, const T* st, T* Fi, T* A) {
+  T F[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) F[k] = G[k] + ((k % 4 == 0) ? T(1) : T(0));
+  const T det = inverse33<T>(F, Fi);
   const int ri[6] = {0, 1, 2, 1, 0, 0}, ci[6] = {0, 1, 2, 2, 2, 1};
   T FD[9];
   {
@@ -361,8 +358,17 @@ __device__ inline void qp_kin(const T* G, const T* st, QPState<T>& s, T* beta, T
 #pragma unroll
     for (int l = 0; l < 3; ++l) v += G[3 * i + l] * G[3 * j + l] + FD[3 * i + l] * F[3 * j + l];
     A[k] = v;
-    s.b[k] = v + ((k < 3) ? T(1) : T(0));
   }
+  return det;
+}
+
+// Kinematics at one point in the principal frame of b_tr (Box 1 step 1, Appendix A): F^-1,
+// principal frame, principal log strains. G: grad_X u (row-major), st: D[6] (Voigt).
+// Returns beta_i and eps_i for the divided differences.
+template <typename T>
+__device__ inline void qp_kin(const T* G, const T* st, QPState<T>& s, T* beta, T* eps) {
+  T A[6];
+  const T det = kinematics<T>(G, st, s.Fi, A);
   // principal values and frame (eq:inelasticity-spectral-decomposition)
   eig_sym3(A, beta, s.N);
   s.bad = !(det > T(0)) || !(beta[0] > T(-1)) || !(beta[1] > T(-1)) || !(beta[2] > T(-1));
@@ -372,7 +378,6 @@ __device__ inline void qp_kin(const T* G, const T* st, QPState<T>& s, T* beta, T
   for (int i = 0; i < 3; ++i) {
     eps[i] = half_log1p(beta[i]);
     s.bd[i] = T(1) + beta[i];
-    s.hinv[i] = T(0.5) * frcp(s.bd[i]);
     s.theta += eps[i];
   }
   const T th3 = s.theta * (T(1) / T(3));
@@ -380,41 +385,29 @@ __device__ inline void qp_kin(const T* G, const T* st, QPState<T>& s, T* beta, T
   for (int i = 0; i < 3; ++i) s.e[i] = eps[i] - th3;
 }
 
-// Degraded Kirchhoff stress in the global frame and the off-diagonal tangent
-// factors g mu c (ln b_i - ln b_j)/(b_i - b_j), from the principal quantities.
+// Off-diagonal tangent factors g mu c (ln b_i - ln b_j)/(b_i - b_j).
 template <typename T>
-__device__ inline void qp_frame_stress(const MatParams<T>& m, const T* beta, const T* eps, QPState<T>& s) {
-  const int ri[6] = {0, 1, 2, 1, 0, 0}, ci[6] = {0, 1, 2, 2, 2, 1};
-  const T* N = s.N;
-#pragma unroll
-  for (int k = 0; k < 6; ++k) {
-    const int i = ri[k], j = ci[k];
-    s.tau[k] = s.taud[0] * N[3 * i] * N[3 * j] + s.taud[1] * N[3 * i + 1] * N[3 * j + 1] +
-               s.taud[2] * N[3 * i + 2] * N[3 * j + 2];
-  }
+__device__ inline void qp_offdiagonal(const MatParams<T>& m, const T* beta, const T* eps, QPState<T>& s) {
   const T gmc = s.g * m.mu * s.c;
-  s.coef[0] = gmc * log_divdiff(beta[1], beta[2], eps[1], eps[2], T(2) * s.hinv[2]);
-  s.coef[1] = gmc * log_divdiff(beta[0], beta[2], eps[0], eps[2], T(2) * s.hinv[2]);
-  s.coef[2] = gmc * log_divdiff(beta[0], beta[1], eps[0], eps[1], T(2) * s.hinv[1]);
+  const T ib1 = frcp(s.bd[1]), ib2 = frcp(s.bd[2]);
+  s.coef[0] = gmc * log_divdiff(beta[1], beta[2], eps[1], eps[2], ib2);
+  s.coef[1] = gmc * log_divdiff(beta[0], beta[2], eps[0], eps[2], ib2);
+  s.coef[2] = gmc * log_divdiff(beta[0], beta[1], eps[0], eps[1], ib1);
 }
 
-// Residual state at one point: steps of Box 1 / Box 2 and Section 3.
-//   G: grad_X u (row-major), phi: phase field at the point, phin: previous phi,
-//   st: D[6] (Voigt), ebar_p, H_n.
+// Degradation, return mapping, split, history and local phase-field residual of a branch
+// (Box 1 / Box 2 and Section 3) from its deviatoric trial strain's square ee = e:e and s.theta.
 //   VOCE = false compiles the linear-hardening return only (kernels launched for
 //   contexts without a Voce phase, so that the iteration widens no register budget);
 //   MAXW = true adds the Maxwell update of a branch with m.am > 0.
-template <typename T, bool VOCE = true, bool MAXW = false>
-__device__ inline void qp_state(const MatParams<T>& m, const FracParams<T>& fr, const T* G, T phi,
-                                T phin, const T* st, QPState<T>& s) {
-  T beta[3], eps[3];
-  qp_kin<T>(G, st, s, beta, eps);
+template <typename T, bool VOCE, bool MAXW, typename State>
+__device__ inline void return_map(const MatParams<T>& m, const FracParams<T>& fr, T phi, T phin, const T* st, T ee,
+                                  State& s) {
   // degradation (eq:degr-funct)
   const T omp = T(1) - phi;
   s.g = omp * omp + fr.eta;
   s.gp = T(-2) * omp;
   // Prandtl branch with the degraded trial stress (Box 2, eq:degraded-yield-condition)
-  const T ee = s.e[0] * s.e[0] + s.e[1] * s.e[1] + s.e[2] * s.e[2];
   const T u15 = T(1.5) * ee;
   const T q = (u15 > T(0)) ? T(2) * m.mu * u15 * frsqrt(u15) : T(0);
   const T sn = VOCE ? yield_stress(m, st[6]) : m.sigma0 + m.H * st[6];
@@ -471,16 +464,9 @@ __device__ inline void qp_state(const MatParams<T>& m, const FracParams<T>& fr, 
     s.c = frcp(T(1) + m.am * s.g);
     s.kphi = -m.am * s.gp * s.c * s.c;
   }
-  // block stress, Amor split, psi^+ (eq:principal-stress-update-eigenvalues,
-  // eq:linear-degraded-stress, principal psi^+ of Appendix A)
+  // Amor split and psi^+ (eq:linear-degraded-stress, psi^+ of Appendix A)
   s.tension = s.theta >= T(0);
   const T kt = m.kappa * s.theta;
-  const T tmu = T(2) * m.mu * s.c;
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    s.taub[i] = tmu * s.e[i] + kt;
-    s.taud[i] = s.tension ? s.g * s.taub[i] : s.g * (tmu * s.e[i]) + kt;
-  }
   s.psi = m.mu * s.c * s.c * ee + (s.tension ? T(0.5) * kt * s.theta : T(0));
   // history (Miehe): strict switch
   s.hactive = s.psi > st[7];
@@ -490,7 +476,19 @@ __device__ inline void qp_state(const MatParams<T>& m, const FracParams<T>& fr, 
   const T alpha_pp = (fr.at == 2) ? T(2) : T(0);
   s.L = s.gp * s.H + m.Gc * fr.inv_c0l0 * alpha_p + fr.zeta * (phi - phin) * fr.inv_dt;
   s.dLcoef = T(2) * s.H + m.Gc * fr.inv_c0l0 * alpha_pp + fr.zeta * fr.inv_dt;
-  qp_frame_stress<T>(m, beta, eps, s);
+}
+
+// Residual state at one point: steps of Box 1 / Box 2 and Section 3.
+//   G: grad_X u (row-major), phi: phase field at the point, phin: previous phi,
+//   st: D[6] (Voigt), ebar_p, H_n.
+//   VOCE, MAXW as for return_map.
+template <typename T, bool VOCE = true, bool MAXW = false>
+__device__ inline void qp_state(const MatParams<T>& m, const FracParams<T>& fr, const T* G, T phi,
+                                T phin, const T* st, QPState<T>& s) {
+  T beta[3], eps[3];
+  qp_kin<T>(G, st, s, beta, eps);
+  return_map<T, VOCE, MAXW>(m, fr, phi, phin, st, s.e[0] * s.e[0] + s.e[1] * s.e[1] + s.e[2] * s.e[2], s);
+  qp_offdiagonal<T>(m, beta, eps, s);
 }
 
 // Linearisation record of one point, taken in FP64 once per linearisation and
@@ -617,19 +615,7 @@ __device__ inline void qp_state_lin(const MatParams<T>& m, const T* G, const Lin
   T F[9];
 #pragma unroll
   for (int k = 0; k < 9; ++k) F[k] = G[k] + ((k % 4 == 0) ? T(1) : T(0));
-  const T c00 = F[4] * F[8] - F[5] * F[7];
-  const T c01 = F[5] * F[6] - F[3] * F[8];
-  const T c02 = F[3] * F[7] - F[4] * F[6];
-  const T idet = frcp(F[0] * c00 + F[1] * c01 + F[2] * c02);
-  s.Fi[0] = c00 * idet;
-  s.Fi[3] = c01 * idet;
-  s.Fi[6] = c02 * idet;
-  s.Fi[1] = (F[2] * F[7] - F[1] * F[8]) * idet;
-  s.Fi[4] = (F[0] * F[8] - F[2] * F[6]) * idet;
-  s.Fi[7] = (F[1] * F[6] - F[0] * F[7]) * idet;
-  s.Fi[2] = (F[1] * F[5] - F[2] * F[4]) * idet;
-  s.Fi[5] = (F[2] * F[3] - F[0] * F[5]) * idet;
-  s.Fi[8] = (F[0] * F[4] - F[1] * F[3]) * idet;
+  inverse33<T>(F, s.Fi);
   {
     const int m = (r.flags >> 3) & 3;
     const T a0 = (T)r.v[R_Q0], a1 = (T)r.v[R_Q0 + 1], a2 = (T)r.v[R_Q0 + 2];
@@ -653,32 +639,12 @@ __device__ inline void qp_state_lin(const MatParams<T>& m, const T* G, const Lin
   for (int i = 0; i < 3; ++i) {
     const T E = (T)r.v[R_E0 + i];  // principal trial log strain: b_i = exp(2 E)
     s.bd[i] = fexp(T(2) * E);
-    s.hinv[i] = T(0.5) * fexp(T(-2) * E);
     s.theta += E;
     s.coef[i] = (T)r.v[R_O0 + i];
   }
   const T th3 = s.theta * (T(1) / T(3));
 #pragma unroll
   for (int i = 0; i < 3; ++i) s.e[i] = (T)r.v[R_E0 + i] - th3;
-  const T kt = m.kappa * s.theta;
-  const T tmu = T(2) * m.mu * s.c;
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    s.taub[i] = tmu * s.e[i] + kt;
-    s.taud[i] = s.tension ? s.g * s.taub[i] : s.g * (tmu * s.e[i]) + kt;
-  }
-}
-
-// First Piola stress P = tau_degr F^-T (eq:mechanical-gradient-transformation).
-template <typename T>
-__device__ inline void piola(const QPState<T>& s, T* P) {
-  const T* t = s.tau;
-  const T tm[9] = {t[0], t[5], t[4], t[5], t[1], t[3], t[4], t[3], t[2]};
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int J = 0; J < 3; ++J)
-      P[3 * i + J] = tm[3 * i] * s.Fi[3 * J] + tm[3 * i + 1] * s.Fi[3 * J + 1] + tm[3 * i + 2] * s.Fi[3 * J + 2];
 }
 
 // Directional derivative (Appendices B-C): (dG, dphi) -> (dP, dL).
@@ -780,116 +746,6 @@ __device__ inline void qp_tangent(const MatParams<T>& m, const QPState<T>& s, co
   T dH;
   qp_tangent_psi<T>(m, s, dG, dphi, dP, dH, s.hactive);
   dL = s.dLcoef * dphi + s.gp * dH;
-}
-
-// Reverse (transpose) of qp_tangent: cotangents (Pb = dP-bar, Lb = dL-bar) ->
-// (Gb = dG-bar, phib = dphi-bar), step by step in the reverse order of the forward
-// map, in the principal frame. Also returns the diagonal of the rotated stress
-// cotangent Xd_i = [N^T (Pb F^-1) N]_ii used by the parameter partials.
-// Core: Hb = the cotangent of psi^+ (zero when the history switch is off); phib
-// starts from phib0 and collects the branch's terms.
-template <typename T>
-__device__ inline void qp_tangent_T_psi(const MatParams<T>& m, const QPState<T>& s, const T* Pb, T Hb, T phib0,
-                                        T* Gb, T& phib, T* Xd) {
-  const T* N = s.N;
-  const T* bd = s.bd;
-  const T tm2 = T(2) * m.mu;
-  phib = phib0;
-  // FiN = F^-1 N (both ends, as in the forward map)
-  T FiN[9];
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      FiN[3 * i + j] = s.Fi[3 * i] * N[j] + s.Fi[3 * i + 1] * N[3 + j] + s.Fi[3 * i + 2] * N[6 + j];
-  // dP = (N Z) FiN^T  ->  Zb = N^T (Pb FiN)
-  T Zt[9], Zb[9];
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      Zt[3 * i + j] = Pb[3 * i] * FiN[j] + Pb[3 * i + 1] * FiN[3 + j] + Pb[3 * i + 2] * FiN[6 + j];
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) Zb[3 * i + j] = N[i] * Zt[j] + N[3 + i] * Zt[3 + j] + N[6 + i] * Zt[6 + j];
-  Xd[0] = Zb[0];
-  Xd[1] = Zb[4];
-  Xd[2] = Zb[8];
-  // Z = Xfull - diag(tau_d) Lt^T: off-diagonal increments and the geometric term
-  // (block deviatoric and degraded principal stresses recomputed from e, c and theta)
-  const T kapth = m.kappa * s.theta, tmc = tm2 * s.c;
-  T taubd[3], td[3];
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    taubd[i] = tmc * s.e[i];
-    td[i] = s.tension ? s.g * (taubd[i] + kapth) : s.g * taubd[i] + kapth;
-  }
-  T Ltb[9];
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int b = 0; b < 3; ++b) Ltb[3 * a + b] = -td[b] * Zb[3 * b + a];
-  const T ob12 = (Zb[5] + Zb[7]) * s.coef[0];
-  const T ob02 = (Zb[2] + Zb[6]) * s.coef[1];
-  const T ob01 = (Zb[1] + Zb[3]) * s.coef[2];
-  Ltb[5] += bd[2] * ob12;
-  Ltb[7] += bd[1] * ob12;
-  Ltb[2] += bd[2] * ob02;
-  Ltb[6] += bd[0] * ob02;
-  Ltb[1] += bd[1] * ob01;
-  Ltb[3] += bd[0] * ob01;
-  // principal stress increments
-  T dceb[3];
-  T dthb = T(0);
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    const T xb = Zb[4 * i];
-    dceb[i] = s.g * tm2 * xb;
-    if (s.tension) {
-      dthb += s.g * m.kappa * xb;
-      phib += s.gp * (taubd[i] + kapth) * xb;
-    } else {
-      dthb += m.kappa * xb;
-      phib += s.gp * taubd[i] * xb;
-    }
-  }
-  // psi^+: dpsi = 2 mu c e.dce + tension kappa theta dth
-  if (Hb != T(0)) {
-#pragma unroll
-    for (int i = 0; i < 3; ++i) dceb[i] += tm2 * s.c * s.e[i] * Hb;
-    if (s.tension) dthb += kapth * Hb;
-  }
-  // dce_i = c de_i + e_i (kq e.de + kphi dphi)
-  const T sdot = s.e[0] * dceb[0] + s.e[1] * dceb[1] + s.e[2] * dceb[2];
-  T deb[3];
-#pragma unroll
-  for (int i = 0; i < 3; ++i) deb[i] = s.c * dceb[i] + s.kq * sdot * s.e[i];
-  phib += s.kphi * sdot;
-  // de_i = deps_i - dth/3, dth = sum deps, deps_i = Lt_ii
-  const T mdeb = (deb[0] + deb[1] + deb[2]) * (T(1) / T(3));
-#pragma unroll
-  for (int i = 0; i < 3; ++i) Ltb[4 * i] += deb[i] - mdeb + dthb;
-  // Lt = N^T dG FiN  ->  Gb = (N Ltb) FiN^T
-  T R[9];
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      R[3 * i + j] = N[3 * i] * Ltb[j] + N[3 * i + 1] * Ltb[3 + j] + N[3 * i + 2] * Ltb[6 + j];
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int J = 0; J < 3; ++J)
-      Gb[3 * i + J] = R[3 * i] * FiN[3 * J] + R[3 * i + 1] * FiN[3 * J + 1] + R[3 * i + 2] * FiN[3 * J + 2];
-}
-
-// Transpose of the single block's tangent: dL = dLcoef dphi + g' dH, dH = dpsi^+ when
-// the history switch is on.
-template <typename T>
-__device__ inline void qp_tangent_T(const MatParams<T>& m, const QPState<T>& s, const T* Pb, T Lb, T* Gb,
-                                    T& phib, T* Xd) {
-  qp_tangent_T_psi<T>(m, s, Pb, s.hactive ? s.gp * Lb : T(0), s.dLcoef * Lb, Gb, phib, Xd);
 }
 
 }  // namespace pfmf

@@ -1,0 +1,412 @@
+// Pointwise functions of the FP64 applies in tensor form: trial log strain, return
+// mapping, tangent and its transpose without a principal frame.
+//
+// With b_tr = m (I + S), m = tr b_tr / 3 and S traceless, the deviatoric trial log strain
+// is an isotropic function of S,
+//     e = c1 S + c2 Q,    Q = S^2 - (2/3) J2 I,   J2 = tr S^2 / 2,   J3 = det S,
+// whose coefficients depend on (J2, J3) only. For f(s) = log(1 + s) / 2 = sum_n f_n s^n
+// the Cayley-Hamilton theorem gives S^n = h_{n-2} S^2 + h_{n-1} S + ..., h_n = J2 h_{n-2} +
+// J3 h_{n-3}, so c1 = sum f_n h_{n-1} and c2 = sum f_n h_{n-2}; their derivatives
+//     g3 = dc1/dJ2,   g4 = dc1/dJ3 = dc2/dJ2,   g5 = dc2/dJ3
+// are the same sums over the coefficients of 1 / (1 - J2 t^2 - J3 t^3)^2. Nothing is divided
+// by a difference of eigenvalues, so repeated eigenvalues need no case of their own, and the
+// strain's derivative (Appendices A-B) is
+//     de = c1 dS + c2 dev(S dS + dS S) + (g3 dJ2 + g4 dJ3) S + (g4 dJ2 + g5 dJ3) Q,
+// dJ2 = S:dS, dJ3 = Q:dS, a self-adjoint map of dS (the transpose uses it again).
+//
+// The FP64 applies are bound by VALU issue. The principal form (eigenvalues, an orthonormal
+// frame with polish rotations, three logarithms, divided differences, the tangent rotated
+// there and back) took 1,152 vector instructions per order-3 element in the Jacobian beside its
+// 93 matrix-core ones; this form takes 860, and 175 registers instead of 217. Order-3 Jacobian on
+// 48^3 elements 0.462 -> 0.400 ms, with two extra branches on 32^3 0.310 -> 0.238 (18 spilled
+// registers -> none), order 4 on 40^3 0.644 -> 0.588, order 2 on 32^3 0.097 -> 0.091. The
+// linearisation record and the state commit keep the principal form (their data are principal).
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "pf_qf.hpp"
+
+namespace pfmf {
+
+// The point's state for the residual, the tangent and its transpose. Symmetric tensors are
+// {xx, yy, zz, yz, xz, xy}.
+struct TState {
+  double Fi[9];               // F^-1
+  double S[6], Q[6];          // b_tr / m - I and dev(S^2)
+  double J2, J3;              // invariants of S
+  double c1, c2, g3, g4, g5;  // log coefficients and their derivatives
+  double e[6];                // deviatoric trial log strain
+  double ee, theta;           // e:e and tr eps
+  double g, gp, c, kq, kphi;  // degradation, return factor and its tangent (as in QPState)
+  double psi, H, L, dLcoef, ddg_s0, ddg_visc, dg;
+  bool tension, hactive, plastic, bad;
+};
+
+// A constant formed in scalar registers where it is used. The kernels that loop over two
+// elements would otherwise hold every constant of the point function in vector registers
+// across the loop (some 60 of them, the difference between 2 and 3 waves per SIMD).
+__device__ inline double kst(double c) {
+  asm volatile("" : "+s"(c));
+  return c;
+}
+
+// Up to this J2 every |s_i| <= 2 sqrt(J2 / 3) is at most 0.1 (principal log strains within 5 %
+// of their mean): the coefficients are sums of 13 terms there, 46 multiply-adds in all.
+constexpr double LOG_SERIES_J2 = 0.0075;
+
+// c1, c2 (and, with TAN, g3, g4, g5) of log(1 + s) / 2 for J2 <= LOG_SERIES_J2: f' = 1 / (2 (1 + s))
+// interpolated at 13 Chebyshev nodes of [-0.1, 0.1] and integrated (relative error of f and of
+// f' below 4e-17), summed downwards: b_k = sum_n f_n h_{n-k} and q_k = sum_n f_n d_{n-k}, h_n and
+// d_n the coefficients of 1 / (1 - J2 t^2 - J3 t^3) and of its square.
+template <bool TAN>
+__device__ inline void log_series(double J2, double J3, TState& s) {
+  constexpr int N = 13;
+  constexpr double f[N + 1] = {0.0,
+                               0.5,
+                               -0.24999999999999917,
+                               0.16666666666666613,
+                               -0.12500000000114728,
+                               0.10000000000091781,
+                               -0.08333333272200438,
+                               0.07142857090457519,
+                               -0.06250015693704912,
+                               0.05555569505515478,
+                               -0.04997913947686155,
+                               0.04543558134260141,
+                               -0.04304835441590142,
+                               0.03973694253775516};
+  double b[N + 4], q[N + 4];
+  b[N + 1] = b[N + 2] = b[N + 3] = 0.0;
+  q[N + 1] = q[N + 2] = q[N + 3] = 0.0;
+#pragma unroll
+  for (int k = N; k >= 1; --k) {
+    const double fk = k == 1 ? f[k] : kst(f[k]);
+    b[k] = k + 2 <= N ? fma(J2, b[k + 2], fk) : fk;
+    if (k + 3 <= N) b[k] = fma(J3, b[k + 3], b[k]);
+    if (TAN && k >= 3) {
+      q[k] = k + 2 <= N ? fma(J2, q[k + 2], b[k]) : b[k];
+      if (k + 3 <= N) q[k] = fma(J3, q[k + 3], q[k]);
+    }
+  }
+  s.c1 = b[1];
+  s.c2 = b[2];
+  if (TAN) {
+    s.g3 = q[3];
+    s.g4 = q[4];
+    s.g5 = q[5];
+  }
+}
+
+// The same for any positive definite I + S, I2 = 3 - J2 > 0 and I3 = det(I + S) > 0 given:
+// f(s) = (1/2) int_0^1 s / (1 + t s) dt, so with D(t) = det(I + t S) the sums are integrals of
+// (1, -t) / D and (t^2, -t^3, t^4) / D^2, taken by 12-point Gauss rules on panels that halve
+// towards t = 1, the last one no longer than the distance of the pole beyond it (the error of
+// the rule is then below 1e-17). D in powers of t and 1 - t has positive terms only. About 20
+// instructions per node, 12 nodes up to |s_i| = 0.5 and 12 more for every halving of the
+// smallest 1 + s_i: at most the cost of a principal frame up to stretches of 2 : 1.
+template <bool TAN>
+__device__ inline void log_quadrature(double I2, double I3, TState& s) {
+  constexpr int NG = 12;
+  static constexpr double xg[NG] = {0.009219682876640375, 0.04794137181476257, 0.11504866290284765, 0.2063410228566913,
+                                    0.3160842505009099,   0.43738329574426554, 0.5626167042557345,  0.6839157494990901,
+                                    0.7936589771433087,   0.8849513370971523,  0.9520586281852375,  0.9907803171233597};
+  static constexpr double wg[NG] = {0.023587668193255914, 0.05346966299765921, 0.08003916427167311, 0.10158371336153296,
+                                    0.1167462682691774,   0.12457352290670139, 0.12457352290670139, 0.1167462682691774,
+                                    0.10158371336153296,  0.08003916427167311, 0.05346966299765921, 0.023587668193255914};
+  // a lower bound of the smallest eigenvalue: the other two have at most the mean (3 - l) / 2,
+  // and |s_i| <= 2 sqrt(J2 / 3)
+  const double J = (kst(3.0) - I2) * kst(1.0 / 3.0);
+  const double lam = fmax(kst(4.0 / 9.0) * I3, 1.0 - 2.0 * J * frsqrt(J));
+  double t0 = 0.0, h = 1.0, c1 = 0.0, c2 = 0.0, g3 = 0.0, g4 = 0.0, g5 = 0.0;
+  for (int panel = 0; panel < 64; ++panel) {
+    const bool last = h * (1.0 - lam) <= lam || panel == 63;
+    const double hp = last ? h : 0.5 * h;
+#pragma unroll 1
+    for (int k = 0; k < NG; ++k) {
+      const double t = fma(hp, xg[k], t0), r = 1.0 - t;
+      const double iD = frcp(fma(t * t, fma(t, I3, r * I2), r * r * fma(2.0, t, 1.0)));
+      const double w = 0.5 * hp * wg[k] * iD, wt = w * t;
+      c1 += w;
+      c2 -= wt;
+      if (TAN) {
+        const double u = wt * t * iD, ut = u * t;
+        g3 += u;
+        g4 -= ut;
+        g5 = fma(ut, t, g5);
+      }
+    }
+    if (last) break;
+    t0 += hp;
+    h = hp;
+  }
+  s.c1 = c1;
+  s.c2 = c2;
+  if (TAN) {
+    s.g3 = g3;
+    s.g4 = g4;
+    s.g5 = g5;
+  }
+}
+
+// Y = S D + D S of symmetric traceless S and D: with a zero trace S_ii + S_jj = -S_kk.
+__device__ inline void sym_anticommutator(const double* S, const double* D, double* Y) {
+  Y[0] = 2.0 * (S[0] * D[0] + S[5] * D[5] + S[4] * D[4]);
+  Y[1] = 2.0 * (S[5] * D[5] + S[1] * D[1] + S[3] * D[3]);
+  Y[2] = 2.0 * (S[4] * D[4] + S[3] * D[3] + S[2] * D[2]);
+  Y[3] = S[5] * D[4] + S[4] * D[5] - (S[0] * D[3] + S[3] * D[0]);
+  Y[4] = S[5] * D[3] + S[3] * D[5] - (S[1] * D[4] + S[4] * D[1]);
+  Y[5] = S[4] * D[3] + S[3] * D[4] - (S[2] * D[5] + S[5] * D[2]);
+}
+
+// Frobenius product of two symmetric tensors.
+__device__ inline double sym_dot(const double* a, const double* b) {
+  return a[0] * b[0] + a[1] * b[1] + a[2] * b[2] + 2.0 * (a[3] * b[3] + a[4] * b[4] + a[5] * b[5]);
+}
+
+// de = L(dS) of the header comment for traceless dS; dJ2 = S:dS and dJ3 = Q:dS given.
+__device__ inline void log_tangent(const TState& s, const double* dS, double dJ2, double dJ3, double* de) {
+  double Y[6];
+  sym_anticommutator(s.S, dS, Y);
+  const double a = s.g3 * dJ2 + s.g4 * dJ3, b = s.g4 * dJ2 + s.g5 * dJ3;
+  const double tr = kst(2.0 / 3.0) * s.c2 * dJ2;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    double v = s.c1 * dS[k] + s.c2 * Y[k] + a * s.S[k] + b * s.Q[k];
+    if (k < 3) v -= tr;
+    de[k] = v;
+  }
+}
+
+// Row-major 3x3 times symmetric: M = A B.
+__device__ inline void mul_sym(const double* A, const double* B, double* M) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const double a0 = A[3 * i], a1 = A[3 * i + 1], a2 = A[3 * i + 2];
+    M[3 * i + 0] = a0 * B[0] + a1 * B[5] + a2 * B[4];
+    M[3 * i + 1] = a0 * B[5] + a1 * B[1] + a2 * B[3];
+    M[3 * i + 2] = a0 * B[4] + a1 * B[3] + a2 * B[2];
+  }
+}
+
+// M = A B and M = A B^T, row-major 3x3.
+__device__ inline void mul33(const double* A, const double* B, double* M) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) M[3 * i + j] = A[3 * i] * B[j] + A[3 * i + 1] * B[3 + j] + A[3 * i + 2] * B[6 + j];
+}
+__device__ inline void mul33t(const double* A, const double* B, double* M) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+      M[3 * i + j] = A[3 * i] * B[3 * j] + A[3 * i + 1] * B[3 * j + 1] + A[3 * i + 2] * B[3 * j + 2];
+}
+
+// log(x) / 2 for x > 0 (not a number otherwise): x = 2^n y, y in [sqrt(1/2), sqrt(2)), and
+// 2 atanh((y - 1) / (y + 1)) by its series, whose coefficients are formed in the loop. For the
+// points whose volume changes by more than a quarter; no constants for the common path to hold.
+__device__ inline double half_log(double x) {
+  double y = __builtin_amdgcn_frexp_mant(x);
+  int n = __builtin_amdgcn_frexp_exp(x);
+  if (y < kst(0.70710678118654752440)) {
+    y += y;
+    --n;
+  }
+  const double z = (y - 1.0) * frcp(y + 1.0), z2 = z * z;
+  double r = 0.0;
+#pragma unroll 1
+  for (int k = 12; k >= 0; --k) r = fma(r, z2, frcp((double)(2 * k + 1)));
+  r = fma(z, r, (double)n * kst(0.34657359027997265471));
+  return x > 0.0 ? r : __builtin_nan("");
+}
+
+// log(1 + x) / 2 = atanh(x / (2 + x)) for |x| <= 1/4: 6 terms of the series where 1e-3 bounds
+// the squared argument (truncation below 1e-19), else 11.
+__device__ inline double half_log1p_near(double x) {
+  const double z = x * frcp(2.0 + x), z2 = z * z;
+  double r;
+  if (z2 <= kst(1e-3)) {
+    r = kst(1.0 / 11.0);
+  } else {
+    r = kst(1.0 / 21.0);
+#pragma unroll
+    for (int k = 9; k >= 5; --k) r = fma(r, z2, kst(1.0 / (2 * k + 1)));
+  }
+#pragma unroll
+  for (int k = 4; k >= 1; --k) r = fma(r, z2, kst(1.0 / (2 * k + 1)));
+  return fma(z * z2, r, z);
+}
+
+// det(I + D) of D = st[0..5].
+__device__ inline double det_plus_one(const double* st) {
+  const double a = 1.0 + st[0], b = 1.0 + st[1], c = 1.0 + st[2];
+  return a * (b * c - st[3] * st[3]) - st[5] * (st[5] * c - st[3] * st[4]) + st[4] * (st[5] * st[3] - b * st[4]);
+}
+
+// Residual state at one point (Box 1 / Box 2 and Section 3); arguments as for qp_state.
+// TAN: also the derivatives of the log coefficients (the tangent and its transpose).
+template <bool TAN, bool VOCE, bool MAXW = false>
+__device__ inline void ts_state(const MatParams<double>& m, const FracParams<double>& fr, const double* G, double phi,
+                                double phin, const double* st, TState& s) {
+  double A[6];
+  const double det = kinematics<double>(G, st, s.Fi, A);
+  const double third = kst(1.0 / 3.0);
+  const double t = (A[0] + A[1] + A[2]) * third;
+  const double im = frcp(1.0 + t);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) s.S[k] = (k < 3 ? A[k] - t : A[k]) * im;
+  const double* S = s.S;
+  double SS[6];  // S^2
+  SS[0] = S[0] * S[0] + S[5] * S[5] + S[4] * S[4];
+  SS[1] = S[5] * S[5] + S[1] * S[1] + S[3] * S[3];
+  SS[2] = S[4] * S[4] + S[3] * S[3] + S[2] * S[2];
+  SS[3] = S[5] * S[4] - S[0] * S[3];
+  SS[4] = S[5] * S[3] - S[1] * S[4];
+  SS[5] = S[4] * S[3] - S[2] * S[5];
+  s.J2 = 0.5 * (SS[0] + SS[1] + SS[2]);
+  s.J3 = third * sym_dot(S, SS);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) s.Q[k] = k < 3 ? fma(-2.0 * third, s.J2, SS[k]) : SS[k];
+  // det F <= 0 or an eigenvalue of b_tr <= 0 (trace, second invariant or determinant <= 0):
+  // not physical, the point's values are NaN
+  s.bad = !(det > 0.0) || !(t > -1.0);
+  if (s.J2 <= kst(LOG_SERIES_J2)) {
+    log_series<TAN>(s.J2, s.J3, s);
+  } else {
+    const double I2 = 3.0 - s.J2, I3 = det * det * det_plus_one(st) * (im * im * im);
+    s.bad |= !(I2 > 0.0) || !(I3 > 0.0);
+    if (!s.bad) log_quadrature<TAN>(I2, I3, s);
+  }
+  if (s.bad) s.c1 = s.c2 = __builtin_nan("");
+#pragma unroll
+  for (int k = 0; k < 6; ++k) s.e[k] = s.c1 * s.S[k] + s.c2 * s.Q[k];
+  s.ee = sym_dot(s.e, s.e);
+  // tr eps = log(det b_tr) / 2: det b_tr = m^3 (1 - J2 + J3) formed about 1 where it is near 1,
+  // else det F^2 det(I + D)
+  const double v = t * fma(t, kst(3.0) + t, kst(3.0)), w = s.J3 - s.J2, x = v + w + v * w;
+  if (fabs(x) <= 0.25)
+    s.theta = half_log1p_near(x);
+  else
+    s.theta = half_log(det * det * det_plus_one(st));
+  return_map<double, VOCE, MAXW>(m, fr, phi, phin, st, s.ee, s);
+}
+
+// Degraded Kirchhoff stress tau_degr (symmetric).
+__device__ inline void ts_stress(const MatParams<double>& m, const TState& s, double* tau) {
+  const double a = 2.0 * m.mu * s.c * s.g, kt = m.kappa * s.theta, vol = s.tension ? s.g * kt : kt;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) tau[k] = k < 3 ? fma(a, s.e[k], vol) : a * s.e[k];
+}
+
+// First Piola stress P = tau_degr F^-T (eq:mechanical-gradient-transformation).
+__device__ inline void ts_piola(const MatParams<double>& m, const TState& s, double* P) {
+  double t[6];
+  ts_stress(m, s, t);
+  const double tm[9] = {t[0], t[5], t[4], t[5], t[1], t[3], t[4], t[3], t[2]};
+  mul33t(tm, s.Fi, P);
+}
+
+// Directional derivative (Appendices B-C): (dG, dphi) -> (dP, dpsi^+). With dl = dG F^-1 and
+// U = dl (I + S), the perturbation of b_tr is m (U + U^T) =: m X, so dS = dev X - (tr X / 3) S,
+// and dP = (dtau - tau dl^T) F^-T.
+__device__ inline void ts_tangent_psi(const MatParams<double>& m, const TState& s, const double* dG, double dphi,
+                                      double* dP, double& dpsi) {
+  double dl[9], U[9];
+  mul33(dG, s.Fi, dl);
+  mul_sym(dl, s.S, U);
+#pragma unroll
+  for (int k = 0; k < 9; ++k) U[k] += dl[k];
+  double dS[6] = {2.0 * U[0], 2.0 * U[4], 2.0 * U[8], U[5] + U[7], U[2] + U[6], U[1] + U[3]};  // X
+  const double t3 = (dS[0] + dS[1] + dS[2]) * kst(1.0 / 3.0);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) dS[k] = (k < 3 ? dS[k] - t3 : dS[k]) - t3 * s.S[k];
+  const double dJ2 = sym_dot(s.S, dS), dJ3 = sym_dot(s.Q, dS);
+  double de[6];
+  log_tangent(s, dS, dJ2, dJ3, de);
+  const double dth = dl[0] + dl[4] + dl[8];
+  // linearised return: d(c e) = c de + e (kq e:de + kphi dphi)
+  const double ede = sym_dot(s.e, de);
+  const double kk = s.kq * ede + s.kphi * dphi;
+  // degraded stress increment (eq:linear-degraded-stress-linearization) a de + b e + vol I
+  const double tm2 = 2.0 * m.mu, kt = m.kappa * s.theta, kdt = m.kappa * dth;
+  const double a = s.g * tm2 * s.c, b = tm2 * (s.g * kk + s.gp * dphi * s.c);
+  const double vol = s.tension ? s.g * kdt + s.gp * dphi * kt : kdt;
+  double dt[6], tau[6];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) dt[k] = a * de[k] + b * s.e[k] + (k < 3 ? vol : 0.0);
+  ts_stress(m, s, tau);
+  const int ix[9] = {0, 5, 4, 5, 1, 3, 4, 3, 2};
+  double Z[9];
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+      Z[3 * i + j] = dt[ix[3 * i + j]] - (tau[ix[3 * i]] * dl[3 * j] + tau[ix[3 * i + 1]] * dl[3 * j + 1] +
+                                          tau[ix[3 * i + 2]] * dl[3 * j + 2]);
+  mul33t(Z, s.Fi, dP);
+  // psi^+ increment (eq:energy-displacement-linearization)
+  dpsi = tm2 * s.c * (s.c * ede + s.ee * kk) + (s.tension ? kt * dth : 0.0);
+}
+
+// The tangent of a single block: dL = dLcoef dphi + g' dH, dH = dpsi^+ when the history
+// switch is on (eq:history-field-linearization, eq:linearized-local-damage-residual).
+__device__ inline void ts_tangent(const MatParams<double>& m, const TState& s, const double* dG, double dphi,
+                                  double* dP, double& dL) {
+  double dpsi;
+  ts_tangent_psi(m, s, dG, dphi, dP, dpsi);
+  dL = s.dLcoef * dphi + (s.hactive ? s.gp * dpsi : 0.0);
+}
+
+// Transpose of ts_tangent_psi, step by step in reverse: cotangents (Pb of dP, Hb of dpsi^+;
+// Hb = 0 when the history switch is off) -> (Gb of dG, phib = phib0 + the branch's terms).
+// xe = (Pb F^-1):e, the stress cotangent along e used by the parameter partials.
+__device__ inline void ts_tangent_T_psi(const MatParams<double>& m, const TState& s, const double* Pb, double Hb,
+                                        double phib0, double* Gb, double& phib, double& xe) {
+  const double tm2 = 2.0 * m.mu, kt = m.kappa * s.theta;
+  double Zb[9], tau[6];
+  mul33(Pb, s.Fi, Zb);
+  ts_stress(m, s, tau);
+  double E[6] = {Zb[0], Zb[4], Zb[8], 0.5 * (Zb[5] + Zb[7]), 0.5 * (Zb[2] + Zb[6]), 0.5 * (Zb[1] + Zb[3])};
+  xe = sym_dot(E, s.e);
+  const double tz = Zb[0] + Zb[4] + Zb[8];
+  // dtau = a de + b e + vol I
+  phib = phib0 + tm2 * s.gp * s.c * xe + (s.tension ? s.gp * kt * tz : 0.0);
+  double kkb = tm2 * s.g * xe + tm2 * s.c * s.ee * Hb;
+  double dthb = (s.tension ? s.g * m.kappa : m.kappa) * tz + (s.tension ? kt * Hb : 0.0);
+  phib += s.kphi * kkb;
+  const double edeb = s.kq * kkb + tm2 * s.c * s.c * Hb;
+  const double a = s.g * tm2 * s.c, tz3 = tz * kst(1.0 / 3.0);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) E[k] = a * (k < 3 ? E[k] - tz3 : E[k]) + edeb * s.e[k];
+  // de = L(dS), dS = dev X - (tr X / 3) S
+  const double eS = sym_dot(s.S, E), eQ = sym_dot(s.Q, E);
+  double Xb[6];
+  log_tangent(s, E, eS, eQ, Xb);
+  const double xs3 = sym_dot(s.S, Xb) * kst(1.0 / 3.0);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) Xb[k] -= xs3;
+  // X = U + U^T, U = dl (I + S): dl's cotangent 2 Xb (I + S) - (Zb^T tau), and dth = tr dl
+  const int ix[9] = {0, 5, 4, 5, 1, 3, 4, 3, 2};
+  double X2[9], lb[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) X2[k] = 2.0 * Xb[ix[k]];
+  mul_sym(X2, s.S, lb);
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+      lb[3 * i + j] += X2[3 * i + j] - (Zb[i] * tau[ix[j]] + Zb[3 + i] * tau[ix[3 + j]] + Zb[6 + i] * tau[ix[6 + j]]);
+  lb[0] += dthb;
+  lb[4] += dthb;
+  lb[8] += dthb;
+  mul33t(lb, s.Fi, Gb);
+}
+
+// Transpose of the single block's tangent.
+__device__ inline void ts_tangent_T(const MatParams<double>& m, const TState& s, const double* Pb, double Lb,
+                                    double* Gb, double& phib, double& xe) {
+  ts_tangent_T_psi(m, s, Pb, s.hactive ? s.gp * Lb : 0.0, s.dLcoef * Lb, Gb, phib, xe);
+}
+
+}  // namespace pfmf
