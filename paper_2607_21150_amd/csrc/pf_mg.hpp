@@ -209,7 +209,7 @@ __global__ __launch_bounds__(NT) void k_linearize(LinArgs a, int colour, DevTabl
       bad_pid |= pid >= a.nph;  // an id outside the phase table raises the phase flag
       const MatParams<double> mp = a.mats[pid < a.nph ? pid : 0];
       QPState<double> s;
-      qp_state<double>(mp, a.fr, G, phi, 0.0, st, s);
+      qp_state<>(mp, a.fr, G, phi, 0.0, st, s);
       any_bad |= s.bad;
       if (MODE == 2) {
         // extra branches: one record layer each; the block's layer takes the point's
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(NT) void k_linearize(LinArgs a, int colour, DevTabl
           for (int k = 0; k < 7; ++k) xs[k] = b.kind == XB_HOOKE ? 0.0 : a.xstate[(int64_t)(7 * j + k) * a.n_q + gq];
           xs[7] = 0.0;
           QPState<double> sj;
-          qp_state<double, true, true>(b.m, a.fr, G, phi, 0.0, xs, sj);
+          qp_state<true, true>(b.m, a.fr, G, phi, 0.0, xs, sj);
           any_bad |= sj.bad;
           psi += sj.psi;
           LinRecord rj;
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(NT) void k_linearize(LinArgs a, int colour, DevTabl
 #pragma unroll
           for (int k = 0; k < 8; ++k) xk[k] = b.kind == XB_HOOKE ? 0.0 : xs[k];
           QPState<double> sj;
-          qp_state<double, true, true>(b.m, a.fr, G, phi, 0.0, xk, sj);
+          qp_state<true, true>(b.m, a.fr, G, phi, 0.0, xk, sj);
           any_bad |= sj.bad;
           psi += sj.psi;
           double nj[8];

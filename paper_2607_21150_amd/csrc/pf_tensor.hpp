@@ -42,14 +42,6 @@ struct TState {
   bool tension, hactive, plastic, bad;
 };
 
-// A constant formed in scalar registers where it is used. The kernels that loop over two
-// elements would otherwise hold every constant of the point function in vector registers
-// across the loop (some 60 of them, the difference between 2 and 3 waves per SIMD).
-__device__ inline double kst(double c) {
-  asm volatile("" : "+s"(c));
-  return c;
-}
-
 // Up to this J2 every |s_i| <= 2 sqrt(J2 / 3) is at most 0.1 (principal log strains within 5 %
 // of their mean): the coefficients are sums of 13 terms there, 46 multiply-adds in all.
 constexpr double LOG_SERIES_J2 = 0.0075;
@@ -289,7 +281,7 @@ __device__ inline void ts_state(const MatParams<double>& m, const FracParams<dou
     s.theta = half_log1p_near(x);
   else
     s.theta = half_log(det * det * det_plus_one(st));
-  return_map<double, VOCE, MAXW>(m, fr, phi, phin, st, s.ee, s);
+  return_map<VOCE, MAXW>(m, fr, phi, phin, st, s.ee, s);
 }
 
 // Degraded Kirchhoff stress tau_degr (symmetric).
