@@ -17,6 +17,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <cstdint>
+
 namespace pfmf {
 
 constexpr int NT = 256;  // threads per workgroup
@@ -44,9 +46,24 @@ struct BrickGeom {
   bool last_x, last_y, last_z;
 };
 
+// Division of 0 <= n < 2^31 by a fixed d >= 1 as a multiplication: m = ceil(2^(31 + s) / d) with
+// 2^s >= d, so n m / 2^(31 + s) exceeds n / d by less than 1 / d. Uniform arguments stay in
+// scalar registers (an integer division would go through the vector unit).
+struct FastDiv {
+  uint32_t d, m, s;
+  __host__ __device__ int div(int n) const { return (int)(((uint64_t)(uint32_t)n * m) >> (31 + s)); }
+  static FastDiv of(int d) {
+    FastDiv f{(uint32_t)d, 0, 0};
+    while ((1ull << f.s) < (uint64_t)d) ++f.s;
+    f.m = (uint32_t)(((1ull << (31 + f.s)) + d - 1) / d);
+    return f;
+  }
+};
+
 struct MeshDev {
   int nx, ny, nz;
   int nbx, nby, nbz;     // bricks per direction
+  FastDiv by_nx, by_ny, by_nbx, by_nby;
   double hx, hy, hz;
   double ih[3];          // 2 / h per direction (reference-to-physical gradient factor)
   double jdet;           // hx hy hz / 8 (affine Jacobian determinant)
@@ -98,15 +115,16 @@ __host__ __device__ inline int xcd_grid_all(int nbx, int nby, int nbz) {
   return ((rows + 7) / 8) * 8 * nbx;
 }
 __device__ inline int xcd_brick_all(const MeshDev& m, int id) {
-  const int t = id >> 3;
-  const int row = (t / m.nbx) * 8 + (id & 7);
-  return row < m.nby * m.nbz ? (t % m.nbx) + m.nbx * row : -1;
+  const int t = id >> 3, q = m.by_nbx.div(t);
+  const int row = q * 8 + (id & 7);
+  return row < m.nby * m.nbz ? (t - q * m.nbx) + m.nbx * row : -1;
 }
 __device__ inline BrickGeom decode_brick_lin(const MeshDev& m, int b) {
   BrickGeom g;
-  g.bx = b % m.nbx;
-  g.by = (b / m.nbx) % m.nby;
-  g.bz = b / (m.nbx * m.nby);
+  const int row = m.by_nbx.div(b);
+  g.bx = b - row * m.nbx;
+  g.bz = m.by_nby.div(row);
+  g.by = row - g.bz * m.nby;
   g.ex0 = 2 * g.bx;
   g.ey0 = 2 * g.by;
   g.ez0 = 2 * g.bz;

@@ -164,4 +164,15 @@ __device__ inline void phys_to_ref(const double f[3], const double ih[3], const 
   for (int K = 0; K < 3; ++K) out[K] = GEO ? f[0] * A[3 * K] + f[1] * A[3 * K + 1] + f[2] * A[3 * K + 2] : f[K] * ih[K];
 }
 
+// The transpose with a weight: on the box the caller's factors wih hold it (w 2/h per
+// direction, formed once), on mapped elements it multiplies the result.
+template <bool GEO>
+__device__ inline void phys_to_ref_w(const double f[3], const double wih[3], const double* A, double w, double out[3]) {
+  phys_to_ref<GEO>(f, wih, A, out);
+  if (GEO) {
+#pragma unroll
+    for (int K = 0; K < 3; ++K) out[K] *= w;
+  }
+}
+
 }  // namespace pfmf

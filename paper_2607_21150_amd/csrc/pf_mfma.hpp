@@ -210,38 +210,48 @@ __host__ __device__ inline int64_t ext_index(const MeshDev& m, int NB, int f, in
 }
 
 // First half: the brick's node sums (same order as scatter_brick4) stored
-// unconditionally into the extended grid.
+// unconditionally into the extended grid. A node belongs to one element slot per axis, and on
+// the middle face (local index p) to the second one too: its first value sits at a base address,
+// the others at constant offsets from it, read by the face lanes only.
 template <typename T, int P, int NF>
 __device__ inline void store_brick4(const T* ev, const MeshDev& m, const BrickGeom& g, T* __restrict__ eb) {
   constexpr int p = P - 1, NB = 2 * P - 1, NB3 = NB * NB * NB;
+  constexpr int DX = NF * 64 - p, DY = 2 * NF * 64 - 4 * p, DZ = 4 * NF * 64 - 16 * p;
   const int mx = g.nex * p + 1, my = g.ney * p + 1, mz = g.nez * p + 1;
-  for (int t = threadIdx.x; t < NB3; t += NT) {
+  const uint32_t NXe = (uint32_t)m.nbx * NB, NYe = (uint32_t)m.nby * NB;
+  const int64_t fs = (int64_t)m.nbz * NB * NYe * NXe;
+  T* eb0 = eb + ext_index(m, NB, 0, NB * g.bx, NB * g.by, NB * g.bz);
+#pragma unroll
+  for (int t0 = 0; t0 < NB3; t0 += NT) {
+    const int t = t0 + (int)threadIdx.x;
     const int lx = t % NB, ly = (t / NB) % NB, lz = t / (NB * NB);
-    if (!(lx < mx && ly < my && lz < mz)) continue;
+    if (t >= NB3 || !(lx < mx && ly < my && lz < mz)) continue;
+    const int hx = lx > p, hy = ly > p, hz = lz > p;
+    const T* a = ev + (lx + 4 * ly + 16 * lz + hx * DX + hy * DY + hz * DZ);
+    const bool fx = lx == p && g.nex == 2, fy = ly == p && g.ney == 2, fz = lz == p && g.nez == 2;
     T acc[NF];
 #pragma unroll
-    for (int f = 0; f < NF; ++f) acc[f] = T(0);
+    for (int f = 0; f < NF; ++f) acc[f] = a[f * 64];
+    auto add = [&](int off) {
 #pragma unroll
-    for (int sz = 0; sz < 2; ++sz) {
-      const int k = lz - sz * p;
-      if (k < 0 || k > p || sz >= g.nez) continue;
-#pragma unroll
-      for (int sy = 0; sy < 2; ++sy) {
-        const int j = ly - sy * p;
-        if (j < 0 || j > p || sy >= g.ney) continue;
-#pragma unroll
-        for (int sx = 0; sx < 2; ++sx) {
-          const int i = lx - sx * p;
-          if (i < 0 || i > p || sx >= g.nex) continue;
-          const int slot = sx + 2 * sy + 4 * sz;
-          const int a = i + 4 * j + 16 * k;
-#pragma unroll
-          for (int f = 0; f < NF; ++f) acc[f] += ev[(slot * NF + f) * 64 + a];
-        }
+      for (int f = 0; f < NF; ++f) acc[f] += a[off + f * 64];
+    };
+    if (fx) add(DX);
+    if (fy) {
+      add(DY);
+      if (fx) add(DY + DX);
+    }
+    if (fz) {
+      add(DZ);
+      if (fx) add(DZ + DX);
+      if (fy) {
+        add(DZ + DY);
+        if (fx) add(DZ + DY + DX);
       }
     }
+    const int64_t o = (int64_t)lx + (int64_t)NXe * ((int64_t)ly + (int64_t)NYe * lz);
 #pragma unroll
-    for (int f = 0; f < NF; ++f) eb[ext_index(m, NB, f, NB * g.bx + lx, NB * g.by + ly, NB * g.bz + lz)] = acc[f];
+    for (int f = 0; f < NF; ++f) eb0[f * fs + o] = acc[f];
   }
 }
 
@@ -316,15 +326,28 @@ __global__ __launch_bounds__(NT) void k_gather_ext(const T* __restrict__ eb, int
   }
 }
 
-// Global node of lane (x, y, z) of element slot (sx, sy, sz) of the brick; -1 if
-// the lane is outside the element's P^3 nodes.
+// Wave index in the workgroup, in a scalar register (so that the wave's element and every
+// address derived from it are scalar).
+__device__ inline int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
+
+// Node gathers of a lattice: the first node of an element slot (uniform over the wave) plus the
+// lane's node (x, y, z) relative to it, the same for every element and field. Lanes outside
+// the P^3 nodes take node 0 (lane_has_node is false there).
 template <int P>
-__device__ inline int64_t lane_node(const BrickGeom& g, int sx, int sy, int sz, int nx1, int ny1) {
+__device__ inline bool lane_has_node() {
   const int l = threadIdx.x & 63;
-  const int x = l & 3, y = (l >> 2) & 3, z = l >> 4;
-  if (x >= P || y >= P || z >= P) return -1;
+  return P == 4 || ((l & 3) < P && ((l >> 2) & 3) < P && (l >> 4) < P);
+}
+template <int P>
+__device__ inline uint32_t lane_node(int nx1, int ny1) {
+  const int l = threadIdx.x & 63;
+  const uint32_t n = (uint32_t)(l & 3) + (uint32_t)nx1 * ((uint32_t)((l >> 2) & 3) + (uint32_t)ny1 * (uint32_t)(l >> 4));
+  return lane_has_node<P>() ? n : 0u;
+}
+template <int P>
+__device__ inline int64_t first_node(const BrickGeom& g, int sx, int sy, int sz, int nx1, int ny1) {
   constexpr int p = P - 1;
-  return (int64_t)((g.ex0 + sx) * p + x) + (int64_t)nx1 * (((g.ey0 + sy) * p + y) + (int64_t)ny1 * ((g.ez0 + sz) * p + z));
+  return (int64_t)((g.ex0 + sx) * p) + (int64_t)nx1 * ((int64_t)((g.ey0 + sy) * p) + (int64_t)ny1 * ((g.ez0 + sz) * p));
 }
 
 // Table restriction: global node of lane (x, y, z) of element e, -1 outside its P^3 nodes.
@@ -342,7 +365,7 @@ __device__ inline int64_t tab_lane_node(const OpArgs& a, int64_t e) {
 // lane l of an element reads global node a.conn[e * 64 + l], and the element vector goes
 // straight to a.evec (summed per node afterwards by k_gather_csr).
 template <int MODE, bool BB, bool VOCE, bool MB, bool GEO, bool TAB = false>
-__global__ __launch_bounds__(NT, 2) void k_op64_q3(OpArgs a, int colour, DevTables* __restrict__ tabs) {
+__global__ __launch_bounds__(NT, MB || GEO || MODE == M_ADJ ? 2 : 3) void k_op64_q3(OpArgs a, int colour, DevTables* __restrict__ tabs) {
   static_assert(!TAB || (GEO && !MB), "the table restriction runs on mapped elements without branches");
   __shared__ double ev[8 * 4 * 64];
   __shared__ double red[NT];
@@ -355,11 +378,15 @@ __global__ __launch_bounds__(NT, 2) void k_op64_q3(OpArgs a, int colour, DevTabl
   if (brick < 0) return;  // padding workgroup (uniform)
   const BrickGeom g = TAB ? BrickGeom{} : (BB ? decode_brick_lin(a.m, brick) : decode_brick(a.m, colour, brick));
   const Basis4 bs = load_basis4<4>(tabs);
-  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int l = threadIdx.x & 63, wv = wave_id();
   const int qx = l & 3, qz = (l >> 2) & 3, qy = l >> 4;
   const int ql = qx + 4 * qy + 16 * qz;
+  const uint32_t ln = TAB ? 0u : lane_node<4>(a.nx1, a.ny1);
   const double ih[3] = {a.m.ih[0], a.m.ih[1], a.m.ih[2]};
   const double wbox = tabs->w[4][qx] * tabs->w[4][qy] * tabs->w[4][qz] * a.m.jdet;
+  // the backward map's factors: the weight times 2/h (the adjoint's cotangents carry it already)
+  const double wb = MODE == M_ADJ ? 1.0 : wbox;
+  const double wih[3] = {wb * ih[0], wb * ih[1], wb * ih[2]};
   // adjoint: parameter partials and phase id of every point of the brick (slot, lane)
   __shared__ double gpq[MODE == M_ADJ ? 8 * 3 * 64 : 1];
   __shared__ unsigned char gpid[MODE == M_ADJ ? 8 * 64 : 1];
@@ -375,30 +402,31 @@ __global__ __launch_bounds__(NT, 2) void k_op64_q3(OpArgs a, int colour, DevTabl
     if (TAB ? (int64_t)brick * 8 + slot >= a.n_elem : !(sx < g.nex && sy < g.ney && sz < g.nez)) continue;  // uniform per wave
     const int64_t e = TAB ? (int64_t)brick * 8 + slot
                           : (int64_t)(g.ex0 + sx) + (int64_t)a.m.nx * ((g.ey0 + sy) + (int64_t)a.m.ny * (g.ez0 + sz));
-    const int64_t gn = TAB ? tab_lane_node<4>(a, e) : lane_node<4>(g, sx, sy, sz, a.nx1, a.ny1);
+    const int64_t n0 = TAB ? 0 : first_node<4>(g, sx, sy, sz, a.nx1, a.ny1);
+    const int64_t gn = TAB ? tab_lane_node<4>(a, e) : (int64_t)ln;
     // gather the element's nodal values (lane = node)
     double zu[4], wu[4], pn = 0.0;
 #pragma unroll
-    for (int f = 0; f < 4; ++f) zu[f] = a.z[f * a.n_nodes + gn];
+    for (int f = 0; f < 4; ++f) zu[f] = (a.z + (f * a.n_nodes + n0))[gn];
     if (MODE != M_RES) {
 #pragma unroll
-      for (int f = 0; f < 4; ++f) wu[f] = a.w[f * a.n_nodes + gn];
+      for (int f = 0; f < 4; ++f) wu[f] = (a.w + (f * a.n_nodes + n0))[gn];
     } else {
-      pn = a.phin[gn];
+      pn = (a.phin + n0)[gn];
     }
     // per-point state, issued early
     const int64_t gq = e * 64 + ql;
     double st[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) st[k] = a.state[k * a.n_q + gq];
-    const int pid = a.phase[gq];
+    for (int k = 0; k < 8; ++k) st[k] = (a.state + (k * a.n_q + e * 64))[ql];
+    const int pid = (a.phase + e * 64)[ql];
     // mapped elements: the point's J^-1 and weight
     double gA[GEO ? 9 : 1];
     double wdet = wbox;
     if (GEO) {
 #pragma unroll
-      for (int k = 0; k < 9; ++k) gA[k] = a.qd[k * a.n_q + gq];
-      wdet = a.qd[9 * a.n_q + gq];
+      for (int k = 0; k < 9; ++k) gA[k] = (a.qd + (k * a.n_q + e * 64))[ql];
+      wdet = (a.qd + (9 * a.n_q + e * 64))[ql];
     }
     // forward sum factorisation
     double G[9], phi = 0.0, gphi[3] = {0.0, 0.0, 0.0}, phin = 0.0;
@@ -443,11 +471,9 @@ __global__ __launch_bounds__(NT, 2) void k_op64_q3(OpArgs a, int colour, DevTabl
       ts_piola(mp, s, Fu);
       double L = s.L;
       if (MB) L = mb_residual<VOCE>(a, mp, pidc, gq, true, sG, phi, phin, st[7], s.psi, s.gp, Fu, any_bad);
-#pragma unroll
-      for (int k = 0; k < 9; ++k) Fu[k] *= wdet;
       f0 = wdet * a.fr.s_phi * L;
 #pragma unroll
-      for (int J = 0; J < 3; ++J) f1[J] = wdet * kfg * gphi[J];
+      for (int J = 0; J < 3; ++J) f1[J] = kfg * gphi[J];
     } else if (MODE == M_JAC) {
       double dL;
       if (MB) {
@@ -455,11 +481,9 @@ __global__ __launch_bounds__(NT, 2) void k_op64_q3(OpArgs a, int colour, DevTabl
         dL = mb_jacobian<VOCE>(a, mp, s, pidc, gq, true, sG, phi, phi, st[7], W, sW, wphi, Fu, any_bad);
       } else
         ts_tangent(mp, s, W, wphi, Fu, dL);
-#pragma unroll
-      for (int k = 0; k < 9; ++k) Fu[k] *= wdet;
       f0 = wdet * a.fr.s_phi * dL;
 #pragma unroll
-      for (int J = 0; J < 3; ++J) f1[J] = wdet * kfg * gw[J];
+      for (int J = 0; J < 3; ++J) f1[J] = kfg * gw[J];
     } else {
       double Pb[9];
 #pragma unroll
@@ -495,14 +519,15 @@ __global__ __launch_bounds__(NT, 2) void k_op64_q3(OpArgs a, int colour, DevTabl
     }
     // backward into the element vector
     {
+      const double ws = MODE == M_ADJ ? 1.0 : wdet;
       double b0[4], b1[4][3], r[4];
 #pragma unroll
       for (int f = 0; f < 3; ++f) {
         b0[f] = 0.0;
-        phys_to_ref<GEO>(Fu + 3 * f, ih, gA, b1[f]);
+        phys_to_ref_w<GEO>(Fu + 3 * f, wih, gA, ws, b1[f]);
       }
       b0[3] = f0;
-      phys_to_ref<GEO>(f1, ih, gA, b1[3]);
+      phys_to_ref_w<GEO>(f1, wih, gA, ws, b1[3]);
       sf4_bwd_n<4>(b0, b1, 0x8u, bs, r);
 #pragma unroll
       for (int f = 0; f < 4; ++f) {
@@ -590,7 +615,9 @@ __global__ __launch_bounds__(NT, (MB || GEO) ? 2 : 3) void k_op64_q2(OpArgs a, i
   if (brick < 0) return;  // padding workgroup (uniform)
   const BrickGeom g = TAB ? BrickGeom{} : (BB ? decode_brick_lin(a.m, brick) : decode_brick(a.m, colour, brick));
   const Basis4 bs = load_basis_pq<3, 3>(tabs);
-  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int l = threadIdx.x & 63, wv = wave_id();
+  const uint32_t ln = TAB ? 0u : lane_node<3>(a.nx1, a.ny1);
+  const bool has_node = lane_has_node<3>();
   // the wave's two elements: slot wv (sz = 0) and slot wv + 4 (sz = 1)
   const int sx = wv & 1, sy = wv >> 1;
   const int64_t e0 = (int64_t)brick * 8 + wv;  // TAB: elements e0 (half 0) and e0 + 4 (half 1)
@@ -618,10 +645,11 @@ __global__ __launch_bounds__(NT, (MB || GEO) ? 2 : 3) void k_op64_q2(OpArgs a, i
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       if (half == 1 && !hasB) break;  // uniform
-      const int64_t gn = TAB ? tab_lane_node<3>(a, e0 + 4 * half) : lane_node<3>(g, sx, sy, half, a.nx1, a.ny1);
+      const int64_t n0 = TAB ? 0 : first_node<3>(g, sx, sy, half, a.nx1, a.ny1);
+      const int64_t gn = TAB ? tab_lane_node<3>(a, e0 + 4 * half) : (int64_t)ln;
       double zu[4];
 #pragma unroll
-      for (int f = 0; f < 4; ++f) zu[f] = gn >= 0 ? a.z[f * a.n_nodes + gn] : 0.0;
+      for (int f = 0; f < 4; ++f) zu[f] = has_node ? (a.z + (f * a.n_nodes + n0))[gn] : 0.0;
       double v[4], d[4][3];
       sf4_fwd_n<4>(zu, bs, 0x8u, MODE == M_JAC ? 0x7u : 0xFu, v, d);
       const bool mine = E == half;
@@ -642,7 +670,7 @@ __global__ __launch_bounds__(NT, (MB || GEO) ? 2 : 3) void k_op64_q2(OpArgs a, i
         }
       }
       if (MODE == M_RES) {
-        double pn = gn >= 0 ? a.phin[gn] : 0.0, pv[1], pd[1][3];
+        double pn = has_node ? (a.phin + n0)[gn] : 0.0, pv[1], pd[1][3];
         sf4_fwd_n<1>(&pn, bs, 0x1u, 0x0u, pv, pd);
         const double r = lane_read(pv[0], src_fwd);
         if (mine) phin = r;
@@ -689,10 +717,11 @@ __global__ __launch_bounds__(NT, (MB || GEO) ? 2 : 3) void k_op64_q2(OpArgs a, i
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
         if (half == 1 && !hasB) break;
-        const int64_t gn = TAB ? tab_lane_node<3>(a, e0 + 4 * half) : lane_node<3>(g, sx, sy, half, a.nx1, a.ny1);
+        const int64_t n0 = TAB ? 0 : first_node<3>(g, sx, sy, half, a.nx1, a.ny1);
+      const int64_t gn = TAB ? tab_lane_node<3>(a, e0 + 4 * half) : (int64_t)ln;
         double wu[4];
 #pragma unroll
-        for (int f = 0; f < 4; ++f) wu[f] = gn >= 0 ? a.w[f * a.n_nodes + gn] : 0.0;
+        for (int f = 0; f < 4; ++f) wu[f] = has_node ? (a.w + (f * a.n_nodes + n0))[gn] : 0.0;
         double v[4], d[4][3];
         sf4_fwd_n<4>(wu, bs, 0x8u, 0xFu, v, d);
         const bool mine = E == half;
@@ -728,11 +757,9 @@ __global__ __launch_bounds__(NT, (MB || GEO) ? 2 : 3) void k_op64_q2(OpArgs a, i
       ts_piola(mp, s, Fu);
       double L = s.L;
       if (MB) L = mb_residual<VOCE>(a, mp, pidc, gq, valid, sG, phi, phin, st[7], s.psi, s.gp, Fu, xbad);
-#pragma unroll
-      for (int k = 0; k < 9; ++k) Fu[k] *= wdet;
       f0 = wdet * a.fr.s_phi * L;
 #pragma unroll
-      for (int J = 0; J < 3; ++J) f1[J] = wdet * kfg * gphi[J];
+      for (int J = 0; J < 3; ++J) f1[J] = kfg * gphi[J];
     } else if (MODE == M_JAC) {
       double dL;
       if (MB) {
@@ -740,11 +767,9 @@ __global__ __launch_bounds__(NT, (MB || GEO) ? 2 : 3) void k_op64_q2(OpArgs a, i
         dL = mb_jacobian<VOCE>(a, mp, s, pidc, gq, valid, sG, phi, phi, st[7], W, sW, wphi, Fu, xbad);
       } else
         ts_tangent(mp, s, W, wphi, Fu, dL);
-#pragma unroll
-      for (int k = 0; k < 9; ++k) Fu[k] *= wdet;
       f0 = wdet * a.fr.s_phi * dL;
 #pragma unroll
-      for (int J = 0; J < 3; ++J) f1[J] = wdet * kfg * gw[J];
+      for (int J = 0; J < 3; ++J) f1[J] = kfg * gw[J];
     } else {
       double Pb[9];
 #pragma unroll
@@ -777,11 +802,13 @@ __global__ __launch_bounds__(NT, (MB || GEO) ? 2 : 3) void k_op64_q2(OpArgs a, i
     }
     if (MB) any_bad |= valid && xbad;
     // ---- back to the padded layout of each element, transposed interpolation
+    const double ws = MODE == M_ADJ ? 1.0 : wdet;
+    const double wih[3] = {ws * ih[0], ws * ih[1], ws * ih[2]};
     double b1p[4][3];
     double b0p[4];
 #pragma unroll
-    for (int f = 0; f < 3; ++f) phys_to_ref<GEO>(Fu + 3 * f, ih, gA, b1p[f]);
-    phys_to_ref<GEO>(f1, ih, gA, b1p[3]);
+    for (int f = 0; f < 3; ++f) phys_to_ref_w<GEO>(Fu + 3 * f, wih, gA, ws, b1p[f]);
+    phys_to_ref_w<GEO>(f1, wih, gA, ws, b1p[3]);
     b0p[3] = f0;
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
@@ -876,7 +903,9 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2(LinApplyArgs<V> a, int colour,
   const BrickGeom g = BB ? decode_brick_lin(a.m, brick) : decode_brick(a.m, colour, brick);
   const Basis4 bf = load_basis_pq<3, 3>(tabs);
   const Basis4 bc = load_basis_pq<PC, 3>(tabs);
-  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int l = threadIdx.x & 63, wv = wave_id();
+  const uint32_t lf = lane_node<3>(a.fine.nx1, a.fine.ny1), lc = lane_node<PC>(a.lev.nx1, a.lev.ny1);
+  const bool has_f = lane_has_node<3>(), has_c = lane_has_node<PC>();
   const int sx = wv & 1, sy = wv >> 1;
   const bool hasA = sx < g.nex && sy < g.ney;  // uniform per wave
   const bool hasB = hasA && g.nez > 1;
@@ -890,6 +919,7 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2(LinApplyArgs<V> a, int colour,
   const V ih[3] = {(V)a.m.ih[0], (V)a.m.ih[1], (V)a.m.ih[2]};
   const V wbox = (V)(tabs->w[3][cqx < 3 ? cqx : 0] * tabs->w[3][cqy] * tabs->w[3][cqz < 3 ? cqz : 0] *
                              a.m.jdet);
+  const V wih[3] = {wbox * ih[0], wbox * ih[1], wbox * ih[2]};
   if (hasA) {
     V G[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     V W[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
@@ -897,13 +927,13 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2(LinApplyArgs<V> a, int colour,
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       if (half == 1 && !hasB) break;  // uniform
-      const int64_t gf = lane_node<3>(g, sx, sy, half, a.fine.nx1, a.fine.ny1);
-      const int64_t gc = lane_node<PC>(g, sx, sy, half, a.lev.nx1, a.lev.ny1);
+      const int64_t nf = first_node<3>(g, sx, sy, half, a.fine.nx1, a.fine.ny1);
+      const int64_t nc = first_node<PC>(g, sx, sy, half, a.lev.nx1, a.lev.ny1);
       double zu[3], wu[4];
 #pragma unroll
-      for (int f = 0; f < 3; ++f) zu[f] = gf >= 0 ? (double)a.z32[f * a.fine.n_nodes + gf] : 0.0;
+      for (int f = 0; f < 3; ++f) zu[f] = has_f ? (double)(a.z32 + (f * a.fine.n_nodes + nf))[lf] : 0.0;
 #pragma unroll
-      for (int f = 0; f < 4; ++f) wu[f] = gc >= 0 ? (double)a.dz[f * a.lev.n_nodes + gc] : 0.0;
+      for (int f = 0; f < 4; ++f) wu[f] = has_c ? (double)(a.dz + (f * a.lev.n_nodes + nc))[lc] : 0.0;
       const bool mine = E == half;
       {
         double v[3], d[3][3];
@@ -977,9 +1007,9 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2(LinApplyArgs<V> a, int colour,
 #pragma unroll
       for (int f = 0; f < 3; ++f)
 #pragma unroll
-        for (int J = 0; J < 3; ++J) b1p[f][J] = (double)(wdet * Fu[3 * f + J] * ih[J]);
+        for (int J = 0; J < 3; ++J) b1p[f][J] = (double)(Fu[3 * f + J] * wih[J]);
 #pragma unroll
-      for (int J = 0; J < 3; ++J) b1p[3][J] = (double)(wdet * kfg * gw[J] * ih[J]);
+      for (int J = 0; J < 3; ++J) b1p[3][J] = (double)(kfg * gw[J] * wih[J]);
     }
     b0p3 = (double)(wdet * a.fr.s_phi * dL);
     // back to each element's padded layout, transposed interpolation
@@ -1026,37 +1056,40 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q3(LinApplyArgs<V> a, int colour,
   const BrickGeom g = BB ? decode_brick_lin(a.m, brick) : decode_brick(a.m, colour, brick);
   const Basis4 bf = load_basis4<4>(tabs);
   const Basis4 bc = load_basis4<PC>(tabs);
-  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int l = threadIdx.x & 63, wv = wave_id();
+  const uint32_t lf = lane_node<4>(a.fine.nx1, a.fine.ny1), lc = lane_node<PC>(a.lev.nx1, a.lev.ny1);
+  const bool has_c = lane_has_node<PC>();
   const int qx = l & 3, qz = (l >> 2) & 3, qy = l >> 4;
   const int ql = qx + 4 * qy + 16 * qz;
   const V ih[3] = {(V)a.m.ih[0], (V)a.m.ih[1], (V)a.m.ih[2]};
   const V wbox = (V)(tabs->w[4][qx] * tabs->w[4][qy] * tabs->w[4][qz] * a.m.jdet);
+  const V wih[3] = {wbox * ih[0], wbox * ih[1], wbox * ih[2]};
 #pragma unroll 1
   for (int half = 0; half < 2; ++half) {
     const int slot = wv + 4 * half;
     const int sx = slot & 1, sy = (slot >> 1) & 1, sz = slot >> 2;
     if (!(sx < g.nex && sy < g.ney && sz < g.nez)) continue;  // uniform per wave
-    const int64_t gf = lane_node<4>(g, sx, sy, sz, a.fine.nx1, a.fine.ny1);
-    const int64_t gc = lane_node<PC>(g, sx, sy, sz, a.lev.nx1, a.lev.ny1);
+    const int64_t nf = first_node<4>(g, sx, sy, sz, a.fine.nx1, a.fine.ny1);
+    const int64_t nc = first_node<PC>(g, sx, sy, sz, a.lev.nx1, a.lev.ny1);
     double zu[3], wu[4];
 #pragma unroll
-    for (int f = 0; f < 3; ++f) zu[f] = (double)a.z32[f * a.fine.n_nodes + gf];
+    for (int f = 0; f < 3; ++f) zu[f] = (double)(a.z32 + (f * a.fine.n_nodes + nf))[lf];
 #pragma unroll
-    for (int f = 0; f < 4; ++f) wu[f] = gc >= 0 ? (double)a.dz[f * a.lev.n_nodes + gc] : 0.0;
+    for (int f = 0; f < 4; ++f) wu[f] = has_c ? (double)(a.dz + (f * a.lev.n_nodes + nc))[lc] : 0.0;
     const int64_t e = (int64_t)(g.ex0 + sx) + (int64_t)a.m.nx * ((g.ey0 + sy) + (int64_t)a.m.ny * (g.ez0 + sz));
     const int64_t gq = e * 64 + ql;
     LinRecordT<V> rc;
 #pragma unroll
-    for (int k = 0; k < REC_N; ++k) rc.v[k] = a.rec.rec[k * a.n_q + gq];
-    rc.flags = a.rec.flags[gq];
-    const int pid = a.phase[gq];
+    for (int k = 0; k < REC_N; ++k) rc.v[k] = (a.rec.rec + (k * a.n_q + e * 64))[ql];
+    rc.flags = (a.rec.flags + e * 64)[ql];
+    const int pid = (a.phase + e * 64)[ql];
     // mapped elements: the point's J^-1 and weight
     double gA[GEO ? 9 : 1];
     V wdet = wbox;
     if (GEO) {
 #pragma unroll
-      for (int k = 0; k < 9; ++k) gA[k] = a.qd[k * a.n_q + gq];
-      wdet = (V)a.qd[9 * a.n_q + gq];
+      for (int k = 0; k < 9; ++k) gA[k] = (a.qd + (k * a.n_q + e * 64))[ql];
+      wdet = (V)(a.qd + (9 * a.n_q + e * 64))[ql];
     }
     V G[9], W[9], wphi, gw[3];
     {
@@ -1111,10 +1144,10 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q3(LinApplyArgs<V> a, int colour,
       for (int f = 0; f < 3; ++f) {
         b0[f] = 0.0;
 #pragma unroll
-        for (int J = 0; J < 3; ++J) b1[f][J] = (double)(wdet * Fu[3 * f + J] * ih[J]);
+        for (int J = 0; J < 3; ++J) b1[f][J] = (double)(Fu[3 * f + J] * wih[J]);
       }
 #pragma unroll
-      for (int J = 0; J < 3; ++J) b1[3][J] = (double)(wdet * kfg * gw[J] * ih[J]);
+      for (int J = 0; J < 3; ++J) b1[3][J] = (double)(kfg * gw[J] * wih[J]);
     }
     b0[3] = (double)(wdet * a.fr.s_phi * dL);
     sf4_bwd_n<4>(b0, b1, 0x8u, bc, r);

@@ -52,12 +52,12 @@ __device__ inline bool xcd_elem(const MeshDev& m, int colour, int id, ElemGeom& 
 // elements on one XCD, back to back).
 __host__ __device__ inline int xcd_grid_elems(int nx, int ny, int nz) { return ((ny * nz + 7) / 8) * 8 * nx; }
 __device__ inline bool xcd_elem_all(const MeshDev& m, int id, ElemGeom& g) {
-  const int t = id >> 3;
-  const int row = (t / m.nx) * 8 + (id & 7);
+  const int t = id >> 3, q = m.by_nx.div(t);
+  const int row = q * 8 + (id & 7);
   if (row >= m.ny * m.nz) return false;
-  g.ex = t % m.nx;
-  g.ey = row % m.ny;
-  g.ez = row / m.ny;
+  g.ex = t - q * m.nx;
+  g.ez = m.by_ny.div(row);
+  g.ey = row - g.ez * m.ny;
   return true;
 }
 
@@ -420,7 +420,7 @@ template <int P, int Q, bool CV = false> struct Q5Lds {
 // GEO): table restriction, element e = workgroup (XCD-aware order), nodes from a.conn,
 // the element vector stored node-major to a.evec (summed per node by k_gather_csr).
 template <int MODE, bool VOCE, bool MB, bool GEO, bool EV = false, bool TAB = false>
-__global__ __launch_bounds__(NT5, 2) void k_op64_q4(OpArgs a, int colour, DevTables* __restrict__ tabs) {
+__global__ __launch_bounds__(NT5, MB || GEO ? 2 : 3) void k_op64_q4(OpArgs a, int colour, DevTables* __restrict__ tabs) {
   static_assert(!TAB || (GEO && !MB), "the table restriction runs on mapped elements without branches");
   constexpr int P = 5, Q = 5, Q3 = 125;
   // compact point arrays (13 of 125 values each): 25 KB of LDS per element instead of 28,
@@ -512,11 +512,9 @@ __global__ __launch_bounds__(NT5, 2) void k_op64_q4(OpArgs a, int colour, DevTab
     ts_piola(mp, s, Fu);
     double Lr = s.L;
     if (MB) Lr = mb_residual<VOCE>(a, mp, pidc, gq, pt, sG, phi, phin, st[7], s.psi, s.gp, Fu, xbad);
-#pragma unroll
-    for (int k = 0; k < 9; ++k) Fu[k] *= wdet;
     f0 = wdet * a.fr.s_phi * Lr;
 #pragma unroll
-    for (int J = 0; J < 3; ++J) f1[J] = wdet * kfg * gphi[J];
+    for (int J = 0; J < 3; ++J) f1[J] = kfg * gphi[J];
   } else if (MODE == M_JAC) {
     double dL;
     if (MB) {
@@ -524,11 +522,9 @@ __global__ __launch_bounds__(NT5, 2) void k_op64_q4(OpArgs a, int colour, DevTab
       dL = mb_jacobian<VOCE>(a, mp, s, pidc, gq, pt, sG, phi, phi, st[7], W, sW, wphi, Fu, xbad);
     } else
       ts_tangent(mp, s, W, wphi, Fu, dL);
-#pragma unroll
-    for (int k = 0; k < 9; ++k) Fu[k] *= wdet;
     f0 = wdet * a.fr.s_phi * dL;
 #pragma unroll
-    for (int J = 0; J < 3; ++J) f1[J] = wdet * kfg * gw[J];
+    for (int J = 0; J < 3; ++J) f1[J] = kfg * gw[J];
   } else {
     double Pb[9];
 #pragma unroll
@@ -561,10 +557,12 @@ __global__ __launch_bounds__(NT5, 2) void k_op64_q4(OpArgs a, int colour, DevTab
   if (MB) bad |= pt && xbad;
   // point coefficients into Qi (bufB is free: every thread has read its values)
   if (pt) {
+    const double ws = MODE == M_ADJ ? 1.0 : wdet;  // the adjoint's cotangents carry the weight already
+    const double wih[3] = {ws * ih[0], ws * ih[1], ws * ih[2]};
 #pragma unroll
     for (int f = 0; f < 4; ++f) {
       double b[3];
-      phys_to_ref<GEO>(f < 3 ? Fu + 3 * f : f1, ih, gA, b);
+      phys_to_ref_w<GEO>(f < 3 ? Fu + 3 * f : f1, wih, gA, ws, b);
 #pragma unroll
       for (int K = 0; K < 3; ++K) bufB[qslot<true>(f, 1 + K) * Q3 + ql] = b[K];
     }
@@ -694,13 +692,14 @@ __global__ __launch_bounds__(NT5, 2) void k_a32_q4(LinApplyArgs<V> a, int colour
     }
     bufB[qslot<true>(3, 0) * Q3 + ql] = wdet * a.fr.s_phi * dL;
   } else if (pt) {
+    const V wih[3] = {wdet * ih[0], wdet * ih[1], wdet * ih[2]};
 #pragma unroll
     for (int f = 0; f < 3; ++f)
 #pragma unroll
-      for (int J = 0; J < 3; ++J) bufB[qslot<true>(f, 1 + J) * Q3 + ql] = wdet * Fu[3 * f + J] * ih[J];
+      for (int J = 0; J < 3; ++J) bufB[qslot<true>(f, 1 + J) * Q3 + ql] = Fu[3 * f + J] * wih[J];
     bufB[qslot<true>(3, 0) * Q3 + ql] = wdet * a.fr.s_phi * dL;
 #pragma unroll
-    for (int J = 0; J < 3; ++J) bufB[qslot<true>(3, 1 + J) * Q3 + ql] = wdet * kfg * gw[J] * ih[J];
+    for (int J = 0; J < 3; ++J) bufB[qslot<true>(3, 1 + J) * Q3 + ql] = kfg * gw[J] * wih[J];
   }
   __syncthreads();
   sf5_bwd<V, Tab, PC, Q, 4, true>(bufB, bufA, tabs);
@@ -794,13 +793,14 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2r(LinApplyArgs<V> a, const type
   lin_tangent<V, false>(a.rec, a.n_q, a.xmats, a.n_extra, mp, s, pidc, gq, pt, G, W, wphi, Fu, dL);
   const V kfg = a.fr.kf * mp.Gc;
   if (pt) {
+    const V wih[3] = {wdet * ih[0], wdet * ih[1], wdet * ih[2]};
 #pragma unroll
     for (int f = 0; f < 3; ++f)
 #pragma unroll
-      for (int J = 0; J < 3; ++J) B[qslot<true>(f, 1 + J) * Q3 + ql] = wdet * Fu[3 * f + J] * ih[J];
+      for (int J = 0; J < 3; ++J) B[qslot<true>(f, 1 + J) * Q3 + ql] = Fu[3 * f + J] * wih[J];
     B[qslot<true>(3, 0) * Q3 + ql] = wdet * a.fr.s_phi * dL;
 #pragma unroll
-    for (int J = 0; J < 3; ++J) B[qslot<true>(3, 1 + J) * Q3 + ql] = wdet * kfg * gw[J] * ih[J];
+    for (int J = 0; J < 3; ++J) B[qslot<true>(3, 1 + J) * Q3 + ql] = kfg * gw[J] * wih[J];
   }
   __syncthreads();
   sf5_bwd<V, Tab, PC, Q, 4, true, NE, NT>(bufB, bufA, tabs, L::B, L::A);
@@ -906,19 +906,15 @@ __global__ __launch_bounds__(NT, 2) void k_op64_q2r(OpArgs a, DevTables* __restr
   double gsum[3] = {0.0, 0.0, 0.0};
   if (MODE == M_RES) {
     ts_piola(mp, s, Fu);
-#pragma unroll
-    for (int k = 0; k < 9; ++k) Fu[k] *= wdet;
     f0 = wdet * a.fr.s_phi * s.L;
 #pragma unroll
-    for (int J = 0; J < 3; ++J) f1[J] = wdet * kfg * gphi[J];
+    for (int J = 0; J < 3; ++J) f1[J] = kfg * gphi[J];
   } else if (MODE == M_JAC) {
     double dL;
     ts_tangent(mp, s, W, wphi, Fu, dL);
-#pragma unroll
-    for (int k = 0; k < 9; ++k) Fu[k] *= wdet;
     f0 = wdet * a.fr.s_phi * dL;
 #pragma unroll
-    for (int J = 0; J < 3; ++J) f1[J] = wdet * kfg * gw[J];
+    for (int J = 0; J < 3; ++J) f1[J] = kfg * gw[J];
   } else {
     double Pb[9];
 #pragma unroll
@@ -944,10 +940,12 @@ __global__ __launch_bounds__(NT, 2) void k_op64_q2r(OpArgs a, DevTables* __restr
   }
   // point coefficients into the point arrays (every thread has read its values)
   if (pt) {
+    const double ws = MODE == M_ADJ ? 1.0 : wdet;  // the adjoint's cotangents carry the weight already
+    const double wih[3] = {ws * ih[0], ws * ih[1], ws * ih[2]};
 #pragma unroll
     for (int f = 0; f < 4; ++f)
 #pragma unroll
-      for (int K = 0; K < 3; ++K) B[qslot<true>(f, 1 + K) * Q3 + ql] = (f < 3 ? Fu[3 * f + K] : f1[K]) * ih[K];
+      for (int K = 0; K < 3; ++K) B[qslot<true>(f, 1 + K) * Q3 + ql] = (f < 3 ? Fu[3 * f + K] : f1[K]) * wih[K];
     B[qslot<true>(3, 0) * Q3 + ql] = f0;
   }
   __syncthreads();

@@ -368,32 +368,30 @@ __device__ inline T inverse33(const T* F, T* Fi) {
 }
 
 // F^-1, A = b_tr - I (Voigt) and det F from G = grad_X u (row-major) and D = st[0..5] (Voigt):
-// A = G + G^T + G G^T + F D F^T (eq:inelasticity-be-update, Cin^-1 = I + D).
+// A = G + G^T + G G^T + F D F^T (eq:inelasticity-be-update, Cin^-1 = I + D), formed as
+// G^T + H + H G^T with H = F Cin^-1 - I = G + F D.
 template <typename T>
 __device__ inline T kinematics(const T* G, const T* st, T* Fi, T* A) {
   T F[9];
 #pragma unroll
   for (int k = 0; k < 9; ++k) F[k] = G[k] + ((k % 4 == 0) ? T(1) : T(0));
   const T det = inverse33<T>(F, Fi);
-  const int ri[6] = {0, 1, 2, 1, 0, 0}, ci[6] = {0, 1, 2, 2, 2, 1};
-  T FD[9];
+  T H[9];
   {
     const T D00 = st[0], D11 = st[1], D22 = st[2], D12 = st[3], D02 = st[4], D01 = st[5];
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
       const T f0 = F[3 * i], f1 = F[3 * i + 1], f2 = F[3 * i + 2];
-      FD[3 * i + 0] = f0 * D00 + f1 * D01 + f2 * D02;
-      FD[3 * i + 1] = f0 * D01 + f1 * D11 + f2 * D12;
-      FD[3 * i + 2] = f0 * D02 + f1 * D12 + f2 * D22;
+      H[3 * i + 0] = G[3 * i + 0] + f0 * D00 + f1 * D01 + f2 * D02;
+      H[3 * i + 1] = G[3 * i + 1] + f0 * D01 + f1 * D11 + f2 * D12;
+      H[3 * i + 2] = G[3 * i + 2] + f0 * D02 + f1 * D12 + f2 * D22;
     }
   }
+  const int ri[6] = {0, 1, 2, 1, 0, 0}, ci[6] = {0, 1, 2, 2, 2, 1};
 #pragma unroll
   for (int k = 0; k < 6; ++k) {
     const int i = ri[k], j = ci[k];
-    T v = G[3 * i + j] + G[3 * j + i];
-#pragma unroll
-    for (int l = 0; l < 3; ++l) v += G[3 * i + l] * G[3 * j + l] + FD[3 * i + l] * F[3 * j + l];
-    A[k] = v;
+    A[k] = G[3 * j + i] + H[3 * i + j] + H[3 * i] * G[3 * j] + H[3 * i + 1] * G[3 * j + 1] + H[3 * i + 2] * G[3 * j + 2];
   }
   return det;
 }

@@ -12,15 +12,17 @@
 // by a difference of eigenvalues, so repeated eigenvalues need no case of their own, and the
 // strain's derivative (Appendices A-B) is
 //     de = c1 dS + c2 dev(S dS + dS S) + (g3 dJ2 + g4 dJ3) S + (g4 dJ2 + g5 dJ3) Q,
-// dJ2 = S:dS, dJ3 = Q:dS, a self-adjoint map of dS (the transpose uses it again).
+// dJ2 = S:dS, dJ3 = Q:dS, a self-adjoint map of dS (the transpose uses it again). The products
+// of e come from the invariants as well: S:S = 2 J2, S:Q = 3 J3, Q:Q = (2/3) J2^2.
 //
 // The FP64 applies are bound by VALU issue. The principal form (eigenvalues, an orthonormal
 // frame with polish rotations, three logarithms, divided differences, the tangent rotated
 // there and back) took 1,152 vector instructions per order-3 element in the Jacobian beside its
-// 93 matrix-core ones; this form takes 860, and 175 registers instead of 217. Order-3 Jacobian on
-// 48^3 elements 0.462 -> 0.400 ms, with two extra branches on 32^3 0.310 -> 0.238 (18 spilled
-// registers -> none), order 4 on 40^3 0.644 -> 0.588, order 2 on 32^3 0.097 -> 0.091. The
-// linearisation record and the state commit keep the principal form (their data are principal).
+// 93 matrix-core ones; this form takes 768, and 168 registers (3 waves per SIMD) instead of
+// 217. Order-3 Jacobian on 48^3 elements 0.465 -> 0.377 ms, with two extra branches on 32^3
+// 0.310 -> 0.237 (18 spilled registers -> none), order 4 on 40^3 0.644 -> 0.576, order 2 on 32^3
+// 0.097 -> 0.088. The linearisation record and the state commit keep the principal form (their
+// data are principal).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -35,7 +37,6 @@ struct TState {
   double S[6], Q[6];          // b_tr / m - I and dev(S^2)
   double J2, J3;              // invariants of S
   double c1, c2, g3, g4, g5;  // log coefficients and their derivatives
-  double e[6];                // deviatoric trial log strain
   double ee, theta;           // e:e and tr eps
   double g, gp, c, kq, kphi;  // degradation, return factor and its tangent (as in QPState)
   double psi, H, L, dLcoef, ddg_s0, ddg_visc, dg;
@@ -155,17 +156,31 @@ __device__ inline double sym_dot(const double* a, const double* b) {
   return a[0] * b[0] + a[1] * b[1] + a[2] * b[2] + 2.0 * (a[3] * b[3] + a[4] * b[4] + a[5] * b[5]);
 }
 
-// de = L(dS) of the header comment for traceless dS; dJ2 = S:dS and dJ3 = Q:dS given.
-__device__ inline void log_tangent(const TState& s, const double* dS, double dJ2, double dJ3, double* de) {
+// A tensor as c1 D + c2 dev(S D + D S) + a S + b Q of the point's S and Q and a traceless D.
+struct LogMap {
+  double c1, c2, a, b;
+};
+
+// L(dS) of the header comment, its inner products dJ2 = S:dS and dJ3 = Q:dS given; ede = e:de.
+__device__ inline LogMap log_tangent(const TState& s, double dJ2, double dJ3, double& ede) {
+  const LogMap m{s.c1, s.c2, s.g3 * dJ2 + s.g4 * dJ3, s.g4 * dJ2 + s.g5 * dJ3};
+  const double j2 = kst(2.0 / 3.0) * s.J2 * s.c2, j3 = 3.0 * s.J3;
+  // e:dS = c1 dJ2 + c2 dJ3, e:(S dS + dS S) = 2 c1 dJ3 + (2/3) c2 J2 dJ2
+  ede = m.c1 * (m.c1 * dJ2 + m.c2 * dJ3) + m.c2 * (2.0 * m.c1 * dJ3 + j2 * dJ2) +
+        m.a * (2.0 * m.c1 * s.J2 + m.c2 * j3) + m.b * (m.c1 * j3 + j2 * s.J2);
+  return m;
+}
+
+// out = the tensor of m for D with S:D = SD.
+__device__ inline void log_expand(const TState& s, const LogMap& m, const double* D, double SD, double* out) {
   double Y[6];
-  sym_anticommutator(s.S, dS, Y);
-  const double a = s.g3 * dJ2 + s.g4 * dJ3, b = s.g4 * dJ2 + s.g5 * dJ3;
-  const double tr = kst(2.0 / 3.0) * s.c2 * dJ2;
+  sym_anticommutator(s.S, D, Y);
+  const double tr = kst(2.0 / 3.0) * m.c2 * SD;
 #pragma unroll
   for (int k = 0; k < 6; ++k) {
-    double v = s.c1 * dS[k] + s.c2 * Y[k] + a * s.S[k] + b * s.Q[k];
+    double v = m.c1 * D[k] + m.c2 * Y[k] + m.a * s.S[k] + m.b * s.Q[k];
     if (k < 3) v -= tr;
-    de[k] = v;
+    out[k] = v;
   }
 }
 
@@ -271,9 +286,7 @@ __device__ inline void ts_state(const MatParams<double>& m, const FracParams<dou
     if (!s.bad) log_quadrature<TAN>(I2, I3, s);
   }
   if (s.bad) s.c1 = s.c2 = __builtin_nan("");
-#pragma unroll
-  for (int k = 0; k < 6; ++k) s.e[k] = s.c1 * s.S[k] + s.c2 * s.Q[k];
-  s.ee = sym_dot(s.e, s.e);
+  s.ee = 2.0 * s.c1 * (s.c1 * s.J2 + 3.0 * s.c2 * s.J3) + kst(2.0 / 3.0) * (s.c2 * s.J2) * (s.c2 * s.J2);
   // tr eps = log(det b_tr) / 2: det b_tr = m^3 (1 - J2 + J3) formed about 1 where it is near 1,
   // else det F^2 det(I + D)
   const double v = t * fma(t, kst(3.0) + t, kst(3.0)), w = s.J3 - s.J2, x = v + w + v * w;
@@ -287,8 +300,9 @@ __device__ inline void ts_state(const MatParams<double>& m, const FracParams<dou
 // Degraded Kirchhoff stress tau_degr (symmetric).
 __device__ inline void ts_stress(const MatParams<double>& m, const TState& s, double* tau) {
   const double a = 2.0 * m.mu * s.c * s.g, kt = m.kappa * s.theta, vol = s.tension ? s.g * kt : kt;
+  const double a1 = a * s.c1, a2 = a * s.c2;
 #pragma unroll
-  for (int k = 0; k < 6; ++k) tau[k] = k < 3 ? fma(a, s.e[k], vol) : a * s.e[k];
+  for (int k = 0; k < 6; ++k) tau[k] = fma(a1, s.S[k], k < 3 ? fma(a2, s.Q[k], vol) : a2 * s.Q[k]);
 }
 
 // First Piola stress P = tau_degr F^-T (eq:mechanical-gradient-transformation).
@@ -309,24 +323,30 @@ __device__ inline void ts_tangent_psi(const MatParams<double>& m, const TState& 
   mul_sym(dl, s.S, U);
 #pragma unroll
   for (int k = 0; k < 9; ++k) U[k] += dl[k];
-  double dS[6] = {2.0 * U[0], 2.0 * U[4], 2.0 * U[8], U[5] + U[7], U[2] + U[6], U[1] + U[3]};  // X
-  const double t3 = (dS[0] + dS[1] + dS[2]) * kst(1.0 / 3.0);
+  double X[6] = {2.0 * U[0], 2.0 * U[4], 2.0 * U[8], U[5] + U[7], U[2] + U[6], U[1] + U[3]};
+  const double t3 = (X[0] + X[1] + X[2]) * kst(1.0 / 3.0);
 #pragma unroll
-  for (int k = 0; k < 6; ++k) dS[k] = (k < 3 ? dS[k] - t3 : dS[k]) - t3 * s.S[k];
-  const double dJ2 = sym_dot(s.S, dS), dJ3 = sym_dot(s.Q, dS);
-  double de[6];
-  log_tangent(s, dS, dJ2, dJ3, de);
+  for (int k = 0; k < 3; ++k) X[k] -= t3;  // dev X: dS = dev X - t3 S
+  const double SX = sym_dot(s.S, X);
+  const double dJ2 = SX - 2.0 * t3 * s.J2, dJ3 = sym_dot(s.Q, X) - 3.0 * t3 * s.J3;
+  double ede;
+  LogMap de = log_tangent(s, dJ2, dJ3, ede);
   const double dth = dl[0] + dl[4] + dl[8];
   // linearised return: d(c e) = c de + e (kq e:de + kphi dphi)
-  const double ede = sym_dot(s.e, de);
   const double kk = s.kq * ede + s.kphi * dphi;
-  // degraded stress increment (eq:linear-degraded-stress-linearization) a de + b e + vol I
+  // degraded stress increment (eq:linear-degraded-stress-linearization) a de + b e + vol I, in
+  // terms of dev X: dev(S dS + dS S) = dev(S X + X S) - 2 t3 Q
   const double tm2 = 2.0 * m.mu, kt = m.kappa * s.theta, kdt = m.kappa * dth;
   const double a = s.g * tm2 * s.c, b = tm2 * (s.g * kk + s.gp * dphi * s.c);
   const double vol = s.tension ? s.g * kdt + s.gp * dphi * kt : kdt;
+  de.a = a * (de.a - t3 * de.c1) + b * s.c1;
+  de.b = a * (de.b - 2.0 * t3 * de.c2) + b * s.c2;
+  de.c1 *= a;
+  de.c2 *= a;
   double dt[6], tau[6];
+  log_expand(s, de, X, SX, dt);
 #pragma unroll
-  for (int k = 0; k < 6; ++k) dt[k] = a * de[k] + b * s.e[k] + (k < 3 ? vol : 0.0);
+  for (int k = 0; k < 3; ++k) dt[k] += vol;
   ts_stress(m, s, tau);
   const int ix[9] = {0, 5, 4, 5, 1, 3, 4, 3, 2};
   double Z[9];
@@ -360,7 +380,8 @@ __device__ inline void ts_tangent_T_psi(const MatParams<double>& m, const TState
   mul33(Pb, s.Fi, Zb);
   ts_stress(m, s, tau);
   double E[6] = {Zb[0], Zb[4], Zb[8], 0.5 * (Zb[5] + Zb[7]), 0.5 * (Zb[2] + Zb[6]), 0.5 * (Zb[1] + Zb[3])};
-  xe = sym_dot(E, s.e);
+  const double eS0 = sym_dot(s.S, E), eQ0 = sym_dot(s.Q, E);
+  xe = s.c1 * eS0 + s.c2 * eQ0;
   const double tz = Zb[0] + Zb[4] + Zb[8];
   // dtau = a de + b e + vol I
   phib = phib0 + tm2 * s.gp * s.c * xe + (s.tension ? s.gp * kt * tz : 0.0);
@@ -370,11 +391,17 @@ __device__ inline void ts_tangent_T_psi(const MatParams<double>& m, const TState
   const double edeb = s.kq * kkb + tm2 * s.c * s.c * Hb;
   const double a = s.g * tm2 * s.c, tz3 = tz * kst(1.0 / 3.0);
 #pragma unroll
-  for (int k = 0; k < 6; ++k) E[k] = a * (k < 3 ? E[k] - tz3 : E[k]) + edeb * s.e[k];
-  // de = L(dS), dS = dev X - (tr X / 3) S
-  const double eS = sym_dot(s.S, E), eQ = sym_dot(s.Q, E);
+  for (int k = 0; k < 3; ++k) E[k] -= tz3;  // the stress cotangent's deviator; de's is a E + edeb e
+  // L of it: L(E) by the map, L(e) = the tensor of (c1 e + c2 dev(S e + e S) + ...), with
+  // dev(S S + S S) = 2 Q and dev(S Q + Q S) = (2/3) J2 S
+  const double j2 = kst(2.0 / 3.0) * s.J2, j3 = 3.0 * s.J3;
+  const double eS = a * eS0 + edeb * (2.0 * s.c1 * s.J2 + s.c2 * j3);
+  const double eQ = a * eQ0 + edeb * (s.c1 * j3 + s.c2 * j2 * s.J2);
+  const LogMap lm{a * s.c1, a * s.c2, s.g3 * eS + s.g4 * eQ + edeb * (s.c1 * s.c1 + j2 * s.c2 * s.c2),
+                  s.g4 * eS + s.g5 * eQ + 3.0 * edeb * s.c1 * s.c2};
   double Xb[6];
-  log_tangent(s, E, eS, eQ, Xb);
+  log_expand(s, lm, E, eS0, Xb);
+  // dS = dev X - (tr X / 3) S
   const double xs3 = sym_dot(s.S, Xb) * kst(1.0 / 3.0);
 #pragma unroll
   for (int k = 0; k < 3; ++k) Xb[k] -= xs3;

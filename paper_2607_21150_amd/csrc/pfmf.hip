@@ -55,6 +55,11 @@ MeshDev mesh_dev(const pf_ctx* c) {
   m.nbx = c->nbx;
   m.nby = c->nby;
   m.nbz = c->nbz;
+  // (a mesh given by its table has no lattice: its zero sides are never divided by)
+  m.by_nx = FastDiv::of(std::max(m.nx, 1));
+  m.by_ny = FastDiv::of(std::max(m.ny, 1));
+  m.by_nbx = FastDiv::of(std::max(m.nbx, 1));
+  m.by_nby = FastDiv::of(std::max(m.nby, 1));
   m.hx = c->mesh.lx / c->mesh.nx;
   m.hy = c->mesh.ly / c->mesh.ny;
   m.hz = c->mesh.lz / c->mesh.nz;
