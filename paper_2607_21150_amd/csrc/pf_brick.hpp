@@ -37,6 +37,9 @@ struct DevTablesF {
   float D[6][6][5][5];
   float w[6][5];
   float G[6][5][5];
+  // products of two order-1 bases at the Q points: pair[Q][type][a + 2 b][q] = T[q][a] U[q][b],
+  // T = D for type & 1 (else B), U = D for type & 2
+  float pair[6][4][4][5];
 };
 
 struct BrickGeom {

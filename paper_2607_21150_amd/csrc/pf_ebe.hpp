@@ -12,6 +12,7 @@
 
 #include "pf_brick.hpp"
 #include "pf_mg.hpp"
+#include "pf_q4.hpp"
 #include "pf_qf.hpp"
 
 namespace pfmf {
@@ -32,187 +33,366 @@ struct EbeArgs {
   const double* qd;     // GEO: mapped elements' geometry record [10][n_q] (J^-1, w det J)
 };
 
-// One workgroup per element. The threads evaluate the tangent of the points on the
-// 10 unit directions (dG_ij, dphi) into LDS; the element matrix is then the
-// point sum of (test basis) x tangent x (trial basis), contracted in two steps.
-// GEO: mapped elements (gradients and weights from the points' geometry record).
-template <int PF, bool MB, bool GEO = false>
-__global__ __launch_bounds__(NT) void k_ebe_assemble(EbeArgs a, DevTablesF* __restrict__ tabs) {
-  constexpr int Q = PF, Q3 = Q * Q * Q, P3 = PF * PF * PF;
-  __shared__ float ub[3 * P3];      // fine u of the element
-  __shared__ float Cq[Q3][101];     // tangent columns (10 x 10) and wdet per point
-  __shared__ float Bf[Q * PF], Df[Q * PF], B1[Q * 2], D1[Q * 2], wq[Q];
-  constexpr int QC = 8;              // points per chunk of the second contraction
-  __shared__ float Nq[Q3][8], Gq[Q3][8][3], kq[Q3];
-  __shared__ float Tq[QC][10][32];
-  const int64_t e = blockIdx.x;
-  const int ex = (int)(e % a.m.nx), ey = (int)((e / a.m.nx) % a.m.ny), ez = (int)(e / ((int64_t)a.m.nx * a.m.ny));
-  const int t = threadIdx.x;
-  for (int i = t; i < Q * PF; i += NT) {
-    Bf[i] = tabs->B[PF][Q][i / PF][i % PF];
-    Df[i] = tabs->D[PF][Q][i / PF][i % PF];
-  }
-  if (t < 2 * Q) {
-    B1[t] = tabs->B[2][Q][t / 2][t % 2];
-    D1[t] = tabs->D[2][Q][t / 2][t % 2];
-  }
-  if (t < Q) wq[t] = tabs->w[Q][t];
-  constexpr int p = PF - 1;
-  for (int i = t; i < 3 * P3; i += NT) {
-    const int f = i / P3, n = i % P3;
-    const int ax = n % PF, ay = (n / PF) % PF, az = n / (PF * PF);
-    const int64_t gi = (int64_t)(ex * p + ax) + (int64_t)a.fine.nx1 * ((ey * p + ay) + (int64_t)a.fine.ny1 * (ez * p + az));
-    ub[i] = a.z32[f * a.fine.n_nodes + gi];
-  }
-  __syncthreads();
-  const float ih[3] = {(float)a.m.ih[0], (float)a.m.ih[1], (float)a.m.ih[2]};
-  const float jdet = (float)a.m.jdet;
-  // the displacement gradient of each point, once, for the NG thread groups below: one
-  // task per (point, displacement field) when they fit the workgroup in one round, else
-  // one per point (the basis products then serve the three fields). Gs lives in Tq, which
-  // the second contraction fills only after the tangents have been taken.
-  static_assert(Q3 * 9 <= QC * 10 * 32, "the point gradients fit the contraction buffer");
-  float (*Gs)[9] = reinterpret_cast<float (*)[9]>(&Tq[0][0][0]);
-  constexpr int NFT = 3 * Q3 <= NT ? 1 : 3;  // fields per task
-  for (int task = t; task < (3 / NFT) * Q3; task += NT) {
-    const int q = task % Q3, f0 = (task / Q3) * NFT;
-    const int qx = q % Q, qy = (q / Q) % Q, qz = q / (Q * Q);
-    float g[NFT][3];
+// The tangent of one record layer by the displacement gradient's components: with
+// E_ab(kL) = N_ka (F^-1 N)_Lb, Lt_ab = sum E_ab(kL) dG_kL (the principal-frame form of
+// qp_tangent_psi), Z_aa = sum_b M_ab Lt_bb and Z_ab = p_ab Lt_ab + q_ab Lt_ba, the tangent is
+// dP_fJ = sum_ab N_fa (F^-1 N)_Jb Z_ab, dpsi^+ = sum_b h_b Lt_bb + hphi dphi and
+// dP/dphi = sum_a N_fa (F^-1 N)_Ja zphi_a.
+struct TangentFactors {
+  float N[9], R[9];   // frame and F^-1 N, the latter in reference directions (times J^-1 or 2/h)
+  float M[9];         // diagonal block
+  float p[9], q[9];   // off-diagonal factors (a != b)
+  float zphi[3], h[3], hphi;
+};
+
+__device__ inline void tangent_factors(const MatParams<float>& m, const QPState<float>& s, TangentFactors& t) {
+  const float tm2 = 2.f * m.mu, kt = m.kappa * s.theta, tmc = tm2 * s.c;
+  const float kap = s.tension ? s.g * m.kappa : m.kappa;
+  const float ee = s.e[0] * s.e[0] + s.e[1] * s.e[1] + s.e[2] * s.e[2];
+  float td[3];
 #pragma unroll
-    for (int k = 0; k < NFT; ++k) g[k][0] = g[k][1] = g[k][2] = 0.f;
-    for (int n = 0; n < P3; ++n) {
-      const int ax = n % PF, ay = (n / PF) % PF, az = n / (PF * PF);
-      const float bx = Bf[qx * PF + ax], by = Bf[qy * PF + ay], bz = Bf[qz * PF + az];
-      const float dx = Df[qx * PF + ax] * by * bz, dy = bx * Df[qy * PF + ay] * bz, dz = bx * by * Df[qz * PF + az];
+  for (int i = 0; i < 3; ++i) {
+    const float taubd = tmc * s.e[i];
+    td[i] = s.tension ? s.g * (taubd + kt) : s.g * taubd + kt;
+    t.zphi[i] = tm2 * s.g * s.e[i] * s.kphi + s.gp * (s.tension ? taubd + kt : taubd);
+    t.h[i] = tmc * (s.c + ee * s.kq) * s.e[i] + (s.tension ? kt : 0.f);
+  }
+  t.hphi = tmc * ee * s.kphi;
+  const float co[9] = {0.f, s.coef[2], s.coef[1], s.coef[2], 0.f, s.coef[0], s.coef[1], s.coef[0], 0.f};
 #pragma unroll
-      for (int k = 0; k < NFT; ++k) {
-        const float u = ub[(f0 + k) * P3 + n];
-        g[k][0] += u * dx;
-        g[k][1] += u * dy;
-        g[k][2] += u * dz;
-      }
-    }
-    double gA[GEO ? 9 : 1];
-    if (GEO) {
-      const int64_t gq = e * Q3 + q;
+  for (int i = 0; i < 3; ++i)
 #pragma unroll
-      for (int k = 0; k < 9; ++k) gA[k] = a.qd[k * a.n_q + gq];
+    for (int j = 0; j < 3; ++j) {
+      t.M[3 * i + j] = s.g * (tmc * ((i == j ? 1.f : 0.f) - 1.f / 3.f) + tm2 * s.kq * s.e[i] * s.e[j]) + kap -
+                       (i == j ? td[i] : 0.f);
+      t.p[3 * i + j] = co[3 * i + j] * s.bd[j];
+      t.q[3 * i + j] = co[3 * i + j] * s.bd[i] - td[i];
     }
 #pragma unroll
-    for (int k = 0; k < NFT; ++k) {
-      if (GEO) {  // reference derivatives to physical ones
-        map_grad<float>(g[k][0], g[k][1], g[k][2], gA, g[k]);
+  for (int k = 0; k < 9; ++k) t.N[k] = s.N[k];
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+      t.R[3 * i + j] = s.Fi[3 * i] * s.N[j] + s.Fi[3 * i + 1] * s.N[3 + j] + s.Fi[3 * i + 2] * s.N[6 + j];
+}
+
+// Adds the columns of trial field K: C[3 (3 f + J) + L] += dP_fJ / dG_KL and
+// H[L] += dpsi^+ / dG_KL (reference directions J, L).
+template <int K>
+__device__ inline void tangent_columns(const TangentFactors& t, float* C, float* H) {
+  const float n[3] = {t.N[3 * K], t.N[3 * K + 1], t.N[3 * K + 2]};
+  float O[9][3];  // O_ab(L) = sum of (M, p, q) E
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      if (a == b) {
+        const float c0 = t.M[3 * a] * n[0], c1 = t.M[3 * a + 1] * n[1], c2 = t.M[3 * a + 2] * n[2];
+#pragma unroll
+        for (int L = 0; L < 3; ++L) O[4 * a][L] = c0 * t.R[3 * L] + c1 * t.R[3 * L + 1] + c2 * t.R[3 * L + 2];
       } else {
+        const float cp = t.p[3 * a + b] * n[a], cq = t.q[3 * a + b] * n[b];
 #pragma unroll
-        for (int J = 0; J < 3; ++J) g[k][J] *= ih[J];
+        for (int L = 0; L < 3; ++L) O[3 * a + b][L] = cp * t.R[3 * L + b] + cq * t.R[3 * L + a];
       }
-#pragma unroll
-      for (int J = 0; J < 3; ++J) Gs[q][3 * (f0 + k) + J] = g[k][J];
     }
+#pragma unroll
+  for (int f = 0; f < 3; ++f) {
+    float X[3][3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+#pragma unroll
+      for (int L = 0; L < 3; ++L)
+        X[b][L] = t.N[3 * f] * O[b][L] + t.N[3 * f + 1] * O[3 + b][L] + t.N[3 * f + 2] * O[6 + b][L];
+#pragma unroll
+    for (int J = 0; J < 3; ++J)
+#pragma unroll
+      for (int L = 0; L < 3; ++L)
+        C[3 * (3 * f + J) + L] += t.R[3 * J] * X[0][L] + t.R[3 * J + 1] * X[1][L] + t.R[3 * J + 2] * X[2][L];
+  }
+#pragma unroll
+  for (int L = 0; L < 3; ++L)
+    H[L] += t.h[0] * n[0] * t.R[3 * L] + t.h[1] * n[1] * t.R[3 * L + 1] + t.h[2] * n[2] * t.R[3 * L + 2];
+}
+
+// Element matrices of the order-1 level, K_e[r][c] (r, c = field * 8 + node): the fine-quadrature
+// sum of (test basis) x tangent x (trial basis). One thread per point of NE elements; the trial
+// fields are taken in turn, and each turn's tangent entries (test field and direction J, trial
+// direction L) go through LDS in sum-factorised form: the pair of 1-D order-1 bases of an axis
+// contracts that axis' points into the 2 x 2 (test, trial) nodes, x, then y, then z with the sum
+// over (J, L). An entry's 1-D pair is B or D on either side by its J and L, so it is uniform over
+// a wave and its products come from a table (tabs->pair) through scalar registers.
+//
+// Bound by vector instructions. Contracting the 10 x 10 tangent of a point with the 32 trial and
+// 32 test functions takes 260 k multiply-adds per order-3 element, and forming the tangent by
+// ten directional derivatives 130 k more; the factored form takes 60 k and 50 k. Order 3 on 32^3
+// elements 1.49 -> 0.31 ms, order 4 on 40^3 9.67 -> 1.38 ms.
+// GEO: mapped elements (gradients and weights from the points' geometry record).
+template <int PF> struct EbeShape {
+  static constexpr int Q = PF, Q2 = Q * Q, Q3 = Q * Q * Q;
+  // elements per workgroup: a line per lane in the x pass (NE Q^2 <= 64), a point per thread
+  static constexpr int NE = PF == 2 ? 8 : (PF == 3 ? 5 : (PF == 4 ? 4 : 2));
+  static constexpr int LQ = Q > 4 ? Q : 4;           // line stride: Q points, then 4 node pairs
+  static constexpr int ES = Q * LQ * LQ + 4;         // entry and element stride (padded against bank conflicts)
+  static constexpr int NENT = 30;                    // entries of one trial field
+  using L = Q5Lds<PF, PF>;
+  static constexpr int FWD = NE * (L::A + L::B);     // sum factorisation of the displacement gradient
+  static constexpr int CON = NENT * NE * ES;
+  static constexpr int LDS = FWD > CON ? FWD : CON;
+};
+
+template <int PF, bool MB, bool GEO = false>
+__global__ __launch_bounds__(NT) void k_ebe_assemble(EbeArgs a, const DevTablesF* __restrict__ tabs) {
+  using S = EbeShape<PF>;
+  constexpr int Q = S::Q, Q2 = S::Q2, Q3 = S::Q3, NE = S::NE, LQ = S::LQ, ES = S::ES, P3 = Q3;
+  static_assert(NE * Q2 <= 64 && NE * Q3 <= NT, "a line per lane, a point per thread");
+  __shared__ float lds[S::LDS];
+  const int t = threadIdx.x, l = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int64_t n_elem = (int64_t)a.m.nx * a.m.ny * a.m.nz;
+  const int64_t e0 = (int64_t)blockIdx.x * NE;
+  const int el = t / Q3, ql = t - el * Q3;
+  const int qx = ql % Q, qy = (ql / Q) % Q, qz = ql / Q2;
+  const int64_t e = e0 + el;
+  const bool pt = el < NE && e < n_elem;
+  const int64_t gq = e * Q3 + ql;
+  // displacement gradient of every point
+  float* bufA = lds;
+  float* bufB = lds + NE * S::L::A;
+  if (pt) {
+    const int ex = (int)(e % a.m.nx), ey = (int)((e / a.m.nx) % a.m.ny), ez = (int)(e / ((int64_t)a.m.nx * a.m.ny));
+    const int64_t gn = lattice_node<PF>(a.fine.nx1, a.fine.ny1, ElemGeom{ex, ey, ez}, ql);
+#pragma unroll
+    for (int f = 0; f < 3; ++f) bufA[el * S::L::A + f * P3 + ql] = a.z32[f * a.fine.n_nodes + gn];
   }
   __syncthreads();
-  // NG thread groups per point share its 10 tangent directions (each recomputes the point
-  // state from the record)
-  constexpr int NG = (NT / Q3) < 10 ? (NT / Q3) : 10;
-  static_assert(NG >= 1, "a point per thread");
-  if (t < NG * Q3) {
-    const int q = t % Q3, grp = t / Q3;
-    const int qx = q % Q, qy = (q / Q) % Q, qz = q / (Q * Q);
-    float G[9];
+  sf5_fwd<float, DevTablesF, PF, Q, 3, false, true, NE, NT>(bufA, bufB, tabs, S::L::A, S::L::B);
+  const float ih[3] = {(float)a.m.ih[0], (float)a.m.ih[1], (float)a.m.ih[2]};
+  float A[9], w = 0.f;  // reference-to-physical factors d xi_K / d x_J and weight
 #pragma unroll
-    for (int k = 0; k < 9; ++k) G[k] = Gs[q][k];
-    const int64_t gq = e * Q3 + q;
+  for (int k = 0; k < 9; ++k) A[k] = GEO ? (pt ? (float)a.qd[k * a.n_q + gq] : 0.f) : (k % 4 == 0 ? ih[k / 4] : 0.f);
+  if (pt) w = GEO ? (float)a.qd[9 * a.n_q + gq] : tabs->w[Q][qx] * tabs->w[Q][qy] * tabs->w[Q][qz] * (float)a.m.jdet;
+  float G[9];
+#pragma unroll
+  for (int f = 0; f < 3; ++f) {
+    float d[3] = {0.f, 0.f, 0.f};
+    if (pt) {
+#pragma unroll
+      for (int K = 0; K < 3; ++K) d[K] = bufB[el * S::L::B + (4 * f + 1 + K) * Q3 + ql];
+    }
+#pragma unroll
+    for (int J = 0; J < 3; ++J)
+      G[3 * f + J] = GEO ? d[0] * A[J] + d[1] * A[3 + J] + d[2] * A[6 + J] : d[J] * ih[J];
+  }
+  __syncthreads();
+  const int pid = pt ? a.phase[gq] : 0;
+  const int pidc = pid < a.nph ? pid : 0;
+  const MatParams<float> mp = a.mats[pidc];
+  // the tangent's factors of record layer j (0: the block, 1 + j: extra branch j); false: empty
+  bool hact = false;
+  float gp = 0.f, dLc = 0.f;
+  auto layer = [&](int j, TangentFactors& tf) -> bool {
+    const int64_t o = (int64_t)j * a.n_q + gq;
     LinRecord rc;
+    rc.flags = pt ? a.rec.flags[o] : 0;
+    if (j > 0 && (!pt || (rc.flags & REC_EMPTY))) return false;
 #pragma unroll
-    for (int k = 0; k < REC_N; ++k) rc.v[k] = a.rec.rec[k * a.n_q + gq];
-    rc.flags = a.rec.flags[gq];
-    const int pid = a.phase[gq];
-    const int pidc = pid < a.nph ? pid : 0;
-    const MatParams<float> mp = a.mats[pidc];
+    for (int k = 0; k < REC_N; ++k) rc.v[k] = pt ? a.rec.rec[((int64_t)j * REC_N + k) * a.n_q + gq] : 0.f;
+    const MatParams<float> bm = j == 0 ? mp : a.xmats[pidc * a.n_extra + j - 1];
     QPState<float> s;
-    qp_state_lin<float>(mp, G, rc, s);
-    for (int in = grp; in < 10; in += NG) {
-      float dG[9], dP[9], dL;
-#pragma unroll
-      for (int k = 0; k < 9; ++k) dG[k] = (k == in) ? 1.f : 0.f;
-      lin_tangent<float, MB>(a.rec, a.n_q, a.xmats, a.n_extra, mp, s, pidc, gq, true, G, dG, in == 9 ? 1.f : 0.f, dP, dL);
-#pragma unroll
-      for (int o = 0; o < 9; ++o) Cq[q][o * 10 + in] = dP[o];
-      Cq[q][90 + in] = dL;
+    qp_state_lin<float>(bm, G, rc, s);
+    if (j == 0) {
+      hact = s.hactive;
+      gp = s.gp;
+      dLc = s.dLcoef;
     }
-    if (grp == 0) Cq[q][100] = GEO ? (float)a.qd[9 * a.n_q + gq] : wq[qx] * wq[qy] * wq[qz] * jdet;
-  }
-  // order-1 basis at the points (values and physical gradients) and the fracture
-  // gradient coefficient of each point's phase
-  for (int i = t; i < Q3 * 8; i += NT) {
-    const int q = i >> 3, nb = i & 7;
-    const int qx = q % Q, qy = (q / Q) % Q, qz = q / (Q * Q);
-    const int bx = nb & 1, by = (nb >> 1) & 1, bz = nb >> 2;
-    const float vx = B1[qx * 2 + bx], vy = B1[qy * 2 + by], vz = B1[qz * 2 + bz];
-    Nq[q][nb] = vx * vy * vz;
-    if (GEO) {
-      const int64_t gq = e * Q3 + q;
-      double gA[9];
+    tangent_factors(bm, s, tf);
+    float R[9];
 #pragma unroll
-      for (int k = 0; k < 9; ++k) gA[k] = a.qd[k * a.n_q + gq];
-      float gr[3];
-      map_grad<float>(D1[qx * 2 + bx] * vy * vz, vx * D1[qy * 2 + by] * vz, vx * vy * D1[qz * 2 + bz], gA, gr);
-      Gq[q][nb][0] = gr[0];
-      Gq[q][nb][1] = gr[1];
-      Gq[q][nb][2] = gr[2];
-    } else {
-      Gq[q][nb][0] = D1[qx * 2 + bx] * vy * vz * ih[0];
-      Gq[q][nb][1] = vx * D1[qy * 2 + by] * vz * ih[1];
-      Gq[q][nb][2] = vx * vy * D1[qz * 2 + bz] * ih[2];
-    }
-  }
-  for (int q = t; q < Q3; q += NT) {
-    const int pid = a.phase[e * Q3 + q];
-    kq[q] = a.fr.kf * a.mats[pid < a.nph ? pid : 0].Gc;
-  }
-  // Each thread owns row node na = t / 32 and column c = t % 32 (field g, node nb) for
-  // the four row fields. Per chunk of points: T[q][i][c] = tangent row i applied to the
-  // column's trial function, then K[f na][c] += wdet grad N_na . T[q][3f..3f+2][c]
-  // (f < 3) and wdet (s_phi N_na T[q][9][c] + kf Gc grad N_na . grad N_nb [g = 3]).
-  static_assert(NT == 256, "one thread per (row node, column)");
-  const int na = t >> 5, c = t & 31, g = c >> 3, nbc = c & 7;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  __syncthreads();
-  for (int q0 = 0; q0 < Q3; q0 += QC) {
-    const int nq = Q3 - q0 < QC ? Q3 - q0 : QC;
+    for (int K = 0; K < 3; ++K)
+#pragma unroll
+      for (int b = 0; b < 3; ++b)
+        R[3 * K + b] = GEO ? A[3 * K] * tf.R[b] + A[3 * K + 1] * tf.R[3 + b] + A[3 * K + 2] * tf.R[6 + b]
+                           : ih[K] * tf.R[3 * K + b];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) tf.R[k] = R[k];
+    return true;
+  };
+  TangentFactors tf0;
+  layer(0, tf0);
+  float* con = lds;
+  float* my = con + el * ES + (qz * LQ + qy) * LQ + qx;  // this point's slot of entry 0
+  // entry index: trial field g < 3: (3 f + J) 3 + L (f < 3), 27 + L (test phi); g = 3: 3 f + J
+  // (trial value), 9 (phi value with phi value), 10 + 3 J + L (grad phi with grad phi)
 #pragma unroll 1
-    for (int i = t; i < nq * 320; i += NT) {
-      const int qq = i / 320, rem = i - qq * 320, row = rem >> 5, cc = rem & 31;
-      const int gg = cc >> 3, nb = cc & 7, q = q0 + qq;
-      const float* C = Cq[q];
-      float v;
-      if (gg < 3)
-        v = C[row * 10 + 3 * gg] * Gq[q][nb][0] + C[row * 10 + 3 * gg + 1] * Gq[q][nb][1] +
-            C[row * 10 + 3 * gg + 2] * Gq[q][nb][2];
-      else
-        v = C[row * 10 + 9] * Nq[q][nb];
-      Tq[qq][row][cc] = v;
-    }
-    __syncthreads();
-    {
-#pragma unroll 2
-      for (int qq = 0; qq < nq; ++qq) {
-        const int q = q0 + qq;
-        const float w = Cq[q][100];
-        const float g0 = Gq[q][na][0], g1 = Gq[q][na][1], g2 = Gq[q][na][2];
+  for (int g = 0; g < 4; ++g) {
+    const int nent = g < 3 ? 30 : 19;
+    if (g < 3) {
+      float C[27], H[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < 27; ++k) C[k] = 0.f;
+      auto columns = [&](const TangentFactors& tf) {
+        if (g == 0)
+          tangent_columns<0>(tf, C, H);
+        else if (g == 1)
+          tangent_columns<1>(tf, C, H);
+        else
+          tangent_columns<2>(tf, C, H);
+      };
+      columns(tf0);
+      if (MB) {
+#pragma unroll 1
+        for (int j = 0; j < a.n_extra; ++j) {
+          TangentFactors tj;
+          if (layer(1 + j, tj)) columns(tj);
+        }
+      }
+      if (el < NE) {
+        const float wr = hact ? w * a.fr.s_phi * gp : 0.f;
+#pragma unroll
+        for (int k = 0; k < 27; ++k) my[k * NE * ES] = w * C[k];
+#pragma unroll
+        for (int L = 0; L < 3; ++L) my[(27 + L) * NE * ES] = wr * H[L];
+      }
+    } else {
+      float C[9], hphi = tf0.hphi;
+      auto phi_column = [&](const TangentFactors& tf) {
 #pragma unroll
         for (int f = 0; f < 3; ++f)
-          acc[f] += w * (g0 * Tq[qq][3 * f][c] + g1 * Tq[qq][3 * f + 1][c] + g2 * Tq[qq][3 * f + 2][c]);
-        float v = a.fr.s_phi * Nq[q][na] * Tq[qq][9][c];
-        if (g == 3) v += kq[q] * (g0 * Gq[q][nbc][0] + g1 * Gq[q][nbc][1] + g2 * Gq[q][nbc][2]);
-        acc[3] += w * v;
+#pragma unroll
+          for (int J = 0; J < 3; ++J)
+            C[3 * f + J] += tf.N[3 * f] * tf.zphi[0] * tf.R[3 * J] + tf.N[3 * f + 1] * tf.zphi[1] * tf.R[3 * J + 1] +
+                            tf.N[3 * f + 2] * tf.zphi[2] * tf.R[3 * J + 2];
+      };
+#pragma unroll
+      for (int k = 0; k < 9; ++k) C[k] = 0.f;
+      phi_column(tf0);
+      if (MB) {
+#pragma unroll 1
+        for (int j = 0; j < a.n_extra; ++j) {
+          TangentFactors tj;
+          if (layer(1 + j, tj)) {
+            phi_column(tj);
+            hphi += tj.hphi;
+          }
+        }
+      }
+      if (el < NE) {
+        const float kfg = w * a.fr.kf * mp.Gc;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) my[k * NE * ES] = w * C[k];
+        my[9 * NE * ES] = w * a.fr.s_phi * (dLc + (hact ? gp * hphi : 0.f));
+#pragma unroll
+        for (int J = 0; J < 3; ++J)
+#pragma unroll
+          for (int L = 0; L < 3; ++L)
+            my[(10 + 3 * J + L) * NE * ES] =
+                kfg * (A[3 * J] * A[3 * L] + A[3 * J + 1] * A[3 * L + 1] + A[3 * J + 2] * A[3 * L + 2]);
       }
     }
     __syncthreads();
-  }
-  {
+    // test and trial direction of an entry (3: value)
+    auto dirs = [&](int ent, int& J, int& L) {
+      if (g < 3) {
+        L = ent % 3;
+        J = ent < 27 ? (ent / 3) % 3 : 3;
+      } else if (ent < 10) {
+        J = ent < 9 ? ent % 3 : 3;
+        L = 3;
+      } else {
+        J = (ent - 10) / 3;
+        L = (ent - 10) % 3;
+      }
+    };
+    // x: a line (element, qz, qy) per lane, entries over the waves
+#pragma unroll 1
+    for (int ent = wv; ent < nent; ent += NT / 64) {
+      int J, L;
+      dirs(ent, J, L);
+      const float* pr = tabs->pair[Q][(J == 0 ? 1 : 0) + (L == 0 ? 2 : 0)][0];
+      if (l < NE * Q2) {
+        const int le = l / Q2, r = l - le * Q2;
+        float* line = con + (ent * NE + le) * ES + ((r / Q) * LQ + r % Q) * LQ;
+        float v[Q];
 #pragma unroll
-    for (int f = 0; f < 4; ++f) a.K[e * 1024 + (f * 8 + na) * 32 + c] = acc[f];
+        for (int q = 0; q < Q; ++q) v[q] = line[q];
+#pragma unroll
+        for (int ab = 0; ab < 4; ++ab) {
+          float acc = 0.f;
+#pragma unroll
+          for (int q = 0; q < Q; ++q) acc += pr[ab * 5 + q] * v[q];
+          line[ab] = acc;
+        }
+      }
+    }
+    __syncthreads();
+    // y: a line (element, qz, x pair) per lane
+#pragma unroll 1
+    for (int ent = wv; ent < nent; ent += NT / 64) {
+      int J, L;
+      dirs(ent, J, L);
+      const float* pr = tabs->pair[Q][(J == 1 ? 1 : 0) + (L == 1 ? 2 : 0)][0];
+#pragma unroll
+      for (int l0 = 0; l0 < NE * Q * 4; l0 += 64) {
+        const int lt = l0 + l;
+        if (lt < NE * Q * 4) {
+          const int le = lt / (Q * 4), r = lt - le * (Q * 4);
+          float* line = con + (ent * NE + le) * ES + (r >> 2) * LQ * LQ + (r & 3);
+          float v[Q];
+#pragma unroll
+          for (int q = 0; q < Q; ++q) v[q] = line[q * LQ];
+#pragma unroll
+          for (int ab = 0; ab < 4; ++ab) {
+            float acc = 0.f;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) acc += pr[ab * 5 + q] * v[q];
+            line[ab * LQ] = acc;
+          }
+        }
+      }
+    }
+    __syncthreads();
+    // z: a test field per wave, (element, xy pair) per lane, the four z pairs summed over (J, L)
+#pragma unroll
+    for (int r0 = 0; r0 < NE * 16; r0 += 64) {
+      const int f = wv, r = r0 + l;
+      if (r >= NE * 16) continue;
+      const int le = r >> 4, xy = r & 15;
+      float acc[4] = {0.f, 0.f, 0.f, 0.f};
+      auto add = [&](int ent, int type) {
+        const float* col = con + (ent * NE + le) * ES + (xy >> 2) * LQ + (xy & 3);
+        const float* pr = tabs->pair[Q][type][0];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          const float v = col[q * LQ * LQ];
+#pragma unroll
+          for (int ab = 0; ab < 4; ++ab) acc[ab] += pr[ab * 5 + q] * v;
+        }
+      };
+      const int nL = g < 3 ? 3 : 1, nJ = f < 3 ? 3 : 1;
+#pragma unroll 1
+      for (int J = 0; J < nJ; ++J)
+#pragma unroll 1
+        for (int L = 0; L < nL; ++L) {
+          const int ent = g < 3 ? (f < 3 ? 3 * (3 * f + J) + L : 27 + L) : (f < 3 ? 3 * f + J : 9);
+          add(ent, (nJ == 3 && J == 2 ? 1 : 0) + (nL == 3 && L == 2 ? 2 : 0));
+        }
+      if (g == 3 && f == 3) {
+#pragma unroll 1
+        for (int k = 0; k < 9; ++k) add(10 + k, (k / 3 == 2 ? 1 : 0) + (k % 3 == 2 ? 2 : 0));
+      }
+      // pair index: test node + 2 trial node per axis
+      if (e0 + le < n_elem) {
+        const int ax = xy & 1, bx = (xy >> 1) & 1, ay = (xy >> 2) & 1, by = xy >> 3;
+        float* Ke = a.K + (e0 + le) * 1024;
+#pragma unroll
+        for (int ab = 0; ab < 4; ++ab) {
+          const int na = ax + 2 * ay + 4 * (ab & 1), nb = bx + 2 * by + 4 * (ab >> 1);
+          Ke[(f * 8 + na) * 32 + g * 8 + nb] = acc[ab];
+        }
+      }
+    }
+    __syncthreads();
   }
 }
 

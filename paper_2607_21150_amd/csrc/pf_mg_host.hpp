@@ -398,32 +398,38 @@ EbeArgs ebe_args(pf_ctx* c) {
   return a;
 }
 
-pf_status ebe_assemble(pf_ctx* c, hipStream_t s) {
-  const EbeArgs a = ebe_args(c);
-  const int n_elem = c->mesh.nx * c->mesh.ny * c->mesh.nz;
+template <int PF>
+pf_status launch_ebe(const EbeArgs& a, const DevTablesF* tabs, hipStream_t s) {
+  const int64_t n_elem = (int64_t)a.m.nx * a.m.ny * a.m.nz;
+  const dim3 nb((unsigned)((n_elem + EbeShape<PF>::NE - 1) / EbeShape<PF>::NE));
   const bool mb = a.n_extra > 0;
-  if (a.qd) {  // mapped elements
-    switch (c->mg.lv[0].P * 2 + (mb ? 1 : 0)) {
-      case 6: hipLaunchKernelGGL((k_ebe_assemble<3, false, true>), dim3(n_elem), dim3(NT), 0, s, a, c->d_tabf); break;
-      case 7: hipLaunchKernelGGL((k_ebe_assemble<3, true, true>), dim3(n_elem), dim3(NT), 0, s, a, c->d_tabf); break;
-      case 8: hipLaunchKernelGGL((k_ebe_assemble<4, false, true>), dim3(n_elem), dim3(NT), 0, s, a, c->d_tabf); break;
-      case 9: hipLaunchKernelGGL((k_ebe_assemble<4, true, true>), dim3(n_elem), dim3(NT), 0, s, a, c->d_tabf); break;
-      case 10: hipLaunchKernelGGL((k_ebe_assemble<5, false, true>), dim3(n_elem), dim3(NT), 0, s, a, c->d_tabf); break;
-      case 11: hipLaunchKernelGGL((k_ebe_assemble<5, true, true>), dim3(n_elem), dim3(NT), 0, s, a, c->d_tabf); break;
-      default: return fail(PF_EUNSUPPORTED, "order not built");
-    }
-  } else switch (c->mg.lv[0].P * 2 + (mb ? 1 : 0)) {
-    case 4: hipLaunchKernelGGL((k_ebe_assemble<2, false>), dim3(n_elem), dim3(NT), 0, s, a, c->d_tabf); break;
-    case 5: hipLaunchKernelGGL((k_ebe_assemble<2, true>), dim3(n_elem), dim3(NT), 0, s, a, c->d_tabf); break;
-    case 6: hipLaunchKernelGGL((k_ebe_assemble<3, false>), dim3(n_elem), dim3(NT), 0, s, a, c->d_tabf); break;
-    case 7: hipLaunchKernelGGL((k_ebe_assemble<3, true>), dim3(n_elem), dim3(NT), 0, s, a, c->d_tabf); break;
-    case 8: hipLaunchKernelGGL((k_ebe_assemble<4, false>), dim3(n_elem), dim3(NT), 0, s, a, c->d_tabf); break;
-    case 9: hipLaunchKernelGGL((k_ebe_assemble<4, true>), dim3(n_elem), dim3(NT), 0, s, a, c->d_tabf); break;
-    case 10: hipLaunchKernelGGL((k_ebe_assemble<5, false>), dim3(n_elem), dim3(NT), 0, s, a, c->d_tabf); break;
-    case 11: hipLaunchKernelGGL((k_ebe_assemble<5, true>), dim3(n_elem), dim3(NT), 0, s, a, c->d_tabf); break;
-    default: return fail(PF_EUNSUPPORTED, "order not built");
+  if constexpr (PF == 2) {  // order 1: no branches, no mapped elements
+    hipLaunchKernelGGL((k_ebe_assemble<PF, false>), nb, dim3(NT), 0, s, a, tabs);
+  } else {
+    if (a.qd && mb)
+      hipLaunchKernelGGL((k_ebe_assemble<PF, true, true>), nb, dim3(NT), 0, s, a, tabs);
+    else if (a.qd)
+      hipLaunchKernelGGL((k_ebe_assemble<PF, false, true>), nb, dim3(NT), 0, s, a, tabs);
+    else if (mb)
+      hipLaunchKernelGGL((k_ebe_assemble<PF, true>), nb, dim3(NT), 0, s, a, tabs);
+    else
+      hipLaunchKernelGGL((k_ebe_assemble<PF, false>), nb, dim3(NT), 0, s, a, tabs);
   }
   HIPCHK(hipGetLastError());
+  return PF_OK;
+}
+
+pf_status ebe_assemble(pf_ctx* c, hipStream_t s) {
+  const EbeArgs a = ebe_args(c);
+  pf_status st;
+  switch (c->mg.lv[0].P) {
+    case 2: st = launch_ebe<2>(a, c->d_tabf, s); break;
+    case 3: st = launch_ebe<3>(a, c->d_tabf, s); break;
+    case 4: st = launch_ebe<4>(a, c->d_tabf, s); break;
+    case 5: st = launch_ebe<5>(a, c->d_tabf, s); break;
+    default: return fail(PF_EUNSUPPORTED, "order not built");
+  }
+  if (st) return st;
   const MGLevel& L = c->mg.lv[c->mg.ebe_level];
   const int64_t nall = 27 * L.n_nodes;
   const int nb = (int)std::min<int64_t>((nall + NT - 1) / NT, 65536);

@@ -190,6 +190,11 @@ pf_status build_tables(pf_ctx* c) {
       }
     }
   }
+  for (int Q = 2; Q <= 5; ++Q)
+    for (int type = 0; type < 4; ++type)
+      for (int ab = 0; ab < 4; ++ab)
+        for (int q = 0; q < Q; ++q)
+          tf->pair[Q][type][ab][q] = (float)((type & 1 ? t->D : t->B)[2][Q][q][ab & 1] * (type & 2 ? t->D : t->B)[2][Q][q][ab >> 1]);
   hipError_t e1 = hipMalloc(&c->d_tab, sizeof(DevTables));
   hipError_t e2 = hipMalloc(&c->d_tabf, sizeof(DevTablesF));
   if (e1 != hipSuccess || e2 != hipSuccess) {
