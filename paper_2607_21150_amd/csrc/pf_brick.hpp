@@ -40,6 +40,8 @@ struct DevTablesF {
   // products of two order-1 bases at the Q points: pair[Q][type][a + 2 b][q] = T[q][a] U[q][b],
   // T = D for type & 1 (else B), U = D for type & 2
   float pair[6][4][4][5];
+  // squared bases of P nodes: square[P][Q][type][i][q] = B B, B D or D D of node i (type 0, 1, 2)
+  float square[6][6][3][5][5];
 };
 
 struct BrickGeom {

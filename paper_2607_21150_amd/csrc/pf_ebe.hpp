@@ -19,7 +19,7 @@ namespace pfmf {
 
 struct EbeArgs {
   MeshDev m;
-  LevelDev fine, lev;   // fine level (kinematics) and the order-1 level
+  LevelDev fine;        // fine level (kinematics)
   int64_t n_q;
   const float* z32;     // fine u mirror [3][n_fine]
   RecordSoA rec;
@@ -116,19 +116,7 @@ __device__ inline void tangent_columns(const TangentFactors& t, float* C, float*
     H[L] += t.h[0] * n[0] * t.R[3 * L] + t.h[1] * n[1] * t.R[3 * L + 1] + t.h[2] * n[2] * t.R[3 * L + 2];
 }
 
-// Element matrices of the order-1 level, K_e[r][c] (r, c = field * 8 + node): the fine-quadrature
-// sum of (test basis) x tangent x (trial basis). One thread per point of NE elements; the trial
-// fields are taken in turn, and each turn's tangent entries (test field and direction J, trial
-// direction L) go through LDS in sum-factorised form: the pair of 1-D order-1 bases of an axis
-// contracts that axis' points into the 2 x 2 (test, trial) nodes, x, then y, then z with the sum
-// over (J, L). An entry's 1-D pair is B or D on either side by its J and L, so it is uniform over
-// a wave and its products come from a table (tabs->pair) through scalar registers.
-//
-// Bound by vector instructions. Contracting the 10 x 10 tangent of a point with the 32 trial and
-// 32 test functions takes 260 k multiply-adds per order-3 element, and forming the tangent by
-// ten directional derivatives 130 k more; the factored form takes 60 k and 50 k. Order 3 on 32^3
-// elements 1.49 -> 0.31 ms, order 4 on 40^3 9.67 -> 1.38 ms.
-// GEO: mapped elements (gradients and weights from the points' geometry record).
+// Shapes of the kernels below for order PF - 1 elements.
 template <int PF> struct EbeShape {
   static constexpr int Q = PF, Q2 = Q * Q, Q3 = Q * Q * Q;
   // elements per workgroup: a line per lane in the x pass (NE Q^2 <= 64), a point per thread
@@ -142,84 +130,132 @@ template <int PF> struct EbeShape {
   static constexpr int LDS = FWD > CON ? FWD : CON;
 };
 
-template <int PF, bool MB, bool GEO = false>
-__global__ __launch_bounds__(NT) void k_ebe_assemble(EbeArgs a, const DevTablesF* __restrict__ tabs) {
+// A point of the element matrices' and diagonals' kernels: thread t holds point ql of element
+// el (of the workgroup's NE); the displacement gradient, the reference-to-physical factors
+// A[3 K + J] = d xi_K / d x_J and the weight (0 for threads without a point).
+struct EbePoint {
+  int64_t e, gq;
+  int el, qx, qy, qz, pidc;
+  bool pt;
+  float G[9], A[9], w;
+};
+
+// Fills p (the fine displacement's gradient by sum factorisation through lds, EbeShape::FWD
+// values; starts and ends so that lds is free).
+template <int PF, bool GEO>
+__device__ inline void ebe_point(const EbeArgs& a, const DevTablesF* __restrict__ tabs, float* lds, EbePoint& p) {
   using S = EbeShape<PF>;
-  constexpr int Q = S::Q, Q2 = S::Q2, Q3 = S::Q3, NE = S::NE, LQ = S::LQ, ES = S::ES, P3 = Q3;
-  static_assert(NE * Q2 <= 64 && NE * Q3 <= NT, "a line per lane, a point per thread");
-  __shared__ float lds[S::LDS];
-  const int t = threadIdx.x, l = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  constexpr int Q = S::Q, Q2 = S::Q2, Q3 = S::Q3, NE = S::NE;
+  const int t = threadIdx.x;
   const int64_t n_elem = (int64_t)a.m.nx * a.m.ny * a.m.nz;
-  const int64_t e0 = (int64_t)blockIdx.x * NE;
-  const int el = t / Q3, ql = t - el * Q3;
-  const int qx = ql % Q, qy = (ql / Q) % Q, qz = ql / Q2;
-  const int64_t e = e0 + el;
-  const bool pt = el < NE && e < n_elem;
-  const int64_t gq = e * Q3 + ql;
-  // displacement gradient of every point
+  p.el = t / Q3;
+  const int ql = t - p.el * Q3;
+  p.qx = ql % Q;
+  p.qy = (ql / Q) % Q;
+  p.qz = ql / Q2;
+  p.e = (int64_t)blockIdx.x * NE + p.el;
+  p.pt = p.el < NE && p.e < n_elem;
+  p.gq = p.e * Q3 + ql;
   float* bufA = lds;
   float* bufB = lds + NE * S::L::A;
-  if (pt) {
-    const int ex = (int)(e % a.m.nx), ey = (int)((e / a.m.nx) % a.m.ny), ez = (int)(e / ((int64_t)a.m.nx * a.m.ny));
+  if (p.pt) {
+    const int ex = (int)(p.e % a.m.nx), ey = (int)((p.e / a.m.nx) % a.m.ny), ez = (int)(p.e / ((int64_t)a.m.nx * a.m.ny));
     const int64_t gn = lattice_node<PF>(a.fine.nx1, a.fine.ny1, ElemGeom{ex, ey, ez}, ql);
 #pragma unroll
-    for (int f = 0; f < 3; ++f) bufA[el * S::L::A + f * P3 + ql] = a.z32[f * a.fine.n_nodes + gn];
+    for (int f = 0; f < 3; ++f) bufA[p.el * S::L::A + f * Q3 + ql] = a.z32[f * a.fine.n_nodes + gn];
   }
   __syncthreads();
   sf5_fwd<float, DevTablesF, PF, Q, 3, false, true, NE, NT>(bufA, bufB, tabs, S::L::A, S::L::B);
   const float ih[3] = {(float)a.m.ih[0], (float)a.m.ih[1], (float)a.m.ih[2]};
-  float A[9], w = 0.f;  // reference-to-physical factors d xi_K / d x_J and weight
 #pragma unroll
-  for (int k = 0; k < 9; ++k) A[k] = GEO ? (pt ? (float)a.qd[k * a.n_q + gq] : 0.f) : (k % 4 == 0 ? ih[k / 4] : 0.f);
-  if (pt) w = GEO ? (float)a.qd[9 * a.n_q + gq] : tabs->w[Q][qx] * tabs->w[Q][qy] * tabs->w[Q][qz] * (float)a.m.jdet;
-  float G[9];
+  for (int k = 0; k < 9; ++k)
+    p.A[k] = GEO ? (p.pt ? (float)a.qd[k * a.n_q + p.gq] : 0.f) : (k % 4 == 0 ? ih[k / 4] : 0.f);
+  p.w = 0.f;
+  if (p.pt)
+    p.w = GEO ? (float)a.qd[9 * a.n_q + p.gq]
+              : tabs->w[Q][p.qx] * tabs->w[Q][p.qy] * tabs->w[Q][p.qz] * (float)a.m.jdet;
 #pragma unroll
   for (int f = 0; f < 3; ++f) {
     float d[3] = {0.f, 0.f, 0.f};
-    if (pt) {
+    if (p.pt) {
 #pragma unroll
-      for (int K = 0; K < 3; ++K) d[K] = bufB[el * S::L::B + (4 * f + 1 + K) * Q3 + ql];
+      for (int K = 0; K < 3; ++K) d[K] = bufB[p.el * S::L::B + (4 * f + 1 + K) * Q3 + ql];
     }
 #pragma unroll
     for (int J = 0; J < 3; ++J)
-      G[3 * f + J] = GEO ? d[0] * A[J] + d[1] * A[3 + J] + d[2] * A[6 + J] : d[J] * ih[J];
+      p.G[3 * f + J] = GEO ? d[0] * p.A[J] + d[1] * p.A[3 + J] + d[2] * p.A[6 + J] : d[J] * ih[J];
   }
   __syncthreads();
-  const int pid = pt ? a.phase[gq] : 0;
-  const int pidc = pid < a.nph ? pid : 0;
-  const MatParams<float> mp = a.mats[pidc];
-  // the tangent's factors of record layer j (0: the block, 1 + j: extra branch j); false: empty
-  bool hact = false;
-  float gp = 0.f, dLc = 0.f;
-  auto layer = [&](int j, TangentFactors& tf) -> bool {
-    const int64_t o = (int64_t)j * a.n_q + gq;
-    LinRecord rc;
-    rc.flags = pt ? a.rec.flags[o] : 0;
-    if (j > 0 && (!pt || (rc.flags & REC_EMPTY))) return false;
+  const int pid = p.pt ? a.phase[p.gq] : 0;
+  p.pidc = pid < a.nph ? pid : 0;
+}
+
+// What the point's phi row takes from its block: the history switch, g' and dL/dphi.
+struct EbeBlock {
+  bool hact;
+  float gp, dLc;
+};
+
+// The tangent's factors of record layer j (0: the block, 1 + j: extra branch j) of point p;
+// false where the layer is empty.
+template <bool GEO>
+__device__ inline bool ebe_layer(const EbeArgs& a, const EbePoint& p, int j, TangentFactors& tf, EbeBlock& blk) {
+  const int64_t o = (int64_t)j * a.n_q + p.gq;
+  LinRecord rc;
+  rc.flags = p.pt ? a.rec.flags[o] : 0;
+  if (j > 0 && (!p.pt || (rc.flags & REC_EMPTY))) return false;
 #pragma unroll
-    for (int k = 0; k < REC_N; ++k) rc.v[k] = pt ? a.rec.rec[((int64_t)j * REC_N + k) * a.n_q + gq] : 0.f;
-    const MatParams<float> bm = j == 0 ? mp : a.xmats[pidc * a.n_extra + j - 1];
-    QPState<float> s;
-    qp_state_lin<float>(bm, G, rc, s);
-    if (j == 0) {
-      hact = s.hactive;
-      gp = s.gp;
-      dLc = s.dLcoef;
-    }
-    tangent_factors(bm, s, tf);
-    float R[9];
+  for (int k = 0; k < REC_N; ++k) rc.v[k] = p.pt ? a.rec.rec[((int64_t)j * REC_N + k) * a.n_q + p.gq] : 0.f;
+  const MatParams<float> m = j == 0 ? a.mats[p.pidc] : a.xmats[p.pidc * a.n_extra + j - 1];
+  QPState<float> s;
+  qp_state_lin<float>(m, p.G, rc, s);
+  if (j == 0) blk = EbeBlock{s.hactive, s.gp, s.dLcoef};
+  tangent_factors(m, s, tf);
+  float R[9];
 #pragma unroll
-    for (int K = 0; K < 3; ++K)
+  for (int K = 0; K < 3; ++K)
 #pragma unroll
-      for (int b = 0; b < 3; ++b)
-        R[3 * K + b] = GEO ? A[3 * K] * tf.R[b] + A[3 * K + 1] * tf.R[3 + b] + A[3 * K + 2] * tf.R[6 + b]
-                           : ih[K] * tf.R[3 * K + b];
+    for (int b = 0; b < 3; ++b)
+      R[3 * K + b] = GEO ? p.A[3 * K] * tf.R[b] + p.A[3 * K + 1] * tf.R[3 + b] + p.A[3 * K + 2] * tf.R[6 + b]
+                         : p.A[4 * K] * tf.R[3 * K + b];
 #pragma unroll
-    for (int k = 0; k < 9; ++k) tf.R[k] = R[k];
-    return true;
-  };
+  for (int k = 0; k < 9; ++k) tf.R[k] = R[k];
+  return true;
+}
+
+// Element matrices of the order-1 level, K_e[r][c] (r, c = field * 8 + node): the fine-quadrature
+// sum of (test basis) x tangent x (trial basis). One thread per point of NE elements; the trial
+// fields are taken in turn, and each turn's tangent entries (test field and direction J, trial
+// direction L) go through LDS in sum-factorised form: the pair of 1-D order-1 bases of an axis
+// contracts that axis' points into the 2 x 2 (test, trial) nodes, x, then y, then z with the sum
+// over (J, L). An entry's 1-D pair is B or D on either side by its J and L, so it is uniform over
+// a wave and its products come from a table (tabs->pair) through scalar registers.
+//
+// Bound by vector instructions. Contracting the 10 x 10 tangent of a point with the 32 trial and
+// 32 test functions takes 260 k multiply-adds per order-3 element, and forming the tangent by
+// ten directional derivatives 130 k more; the factored form takes 60 k and 50 k. Order 3 on 32^3
+// elements 1.49 -> 0.31 ms, order 4 on 40^3 9.67 -> 1.38 ms.
+// GEO: mapped elements (gradients and weights from the points' geometry record).
+template <int PF, bool MB, bool GEO = false>
+__global__ __launch_bounds__(NT) void k_ebe_assemble(EbeArgs a, const DevTablesF* __restrict__ tabs) {
+  using S = EbeShape<PF>;
+  constexpr int Q = S::Q, Q2 = S::Q2, Q3 = S::Q3, NE = S::NE, LQ = S::LQ, ES = S::ES;
+  static_assert(NE * Q2 <= 64 && NE * Q3 <= NT, "a line per lane, a point per thread");
+  __shared__ float lds[S::LDS];
+  const int l = threadIdx.x & 63, wv = wave_id();
+  const int64_t n_elem = (int64_t)a.m.nx * a.m.ny * a.m.nz;
+  const int64_t e0 = (int64_t)blockIdx.x * NE;
+  EbePoint p;
+  ebe_point<PF, GEO>(a, tabs, lds, p);
+  const int el = p.el, qx = p.qx, qy = p.qy, qz = p.qz;
+  const float w = p.w;
+  const float* A = p.A;
+  const MatParams<float> mp = a.mats[p.pidc];
+  EbeBlock blk;
   TangentFactors tf0;
-  layer(0, tf0);
+  ebe_layer<GEO>(a, p, 0, tf0, blk);
+  const bool hact = blk.hact;
+  const float gp = blk.gp, dLc = blk.dLc;
   float* con = lds;
   float* my = con + el * ES + (qz * LQ + qy) * LQ + qx;  // this point's slot of entry 0
   // entry index: trial field g < 3: (3 f + J) 3 + L (f < 3), 27 + L (test phi); g = 3: 3 f + J
@@ -244,7 +280,8 @@ __global__ __launch_bounds__(NT) void k_ebe_assemble(EbeArgs a, const DevTablesF
 #pragma unroll 1
         for (int j = 0; j < a.n_extra; ++j) {
           TangentFactors tj;
-          if (layer(1 + j, tj)) columns(tj);
+          EbeBlock bj;
+          if (ebe_layer<GEO>(a, p, 1 + j, tj, bj)) columns(tj);
         }
       }
       if (el < NE) {
@@ -271,7 +308,8 @@ __global__ __launch_bounds__(NT) void k_ebe_assemble(EbeArgs a, const DevTablesF
 #pragma unroll 1
         for (int j = 0; j < a.n_extra; ++j) {
           TangentFactors tj;
-          if (layer(1 + j, tj)) {
+          EbeBlock bj;
+          if (ebe_layer<GEO>(a, p, 1 + j, tj, bj)) {
             phi_column(tj);
             hphi += tj.hphi;
           }
@@ -393,6 +431,177 @@ __global__ __launch_bounds__(NT) void k_ebe_assemble(EbeArgs a, const DevTablesF
       }
     }
     __syncthreads();
+  }
+}
+
+// The diagonal block of displacement field K: D[0..5] += dP_KJ / dG_KL for (J, L) = xx, yy, zz,
+// xy + yx, xz + zx, yz + zy.
+template <int K>
+__device__ inline void tangent_diagonal(const TangentFactors& t, float* D) {
+  const float n[3] = {t.N[3 * K], t.N[3 * K + 1], t.N[3 * K + 2]};
+  float X[3][3];  // sum_a N_Ka O_ab(L)
+#pragma unroll
+  for (int b = 0; b < 3; ++b)
+#pragma unroll
+    for (int L = 0; L < 3; ++L) {
+      float v = n[b] * (t.M[3 * b] * n[0] * t.R[3 * L] + t.M[3 * b + 1] * n[1] * t.R[3 * L + 1] +
+                        t.M[3 * b + 2] * n[2] * t.R[3 * L + 2]);
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        if (c != b) v += n[c] * (t.p[3 * c + b] * n[c] * t.R[3 * L + b] + t.q[3 * c + b] * n[b] * t.R[3 * L + c]);
+      X[b][L] = v;
+    }
+  float C[3][3];
+#pragma unroll
+  for (int J = 0; J < 3; ++J)
+#pragma unroll
+    for (int L = 0; L < 3; ++L) C[J][L] = t.R[3 * J] * X[0][L] + t.R[3 * J + 1] * X[1][L] + t.R[3 * J + 2] * X[2][L];
+  D[0] += C[0][0];
+  D[1] += C[1][1];
+  D[2] += C[2][2];
+  D[3] += C[0][1] + C[1][0];
+  D[4] += C[0][2] + C[2][0];
+  D[5] += C[1][2] + C[2][1];
+}
+
+// Point-Jacobi diagonal of a level of PC nodes per direction, evaluated at the fine points: the
+// element diagonals, stored to the extended node grid ev [4][nz PC][ny PC][nx PC] and summed per
+// node by k_gather_ext<float, PC>. Entries per point: for each displacement field the six
+// coefficients of tangent_diagonal, for phi the value's and the gradient's (3 on the box, 6 on
+// mapped elements); an axis' squared 1-D bases (B B, B D or D D by the entry's directions, a
+// table) contract its points into the PC nodes, x, y, then z with the sum over the entries.
+// Order 3 on 32^3 elements, both levels: 0.82 -> 0.24 ms with the node sums (eight colour launches that
+// took ten directional derivatives per point and summed all Q^3 points for every node).
+template <int PF, int PC, bool MB, bool GEO = false>
+__global__ __launch_bounds__(NT) void k_level_diag(EbeArgs a, float* __restrict__ ev, const DevTablesF* __restrict__ tabs) {
+  using S = EbeShape<PF>;
+  static_assert(PC <= PF, "a level below the fine one");
+  constexpr int Q = S::Q, Q2 = S::Q2, Q3 = S::Q3, NE = S::NE, ES = Q3 + 1;
+  constexpr int NPHI = GEO ? 7 : 4, NENT = 18 + NPHI;
+  constexpr int CON = NENT * NE * ES;
+  __shared__ float lds[CON > S::FWD ? CON : S::FWD];
+  const int l = threadIdx.x & 63, wv = wave_id();
+  const int64_t n_elem = (int64_t)a.m.nx * a.m.ny * a.m.nz;
+  const int64_t e0 = (int64_t)blockIdx.x * NE;
+  EbePoint p;
+  ebe_point<PF, GEO>(a, tabs, lds, p);
+  {
+    const MatParams<float> mp = a.mats[p.pidc];
+    float D[18];
+#pragma unroll
+    for (int k = 0; k < 18; ++k) D[k] = 0.f;
+    EbeBlock blk;
+    float hphi;
+    {
+      TangentFactors tf;
+      ebe_layer<GEO>(a, p, 0, tf, blk);
+      tangent_diagonal<0>(tf, D);
+      tangent_diagonal<1>(tf, D + 6);
+      tangent_diagonal<2>(tf, D + 12);
+      hphi = tf.hphi;
+    }
+    if (MB) {
+#pragma unroll 1
+      for (int j = 0; j < a.n_extra; ++j) {
+        TangentFactors tf;
+        EbeBlock bj;
+        if (ebe_layer<GEO>(a, p, 1 + j, tf, bj)) {
+          tangent_diagonal<0>(tf, D);
+          tangent_diagonal<1>(tf, D + 6);
+          tangent_diagonal<2>(tf, D + 12);
+          hphi += tf.hphi;
+        }
+      }
+    }
+    if (p.el < NE) {
+      float* my = lds + p.el * ES + (p.qz * Q + p.qy) * Q + p.qx;
+      const float kfg = p.w * a.fr.kf * mp.Gc;
+      const float* A = p.A;
+#pragma unroll
+      for (int k = 0; k < 18; ++k) my[k * NE * ES] = p.w * D[k];
+      my[18 * NE * ES] = p.w * a.fr.s_phi * (blk.dLc + (blk.hact ? blk.gp * hphi : 0.f));
+#pragma unroll
+      for (int k = 0; k < NPHI - 1; ++k) {
+        const int J = k < 3 ? k : (k == 5 ? 1 : 0), L = k < 3 ? k : (k == 3 ? 1 : 2);
+        my[(19 + k) * NE * ES] = (k < 3 ? kfg : 2.f * kfg) * (A[3 * J] * A[3 * L] + A[3 * J + 1] * A[3 * L + 1] + A[3 * J + 2] * A[3 * L + 2]);
+      }
+    }
+  }
+  __syncthreads();
+  // type of an entry on an axis: the number of its directions along it (18: the phi value, none)
+  auto type = [](int ent, int axis) {
+    if (ent == 18) return 0;
+    const int k = ent < 18 ? ent % 6 : ent - 19;
+    const int J = k < 3 ? k : (k == 5 ? 1 : 0), L = k < 3 ? k : (k == 3 ? 1 : 2);
+    return (J == axis ? 1 : 0) + (L == axis ? 1 : 0);
+  };
+#pragma unroll 1
+  for (int ent = wv; ent < NENT; ent += NT / 64) {
+    const float* sq = tabs->square[PC][Q][type(ent, 0)][0];
+    if (l < NE * Q2) {
+      const int le = l / Q2, r = l - le * Q2;
+      float* line = lds + (ent * NE + le) * ES + r * Q;
+      float v[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) v[q] = line[q];
+#pragma unroll
+      for (int i = 0; i < PC; ++i) {
+        float acc = 0.f;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) acc += sq[i * 5 + q] * v[q];
+        line[i] = acc;
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int ent = wv; ent < NENT; ent += NT / 64) {
+    const float* sq = tabs->square[PC][Q][type(ent, 1)][0];
+    if (l < NE * Q * PC) {
+      const int le = l / (Q * PC), r = l - le * (Q * PC);
+      float* line = lds + (ent * NE + le) * ES + (r / PC) * Q2 + r % PC;
+      float v[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) v[q] = line[q * Q];
+#pragma unroll
+      for (int i = 0; i < PC; ++i) {
+        float acc = 0.f;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) acc += sq[i * 5 + q] * v[q];
+        line[i * Q] = acc;
+      }
+    }
+  }
+  __syncthreads();
+  // z: a field per wave, (element, y node, x node) per lane
+  static_assert(NE * Q * PC <= 64, "the y lines and z columns fit a wave");
+  const int f = wv;
+  if (l < NE * PC * PC) {
+    const int le = l / (PC * PC), r = l - le * (PC * PC), j = r / PC, i = r % PC;
+    float acc[PC];
+#pragma unroll
+    for (int k = 0; k < PC; ++k) acc[k] = 0.f;
+    const int ent0 = 6 * f, ne = f < 3 ? 6 : NPHI;
+#pragma unroll 1
+    for (int k = 0; k < ne; ++k) {
+      const int ent = ent0 + k;
+      const float* sq = tabs->square[PC][Q][type(ent, 2)][0];
+      const float* col = lds + (ent * NE + le) * ES + j * Q + i;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const float v = col[q * Q2];
+#pragma unroll
+        for (int n = 0; n < PC; ++n) acc[n] += sq[n * 5 + q] * v;
+      }
+    }
+    const int64_t e = e0 + le;
+    if (e < n_elem) {
+      const int ex = (int)(e % a.m.nx), ey = (int)((e / a.m.nx) % a.m.ny), ez = (int)(e / ((int64_t)a.m.nx * a.m.ny));
+      const int64_t NXe = (int64_t)a.m.nx * PC, NYe = (int64_t)a.m.ny * PC, NZe = (int64_t)a.m.nz * PC;
+#pragma unroll
+      for (int n = 0; n < PC; ++n)
+        ev[((f * NZe + (int64_t)ez * PC + n) * NYe + (int64_t)ey * PC + j) * NXe + (int64_t)ex * PC + i] = acc[n];
+    }
   }
 }
 

@@ -65,7 +65,8 @@ struct MGState {
   float* tmpA = nullptr;
   float* tmpB = nullptr;
   double* red = nullptr;  // reduction scratch
-  float* ebe = nullptr;    // element matrices of the order-1 level on the mesh [n_elem][32][32]
+  float* ebe = nullptr;    // element matrices of the order-1 level on the mesh [n_elem][32][32], and the
+                           // levels' element diagonals (both per linearisation)
   float* stencil = nullptr;  // the same level as a block stencil [27][4][4][n_nodes]
   float* ebuf32 = nullptr;   // brick-buffer scatter of the FP32 level applies
   double* rec64 = nullptr;   // stored FP64 linearisation [rec_layers][REC_N][n_q] (flags in rec.flags)
@@ -142,16 +143,16 @@ struct LinArgs {
 // MODE 3: state commit with the extra branches. GEO: mapped elements (gradients through
 // each point's J^-1 from a.qd).
 template <int P, int Q, int MODE, bool GEO = false>
-__global__ __launch_bounds__(NT) void k_linearize(LinArgs a, int colour, DevTables* __restrict__ tabs) {
+__global__ __launch_bounds__(NT) void k_linearize(LinArgs a, DevTables* __restrict__ tabs) {
   using S = OpShape<P, Q>;
   constexpr int NB3 = S::NB3, Q3 = S::Q3, ER = S::ER;
   extern __shared__ double lds[];
   double* zb = lds;
   double* tmp = zb + 4 * NB3;
   double* tab = tmp + S::TMP;
-  const int brick = xcd_brick(a.m, colour, blockIdx.x);
+  const int brick = xcd_brick_all(a.m, blockIdx.x);  // nothing is shared between bricks: one launch
   if (brick < 0) return;  // padding workgroup (uniform)
-  const BrickGeom g = decode_brick(a.m, colour, brick);
+  const BrickGeom g = decode_brick_lin(a.m, brick);
   for (int t = threadIdx.x; t < Q * P; t += NT) {
     tab[t] = tabs->B[P][Q][t / P][t % P];
     tab[Q * P + t] = tabs->D[P][Q][t / P][t % P];
@@ -310,8 +311,7 @@ __global__ __launch_bounds__(NT) void k_linearize(LinArgs a, int colour, DevTabl
 }
 
 // ---------------------------------------------------------------------------
-// FP32 level apply (MODE 0) and point-Jacobi diagonal (MODE 1).
-// PF: fine nodes per direction (kinematics), PC: this level's nodes per direction.
+// Record applies
 // ---------------------------------------------------------------------------
 
 // Arguments of the linearised applies from a record: V = float for the FP32 multigrid
@@ -378,286 +378,6 @@ __device__ inline void lin_tangent(const RecordSoAT<V>& rec, int64_t n_q, const 
   dL = s.dLcoef * dphi + s.gp * (s.hactive ? dpsi : V(0));
 }
 using A32Args = LinApplyArgs<float>;
-
-template <int PF, int PC, int Q> struct A32Shape {
-  static constexpr int PM = PF > PC ? PF : PC;
-  static constexpr int NBF = 2 * PF - 1, NBF3 = NBF * NBF * NBF;
-  static constexpr int NBC = 2 * PC - 1, NBC3 = NBC * NBC * NBC;
-  static constexpr int PC3 = PC * PC * PC, Q3 = Q * Q * Q;
-  static constexpr int ER = (NT / Q3) < 8 ? (NT / Q3) : 8;
-  static constexpr int ROUNDS = (8 + ER - 1) / ER;
-  static constexpr int FWD = 2 * ER * PM * PM * Q + 3 * ER * PM * Q * Q;
-  static constexpr int BWD = 4 * ER * Q3 + 3 * ER * PM * Q * Q + 2 * ER * PM * PM * Q;
-  static constexpr int DIAG = 25 * ER * Q3;  // 22 coefficients on the box, 25 on mapped elements
-  static constexpr int TMP0 = FWD > BWD ? FWD : BWD;
-  static constexpr int TMP = TMP0 > DIAG ? TMP0 : DIAG;
-  static constexpr int EV = 8 * 4 * PC3;
-  static constexpr int TAB = 2 * Q * PF + 2 * Q * PC + Q;
-  static constexpr size_t lds_floats = (size_t)3 * NBF3 + 4 * NBC3 + EV + TMP + TAB;
-  static constexpr size_t lds_bytes = lds_floats * sizeof(float);
-};
-
-// GEO: mapped elements (gradients and weights from the point's geometry record).
-template <int MODE, int PF, int PC, int Q, bool MB, bool GEO = false>
-__global__ __launch_bounds__(NT) void k_level32(A32Args a, int colour, DevTablesF* __restrict__ tabs) {
-  using S = A32Shape<PF, PC, Q>;
-  constexpr int NBF3 = S::NBF3, NBC3 = S::NBC3, PC3 = S::PC3, Q3 = S::Q3, ER = S::ER, PM = S::PM;
-  extern __shared__ float ldsf[];
-  float* ub = ldsf;                 // [3][NBF3] fine u
-  float* wb = ub + 3 * NBF3;        // [4][NBC3] level direction
-  float* ev = wb + 4 * NBC3;        // [8][4][PC3]
-  float* tmp = ev + S::EV;
-  float* tab = tmp + S::TMP;        // Bf, Df (Q x PF), Bc, Dc (Q x PC), w (Q)
-  const int brick = xcd_brick(a.m, colour, blockIdx.x);
-  if (brick < 0) return;  // padding workgroup (uniform)
-  const BrickGeom g = decode_brick(a.m, colour, brick);
-  for (int t = threadIdx.x; t < Q * PF; t += NT) {
-    tab[t] = tabs->B[PF][Q][t / PF][t % PF];
-    tab[Q * PF + t] = tabs->D[PF][Q][t / PF][t % PF];
-  }
-  for (int t = threadIdx.x; t < Q * PC; t += NT) {
-    tab[2 * Q * PF + t] = tabs->B[PC][Q][t / PC][t % PC];
-    tab[2 * Q * PF + Q * PC + t] = tabs->D[PC][Q][t / PC][t % PC];
-  }
-  if (threadIdx.x < Q) tab[2 * Q * PF + 2 * Q * PC + threadIdx.x] = tabs->w[Q][threadIdx.x];
-  stage_brick<float, float, PF, 3>(a.z32, a.fine.n_nodes, a.fine.nx1, a.fine.ny1, g, ub);
-  if (MODE == 0) stage_brick<float, float, PC, 4>(a.dz, a.lev.n_nodes, a.lev.nx1, a.lev.ny1, g, wb);
-  __syncthreads();
-  const TabRef<float> tf{tab, tab + Q * PF};
-  const TabRef<float> tc{tab + 2 * Q * PF, tab + 2 * Q * PF + Q * PC};
-  const float* wq = tab + 2 * Q * PF + 2 * Q * PC;
-  const float ih[3] = {(float)a.m.ih[0], (float)a.m.ih[1], (float)a.m.ih[2]};
-  const float jdet = (float)a.m.jdet;
-  float* xb = tmp;
-  float* xd = xb + ER * PM * PM * Q;
-  float* ybb = xd + ER * PM * PM * Q;
-  float* ydb = ybb + ER * PM * Q * Q;
-  float* ybd = ydb + ER * PM * Q * Q;
-  float* q0 = tmp;
-  float* z0 = q0 + 4 * ER * Q3;
-  float* zx = z0 + ER * PM * Q * Q;
-  float* zy = zx + ER * PM * Q * Q;
-  float* y0 = zy + ER * PM * Q * Q;
-  float* yx = y0 + ER * PM * PM * Q;
-  const int t = threadIdx.x;
-  const int el = t / Q3, ql = t % Q3;
-  const int qx = ql % Q, qy = (ql / Q) % Q, qz = ql / (Q * Q);
-  for (int r = 0; r < S::ROUNDS; ++r) {
-    const int slot0 = r * ER, slot = slot0 + el;
-    const int sx = slot & 1, sy = (slot >> 1) & 1, sz = slot >> 2;
-    const bool active = (t < ER * Q3) && (slot < 8) && sx < g.nex && sy < g.ney && sz < g.nez;
-    // mapped elements: the point's J^-1 (FP64) and weight
-    double gA[GEO ? 9 : 1];
-    float wgeo = 0.f;
-    if (GEO) {
-      const int64_t e = (int64_t)(g.ex0 + sx) + (int64_t)a.m.nx * ((g.ey0 + sy) + (int64_t)a.m.ny * (g.ez0 + sz));
-      const int64_t gq = e * Q3 + ql;
-#pragma unroll
-      for (int k = 0; k < 9; ++k) gA[k] = active ? a.qd[k * a.n_q + gq] : 0.0;
-      wgeo = active ? (float)a.qd[9 * a.n_q + gq] : 0.f;
-    }
-    float G[9], W[9], wphi = 0.f, gw[3] = {0.f, 0.f, 0.f};
-#pragma unroll 1
-    for (int f = 0; f < 3; ++f) {
-      fwd_xy<float, PF, Q, ER>(ub + f * NBF3, slot0, g, tf, true, xb, xd, ybb, ydb, ybd);
-      if (t < ER * Q3) {
-        float v, d[3];
-        fwd_z<float, PF, Q>(ybb, ydb, ybd, el, qx, qy, qz, tf, true, v, d);
-        if (GEO)
-          map_grad<float>(d[0], d[1], d[2], gA, G + 3 * f);
-        else
-#pragma unroll
-          for (int J = 0; J < 3; ++J) G[3 * f + J] = d[J] * ih[J];
-      }
-      __syncthreads();
-    }
-    if (MODE == 0) {
-#pragma unroll 1
-      for (int f = 0; f < 4; ++f) {
-        fwd_xy<float, PC, Q, ER>(wb + f * NBC3, slot0, g, tc, true, xb, xd, ybb, ydb, ybd);
-        if (t < ER * Q3) {
-          float v, d[3];
-          fwd_z<float, PC, Q>(ybb, ydb, ybd, el, qx, qy, qz, tc, true, v, d);
-          float m[3];
-          if (GEO)
-            map_grad<float>(d[0], d[1], d[2], gA, m);
-          else
-#pragma unroll
-            for (int J = 0; J < 3; ++J) m[J] = d[J] * ih[J];
-          if (f < 3) {
-#pragma unroll
-            for (int J = 0; J < 3; ++J) W[3 * f + J] = m[J];
-          } else {
-            wphi = v;
-#pragma unroll
-            for (int J = 0; J < 3; ++J) gw[J] = m[J];
-          }
-        }
-        __syncthreads();
-      }
-    }
-    float Fu[9], f0 = 0.f, f1[3] = {0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k = 0; k < 9; ++k) Fu[k] = 0.f;
-    QPState<float> s;
-    MatParams<float> mp;
-    float wdet = 0.f;
-    int pidc = 0;
-    int64_t gqa = 0;
-    if (active) {
-      const int64_t e = (int64_t)(g.ex0 + sx) + (int64_t)a.m.nx * ((g.ey0 + sy) + (int64_t)a.m.ny * (g.ez0 + sz));
-      const int64_t gq = e * Q3 + ql;
-      LinRecord rc;
-#pragma unroll
-      for (int k = 0; k < REC_N; ++k) rc.v[k] = a.rec.rec[k * a.n_q + gq];
-      rc.flags = a.rec.flags[gq];
-      const int pid = a.phase[gq];
-      pidc = pid < a.nph ? pid : 0;
-      gqa = gq;
-      mp = a.mats[pidc];
-      qp_state_lin<float>(mp, G, rc, s);
-      wdet = GEO ? wgeo : wq[qx] * wq[qy] * wq[qz] * jdet;
-      if (MODE == 0) {
-        float dL;
-        lin_tangent<float, MB>(a.rec, a.n_q, a.xmats, a.n_extra, mp, s, pidc, gq, true, G, W, wphi, Fu, dL);
-#pragma unroll
-        for (int k = 0; k < 9; ++k) Fu[k] *= wdet;
-        f0 = wdet * a.fr.s_phi * dL;
-        const float kfg = a.fr.kf * mp.Gc;
-#pragma unroll
-        for (int J = 0; J < 3; ++J) f1[J] = wdet * kfg * gw[J];
-      }
-    }
-    if (MODE == 0) {
-#pragma unroll 1
-      for (int f = 0; f < 4; ++f) {
-        if (t < ER * Q3) {
-          float fl[3];
-          if (f < 3) {
-            q0[t] = 0.f;
-#pragma unroll
-            for (int J = 0; J < 3; ++J) fl[J] = Fu[3 * f + J];
-          } else {
-            q0[t] = f0;
-#pragma unroll
-            for (int J = 0; J < 3; ++J) fl[J] = f1[J];
-          }
-#pragma unroll
-          for (int K = 0; K < 3; ++K)
-            q0[(1 + K) * ER * Q3 + t] =
-                GEO ? (float)(fl[0] * gA[3 * K] + fl[1] * gA[3 * K + 1] + fl[2] * gA[3 * K + 2]) : fl[K] * ih[K];
-        }
-        __syncthreads();
-        bwd_field<float, PC, Q, ER>(q0, q0 + ER * Q3, q0 + 2 * ER * Q3, q0 + 3 * ER * Q3, f == 3, slot0, ER, tc,
-                                    z0, zx, zy, y0, yx, ev, 4, f);
-      }
-    } else {
-      // diagonal: quadratic-form coefficients per point in reference coordinates,
-      // then every (element, node) pair sums over the points with the 1-D tables
-      constexpr int NCF = GEO ? 25 : 22;
-      float* cf = tmp;  // [NCF][ER*Q3]
-      if (t < ER * Q3) {
-        float c22[NCF];
-#pragma unroll
-        for (int k = 0; k < NCF; ++k) c22[k] = 0.f;
-        if (active) {
-#pragma unroll 1
-          for (int i = 0; i < 3; ++i) {
-            float C[3][3];
-#pragma unroll 1
-            for (int K = 0; K < 3; ++K) {
-              float dG[9], dP[9], dL;
-#pragma unroll
-              for (int k = 0; k < 9; ++k) dG[k] = 0.f;
-              dG[3 * i + K] = 1.f;
-              lin_tangent<float, MB>(a.rec, a.n_q, a.xmats, a.n_extra, mp, s, pidc, gqa, true, G, dG, 0.f, dP, dL);
-#pragma unroll
-              for (int J = 0; J < 3; ++J) C[J][K] = dP[3 * i + J];
-            }
-            // in reference coordinates, Ch = A C A^T (A = J^-1; the box: A = diag(ih));
-            // xx, yy, zz, xy, xz, yz
-            float Ch[3][3];
-#pragma unroll
-            for (int K = 0; K < 3; ++K)
-#pragma unroll
-              for (int L = 0; L < 3; ++L) {
-                if (GEO) {
-                  double acc = 0.0;
-#pragma unroll
-                  for (int J = 0; J < 3; ++J)
-#pragma unroll
-                    for (int J2 = 0; J2 < 3; ++J2) acc += gA[3 * K + J] * (double)C[J][J2] * gA[3 * L + J2];
-                  Ch[K][L] = (float)acc;
-                } else {
-                  Ch[K][L] = ih[K] * ih[L] * C[K][L];
-                }
-              }
-            c22[6 * i + 0] = wdet * Ch[0][0];
-            c22[6 * i + 1] = wdet * Ch[1][1];
-            c22[6 * i + 2] = wdet * Ch[2][2];
-            c22[6 * i + 3] = wdet * (Ch[0][1] + Ch[1][0]);
-            c22[6 * i + 4] = wdet * (Ch[0][2] + Ch[2][0]);
-            c22[6 * i + 5] = wdet * (Ch[1][2] + Ch[2][1]);
-          }
-          float dG[9], dP[9], dL;
-#pragma unroll
-          for (int k = 0; k < 9; ++k) dG[k] = 0.f;
-          lin_tangent<float, MB>(a.rec, a.n_q, a.xmats, a.n_extra, mp, s, pidc, gqa, true, G, dG, 1.f, dP, dL);
-          c22[18] = wdet * a.fr.s_phi * dL;
-          const float kfg = wdet * a.fr.kf * mp.Gc;
-          if (GEO) {
-            // kfg A A^T: diagonal in 19..21, xy, xz, yz (doubled) in 22..24
-            double M[3][3];
-#pragma unroll
-            for (int K = 0; K < 3; ++K)
-#pragma unroll
-              for (int L = 0; L < 3; ++L) M[K][L] = gA[3 * K] * gA[3 * L] + gA[3 * K + 1] * gA[3 * L + 1] + gA[3 * K + 2] * gA[3 * L + 2];
-            c22[19] = kfg * (float)M[0][0];
-            c22[20] = kfg * (float)M[1][1];
-            c22[21] = kfg * (float)M[2][2];
-            c22[NCF - 3] = kfg * (float)(2.0 * M[0][1]);
-            c22[NCF - 2] = kfg * (float)(2.0 * M[0][2]);
-            c22[NCF - 1] = kfg * (float)(2.0 * M[1][2]);
-          } else {
-            c22[19] = kfg * ih[0] * ih[0];
-            c22[20] = kfg * ih[1] * ih[1];
-            c22[21] = kfg * ih[2] * ih[2];
-          }
-        }
-#pragma unroll
-        for (int k = 0; k < NCF; ++k) cf[k * ER * Q3 + t] = c22[k];
-      }
-      __syncthreads();
-      for (int o = t; o < ER * PC3; o += NT) {
-        const int e2 = o / PC3, a2 = o % PC3;
-        const int ax = a2 % PC, ay = (a2 / PC) % PC, az = a2 / (PC * PC);
-        float acc[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int q = 0; q < Q3; ++q) {
-          const int px = q % Q, py = (q / Q) % Q, pz = q / (Q * Q);
-          const float bx = tc.B[px * PC + ax], dx = tc.D[px * PC + ax];
-          const float by = tc.B[py * PC + ay], dy = tc.D[py * PC + ay];
-          const float bz = tc.B[pz * PC + az], dz = tc.D[pz * PC + az];
-          const float gx = dx * by * bz, gy = bx * dy * bz, gz = bx * by * dz, nn = bx * by * bz;
-          const float* cq = cf + e2 * Q3 + q;
-#pragma unroll
-          for (int i = 0; i < 3; ++i) {
-            acc[i] += gx * gx * cq[(6 * i + 0) * ER * Q3] + gy * gy * cq[(6 * i + 1) * ER * Q3] +
-                      gz * gz * cq[(6 * i + 2) * ER * Q3] + gx * gy * cq[(6 * i + 3) * ER * Q3] +
-                      gx * gz * cq[(6 * i + 4) * ER * Q3] + gy * gz * cq[(6 * i + 5) * ER * Q3];
-          }
-          acc[3] += nn * nn * cq[18 * ER * Q3] + gx * gx * cq[19 * ER * Q3] + gy * gy * cq[20 * ER * Q3] +
-                    gz * gz * cq[21 * ER * Q3];
-          if (GEO) acc[3] += gx * gy * cq[(NCF - 3) * ER * Q3] + gx * gz * cq[(NCF - 2) * ER * Q3] +
-                             gy * gz * cq[(NCF - 1) * ER * Q3];
-        }
-#pragma unroll
-        for (int f = 0; f < 4; ++f) ev[((slot0 + e2) * 4 + f) * PC3 + a2] = acc[f];
-      }
-      __syncthreads();
-    }
-  }
-  scatter_brick<float, PC, 4>(ev, a.m, a.lev.nx1, a.lev.ny1, a.lev.n_nodes, g, a.out);
-}
 
 // ---------------------------------------------------------------------------
 // Level transfers (one direction per launch) and vector kernels.

@@ -152,16 +152,15 @@ pf_status mg_alloc_levels(pf_ctx* c, const int* orders, int nl) {
       }
     }
   }
-  // the order-1 level on the mesh itself: element matrices and block stencil
-  for (int l = 0; l < nl; ++l) {
-    if (mg.lv[l].p != 1) continue;
-    const int64_t n_elem = (int64_t)c->mesh.nx * c->mesh.ny * c->mesh.nz;
-    if (hipMalloc(&mg.ebe, (size_t)n_elem * 1024 * sizeof(float)) != hipSuccess ||
-        hipMalloc(&mg.stencil, (size_t)27 * 16 * mg.lv[l].n_nodes * sizeof(float)) != hipSuccess)
-      return fail(PF_ENOMEM, "coarse element matrices: allocation failed");
-    mg.ebe_level = l;
-    break;
-  }
+  // the order-1 level on the mesh itself: block stencil, from element matrices (the levels'
+  // element diagonals, at most 4 (p + 1)^3 values per element, use the same buffer)
+  for (int l = 0; l < nl && mg.ebe_level < 0; ++l)
+    if (mg.lv[l].p == 1) mg.ebe_level = l;
+  const int64_t n_elem = (int64_t)N[0] * N[1] * N[2];
+  if (hipMalloc(&mg.ebe, (size_t)n_elem * 1024 * sizeof(float)) != hipSuccess ||
+      (mg.ebe_level >= 0 &&
+       hipMalloc(&mg.stencil, (size_t)27 * 16 * mg.lv[mg.ebe_level].n_nodes * sizeof(float)) != hipSuccess))
+    return fail(PF_ENOMEM, "coarse element matrices: allocation failed");
   const size_t nfine = 4 * mg.lv[0].n_nodes * sizeof(float);
   if (hipMalloc(&mg.z32, 3 * c->n_nodes * sizeof(float)) != hipSuccess ||
       hipMalloc(&mg.tmpA, nfine) != hipSuccess || hipMalloc(&mg.tmpB, nfine) != hipSuccess ||
@@ -226,47 +225,6 @@ A32Args a32_args(pf_ctx* c, int level, const float* dz, float* out) {
   a.n_extra = c->n_extra;
   a.qd = c->d_qd32;
   return a;
-}
-
-template <int MODE, int PF, int PC, bool MB, bool GEO>
-pf_status launch_level32_v(pf_ctx* c, const A32Args& a, hipStream_t s) {
-  using S = A32Shape<PF, PC, PF>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    HIPCHK(hipFuncSetAttribute((const void*)k_level32<MODE, PF, PC, PF, MB, GEO>,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::lds_bytes));
-    attr_set = true;
-  }
-  for (int col = 0; col < 8; ++col) {
-    const int nb = xcd_grid(c->nbx, c->nby, c->nbz, col);
-    if (nb == 0) continue;
-    hipLaunchKernelGGL((k_level32<MODE, PF, PC, PF, MB, GEO>), dim3(nb), dim3(NT), S::lds_bytes, s, a, col, c->d_tabf);
-    HIPCHK(hipGetLastError());
-  }
-  return PF_OK;
-}
-
-// kernels with the extra branches' record layers only when branches are attached, with
-// the geometry record only on mapped elements (never both: pf_set_geometry checks it)
-template <int MODE, int PF, int PC>
-pf_status launch_level32(pf_ctx* c, const A32Args& a, hipStream_t s) {
-  if (a.qd)
-    return a.n_extra > 0 ? launch_level32_v<MODE, PF, PC, true, true>(c, a, s)
-                         : launch_level32_v<MODE, PF, PC, false, true>(c, a, s);
-  return a.n_extra > 0 ? launch_level32_v<MODE, PF, PC, true, false>(c, a, s)
-                       : launch_level32_v<MODE, PF, PC, false, false>(c, a, s);
-}
-
-template <int MODE, int PF>
-pf_status dispatch_pc(pf_ctx* c, int PC, const A32Args& a, hipStream_t s) {
-  switch (PC) {
-    case 2: return launch_level32<MODE, PF, 2>(c, a, s);
-    case 3: if constexpr (PF >= 3) return launch_level32<MODE, PF, 3>(c, a, s); break;
-    case 4: if constexpr (PF >= 4) return launch_level32<MODE, PF, 4>(c, a, s); break;
-    case 5: if constexpr (PF >= 5) return launch_level32<MODE, PF, 5>(c, a, s); break;
-    default: break;
-  }
-  return fail(PF_EUNSUPPORTED, "level order not built");
 }
 
 // Linearised apply on the matrix cores: PF = 4 (order-3 mesh, k_a32_q3) or PF = 3
@@ -381,9 +339,7 @@ EbeArgs ebe_args(pf_ctx* c) {
   EbeArgs a;
   a.m = mesh_dev(c);
   const MGLevel& F = c->mg.lv[0];
-  const MGLevel& L = c->mg.lv[c->mg.ebe_level];
   a.fine = LevelDev{F.P, F.nx1, F.ny1, F.n_nodes};
-  a.lev = LevelDev{L.P, L.nx1, L.ny1, L.n_nodes};
   a.n_q = c->n_q;
   a.z32 = c->mg.z32;
   a.rec = c->mg.rec;
@@ -451,11 +407,6 @@ pf_status stencil_apply(pf_ctx* c, int level, const float* x, float* out, hipStr
   return PF_OK;
 }
 
-template <int MODE>
-pf_status ebe_apply(pf_ctx* c, const float* x, float* out, hipStream_t s) {
-  return stencil_apply<MODE>(c, c->mg.ebe_level, x, out, s);
-}
-
 // Galerkin stencils of the coarser order-1 lattices, each from the level above it.
 pf_status build_h_levels(pf_ctx* c, hipStream_t s) {
   MGState& mg = c->mg;
@@ -472,52 +423,70 @@ pf_status build_h_levels(pf_ctx* c, hipStream_t s) {
   return PF_OK;
 }
 
-template <int MODE>
+// True where the level's operator is a block stencil: the order-1 level on the mesh and the
+// coarser lattices below it.
+bool is_stencil(const pf_ctx* c, int level) { return c->mg.lv[level].h > 0 || level == c->mg.ebe_level; }
+
+// Level operator out = A dz, unmasked.
 pf_status level_op_raw(pf_ctx* c, int level, const float* dz, float* out, hipStream_t s) {
-  if (c->mg.lv[level].h > 0) return stencil_apply<MODE>(c, level, dz, out, s);
-  if (level == c->mg.ebe_level && c->mg.ebe) return ebe_apply<MODE>(c, dz, out, s);
+  if (is_stencil(c, level)) return stencil_apply<0>(c, level, dz, out, s);
   const A32Args a = a32_args(c, level, dz, out);
-  const int PF = c->mg.lv[0].P, PC = c->mg.lv[level].P;
-  if (MODE == 0 && PF == 5) {
-    switch (PC) {
-      case 5: return launch_a32_q4<5>(c, a, s);
-      case 4: return launch_a32_q4<4>(c, a, s);
-      case 3: return launch_a32_q4<3>(c, a, s);
-      case 2: return launch_a32_q4<2>(c, a, s);
-      default: break;
-    }
-  }
-  if (MODE == 0 && PF == 4) {
-    switch (PC) {
-      case 4: return launch_a32_mfma<4, 4>(c, a, s);
-      case 3: return launch_a32_mfma<4, 3>(c, a, s);
-      case 2: return launch_a32_mfma<4, 2>(c, a, s);
-      default: break;
-    }
-  }
-  if (MODE == 0 && PF == 3) {
-    switch (PC) {
-      case 3: return launch_a32_mfma<3, 3>(c, a, s);
-      case 2: return launch_a32_mfma<3, 2>(c, a, s);
-      default: break;
-    }
-  }
-  switch (PF) {
-    case 2: return dispatch_pc<MODE, 2>(c, PC, a, s);
-    case 3: return dispatch_pc<MODE, 3>(c, PC, a, s);
-    case 4: return dispatch_pc<MODE, 4>(c, PC, a, s);
-    case 5: return dispatch_pc<MODE, 5>(c, PC, a, s);
-    default: return fail(PF_EUNSUPPORTED, "order not built");
+  switch (c->mg.lv[0].P * 10 + c->mg.lv[level].P) {
+    case 55: return launch_a32_q4<5>(c, a, s);
+    case 54: return launch_a32_q4<4>(c, a, s);
+    case 53: return launch_a32_q4<3>(c, a, s);
+    case 44: return launch_a32_mfma<4, 4>(c, a, s);
+    case 43: return launch_a32_mfma<4, 3>(c, a, s);
+    case 33: return launch_a32_mfma<3, 3>(c, a, s);
+    default: return fail(PF_EUNSUPPORTED, "level order not built");
   }
 }
 
 // Level operator; with Dirichlet faces the applied output is masked (M A x), so that
 // vectors that vanish on constrained entries stay in that subspace.
-template <int MODE>
 pf_status level_op(pf_ctx* c, int level, const float* dz, float* out, hipStream_t s) {
-  pf_status st = level_op_raw<MODE>(c, level, dz, out, s);
-  if (st || MODE != 0) return st;
+  pf_status st = level_op_raw(c, level, dz, out, s);
+  if (st) return st;
   return mask_level(c, level, out, s);
+}
+
+// Point-Jacobi diagonal of one level (unmasked).
+template <int PF, int PC>
+pf_status launch_diag(pf_ctx* c, const EbeArgs& a, const MGLevel& L, float* out, hipStream_t s) {
+  const int64_t n_elem = (int64_t)a.m.nx * a.m.ny * a.m.nz;
+  const dim3 nb((unsigned)((n_elem + EbeShape<PF>::NE - 1) / EbeShape<PF>::NE));
+  const bool mb = a.n_extra > 0;
+  float* ev = c->mg.ebe;
+  const DevTablesF* tabs = c->d_tabf;
+  if (a.qd && mb)
+    hipLaunchKernelGGL((k_level_diag<PF, PC, true, true>), nb, dim3(NT), 0, s, a, ev, tabs);
+  else if (a.qd)
+    hipLaunchKernelGGL((k_level_diag<PF, PC, false, true>), nb, dim3(NT), 0, s, a, ev, tabs);
+  else if (mb)
+    hipLaunchKernelGGL((k_level_diag<PF, PC, true>), nb, dim3(NT), 0, s, a, ev, tabs);
+  else
+    hipLaunchKernelGGL((k_level_diag<PF, PC, false>), nb, dim3(NT), 0, s, a, ev, tabs);
+  HIPCHK(hipGetLastError());
+  const int n_rows = (int)(L.n_nodes / L.nx1);
+  hipLaunchKernelGGL((k_gather_ext<float, PC>), dim3(1, std::min((n_rows + 3) / 4, 65535), 4), dim3(NT), 0, s,
+                     (const float*)ev, a.m.nx, a.m.ny, a.m.nz, L.nx1, L.ny1, n_rows, L.n_nodes, out);
+  HIPCHK(hipGetLastError());
+  return PF_OK;
+}
+
+pf_status level_diagonal(pf_ctx* c, int level, float* out, hipStream_t s) {
+  if (is_stencil(c, level)) return stencil_apply<1>(c, level, nullptr, out, s);
+  const EbeArgs a = ebe_args(c);
+  const MGLevel& L = c->mg.lv[level];
+  switch (c->mg.lv[0].P * 10 + L.P) {
+    case 55: return launch_diag<5, 5>(c, a, L, out, s);
+    case 54: return launch_diag<5, 4>(c, a, L, out, s);
+    case 53: return launch_diag<5, 3>(c, a, L, out, s);
+    case 44: return launch_diag<4, 4>(c, a, L, out, s);
+    case 43: return launch_diag<4, 3>(c, a, L, out, s);
+    case 33: return launch_diag<3, 3>(c, a, L, out, s);
+    default: return fail(PF_EUNSUPPORTED, "level order not built");
+  }
 }
 
 template <int P, int MODE, bool GEO = false>
@@ -530,12 +499,9 @@ pf_status launch_linearize(pf_ctx* c, const LinArgs& a, hipStream_t s) {
                                (int)lds));
     attr_set = true;
   }
-  for (int col = 0; col < 8; ++col) {
-    const int nb = xcd_grid(c->nbx, c->nby, c->nbz, col);
-    if (nb == 0) continue;
-    hipLaunchKernelGGL((k_linearize<P, P, MODE, GEO>), dim3(nb), dim3(NT), lds, s, a, col, c->d_tab);
-    HIPCHK(hipGetLastError());
-  }
+  hipLaunchKernelGGL((k_linearize<P, P, MODE, GEO>), dim3(xcd_grid_all(c->nbx, c->nby, c->nbz)), dim3(NT), lds, s, a,
+                     c->d_tab);
+  HIPCHK(hipGetLastError());
   return PF_OK;
 }
 
@@ -606,13 +572,13 @@ pf_status chebyshev(pf_ctx* c, int l, const float* b, float* x, int k, bool x_ze
   if (x_zero) {
     hipLaunchKernelGGL(k_vec_copy, dim3(g), dim3(NT), 0, s, b, L.r, n);
   } else {
-    if ((st = level_op<0>(c, l, x, L.t, s))) return st;
+    if ((st = level_op(c, l, x, L.t, s))) return st;
     hipLaunchKernelGGL(k_vec_sub, dim3(g), dim3(NT), 0, s, b, L.t, L.r, n);
   }
   hipLaunchKernelGGL(k_cheb_first, dim3(g), dim3(NT), 0, s, L.r, L.dinv, L.d, x, (float)(1.0 / theta),
                      x_zero ? 1 : 0, n);
   for (int it = 1; it < k; ++it) {
-    if ((st = level_op<0>(c, l, L.d, L.t, s))) return st;
+    if ((st = level_op(c, l, L.d, L.t, s))) return st;
     const double rn = 1.0 / (2.0 * sigma - rho);
     hipLaunchKernelGGL(k_cheb_step, dim3(g), dim3(NT), 0, s, L.r, L.t, L.dinv, L.d, x, (float)(rn * rho),
                        (float)(2.0 * rn / delta), n);
@@ -634,7 +600,7 @@ pf_status vcycle(pf_ctx* c, int l, const float* b, float* x, const pf_pmg_opts& 
     return PF_OK;
   }
   if ((st = chebyshev(c, l, b, x, o.cheb_degree, true, s))) return st;
-  if ((st = level_op<0>(c, l, x, L.t, s))) return st;
+  if ((st = level_op(c, l, x, L.t, s))) return st;
   hipLaunchKernelGGL(k_vec_sub, dim3(g), dim3(NT), 0, s, b, L.t, L.r, n);
   MGLevel& C = mg.lv[l + 1];
   if ((st = restrict_(c, l, L.r, C.b, s))) return st;
@@ -726,7 +692,7 @@ pf_status pf_linearize(pf_ctx* c, const double* z, void* stream) {
     MGLevel& L = mg.lv[l];
     const int64_t n = 4 * L.n_nodes;
     const int g = vec_grid(n);
-    if ((st = level_op<1>(c, l, nullptr, L.diag, s))) return st;
+    if ((st = level_diagonal(c, l, L.diag, s))) return st;
     hipLaunchKernelGGL(k_vec_inv, dim3(g), dim3(NT), 0, s, L.diag, L.dinv, n);
     hipLaunchKernelGGL(k_hash_fill, dim3(g), dim3(NT), 0, s, L.d, n, (uint64_t)(21150 + l));
     if ((st = mask_level(c, l, L.d, s))) return st;
@@ -734,7 +700,7 @@ pf_status pf_linearize(pf_ctx* c, const double* z, void* stream) {
     hipLaunchKernelGGL(k_norm_finish, dim3(1), dim3(NT), 0, s, mg.red, g, nrm + l, inv);
     hipLaunchKernelGGL(k_vec_axs_dev, dim3(g), dim3(NT), 0, s, L.d, L.d, inv, n);
     for (int it = 0; it < POWER_ITS; ++it) {
-      if ((st = level_op<0>(c, l, L.d, L.t, s))) return st;
+      if ((st = level_op(c, l, L.d, L.t, s))) return st;
       hipLaunchKernelGGL(k_vec_scale, dim3(g), dim3(NT), 0, s, L.dinv, L.t, n);
       hipLaunchKernelGGL(k_sumsq, dim3(g), dim3(NT), 0, s, L.t, n, mg.red);
       hipLaunchKernelGGL(k_norm_finish, dim3(1), dim3(NT), 0, s, mg.red, g, nrm + l, inv);
@@ -897,7 +863,7 @@ pf_status pf_apply_jacobian_f32(pf_ctx* c, int level, const float* dz, float* y,
   const size_t nb = 4 * c->mg.lv[level].n_nodes * sizeof(float);
   if (overlaps(dz, nb, y, nb)) return fail(PF_EINVAL, "y aliases dz");
   c->last_stream = (hipStream_t)stream;
-  return level_op<0>(c, level, dz, y, (hipStream_t)stream);
+  return level_op(c, level, dz, y, (hipStream_t)stream);
 }
 
 // FP64 Jacobian at the linearisation point from the stored FP64 record: the FP32

@@ -186,6 +186,10 @@ pf_status build_tables(pf_ctx* c) {
           t->D[P][Q][q][i] = D[q * P + i];
           tf->B[P][Q][q][i] = (float)B[q * P + i];
           tf->D[P][Q][q][i] = (float)D[q * P + i];
+          const double b = B[q * P + i], d = D[q * P + i];
+          tf->square[P][Q][0][i][q] = (float)(b * b);
+          tf->square[P][Q][1][i][q] = (float)(b * d);
+          tf->square[P][Q][2][i][q] = (float)(d * d);
         }
       }
     }
