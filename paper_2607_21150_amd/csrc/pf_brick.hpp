@@ -74,6 +74,18 @@ struct MeshDev {
   double jdet;           // hx hy hz / 8 (affine Jacobian determinant)
 };
 
+// Fields constrained on each face of the box: bit f of face[k] set means field f
+// (u_x, u_y, u_z, phi) is prescribed on face k = x0, x1, y0, y1, z0, z1.
+struct DirMask {
+  uint32_t face[6];
+};
+
+// Constrained fields (bits) of node (ix, iy, iz) of a lattice of nx1 x ny1 x nz1 nodes.
+__device__ inline uint32_t dir_bits(const DirMask& d, int ix, int iy, int iz, int nx1, int ny1, int nz1) {
+  return (ix == 0 ? d.face[0] : 0u) | (ix == nx1 - 1 ? d.face[1] : 0u) | (iy == 0 ? d.face[2] : 0u) |
+         (iy == ny1 - 1 ? d.face[3] : 0u) | (iz == 0 ? d.face[4] : 0u) | (iz == nz1 - 1 ? d.face[5] : 0u);
+}
+
 __device__ inline BrickGeom decode_brick(const MeshDev& m, int colour, int b) {
   const int cx = colour & 1, cy = (colour >> 1) & 1, cz = (colour >> 2) & 1;
   const int CX = (m.nbx - cx + 1) / 2, CY = (m.nby - cy + 1) / 2;

@@ -48,9 +48,9 @@ pf_status launch_op64_mfma_v(pf_ctx* c, OpArgs a, hipStream_t s) {
       hipLaunchKernelGGL((k_op64_q2<MODE, true, VOCE, MB, GEO>), dim3(ng), dim3(NT), 0, s, a, 0, c->d_tab);
     HIPCHK(hipGetLastError());
     const int n_rows = c->ny1 * c->nz1;
-    hipLaunchKernelGGL((k_gather_ext<double, 2 * P - 1>), dim3(1, std::min((n_rows + 3) / 4, 65535), 4), dim3(NT), 0,
-                       s, (const double*)c->d_ebuf, a.m.nbx, a.m.nby, a.m.nbz, c->nx1, c->ny1, n_rows, c->n_nodes,
-                       a.out);
+    hipLaunchKernelGGL((k_gather_ext<double, 2 * P - 1, E_STORE>), dim3(1, std::min((n_rows + 3) / 4, 65535), 4),
+                       dim3(NT), 0, s, (const double*)c->d_ebuf, a.m.nbx, a.m.nby, a.m.nbz, c->nx1, c->ny1, n_rows,
+                       c->n_nodes, store_epilogue(a.out));
     HIPCHK(hipGetLastError());
     return PF_OK;
   }
@@ -98,8 +98,9 @@ pf_status launch_op64_q4_v(pf_ctx* c, OpArgs a, hipStream_t s) {
     hipLaunchKernelGGL((k_op64_q4<MODE, VOCE, MB, GEO, true>), dim3(ng), dim3(NT5), 0, s, a, 0, c->d_tab);
     HIPCHK(hipGetLastError());
     const int n_rows = c->ny1 * c->nz1;
-    hipLaunchKernelGGL((k_gather_ext<double, 5>), dim3(1, std::min((n_rows + 3) / 4, 65535), 4), dim3(NT), 0, s,
-                       (const double*)c->d_ebuf, a.m.nx, a.m.ny, a.m.nz, c->nx1, c->ny1, n_rows, c->n_nodes, a.out);
+    hipLaunchKernelGGL((k_gather_ext<double, 5, E_STORE>), dim3(1, std::min((n_rows + 3) / 4, 65535), 4), dim3(NT), 0,
+                       s, (const double*)c->d_ebuf, a.m.nx, a.m.ny, a.m.nz, c->nx1, c->ny1, n_rows, c->n_nodes,
+                       store_epilogue(a.out));
     HIPCHK(hipGetLastError());
     return PF_OK;
   }

@@ -641,19 +641,23 @@ static __global__ __launch_bounds__(NT) void k_stencil_from_ebe(const float* __r
   }
 }
 
-// Apply (MODE 0: out = S x) or diagonal (MODE 1) of the stencil; one thread per
-// (node, output field), blockIdx.y = field. Reads of S are coalesced over nodes.
-template <int MODE>
-__global__ __launch_bounds__(NT) void k_stencil_apply(const float* __restrict__ S, int nx1, int ny1, int nz1,
-                                                      int64_t n, const float* __restrict__ x,
-                                                      float* __restrict__ out) {
+// Diagonal of the stencil: out[f][i] = S[0 offset][f][f][i].
+static __global__ __launch_bounds__(NT) void k_stencil_diag(const float* __restrict__ S, int64_t n, float* __restrict__ out) {
   const int f = blockIdx.y;
+  for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT)
+    out[f * n + i] = S[((int64_t)13 * 16 + 5 * f) * n + i];
+}
+
+// Apply of the stencil with the epilogue OP; one thread per (node, output field), blockIdx.y =
+// field. Reads of S are coalesced over nodes. The epilogue must not write x.
+template <int OP>
+__global__ __launch_bounds__(NT) void k_stencil_apply(const float* __restrict__ S, int nx1, int ny1, int nz1,
+                                                      int64_t n, const float* __restrict__ x, Epilogue<float> ep) {
+  const int f = blockIdx.y;
+  double sq = 0.0;
   for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT) {
-    if (MODE == 1) {
-      out[f * n + i] = S[((int64_t)13 * 16 + 5 * f) * n + i];
-      continue;
-    }
     const int ix = (int)(i % nx1), iy = (int)((i / nx1) % ny1), iz = (int)(i / ((int64_t)nx1 * ny1));
+    const EpiIn<float> in = epi_load<OP>(ep, f * n + i);
     float acc = 0.f;
 #pragma unroll
     for (int dz = -1; dz <= 1; ++dz) {
@@ -672,8 +676,11 @@ __global__ __launch_bounds__(NT) void k_stencil_apply(const float* __restrict__ 
         }
       }
     }
-    out[f * n + i] = acc;
+    if (ep.has_dir && ((dir_bits(ep.dir, ix, iy, iz, nx1, ny1, nz1) >> f) & 1u)) acc = 0.f;
+    const float y = epi_apply<OP>(ep, in, f * n + i, acc);
+    if (OP == E_POWER) sq += (double)y * (double)y;
   }
+  if (OP == E_POWER) epi_sum(sq, ep.part, (int)(blockIdx.x + gridDim.x * f));
 }
 
 // Galerkin product of a block stencil on a coarser order-1 lattice: Sc = P^T Sf P with P

@@ -112,6 +112,14 @@ inline bool use_brick_buffer(const pf_ctx* c) {
   return bytes <= PF_SCATTER_AUTO_BYTES;
 }
 
+// The epilogue of a plain apply: every entry stored.
+template <typename T>
+pfmf::Epilogue<T> store_epilogue(T* out) {
+  pfmf::Epilogue<T> e{};
+  e.out = out;
+  return e;
+}
+
 // FP64 residual (MODE 0), Jacobian (1) or adjoint (2) over the context's mesh: every
 // launch of one apply on stream s (defined in pf_dispatch.hpp, instantiated once per mode).
 template <int MODE>

@@ -380,14 +380,113 @@ __device__ inline void lin_tangent(const RecordSoAT<V>& rec, int64_t n_q, const 
 using A32Args = LinApplyArgs<float>;
 
 // ---------------------------------------------------------------------------
+// What a level apply does with each entry of A d as it is formed: the node gather and the block
+// stencil carry the vector operation that follows the apply, so that A d is neither written nor
+// read back (a Chebyshev step on n entries moves 28 n bytes beside the apply instead of 40 n, in
+// one launch less, and the Dirichlet mask needs no launch of its own). Order 4 on 40^3 elements:
+// gather 80 us and step 107 us -> 102 us in one launch, the Newton step on the order-3 32^3 mesh
+// 69.9 -> 60.7 ms.
+// ---------------------------------------------------------------------------
+enum EpiOp {
+  E_STORE,  // out = v
+  E_RESID,  // r = b - v
+  E_FIRST,  // r = b - v, d = c dinv r (the Chebyshev start; x takes d in the first step)
+  E_STEP,   // r = r_in - v, d = a d_in + c dinv r, x = x_in + [d_in] + d
+  E_POWER   // out = dinv v inv[0], and the sum of its squares
+};
+
+template <typename T> struct Epilogue {
+  T *out, *r, *d, *x;
+  const T *b, *r_in, *d_in, *x_in, *dinv;  // x_in null: x starts from zero
+  T a, c;
+  int x_first;          // E_STEP: the first one, x takes d_in too
+  const float* inv;     // E_POWER: 1 / norm of the vector applied
+  double* part;         // E_POWER: one partial sum per workgroup
+  DirMask dir;          // constrained entries: v = 0
+  int has_dir, nz1;
+};
+
+// The epilogue's inputs at entry i, loaded before A d is complete.
+template <typename T> struct EpiIn {
+  T r, d, x, dinv;
+};
+template <int OP, typename T>
+__device__ inline EpiIn<T> epi_load(const Epilogue<T>& e, int64_t i) {
+  EpiIn<T> v{T(0), T(0), T(0), T(0)};
+  if (OP == E_RESID || OP == E_FIRST) v.r = e.b[i];
+  if (OP == E_STEP) {
+    v.r = e.r_in[i];
+    v.d = e.d_in[i];
+    if (e.x_in) v.x = e.x_in[i];
+  }
+  if (OP == E_FIRST || OP == E_STEP || OP == E_POWER) v.dinv = e.dinv[i];
+  return v;
+}
+
+// Entry i of A d is v.
+template <int OP, typename T>
+__device__ inline T epi_apply(const Epilogue<T>& e, const EpiIn<T>& in, int64_t i, T v) {
+  if (OP == E_STORE) {
+    e.out[i] = v;
+  } else if (OP == E_RESID) {
+    e.r[i] = in.r - v;
+  } else if (OP == E_FIRST) {
+    const T r = in.r - v;
+    e.r[i] = r;
+    e.d[i] = e.c * in.dinv * r;
+  } else if (OP == E_STEP) {
+    const T r = in.r - v, d = e.a * in.d + e.c * in.dinv * r;
+    e.r[i] = r;
+    e.d[i] = d;
+    e.x[i] = (e.x_first ? in.x + in.d : in.x) + d;
+  } else {
+    const T y = (in.dinv * v) * (T)e.inv[0];
+    e.out[i] = y;
+    return y;
+  }
+  return T(0);
+}
+
+// E_POWER's partial sum of a workgroup of NT threads (deterministic tree).
+__device__ inline void epi_sum(double s, double* part, int block) {
+  __shared__ double red[NT];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int st = NT / 2; st > 0; st >>= 1) {
+    if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) part[block] = red[0];
+}
+
+// The same on a stored A d (the colour launches write it): one thread per node, blockIdx.y = field.
+template <int OP>
+__global__ __launch_bounds__(NT) void k_epilogue(const float* v, int nx1, int ny1, int64_t n, Epilogue<float> e) {
+  const int f = blockIdx.y;
+  double s = 0.0;
+  for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT) {
+    const EpiIn<float> in = epi_load<OP>(e, f * n + i);
+    float w = v[f * n + i];
+    if (e.has_dir) {
+      const int ix = (int)(i % nx1), iy = (int)((i / nx1) % ny1), iz = (int)(i / ((int64_t)nx1 * ny1));
+      if ((dir_bits(e.dir, ix, iy, iz, nx1, ny1, e.nz1) >> f) & 1u) w = 0.f;
+    }
+    const float y = epi_apply<OP>(e, in, f * n + i, w);
+    if (OP == E_POWER) s += (double)y * (double)y;
+  }
+  if (OP == E_POWER) epi_sum(s, e.part, (int)(blockIdx.x + gridDim.x * f));
+}
+
+// ---------------------------------------------------------------------------
 // Level transfers (one direction per launch) and vector kernels.
 // ---------------------------------------------------------------------------
 
 // out[f][i2][i1][i0] = sum_k w[c*nw + k] in[f][...][base[c] + k][...] along `axis`,
-// where c is the output coordinate along axis. in dims: (n0i, n1i, n2i).
+// where c is the output coordinate along axis. in dims: (n0i, n1i, n2i). add: out += the sum;
+// has_dir: the sum is 0 on constrained entries of the output lattice.
 static __global__ void k_transfer_1d(const float* __restrict__ in, float* __restrict__ out, int n0o, int n1o, int n2o,
                               int n0i, int n1i, int n2i, int axis, const int* __restrict__ base,
-                              const float* __restrict__ w, int nw) {
+                              const float* __restrict__ w, int nw, int add, DirMask dir, int has_dir) {
   const int64_t no = (int64_t)n0o * n1o * n2o;
   const int64_t ni = (int64_t)n0i * n1i * n2i;
   for (int64_t o = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; o < no; o += (int64_t)gridDim.x * blockDim.x) {
@@ -408,14 +507,13 @@ static __global__ void k_transfer_1d(const float* __restrict__ in, float* __rest
 #pragma unroll
       for (int f = 0; f < 4; ++f) acc[f] += wk * in[f * ni + ii];
     }
+    const uint32_t bits = has_dir ? dir_bits(dir, i0, i1, i2, n0o, n1o, n2o) : 0u;
 #pragma unroll
-    for (int f = 0; f < 4; ++f) out[f * no + o] = acc[f];
+    for (int f = 0; f < 4; ++f) {
+      const float v = (bits >> f) & 1u ? 0.f : acc[f];
+      out[f * no + o] = add ? out[f * no + o] + v : v;
+    }
   }
-}
-
-static __global__ void k_vec_zero(float* __restrict__ x, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    x[i] = 0.f;
 }
 
 static __global__ void k_vec_copy(const float* __restrict__ a, float* __restrict__ b, int64_t n) {
@@ -429,44 +527,17 @@ static __global__ void k_vec_add(const float* __restrict__ x, float* __restrict_
     y[i] += x[i];
 }
 
-// r = b - t
-static __global__ void k_vec_sub(const float* __restrict__ b, const float* __restrict__ t, float* __restrict__ r, int64_t n) {
+// Chebyshev start from x = 0: d = s dinv b (the first step's residual is b, its x is d)
+static __global__ void k_cheb_start(const float* __restrict__ b, const float* __restrict__ dinv, float* __restrict__ d,
+                             float s, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    r[i] = b[i] - t[i];
-}
-
-// Chebyshev start: d = s * dinv * r ; x = (x_zero ? 0 : x) + d
-static __global__ void k_cheb_first(const float* __restrict__ r, const float* __restrict__ dinv, float* __restrict__ d,
-                             float* __restrict__ x, float s, int x_zero, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const float di = s * dinv[i] * r[i];
-    d[i] = di;
-    x[i] = (x_zero ? 0.f : x[i]) + di;
-  }
-}
-
-// Chebyshev step: r -= t ; d = a d + b dinv r ; x += d
-static __global__ void k_cheb_step(float* __restrict__ r, const float* __restrict__ t, const float* __restrict__ dinv,
-                            float* __restrict__ d, float* __restrict__ x, float a, float b, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const float ri = r[i] - t[i];
-    r[i] = ri;
-    const float di = a * d[i] + b * dinv[i] * ri;
-    d[i] = di;
-    x[i] += di;
-  }
+    d[i] = s * dinv[i] * b[i];
 }
 
 // dinv = 1 / diag (0 where the diagonal vanishes)
 static __global__ void k_vec_inv(const float* __restrict__ a, float* __restrict__ b, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     b[i] = a[i] != 0.f ? 1.f / a[i] : 0.f;
-}
-
-// x = dinv * x
-static __global__ void k_vec_scale(const float* __restrict__ dinv, float* __restrict__ x, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    x[i] *= dinv[i];
 }
 
 // double-precision sum of squares, per-block partials (deterministic)
@@ -486,13 +557,7 @@ static __global__ void k_sumsq(const float* __restrict__ x, int64_t n, double* _
   if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-// b = a / ||a|| given the squared norm on the host
-static __global__ void k_vec_axs(const float* __restrict__ a, float* __restrict__ b, float s, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    b[i] = s * a[i];
-}
-
-// FP64 -> FP32 mirror of the displacement rows of z
+// FP64 -> FP32 copy
 static __global__ void k_to_f32(const double* __restrict__ x, float* __restrict__ y, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     y[i] = (float)x[i];

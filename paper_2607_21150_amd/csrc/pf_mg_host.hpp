@@ -5,6 +5,7 @@
 namespace {
 
 constexpr int VEC_BLOCKS = 2048;
+constexpr int RED_PARTS = 2048;  // block partials of a reduction (VEC_BLOCKS, or four fields' EPI_BLOCKS)
 
 inline int vec_grid(int64_t n) {
   const int64_t b = (n + NT - 1) / NT;
@@ -164,7 +165,7 @@ pf_status mg_alloc_levels(pf_ctx* c, const int* orders, int nl) {
   const size_t nfine = 4 * mg.lv[0].n_nodes * sizeof(float);
   if (hipMalloc(&mg.z32, 3 * c->n_nodes * sizeof(float)) != hipSuccess ||
       hipMalloc(&mg.tmpA, nfine) != hipSuccess || hipMalloc(&mg.tmpB, nfine) != hipSuccess ||
-      hipMalloc(&mg.red, (VEC_BLOCKS + 16) * sizeof(double)) != hipSuccess)
+      hipMalloc(&mg.red, (RED_PARTS + 16) * sizeof(double)) != hipSuccess)
     return fail(PF_ENOMEM, "multigrid allocation failed");
   return PF_OK;
 }
@@ -204,7 +205,7 @@ pf_status mask_fine64(pf_ctx* c, double* v, hipStream_t s) {
   return PF_OK;
 }
 
-A32Args a32_args(pf_ctx* c, int level, const float* dz, float* out) {
+A32Args a32_args(pf_ctx* c, int level, const float* dz) {
   A32Args a;
   a.m = mesh_dev(c);
   const MGLevel& F = c->mg.lv[0];
@@ -219,7 +220,7 @@ A32Args a32_args(pf_ctx* c, int level, const float* dz, float* out) {
   a.mats = c->d_matsf;
   a.nph = (int)c->phases.size();
   a.fr = frac_params<float>(c->fr);
-  a.out = out;
+  a.out = nullptr;
   a.ebuf = nullptr;
   a.xmats = c->d_xmatsf;
   a.n_extra = c->n_extra;
@@ -227,12 +228,47 @@ A32Args a32_args(pf_ctx* c, int level, const float* dz, float* out) {
   return a;
 }
 
+// Rows of the node gather in flight: E_POWER leaves one partial sum per workgroup, EPI_BLOCKS of
+// them per field.
+constexpr int EPI_BLOCKS = 512;
+template <int OP>
+int epi_blocks(int64_t blocks, int most) {
+  return (int)std::min<int64_t>(blocks, OP == E_POWER ? EPI_BLOCKS : most);
+}
+
+// Node gather of an extended grid of nbx x nby x nbz blocks with the epilogue OP.
+template <typename V, int NB, int OP>
+pf_status launch_gather(const LinApplyArgs<V>& a, int nbx, int nby, int nbz, const Epilogue<V>& ep, hipStream_t s) {
+  const int n_rows = (int)(a.lev.n_nodes / a.lev.nx1);
+  hipLaunchKernelGGL((k_gather_ext<V, NB, OP>), dim3(1, epi_blocks<OP>((n_rows + 3) / 4, 65535), 4), dim3(NT), 0, s,
+                     (const V*)a.ebuf, nbx, nby, nbz, a.lev.nx1, a.lev.ny1, n_rows, a.lev.n_nodes, ep);
+  HIPCHK(hipGetLastError());
+  return PF_OK;
+}
+
+// Colour launches write A dz whole: where E_STORE and E_POWER put their result, and to the spare
+// vector otherwise (the fine level's r, d and x may be the epilogue's inputs); the epilogue follows.
+template <int OP>
+float* colour_out(pf_ctx* c, const LinApplyArgs<float>& a, const Epilogue<float>& ep) {
+  (void)a;
+  return OP == E_STORE || OP == E_POWER ? ep.out : c->mg.tmpA;
+}
+template <int OP>
+pf_status colour_epilogue(const LinApplyArgs<float>& a, const Epilogue<float>& ep, hipStream_t s) {
+  if (OP == E_STORE && !ep.has_dir) return PF_OK;
+  const int nb = epi_blocks<OP>((a.lev.n_nodes + NT - 1) / NT, 65536);
+  hipLaunchKernelGGL(k_epilogue<OP>, dim3(nb, 4), dim3(NT), 0, s, (const float*)a.out, a.lev.nx1, a.lev.ny1,
+                     a.lev.n_nodes, ep);
+  HIPCHK(hipGetLastError());
+  return PF_OK;
+}
+
 // Linearised apply on the matrix cores: PF = 4 (order-3 mesh, k_a32_q3) or PF = 3
 // (order-2 mesh, k_a32_q2); V = float for the FP32 levels, V = double for the apply
 // from the stored FP64 linearisation (fine level). The brick buffer of each precision
 // is sized for the fine level and shared by the coarser ones.
-template <typename V, int PF, int PC, bool MB, bool GEO>
-pf_status launch_lin_mfma_v(pf_ctx* c, LinApplyArgs<V> a, hipStream_t s) {
+template <typename V, int PF, int PC, bool MB, bool GEO, int OP>
+pf_status launch_lin_mfma_v(pf_ctx* c, LinApplyArgs<V> a, const Epilogue<V>& ep, hipStream_t s) {
   if (use_brick_buffer(c)) {
     V** buf;
     if constexpr (sizeof(V) == 4) buf = &c->mg.ebuf32;
@@ -254,13 +290,10 @@ pf_status launch_lin_mfma_v(pf_ctx* c, LinApplyArgs<V> a, hipStream_t s) {
       hipLaunchKernelGGL((k_a32_q2<V, PC, true, MB, GEO>), dim3(ng), dim3(NT), 0, s, a, 0, c->d_tab);
     }
     HIPCHK(hipGetLastError());
-    const int n_rows = (int)(a.lev.n_nodes / a.lev.nx1);
-    hipLaunchKernelGGL((k_gather_ext<V, 2 * PC - 1>), dim3(1, std::min((n_rows + 3) / 4, 65535), 4), dim3(NT), 0, s,
-                       (const V*)a.ebuf, a.m.nbx, a.m.nby, a.m.nbz, a.lev.nx1, a.lev.ny1, n_rows, a.lev.n_nodes,
-                       a.out);
-    HIPCHK(hipGetLastError());
-    return PF_OK;
+    return launch_gather<V, 2 * PC - 1, OP>(a, a.m.nbx, a.m.nby, a.m.nbz, ep, s);
   }
+  if constexpr (sizeof(V) == 4) a.out = colour_out<OP>(c, a, ep);
+  else a.out = ep.out;
   for (int col = 0; col < 8; ++col) {
     const int nb = xcd_grid(c->nbx, c->nby, c->nbz, col);
     if (nb == 0) continue;
@@ -270,25 +303,21 @@ pf_status launch_lin_mfma_v(pf_ctx* c, LinApplyArgs<V> a, hipStream_t s) {
       hipLaunchKernelGGL((k_a32_q2<V, PC, false, MB, GEO>), dim3(nb), dim3(NT), 0, s, a, col, c->d_tab);
     HIPCHK(hipGetLastError());
   }
+  if constexpr (sizeof(V) == 4) return colour_epilogue<OP>(a, ep, s);
   return PF_OK;
 }
 
-template <typename V, int PF, int PC>
-pf_status launch_lin_mfma(pf_ctx* c, const LinApplyArgs<V>& a, hipStream_t s) {
+template <typename V, int PF, int PC, int OP>
+pf_status launch_lin_mfma(pf_ctx* c, const LinApplyArgs<V>& a, const Epilogue<V>& ep, hipStream_t s) {
   if (a.qd)
-    return a.n_extra > 0 ? launch_lin_mfma_v<V, PF, PC, true, true>(c, a, s)
-                         : launch_lin_mfma_v<V, PF, PC, false, true>(c, a, s);
-  return a.n_extra > 0 ? launch_lin_mfma_v<V, PF, PC, true, false>(c, a, s)
-                       : launch_lin_mfma_v<V, PF, PC, false, false>(c, a, s);
+    return a.n_extra > 0 ? launch_lin_mfma_v<V, PF, PC, true, true, OP>(c, a, ep, s)
+                         : launch_lin_mfma_v<V, PF, PC, false, true, OP>(c, a, ep, s);
+  return a.n_extra > 0 ? launch_lin_mfma_v<V, PF, PC, true, false, OP>(c, a, ep, s)
+                       : launch_lin_mfma_v<V, PF, PC, false, false, OP>(c, a, ep, s);
 }
 
-template <int PF, int PC>
-pf_status launch_a32_mfma(pf_ctx* c, A32Args a, hipStream_t s) {
-  return launch_lin_mfma<float, PF, PC>(c, a, s);
-}
-
-template <typename V, int PC, bool MB, bool GEO>
-pf_status launch_lin_q4_v(pf_ctx* c, const LinApplyArgs<V>& a0, hipStream_t s) {
+template <typename V, int PC, bool MB, bool GEO, int OP>
+pf_status launch_lin_q4_v(pf_ctx* c, const LinApplyArgs<V>& a0, const Epilogue<V>& ep, hipStream_t s) {
   LinApplyArgs<V> a = a0;
   if (use_brick_buffer(c)) {
     // element vectors of the level (buffer sized for the fine level), then the node gather
@@ -305,12 +334,10 @@ pf_status launch_lin_q4_v(pf_ctx* c, const LinApplyArgs<V>& a0, hipStream_t s) {
     else
       hipLaunchKernelGGL((k_a32_q4<V, PC, MB, GEO, true>), dim3(ng), dim3(NT5), 0, s, a, 0, c->d_tab);
     HIPCHK(hipGetLastError());
-    const int n_rows = (int)(a.lev.n_nodes / a.lev.nx1);
-    hipLaunchKernelGGL((k_gather_ext<V, PC>), dim3(1, std::min((n_rows + 3) / 4, 65535), 4), dim3(NT), 0, s,
-                       (const V*)a.ebuf, a.m.nx, a.m.ny, a.m.nz, a.lev.nx1, a.lev.ny1, n_rows, a.lev.n_nodes, a.out);
-    HIPCHK(hipGetLastError());
-    return PF_OK;
+    return launch_gather<V, PC, OP>(a, a.m.nx, a.m.ny, a.m.nz, ep, s);
   }
+  if constexpr (sizeof(V) == 4) a.out = colour_out<OP>(c, a, ep);
+  else a.out = ep.out;
   for (int col = 0; col < 8; ++col) {
     const int ng = xcd_grid(c->mesh.nx, c->mesh.ny, c->mesh.nz, col);
     if (ng == 0) continue;
@@ -320,19 +347,17 @@ pf_status launch_lin_q4_v(pf_ctx* c, const LinApplyArgs<V>& a0, hipStream_t s) {
       hipLaunchKernelGGL((k_a32_q4<V, PC, MB, GEO>), dim3(ng), dim3(NT5), 0, s, a, col, c->d_tab);
     HIPCHK(hipGetLastError());
   }
+  if constexpr (sizeof(V) == 4) return colour_epilogue<OP>(a, ep, s);
   return PF_OK;
 }
 
-template <typename V, int PC>
-pf_status launch_lin_q4(pf_ctx* c, const LinApplyArgs<V>& a, hipStream_t s) {
+template <typename V, int PC, int OP>
+pf_status launch_lin_q4(pf_ctx* c, const LinApplyArgs<V>& a, const Epilogue<V>& ep, hipStream_t s) {
   if (a.qd)
-    return a.n_extra > 0 ? launch_lin_q4_v<V, PC, true, true>(c, a, s) : launch_lin_q4_v<V, PC, false, true>(c, a, s);
-  return a.n_extra > 0 ? launch_lin_q4_v<V, PC, true, false>(c, a, s) : launch_lin_q4_v<V, PC, false, false>(c, a, s);
-}
-
-template <int PC>
-pf_status launch_a32_q4(pf_ctx* c, const A32Args& a, hipStream_t s) {
-  return launch_lin_q4<float, PC>(c, a, s);
+    return a.n_extra > 0 ? launch_lin_q4_v<V, PC, true, true, OP>(c, a, ep, s)
+                         : launch_lin_q4_v<V, PC, false, true, OP>(c, a, ep, s);
+  return a.n_extra > 0 ? launch_lin_q4_v<V, PC, true, false, OP>(c, a, ep, s)
+                       : launch_lin_q4_v<V, PC, false, false, OP>(c, a, ep, s);
 }
 
 EbeArgs ebe_args(pf_ctx* c) {
@@ -395,14 +420,17 @@ pf_status ebe_assemble(pf_ctx* c, hipStream_t s) {
   return PF_OK;
 }
 
-// Block-stencil apply (MODE 0) or diagonal (MODE 1) of an order-1 level: the mesh's own
-// order-1 level (mg.stencil) or a coarser lattice (its own S).
-template <int MODE>
-pf_status stencil_apply(pf_ctx* c, int level, const float* x, float* out, hipStream_t s) {
+// Block stencil of an order-1 level: the mesh's own (mg.stencil) or a coarser lattice's S.
+const float* level_stencil(const pf_ctx* c, int level) {
+  return c->mg.lv[level].h > 0 ? c->mg.lv[level].S : c->mg.stencil;
+}
+
+template <int OP>
+pf_status stencil_apply(pf_ctx* c, int level, const float* x, const Epilogue<float>& ep, hipStream_t s) {
   const MGLevel& L = c->mg.lv[level];
-  const float* S = L.h > 0 ? L.S : c->mg.stencil;
-  const int nb = (int)std::min<int64_t>((L.n_nodes + NT - 1) / NT, 65536);
-  hipLaunchKernelGGL(k_stencil_apply<MODE>, dim3(nb, 4), dim3(NT), 0, s, S, L.nx1, L.ny1, L.nz1, L.n_nodes, x, out);
+  const int nb = epi_blocks<OP>((L.n_nodes + NT - 1) / NT, 65536);
+  hipLaunchKernelGGL(k_stencil_apply<OP>, dim3(nb, 4), dim3(NT), 0, s, level_stencil(c, level), L.nx1, L.ny1, L.nz1,
+                     L.n_nodes, x, ep);
   HIPCHK(hipGetLastError());
   return PF_OK;
 }
@@ -427,27 +455,34 @@ pf_status build_h_levels(pf_ctx* c, hipStream_t s) {
 // coarser lattices below it.
 bool is_stencil(const pf_ctx* c, int level) { return c->mg.lv[level].h > 0 || level == c->mg.ebe_level; }
 
-// Level operator out = A dz, unmasked.
-pf_status level_op_raw(pf_ctx* c, int level, const float* dz, float* out, hipStream_t s) {
-  if (is_stencil(c, level)) return stencil_apply<0>(c, level, dz, out, s);
-  const A32Args a = a32_args(c, level, dz, out);
-  switch (c->mg.lv[0].P * 10 + c->mg.lv[level].P) {
-    case 55: return launch_a32_q4<5>(c, a, s);
-    case 54: return launch_a32_q4<4>(c, a, s);
-    case 53: return launch_a32_q4<3>(c, a, s);
-    case 44: return launch_a32_mfma<4, 4>(c, a, s);
-    case 43: return launch_a32_mfma<4, 3>(c, a, s);
-    case 33: return launch_a32_mfma<3, 3>(c, a, s);
+// Level operator with Dirichlet faces (M A dz: vectors that vanish on constrained entries stay in
+// that subspace), each entry passed to the epilogue OP. On a stencil level the epilogue must not
+// write dz.
+template <int OP>
+pf_status level_op(pf_ctx* c, int level, const float* dz, Epilogue<float> ep, hipStream_t s) {
+  const MGLevel& L = c->mg.lv[level];
+  ep.dir = c->dir;
+  ep.has_dir = c->has_dir;
+  ep.nz1 = L.nz1;
+  if (is_stencil(c, level)) return stencil_apply<OP>(c, level, dz, ep, s);
+  const A32Args a = a32_args(c, level, dz);
+  switch (c->mg.lv[0].P * 10 + L.P) {
+    case 55: return launch_lin_q4<float, 5, OP>(c, a, ep, s);
+    case 54: return launch_lin_q4<float, 4, OP>(c, a, ep, s);
+    case 53: return launch_lin_q4<float, 3, OP>(c, a, ep, s);
+    case 44: return launch_lin_mfma<float, 4, 4, OP>(c, a, ep, s);
+    case 43: return launch_lin_mfma<float, 4, 3, OP>(c, a, ep, s);
+    case 33: return launch_lin_mfma<float, 3, 3, OP>(c, a, ep, s);
     default: return fail(PF_EUNSUPPORTED, "level order not built");
   }
 }
 
-// Level operator; with Dirichlet faces the applied output is masked (M A x), so that
-// vectors that vanish on constrained entries stay in that subspace.
-pf_status level_op(pf_ctx* c, int level, const float* dz, float* out, hipStream_t s) {
-  pf_status st = level_op_raw(c, level, dz, out, s);
-  if (st) return st;
-  return mask_level(c, level, out, s);
+// Partial sums that E_POWER leaves on a level (one per workgroup of the launch that runs it).
+pf_status power_parts(const pf_ctx* c, int level, int& parts) {
+  const MGLevel& L = c->mg.lv[level];
+  const int64_t per_block = is_stencil(c, level) || !use_brick_buffer(c) ? NT : 4 * (int64_t)L.nx1;
+  parts = 4 * epi_blocks<E_POWER>((L.n_nodes + per_block - 1) / per_block, 0);
+  return parts <= RED_PARTS ? PF_OK : fail(PF_EHIP, "reduction scratch too small");
 }
 
 // Point-Jacobi diagonal of one level (unmasked).
@@ -468,16 +503,21 @@ pf_status launch_diag(pf_ctx* c, const EbeArgs& a, const MGLevel& L, float* out,
     hipLaunchKernelGGL((k_level_diag<PF, PC, false>), nb, dim3(NT), 0, s, a, ev, tabs);
   HIPCHK(hipGetLastError());
   const int n_rows = (int)(L.n_nodes / L.nx1);
-  hipLaunchKernelGGL((k_gather_ext<float, PC>), dim3(1, std::min((n_rows + 3) / 4, 65535), 4), dim3(NT), 0, s,
-                     (const float*)ev, a.m.nx, a.m.ny, a.m.nz, L.nx1, L.ny1, n_rows, L.n_nodes, out);
+  hipLaunchKernelGGL((k_gather_ext<float, PC, E_STORE>), dim3(1, std::min((n_rows + 3) / 4, 65535), 4), dim3(NT), 0, s,
+                     (const float*)ev, a.m.nx, a.m.ny, a.m.nz, L.nx1, L.ny1, n_rows, L.n_nodes, store_epilogue(out));
   HIPCHK(hipGetLastError());
   return PF_OK;
 }
 
 pf_status level_diagonal(pf_ctx* c, int level, float* out, hipStream_t s) {
-  if (is_stencil(c, level)) return stencil_apply<1>(c, level, nullptr, out, s);
-  const EbeArgs a = ebe_args(c);
   const MGLevel& L = c->mg.lv[level];
+  if (is_stencil(c, level)) {
+    hipLaunchKernelGGL(k_stencil_diag, dim3(vec_grid(L.n_nodes), 4), dim3(NT), 0, s, level_stencil(c, level), L.n_nodes,
+                       out);
+    HIPCHK(hipGetLastError());
+    return PF_OK;
+  }
+  const EbeArgs a = ebe_args(c);
   switch (c->mg.lv[0].P * 10 + L.P) {
     case 55: return launch_diag<5, 5>(c, a, L, out, s);
     case 54: return launch_diag<5, 4>(c, a, L, out, s);
@@ -505,21 +545,8 @@ pf_status launch_linearize(pf_ctx* c, const LinArgs& a, hipStream_t s) {
   return PF_OK;
 }
 
-pf_status sumsq(pf_ctx* c, const float* x, int64_t n, hipStream_t s, double* out) {
-  const int g = vec_grid(n);
-  hipLaunchKernelGGL(k_sumsq, dim3(g), dim3(NT), 0, s, x, n, c->mg.red);
-  HIPCHK(hipGetLastError());
-  std::vector<double> h(g);
-  HIPCHK(hipMemcpyAsync(h.data(), c->mg.red, g * sizeof(double), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
-  double acc = 0.0;
-  for (double v : h) acc += v;
-  *out = acc;
-  return PF_OK;
-}
-
-// y = P x (coarse level l+1 -> level l), separable passes x, y, z.
-pf_status prolong(pf_ctx* c, int l, const float* xc, float* xf, hipStream_t s) {
+// y = P x (coarse level l+1 -> level l) or y += P x, separable passes x, y, z; masked.
+pf_status prolong(pf_ctx* c, int l, const float* xc, float* xf, bool add, hipStream_t s) {
   const MGLevel& F = c->mg.lv[l];
   const MGLevel& C = c->mg.lv[l + 1];
   float* A = c->mg.tmpA;
@@ -527,18 +554,18 @@ pf_status prolong(pf_ctx* c, int l, const float* xc, float* xf, hipStream_t s) {
   int64_t n;
   n = (int64_t)F.nx1 * C.ny1 * C.nz1;
   hipLaunchKernelGGL(k_transfer_1d, dim3(vec_grid(n)), dim3(NT), 0, s, xc, A, F.nx1, C.ny1, C.nz1, C.nx1, C.ny1,
-                     C.nz1, 0, F.pbase[0], F.pw[0], C.P);
+                     C.nz1, 0, F.pbase[0], F.pw[0], C.P, 0, c->dir, 0);
   n = (int64_t)F.nx1 * F.ny1 * C.nz1;
   hipLaunchKernelGGL(k_transfer_1d, dim3(vec_grid(n)), dim3(NT), 0, s, A, B, F.nx1, F.ny1, C.nz1, F.nx1, C.ny1,
-                     C.nz1, 1, F.pbase[1], F.pw[1], C.P);
+                     C.nz1, 1, F.pbase[1], F.pw[1], C.P, 0, c->dir, 0);
   n = F.n_nodes;
   hipLaunchKernelGGL(k_transfer_1d, dim3(vec_grid(n)), dim3(NT), 0, s, B, xf, F.nx1, F.ny1, F.nz1, F.nx1, F.ny1,
-                     C.nz1, 2, F.pbase[2], F.pw[2], C.P);
+                     C.nz1, 2, F.pbase[2], F.pw[2], C.P, add ? 1 : 0, c->dir, c->has_dir ? 1 : 0);
   HIPCHK(hipGetLastError());
-  return mask_level(c, l, xf, s);
+  return PF_OK;
 }
 
-// rc = P^T rf (level l -> coarse level l+1).
+// rc = P^T rf (level l -> coarse level l+1), masked.
 pf_status restrict_(pf_ctx* c, int l, const float* rf, float* rc, hipStream_t s) {
   const MGLevel& F = c->mg.lv[l];
   const MGLevel& C = c->mg.lv[l + 1];
@@ -548,51 +575,69 @@ pf_status restrict_(pf_ctx* c, int l, const float* rf, float* rc, hipStream_t s)
   int64_t n;
   n = (int64_t)C.nx1 * F.ny1 * F.nz1;
   hipLaunchKernelGGL(k_transfer_1d, dim3(vec_grid(n)), dim3(NT), 0, s, rf, A, C.nx1, F.ny1, F.nz1, F.nx1, F.ny1,
-                     F.nz1, 0, F.rbase[0], F.rw[0], nw);
+                     F.nz1, 0, F.rbase[0], F.rw[0], nw, 0, c->dir, 0);
   n = (int64_t)C.nx1 * C.ny1 * F.nz1;
   hipLaunchKernelGGL(k_transfer_1d, dim3(vec_grid(n)), dim3(NT), 0, s, A, B, C.nx1, C.ny1, F.nz1, C.nx1, F.ny1,
-                     F.nz1, 1, F.rbase[1], F.rw[1], nw);
+                     F.nz1, 1, F.rbase[1], F.rw[1], nw, 0, c->dir, 0);
   n = C.n_nodes;
   hipLaunchKernelGGL(k_transfer_1d, dim3(vec_grid(n)), dim3(NT), 0, s, B, rc, C.nx1, C.ny1, C.nz1, C.nx1, C.ny1,
-                     F.nz1, 2, F.rbase[2], F.rw[2], nw);
+                     F.nz1, 2, F.rbase[2], F.rw[2], nw, 0, c->dir, c->has_dir ? 1 : 0);
   HIPCHK(hipGetLastError());
-  return mask_level(c, l + 1, rc, s);
+  return PF_OK;
 }
 
-// Chebyshev(k) with point Jacobi on level l for A x = b, bounds [0.1, 1.1] * lmax.
+// Chebyshev(k) with point Jacobi on level l for A x = b, bounds [0.1, 1.1] * lmax; x_zero: from
+// x = 0 (x is written, not read). The correction d alternates between two vectors, since a
+// stencil level must not overwrite the vector it applies to.
 pf_status chebyshev(pf_ctx* c, int l, const float* b, float* x, int k, bool x_zero, hipStream_t s) {
   MGLevel& L = c->mg.lv[l];
   const int64_t n = 4 * L.n_nodes;
   const int g = vec_grid(n);
-  const double lmax = L.lmax, lmin = 0.1 * L.lmax, lhi = 1.1 * L.lmax;
+  const double lmin = 0.1 * L.lmax, lhi = 1.1 * L.lmax;
   const double theta = 0.5 * (lhi + lmin), delta = 0.5 * (lhi - lmin), sigma = theta / delta;
   double rho = 1.0 / sigma;
-  (void)lmax;
   pf_status st;
+  Epilogue<float> e{};
+  e.dinv = L.dinv;
+  e.c = (float)(1.0 / theta);
   if (x_zero) {
-    hipLaunchKernelGGL(k_vec_copy, dim3(g), dim3(NT), 0, s, b, L.r, n);
+    float* d = k > 1 ? L.d : x;
+    hipLaunchKernelGGL(k_cheb_start, dim3(g), dim3(NT), 0, s, b, L.dinv, d, e.c, n);
+    HIPCHK(hipGetLastError());
+    if (k <= 1) return PF_OK;
   } else {
-    if ((st = level_op(c, l, x, L.t, s))) return st;
-    hipLaunchKernelGGL(k_vec_sub, dim3(g), dim3(NT), 0, s, b, L.t, L.r, n);
+    e.b = b;
+    e.r = L.r;
+    e.d = L.d;
+    if ((st = level_op<E_FIRST>(c, l, x, e, s))) return st;
+    if (k <= 1) {
+      hipLaunchKernelGGL(k_vec_add, dim3(g), dim3(NT), 0, s, (const float*)L.d, x, n);
+      HIPCHK(hipGetLastError());
+      return PF_OK;
+    }
   }
-  hipLaunchKernelGGL(k_cheb_first, dim3(g), dim3(NT), 0, s, L.r, L.dinv, L.d, x, (float)(1.0 / theta),
-                     x_zero ? 1 : 0, n);
+  float *d = L.d, *dn = L.t;
   for (int it = 1; it < k; ++it) {
-    if ((st = level_op(c, l, L.d, L.t, s))) return st;
     const double rn = 1.0 / (2.0 * sigma - rho);
-    hipLaunchKernelGGL(k_cheb_step, dim3(g), dim3(NT), 0, s, L.r, L.t, L.dinv, L.d, x, (float)(rn * rho),
-                       (float)(2.0 * rn / delta), n);
+    e.r_in = it == 1 && x_zero ? b : L.r;
+    e.r = L.r;
+    e.d_in = d;
+    e.d = dn;
+    e.x_in = it == 1 && x_zero ? nullptr : x;
+    e.x = x;
+    e.x_first = it == 1;
+    e.a = (float)(rn * rho);
+    e.c = (float)(2.0 * rn / delta);
+    if ((st = level_op<E_STEP>(c, l, d, e, s))) return st;
+    std::swap(d, dn);
     rho = rn;
   }
-  HIPCHK(hipGetLastError());
   return PF_OK;
 }
 
 pf_status vcycle(pf_ctx* c, int l, const float* b, float* x, const pf_pmg_opts& o, hipStream_t s) {
   MGState& mg = c->mg;
   MGLevel& L = mg.lv[l];
-  const int64_t n = 4 * L.n_nodes;
-  const int g = vec_grid(n);
   pf_status st;
   if (l == mg.n_levels - 1) {
     for (int sw = 0; sw < o.coarse_sweeps; ++sw)
@@ -600,14 +645,14 @@ pf_status vcycle(pf_ctx* c, int l, const float* b, float* x, const pf_pmg_opts& 
     return PF_OK;
   }
   if ((st = chebyshev(c, l, b, x, o.cheb_degree, true, s))) return st;
-  if ((st = level_op(c, l, x, L.t, s))) return st;
-  hipLaunchKernelGGL(k_vec_sub, dim3(g), dim3(NT), 0, s, b, L.t, L.r, n);
+  Epilogue<float> e{};
+  e.b = b;
+  e.r = L.r;
+  if ((st = level_op<E_RESID>(c, l, x, e, s))) return st;
   MGLevel& C = mg.lv[l + 1];
   if ((st = restrict_(c, l, L.r, C.b, s))) return st;
   if ((st = vcycle(c, l + 1, C.b, C.x, o, s))) return st;
-  if ((st = prolong(c, l, C.x, L.t, s))) return st;
-  hipLaunchKernelGGL(k_vec_add, dim3(g), dim3(NT), 0, s, L.t, x, n);
-  HIPCHK(hipGetLastError());
+  if ((st = prolong(c, l, C.x, x, true, s))) return st;
   return chebyshev(c, l, b, x, o.cheb_degree, false, s);
 }
 
@@ -686,8 +731,8 @@ pf_status pf_linearize(pf_ctx* c, const double* z, void* stream) {
   // lambda_max(D^-1 A) per level by 15 power iterations, normalised on the device
   // (no host round trip inside the loop); one synchronisation at the end
   constexpr int POWER_ITS = 15;
-  double* nrm = mg.red + VEC_BLOCKS;             // [n_levels] final norms
-  float* inv = (float*)(mg.red + VEC_BLOCKS + 8);  // scale of the next normalisation
+  double* nrm = mg.red + RED_PARTS;             // [n_levels] final norms
+  float* inv = (float*)(mg.red + RED_PARTS + 8);  // scale of the next vector applied
   for (int l = 0; l < mg.n_levels; ++l) {
     MGLevel& L = mg.lv[l];
     const int64_t n = 4 * L.n_nodes;
@@ -698,15 +743,22 @@ pf_status pf_linearize(pf_ctx* c, const double* z, void* stream) {
     if ((st = mask_level(c, l, L.d, s))) return st;
     hipLaunchKernelGGL(k_sumsq, dim3(g), dim3(NT), 0, s, L.d, n, mg.red);
     hipLaunchKernelGGL(k_norm_finish, dim3(1), dim3(NT), 0, s, mg.red, g, nrm + l, inv);
-    hipLaunchKernelGGL(k_vec_axs_dev, dim3(g), dim3(NT), 0, s, L.d, L.d, inv, n);
-    for (int it = 0; it < POWER_ITS; ++it) {
-      if ((st = level_op(c, l, L.d, L.t, s))) return st;
-      hipLaunchKernelGGL(k_vec_scale, dim3(g), dim3(NT), 0, s, L.dinv, L.t, n);
-      hipLaunchKernelGGL(k_sumsq, dim3(g), dim3(NT), 0, s, L.t, n, mg.red);
-      hipLaunchKernelGGL(k_norm_finish, dim3(1), dim3(NT), 0, s, mg.red, g, nrm + l, inv);
-      hipLaunchKernelGGL(k_vec_axs_dev, dim3(g), dim3(NT), 0, s, L.t, L.d, inv, n);
-    }
     HIPCHK(hipGetLastError());
+    // v <- D^-1 A v / ||v||, the scale applied to A v
+    Epilogue<float> e{};
+    e.dinv = L.dinv;
+    e.inv = inv;
+    e.part = mg.red;
+    float *v = L.d, *w = L.t;
+    int parts = 0;
+    if ((st = power_parts(c, l, parts))) return st;
+    for (int it = 0; it < POWER_ITS; ++it) {
+      e.out = w;
+      if ((st = level_op<E_POWER>(c, l, v, e, s))) return st;
+      hipLaunchKernelGGL(k_norm_finish, dim3(1), dim3(NT), 0, s, mg.red, parts, nrm + l, inv);
+      HIPCHK(hipGetLastError());
+      std::swap(v, w);
+    }
   }
   double lam[MG_MAX_LEVELS];
   HIPCHK(hipMemcpyAsync(lam, nrm, mg.n_levels * sizeof(double), hipMemcpyDeviceToHost, s));
@@ -863,7 +915,7 @@ pf_status pf_apply_jacobian_f32(pf_ctx* c, int level, const float* dz, float* y,
   const size_t nb = 4 * c->mg.lv[level].n_nodes * sizeof(float);
   if (overlaps(dz, nb, y, nb)) return fail(PF_EINVAL, "y aliases dz");
   c->last_stream = (hipStream_t)stream;
-  return level_op(c, level, dz, y, (hipStream_t)stream);
+  return level_op<E_STORE>(c, level, dz, store_epilogue(y), (hipStream_t)stream);
 }
 
 // FP64 Jacobian at the linearisation point from the stored FP64 record: the FP32
@@ -898,9 +950,9 @@ pf_status pf_apply_jacobian_lin(pf_ctx* c, const double* dz, double* y, void* st
   a.n_extra = c->n_extra;
   a.qd = c->d_qd;
   switch (c->mesh.p) {
-    case 2: return launch_lin_mfma<double, 3, 3>(c, a, s);
-    case 3: return launch_lin_mfma<double, 4, 4>(c, a, s);
-    case 4: return launch_lin_q4<double, 5>(c, a, s);
+    case 2: return launch_lin_mfma<double, 3, 3, E_STORE>(c, a, store_epilogue(y), s);
+    case 3: return launch_lin_mfma<double, 4, 4, E_STORE>(c, a, store_epilogue(y), s);
+    case 4: return launch_lin_q4<double, 5, E_STORE>(c, a, store_epilogue(y), s);
     default: return fail(PF_EUNSUPPORTED, "the stored-linearisation apply is built for orders 2-4");
   }
 }
@@ -911,7 +963,7 @@ pf_status pf_prolong(pf_ctx* c, int level, const float* xc, float* xf, void* str
   if (level + 1 >= c->mg.n_levels) return fail(PF_EINVAL, "no coarser level below %d", level);
   if (!xc || !xf) return fail(PF_EINVAL, "null vector");
   c->last_stream = (hipStream_t)stream;
-  return prolong(c, level, xc, xf, (hipStream_t)stream);
+  return prolong(c, level, xc, xf, false, (hipStream_t)stream);
 }
 
 pf_status pf_restrict(pf_ctx* c, int level, const float* rf, float* rc, void* stream) {

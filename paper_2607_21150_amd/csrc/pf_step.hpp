@@ -9,12 +9,6 @@
 
 namespace pfmf {
 
-// Fields constrained on each face of the box: bit f of face[k] set means field f
-// (u_x, u_y, u_z, phi) is prescribed on face k = x0, x1, y0, y1, z0, z1.
-struct DirMask {
-  uint32_t face[6];
-};
-
 // v[f][i] = 0 for every constrained (node, field) of a [4][n] vector on a lattice. The
 // threads run over the nodes of the six boundary faces only (x = 0, x = max, y = 0, ...,
 // each face as its own range); a node on an edge or corner is zeroed once per face that
@@ -80,14 +74,6 @@ static __global__ void k_norm_finish(const double* __restrict__ part, int n, dou
     out[0] = r;
     inv[0] = r > 0.0 ? (float)(1.0 / r) : 0.f;
   }
-}
-
-// b = s[0] * a (scale held in device memory)
-static __global__ void k_vec_axs_dev(const float* __restrict__ a, float* __restrict__ b, const float* __restrict__ s,
-                              int64_t n) {
-  const float f = s[0];
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    b[i] = f * a[i];
 }
 
 // ---------------------------------------------------------------------------
