@@ -271,7 +271,7 @@ __device__ inline void store_brick4(const T* ev, const MeshDev& m, const BrickGe
 // adds the previous position's sum, taken from the neighbouring lane. Lower blocks
 // are added first along each axis (deterministic). The node's sum goes to the epilogue OP.
 // Bound by HBM: rows and their addresses are scalar, the epilogue's inputs are loaded before the
-// sums and two chunks of 64 positions are in flight (FP64, 48^3 order-3 elements: 62 -> 52 us for
+// sums and two chunks of 64 positions are in flight (FP64, 48^3 order-3 elements: 67 -> 60 us for
 // 248 MB).
 template <typename T>
 __device__ inline T lane_take(T v, int src);

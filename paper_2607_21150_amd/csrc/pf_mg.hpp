@@ -384,8 +384,8 @@ using A32Args = LinApplyArgs<float>;
 // stencil carry the vector operation that follows the apply, so that A d is neither written nor
 // read back (a Chebyshev step on n entries moves 28 n bytes beside the apply instead of 40 n, in
 // one launch less, and the Dirichlet mask needs no launch of its own). Order 4 on 40^3 elements:
-// gather 80 us and step 107 us -> 102 us in one launch, the Newton step on the order-3 32^3 mesh
-// 69.9 -> 60.7 ms.
+// gather 77 us and step up to 94 us -> 102 us in one launch, the Newton step on the order-3 32^3 mesh
+// 70.0 -> 60.7 ms.
 // ---------------------------------------------------------------------------
 enum EpiOp {
   E_STORE,  // out = v
