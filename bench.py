@@ -124,7 +124,7 @@ def stored_bytes(mesh, kind):
     node, record 60 + flags 1 + phase 1 per point; stored FP64 Jacobian: u copy (24), dz (32),
     y (32) per node, record 120 + flags 1 + phase 1 per point."""
     if kind == "fp32_apply":
-        return 44 * mesh.n_nodes + 62 * mesh.n_q
+        return 32 * mesh.n_nodes + 98 * mesh.n_q
     if kind == "jacobian_stored":
         return 88 * mesh.n_nodes + 122 * mesh.n_q
     raise ValueError(kind)

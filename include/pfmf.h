@@ -35,7 +35,7 @@
  *  - Applies are asynchronous on the given stream (a hipStream_t passed as
  *    void*, NULL = the legacy default stream) and never synchronise the host,
  *    except where stated.
- *  - The context owns only internal buffers (FP32 mirrors and the linearisation
+ *  - The context owns only internal buffers (the linearisation
  *    record, multigrid vectors, reduction scratch, the device error word). It is
  *    bound to the device current at setup; calls from another device fail with
  *    PF_EINVAL. Concurrent calls on one context from several host threads or
@@ -241,7 +241,7 @@ pf_status pf_apply_adjoint_noalloc(pf_ctx* ctx, const double* z, const double* v
  * smallest components), the principal trial log strains and the off-diagonal tangent
  * factors are taken in FP64 and stored per point (and per branch, see pf_set_branches)
  * as an FP32 record of 15 values and a
- * flag byte (Appendices A-C evaluated once), with an FP32 mirror of u; assembles an
+ * flag byte (Appendices A-C evaluated once), with F^-1 in that frame (9 values); assembles an
  * order-1 level into a block stencil and the Galerkin stencils of any coarser order-1
  * lattices below it; builds every level's point-Jacobi
  * diagonal and Chebyshev bounds (power iteration on the device). Synchronises the

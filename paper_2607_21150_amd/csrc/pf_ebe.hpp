@@ -21,7 +21,7 @@ struct EbeArgs {
   MeshDev m;
   LevelDev fine;        // fine level (kinematics)
   int64_t n_q;
-  const float* z32;     // fine u mirror [3][n_fine]
+  const float* frame;   // F^-1 N of the block (see MGState)
   RecordSoA rec;
   const uint8_t* phase;
   const MatParams<float>* mats;
@@ -69,12 +69,7 @@ __device__ inline void tangent_factors(const MatParams<float>& m, const QPState<
       t.q[3 * i + j] = co[3 * i + j] * s.bd[i] - td[i];
     }
 #pragma unroll
-  for (int k = 0; k < 9; ++k) t.N[k] = s.N[k];
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      t.R[3 * i + j] = s.Fi[3 * i] * s.N[j] + s.Fi[3 * i + 1] * s.N[3 + j] + s.Fi[3 * i + 2] * s.N[6 + j];
+  for (int k = 0; k < 9; ++k) t.N[k] = s.N[k], t.R[k] = s.R[k];
 }
 
 // Adds the columns of trial field K: C[3 (3 f + J) + L] += dP_fJ / dG_KL and
@@ -124,26 +119,21 @@ template <int PF> struct EbeShape {
   static constexpr int LQ = Q > 4 ? Q : 4;           // line stride: Q points, then 4 node pairs
   static constexpr int ES = Q * LQ * LQ + 4;         // entry and element stride (padded against bank conflicts)
   static constexpr int NENT = 30;                    // entries of one trial field
-  using L = Q5Lds<PF, PF>;
-  static constexpr int FWD = NE * (L::A + L::B);     // sum factorisation of the displacement gradient
-  static constexpr int CON = NENT * NE * ES;
-  static constexpr int LDS = FWD > CON ? FWD : CON;
+  static constexpr int LDS = NENT * NE * ES;
 };
 
 // A point of the element matrices' and diagonals' kernels: thread t holds point ql of element
-// el (of the workgroup's NE); the displacement gradient, the reference-to-physical factors
+// el (of the workgroup's NE); the block's F^-1 N, the reference-to-physical factors
 // A[3 K + J] = d xi_K / d x_J and the weight (0 for threads without a point).
 struct EbePoint {
   int64_t e, gq;
   int el, qx, qy, qz, pidc;
   bool pt;
-  float G[9], A[9], w;
+  float R[9], Fi[9], A[9], w;  // Fi: F^-1 in the directions of R's rows (ebe_layer of the block sets it)
 };
 
-// Fills p (the fine displacement's gradient by sum factorisation through lds, EbeShape::FWD
-// values; starts and ends so that lds is free).
 template <int PF, bool GEO>
-__device__ inline void ebe_point(const EbeArgs& a, const DevTablesF* __restrict__ tabs, float* lds, EbePoint& p) {
+__device__ inline void ebe_point(const EbeArgs& a, const DevTablesF* __restrict__ tabs, EbePoint& p) {
   using S = EbeShape<PF>;
   constexpr int Q = S::Q, Q2 = S::Q2, Q3 = S::Q3, NE = S::NE;
   const int t = threadIdx.x;
@@ -156,16 +146,8 @@ __device__ inline void ebe_point(const EbeArgs& a, const DevTablesF* __restrict_
   p.e = (int64_t)blockIdx.x * NE + p.el;
   p.pt = p.el < NE && p.e < n_elem;
   p.gq = p.e * Q3 + ql;
-  float* bufA = lds;
-  float* bufB = lds + NE * S::L::A;
-  if (p.pt) {
-    const int ex = (int)(p.e % a.m.nx), ey = (int)((p.e / a.m.nx) % a.m.ny), ez = (int)(p.e / ((int64_t)a.m.nx * a.m.ny));
-    const int64_t gn = lattice_node<PF>(a.fine.nx1, a.fine.ny1, ElemGeom{ex, ey, ez}, ql);
 #pragma unroll
-    for (int f = 0; f < 3; ++f) bufA[p.el * S::L::A + f * Q3 + ql] = a.z32[f * a.fine.n_nodes + gn];
-  }
-  __syncthreads();
-  sf5_fwd<float, DevTablesF, PF, Q, 3, false, true, NE, NT>(bufA, bufB, tabs, S::L::A, S::L::B);
+  for (int k = 0; k < 9; ++k) p.R[k] = p.pt ? a.frame[rec_at<Q3, 9>(p.e, ql) + k * rec_pad(Q3)] : 0.f;
   const float ih[3] = {(float)a.m.ih[0], (float)a.m.ih[1], (float)a.m.ih[2]};
 #pragma unroll
   for (int k = 0; k < 9; ++k)
@@ -174,18 +156,6 @@ __device__ inline void ebe_point(const EbeArgs& a, const DevTablesF* __restrict_
   if (p.pt)
     p.w = GEO ? (float)a.qd[9 * a.n_q + p.gq]
               : tabs->w[Q][p.qx] * tabs->w[Q][p.qy] * tabs->w[Q][p.qz] * (float)a.m.jdet;
-#pragma unroll
-  for (int f = 0; f < 3; ++f) {
-    float d[3] = {0.f, 0.f, 0.f};
-    if (p.pt) {
-#pragma unroll
-      for (int K = 0; K < 3; ++K) d[K] = bufB[p.el * S::L::B + (4 * f + 1 + K) * Q3 + ql];
-    }
-#pragma unroll
-    for (int J = 0; J < 3; ++J)
-      p.G[3 * f + J] = GEO ? d[0] * p.A[J] + d[1] * p.A[3 + J] + d[2] * p.A[6 + J] : d[J] * ih[J];
-  }
-  __syncthreads();
   const int pid = p.pt ? a.phase[p.gq] : 0;
   p.pidc = pid < a.nph ? pid : 0;
 }
@@ -196,30 +166,41 @@ struct EbeBlock {
   float gp, dLc;
 };
 
-// The tangent's factors of record layer j (0: the block, 1 + j: extra branch j) of point p;
-// false where the layer is empty.
-template <bool GEO>
-__device__ inline bool ebe_layer(const EbeArgs& a, const EbePoint& p, int j, TangentFactors& tf, EbeBlock& blk) {
+// The tangent's factors of record layer j (0: the block, taken first; 1 + j: extra branch j) of
+// point p; false where the layer is empty.
+template <int PF, bool GEO>
+__device__ inline bool ebe_layer(const EbeArgs& a, EbePoint& p, int j, TangentFactors& tf, EbeBlock& blk) {
   const int64_t o = (int64_t)j * a.n_q + p.gq;
   LinRecord rc;
   rc.flags = p.pt ? a.rec.flags[o] : 0;
   if (j > 0 && (!p.pt || (rc.flags & REC_EMPTY))) return false;
+  constexpr int Q3 = PF * PF * PF;
+  const int64_t n_elem = (int64_t)a.m.nx * a.m.ny * a.m.nz;
+  const float* rr = a.rec.rec + rec_at<Q3, REC_N>(j * n_elem + p.e, (int)(p.gq - p.e * Q3));
 #pragma unroll
-  for (int k = 0; k < REC_N; ++k) rc.v[k] = p.pt ? a.rec.rec[((int64_t)j * REC_N + k) * a.n_q + p.gq] : 0.f;
+  for (int k = 0; k < REC_N; ++k) rc.v[k] = p.pt ? rr[k * rec_pad(Q3)] : 0.f;
   const MatParams<float> m = j == 0 ? a.mats[p.pidc] : a.xmats[p.pidc * a.n_extra + j - 1];
   QPState<float> s;
-  qp_state_lin<float>(m, p.G, rc, s);
+  qp_state_lin<float>(rc, s);
+  if (j == 0) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) s.R[k] = p.R[k];
+    frame_times<float>(p.R, s.N, p.Fi);
+  } else {
+    frame_product<float>(p.Fi, s.N, nullptr, s.R);
+  }
   if (j == 0) blk = EbeBlock{s.hactive, s.gp, s.dLcoef};
   tangent_factors(m, s, tf);
-  float R[9];
+  if (GEO) {
+    float R[9];
 #pragma unroll
-  for (int K = 0; K < 3; ++K)
+    for (int K = 0; K < 3; ++K)
 #pragma unroll
-    for (int b = 0; b < 3; ++b)
-      R[3 * K + b] = GEO ? p.A[3 * K] * tf.R[b] + p.A[3 * K + 1] * tf.R[3 + b] + p.A[3 * K + 2] * tf.R[6 + b]
-                         : p.A[4 * K] * tf.R[3 * K + b];
+      for (int b = 0; b < 3; ++b)
+        R[3 * K + b] = p.A[3 * K] * tf.R[b] + p.A[3 * K + 1] * tf.R[3 + b] + p.A[3 * K + 2] * tf.R[6 + b];
 #pragma unroll
-  for (int k = 0; k < 9; ++k) tf.R[k] = R[k];
+    for (int k = 0; k < 9; ++k) tf.R[k] = R[k];
+  }
   return true;
 }
 
@@ -246,14 +227,14 @@ __global__ __launch_bounds__(NT) void k_ebe_assemble(EbeArgs a, const DevTablesF
   const int64_t n_elem = (int64_t)a.m.nx * a.m.ny * a.m.nz;
   const int64_t e0 = (int64_t)blockIdx.x * NE;
   EbePoint p;
-  ebe_point<PF, GEO>(a, tabs, lds, p);
+  ebe_point<PF, GEO>(a, tabs, p);
   const int el = p.el, qx = p.qx, qy = p.qy, qz = p.qz;
   const float w = p.w;
   const float* A = p.A;
   const MatParams<float> mp = a.mats[p.pidc];
   EbeBlock blk;
   TangentFactors tf0;
-  ebe_layer<GEO>(a, p, 0, tf0, blk);
+  ebe_layer<PF, GEO>(a, p, 0, tf0, blk);
   const bool hact = blk.hact;
   const float gp = blk.gp, dLc = blk.dLc;
   float* con = lds;
@@ -281,7 +262,7 @@ __global__ __launch_bounds__(NT) void k_ebe_assemble(EbeArgs a, const DevTablesF
         for (int j = 0; j < a.n_extra; ++j) {
           TangentFactors tj;
           EbeBlock bj;
-          if (ebe_layer<GEO>(a, p, 1 + j, tj, bj)) columns(tj);
+          if (ebe_layer<PF, GEO>(a, p, 1 + j, tj, bj)) columns(tj);
         }
       }
       if (el < NE) {
@@ -309,7 +290,7 @@ __global__ __launch_bounds__(NT) void k_ebe_assemble(EbeArgs a, const DevTablesF
         for (int j = 0; j < a.n_extra; ++j) {
           TangentFactors tj;
           EbeBlock bj;
-          if (ebe_layer<GEO>(a, p, 1 + j, tj, bj)) {
+          if (ebe_layer<PF, GEO>(a, p, 1 + j, tj, bj)) {
             phi_column(tj);
             hphi += tj.hphi;
           }
@@ -479,12 +460,12 @@ __global__ __launch_bounds__(NT) void k_level_diag(EbeArgs a, float* __restrict_
   constexpr int Q = S::Q, Q2 = S::Q2, Q3 = S::Q3, NE = S::NE, ES = Q3 + 1;
   constexpr int NPHI = GEO ? 7 : 4, NENT = 18 + NPHI;
   constexpr int CON = NENT * NE * ES;
-  __shared__ float lds[CON > S::FWD ? CON : S::FWD];
+  __shared__ float lds[CON];
   const int l = threadIdx.x & 63, wv = wave_id();
   const int64_t n_elem = (int64_t)a.m.nx * a.m.ny * a.m.nz;
   const int64_t e0 = (int64_t)blockIdx.x * NE;
   EbePoint p;
-  ebe_point<PF, GEO>(a, tabs, lds, p);
+  ebe_point<PF, GEO>(a, tabs, p);
   {
     const MatParams<float> mp = a.mats[p.pidc];
     float D[18];
@@ -494,7 +475,7 @@ __global__ __launch_bounds__(NT) void k_level_diag(EbeArgs a, float* __restrict_
     float hphi;
     {
       TangentFactors tf;
-      ebe_layer<GEO>(a, p, 0, tf, blk);
+      ebe_layer<PF, GEO>(a, p, 0, tf, blk);
       tangent_diagonal<0>(tf, D);
       tangent_diagonal<1>(tf, D + 6);
       tangent_diagonal<2>(tf, D + 12);
@@ -505,7 +486,7 @@ __global__ __launch_bounds__(NT) void k_level_diag(EbeArgs a, float* __restrict_
       for (int j = 0; j < a.n_extra; ++j) {
         TangentFactors tf;
         EbeBlock bj;
-        if (ebe_layer<GEO>(a, p, 1 + j, tf, bj)) {
+        if (ebe_layer<PF, GEO>(a, p, 1 + j, tf, bj)) {
           tangent_diagonal<0>(tf, D);
           tangent_diagonal<1>(tf, D + 6);
           tangent_diagonal<2>(tf, D + 12);

@@ -945,12 +945,13 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2(LinApplyArgs<V> a, int colour,
   const int pqx = l & 3, pqz = (l >> 2) & 3, pqy = l >> 4;
   const bool pvalid = pqx < 3 && pqy < 3 && pqz < 3;
   const int pq = pqx + 3 * pqy + 9 * pqz;
+  const int64_t n_elem = (int64_t)a.m.nx * a.m.ny * a.m.nz;
   const V ih[3] = {(V)a.m.ih[0], (V)a.m.ih[1], (V)a.m.ih[2]};
   const V wbox = (V)(tabs->w[3][cqx < 3 ? cqx : 0] * tabs->w[3][cqy] * tabs->w[3][cqz < 3 ? cqz : 0] *
                              a.m.jdet);
-  const V wih[3] = {wbox * ih[0], wbox * ih[1], wbox * ih[2]};
+  const V wg[3] = {wbox * ih[0] * ih[0], wbox * ih[1] * ih[1], wbox * ih[2] * ih[2]};
   if (hasA) {
-    V G[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    V G[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};  // FRAME_FROM_U only
     V W[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     V wphi = 0, gw[3] = {0, 0, 0};
 #pragma unroll
@@ -958,14 +959,14 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2(LinApplyArgs<V> a, int colour,
       if (half == 1 && !hasB) break;  // uniform
       const int64_t nf = first_node<3>(g, sx, sy, half, a.fine.nx1, a.fine.ny1);
       const int64_t nc = first_node<PC>(g, sx, sy, half, a.lev.nx1, a.lev.ny1);
-      double zu[3], wu[4];
-#pragma unroll
-      for (int f = 0; f < 3; ++f) zu[f] = has_f ? (double)(a.z32 + (f * a.fine.n_nodes + nf))[lf] : 0.0;
+      double wu[4];
 #pragma unroll
       for (int f = 0; f < 4; ++f) wu[f] = has_c ? (double)(a.dz + (f * a.lev.n_nodes + nc))[lc] : 0.0;
       const bool mine = E == half;
-      {
-        double v[3], d[3][3];
+      if constexpr (FRAME_FROM_U<V>) {
+        double zu[3], v[3], d[3][3];
+#pragma unroll
+        for (int f = 0; f < 3; ++f) zu[f] = has_f ? (double)(a.u + (f * a.fine.n_nodes + nf))[lf] : 0.0;
         sf4_fwd_n<3>(zu, bf, 0x0u, 0x7u, v, d);
 #pragma unroll
         for (int f = 0; f < 3; ++f)
@@ -983,14 +984,14 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2(LinApplyArgs<V> a, int colour,
 #pragma unroll
           for (int J = 0; J < 3; ++J) {
             const double r = lane_read(d[f][J], src_fwd);
-            if (mine) W[3 * f + J] = GEO ? (V)r : (V)r * ih[J];
+            if (mine) W[3 * f + J] = (V)r;  // reference directions
           }
         const double rp = lane_read(v[3], src_fwd);
         if (mine) wphi = (V)rp;
 #pragma unroll
         for (int J = 0; J < 3; ++J) {
           const double r = lane_read(d[3][J], src_fwd);
-          if (mine) gw[J] = GEO ? (V)r : (V)r * ih[J];
+          if (mine) gw[J] = (V)r;
         }
       }
     }
@@ -1006,22 +1007,28 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2(LinApplyArgs<V> a, int colour,
       wdet = valid ? (V)a.qd[9 * a.n_q + gq] : V(0);
 #pragma unroll
       for (int f = 0; f < 3; ++f) {
-        map_grad<V>((double)G[3 * f], (double)G[3 * f + 1], (double)G[3 * f + 2], gA, G + 3 * f);
+        if (FRAME_FROM_U<V>) map_grad<V>((double)G[3 * f], (double)G[3 * f + 1], (double)G[3 * f + 2], gA, G + 3 * f);
         map_grad<V>((double)W[3 * f], (double)W[3 * f + 1], (double)W[3 * f + 2], gA, W + 3 * f);
       }
       map_grad<V>((double)gw[0], (double)gw[1], (double)gw[2], gA, gw);
     }
     LinRecordT<V> rc;
 #pragma unroll
-    for (int k = 0; k < REC_N; ++k) rc.v[k] = valid ? a.rec.rec[k * a.n_q + gq] : V(0);
+    for (int k = 0; k < REC_N; ++k) rc.v[k] = valid ? a.rec.rec[rec_at<27, REC_N>(e, q) + k * rec_pad(27)] : V(0);
     rc.flags = valid ? a.rec.flags[gq] : 0;
     const int pid = valid ? a.phase[gq] : 0;
     const int pidc = pid < a.nph ? pid : 0;
     const MatParams<V> mp = a.mats[pidc];
     QPState<V> s;
-    qp_state_lin<V>(mp, G, rc, s);
+    qp_state_lin<V>(rc, s);
+    if constexpr (FRAME_FROM_U<V>) {
+      frame_from_gradient<V>(G, s.N, GEO ? nullptr : ih, s.R);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) s.R[k] = valid ? a.frame[rec_at<27, 9>(e, q) + k * rec_pad(27)] : V(0);
+    }
     V Fu[9], dL;
-    lin_tangent<V, MB>(a.rec, a.n_q, a.xmats, a.n_extra, mp, s, pidc, gq, valid, G, W, wphi, Fu, dL);
+    lin_tangent<V, 27, MB>(a.rec, n_elem, a.xmats, a.n_extra, mp, s, pidc, e, q, valid, W, wphi, Fu, dL);
     const V kfg = a.fr.kf * mp.Gc;
     double b1p[4][3], b0p3;
     if (GEO) {
@@ -1036,9 +1043,9 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2(LinApplyArgs<V> a, int colour,
 #pragma unroll
       for (int f = 0; f < 3; ++f)
 #pragma unroll
-        for (int J = 0; J < 3; ++J) b1p[f][J] = (double)(Fu[3 * f + J] * wih[J]);
+        for (int J = 0; J < 3; ++J) b1p[f][J] = (double)(wbox * Fu[3 * f + J]);
 #pragma unroll
-      for (int J = 0; J < 3; ++J) b1p[3][J] = (double)(kfg * gw[J] * wih[J]);
+      for (int J = 0; J < 3; ++J) b1p[3][J] = (double)(kfg * gw[J] * wg[J]);
     }
     b0p3 = (double)(wdet * a.fr.s_phi * dL);
     // back to each element's padded layout, transposed interpolation
@@ -1090,9 +1097,10 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q3(LinApplyArgs<V> a, int colour,
   const bool has_c = lane_has_node<PC>();
   const int qx = l & 3, qz = (l >> 2) & 3, qy = l >> 4;
   const int ql = qx + 4 * qy + 16 * qz;
+  const int64_t n_elem = (int64_t)a.m.nx * a.m.ny * a.m.nz;
   const V ih[3] = {(V)a.m.ih[0], (V)a.m.ih[1], (V)a.m.ih[2]};
   const V wbox = (V)(tabs->w[4][qx] * tabs->w[4][qy] * tabs->w[4][qz] * a.m.jdet);
-  const V wih[3] = {wbox * ih[0], wbox * ih[1], wbox * ih[2]};
+  const V wg[3] = {wbox * ih[0] * ih[0], wbox * ih[1] * ih[1], wbox * ih[2] * ih[2]};
 #pragma unroll 1
   for (int half = 0; half < 2; ++half) {
     const int slot = wv + 4 * half;
@@ -1100,17 +1108,24 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q3(LinApplyArgs<V> a, int colour,
     if (!(sx < g.nex && sy < g.ney && sz < g.nez)) continue;  // uniform per wave
     const int64_t nf = first_node<4>(g, sx, sy, sz, a.fine.nx1, a.fine.ny1);
     const int64_t nc = first_node<PC>(g, sx, sy, sz, a.lev.nx1, a.lev.ny1);
-    double zu[3], wu[4];
+    double zu[FRAME_FROM_U<V> ? 3 : 1], wu[4];
+    if constexpr (FRAME_FROM_U<V>) {
 #pragma unroll
-    for (int f = 0; f < 3; ++f) zu[f] = (double)(a.z32 + (f * a.fine.n_nodes + nf))[lf];
+      for (int f = 0; f < 3; ++f) zu[f] = (double)(a.u + (f * a.fine.n_nodes + nf))[lf];
+    }
 #pragma unroll
     for (int f = 0; f < 4; ++f) wu[f] = has_c ? (double)(a.dz + (f * a.lev.n_nodes + nc))[lc] : 0.0;
     const int64_t e = (int64_t)(g.ex0 + sx) + (int64_t)a.m.nx * ((g.ey0 + sy) + (int64_t)a.m.ny * (g.ez0 + sz));
     const int64_t gq = e * 64 + ql;
     LinRecordT<V> rc;
 #pragma unroll
-    for (int k = 0; k < REC_N; ++k) rc.v[k] = (a.rec.rec + (k * a.n_q + e * 64))[ql];
+    for (int k = 0; k < REC_N; ++k) rc.v[k] = (a.rec.rec + (e * REC_N + k) * 64)[ql];
     rc.flags = (a.rec.flags + e * 64)[ql];
+    QPState<V> s;
+    if constexpr (!FRAME_FROM_U<V>) {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) s.R[k] = (a.frame + (e * 9 + k) * 64)[ql];
+    }
     const int pid = (a.phase + e * 64)[ql];
     // mapped elements: the point's J^-1 and weight
     double gA[GEO ? 9 : 1];
@@ -1120,8 +1135,8 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q3(LinApplyArgs<V> a, int colour,
       for (int k = 0; k < 9; ++k) gA[k] = (a.qd + (k * a.n_q + e * 64))[ql];
       wdet = (V)(a.qd + (9 * a.n_q + e * 64))[ql];
     }
-    V G[9], W[9], wphi, gw[3];
-    {
+    V G[FRAME_FROM_U<V> ? 9 : 1], W[9], wphi, gw[3];
+    if constexpr (FRAME_FROM_U<V>) {
       double v[3], d[3][3];
       sf4_fwd_n<3>(zu, bf, 0x0u, 0x7u, v, d);
 #pragma unroll
@@ -1142,21 +1157,21 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q3(LinApplyArgs<V> a, int colour,
           map_grad<V>(d[f][0], d[f][1], d[f][2], gA, W + 3 * f);
         else
 #pragma unroll
-          for (int J = 0; J < 3; ++J) W[3 * f + J] = (V)d[f][J] * ih[J];
+          for (int J = 0; J < 3; ++J) W[3 * f + J] = (V)d[f][J];  // reference directions
       }
       wphi = (V)v[3];
       if (GEO)
         map_grad<V>(d[3][0], d[3][1], d[3][2], gA, gw);
       else
 #pragma unroll
-        for (int J = 0; J < 3; ++J) gw[J] = (V)d[3][J] * ih[J];
+        for (int J = 0; J < 3; ++J) gw[J] = (V)d[3][J];
     }
     const int pidc = pid < a.nph ? pid : 0;
     const MatParams<V> mp = a.mats[pidc];
-    QPState<V> s;
-    qp_state_lin<V>(mp, G, rc, s);
+    qp_state_lin<V>(rc, s);
+    if constexpr (FRAME_FROM_U<V>) frame_from_gradient<V>(G, s.N, GEO ? nullptr : ih, s.R);
     V Fu[9], dL;
-    lin_tangent<V, MB>(a.rec, a.n_q, a.xmats, a.n_extra, mp, s, pidc, gq, true, G, W, wphi, Fu, dL);
+    lin_tangent<V, 64, MB>(a.rec, n_elem, a.xmats, a.n_extra, mp, s, pidc, e, ql, true, W, wphi, Fu, dL);
     const V kfg = a.fr.kf * mp.Gc;
     double b0[4], b1[4][3], r[4];
     if (GEO) {
@@ -1173,10 +1188,10 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q3(LinApplyArgs<V> a, int colour,
       for (int f = 0; f < 3; ++f) {
         b0[f] = 0.0;
 #pragma unroll
-        for (int J = 0; J < 3; ++J) b1[f][J] = (double)(Fu[3 * f + J] * wih[J]);
+        for (int J = 0; J < 3; ++J) b1[f][J] = (double)(wbox * Fu[3 * f + J]);
       }
 #pragma unroll
-      for (int J = 0; J < 3; ++J) b1[3][J] = (double)(kfg * gw[J] * wih[J]);
+      for (int J = 0; J < 3; ++J) b1[3][J] = (double)(kfg * gw[J] * wg[J]);
     }
     b0[3] = (double)(wdet * a.fr.s_phi * dL);
     sf4_bwd_n<4>(b0, b1, 0x8u, bc, r);

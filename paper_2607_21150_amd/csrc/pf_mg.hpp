@@ -7,10 +7,9 @@
 // space is a subspace of the fine space). Below an order-1 level the hierarchy may
 // continue on coarser order-1 lattices (every second node per direction, trilinear
 // interpolation), each operator the Galerkin product of the one above, formed once
-// per linearisation as a block stencil. Kinematics (F, eigenframe, log strains)
-// are recomputed in FP32 from FP32 mirrors of u and D at every apply; the yield,
-// split and history decisions and the return-mapping scalars come from the
-// record taken in FP64 by the linearisation.
+// per linearisation as a block stencil. Everything an apply needs at a point
+// (F^-1 N, frame, log strains, the yield, split and history decisions, the
+// return-mapping scalars) comes from the record taken in FP64 by the linearisation.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -22,10 +21,21 @@
 namespace pfmf {
 
 template <typename V> struct RecordSoAT {
-  V* rec;          // [REC_N][n_q], slots as in LinRecordT
+  V* rec;          // [n_elem][REC_N][rec_pad], slots as in LinRecordT
   uint8_t* flags;  // [n_q]
 };
 using RecordSoA = RecordSoAT<float>;
+
+// The records lie element by element, a slot's points together and padded to 16 bytes, so that an
+// apply reads one run of memory per element with aligned slots. With a slot's points of the whole
+// mesh together (24 streams, order-4 slots off the cache lines) the apply on 40^3 order-4 elements
+// took 260 us and its order-2 level 221, now 201 and 150; on 32^3 order-3 elements 51.1 and 46.4,
+// now 47.5 and 44.4.
+constexpr int64_t rec_pad(int q3) { return (q3 + 3) / 4 * 4; }
+// Slot k of point ql of element e at k * rec_pad(Q3) from here (e: layer * n_elem + element).
+template <int Q3, int SLOTS> __device__ inline int64_t rec_at(int64_t e, int ql) {
+  return e * (SLOTS * rec_pad(Q3)) + ql;
+}
 
 struct LevelDev {
   int P;           // nodes per direction of this level's elements
@@ -60,8 +70,8 @@ struct MGLevel {
 struct MGState {
   int n_levels = 0;
   MGLevel lv[MG_MAX_LEVELS];
-  float* z32 = nullptr;  // FP32 mirror of u on the fine level [3][n_nodes]
-  RecordSoA rec{nullptr, nullptr};  // [rec_layers][REC_N][n_q] and flags [rec_layers][n_q]
+  float* frame = nullptr;  // F^-1 N of the block at the linearisation point [n_elem][9][rec_pad] (QPState::R)
+  RecordSoA rec{nullptr, nullptr};  // [rec_layers][n_elem][REC_N][rec_pad] and flags [rec_layers][n_q]
   float* tmpA = nullptr;
   float* tmpB = nullptr;
   double* red = nullptr;  // reduction scratch
@@ -69,7 +79,7 @@ struct MGState {
                            // levels' element diagonals (both per linearisation)
   float* stencil = nullptr;  // the same level as a block stencil [27][4][4][n_nodes]
   float* ebuf32 = nullptr;   // brick-buffer scatter of the FP32 level applies
-  double* rec64 = nullptr;   // stored FP64 linearisation [rec_layers][REC_N][n_q] (flags in rec.flags)
+  double* rec64 = nullptr;   // stored FP64 linearisation, laid out as rec (flags in rec.flags)
   double* u64 = nullptr;     // u at the linearisation point [3][n_nodes]
   int rec_layers = 0;        // record layers allocated (1 + extra branches)
   int ebe_level = -1;
@@ -91,7 +101,7 @@ inline void mg_free_level(MGLevel& L) {
 
 inline void mg_free(MGState& mg) {
   for (int l = 0; l < MG_MAX_LEVELS; ++l) mg_free_level(mg.lv[l]);
-  (void)hipFree(mg.z32);
+  (void)hipFree(mg.frame);
   (void)hipFree(mg.rec.rec);
   (void)hipFree(mg.rec.flags);
   (void)hipFree(mg.tmpA);
@@ -113,8 +123,8 @@ inline void mg_free(MGState& mg) {
 // Records of a point with extra branches in parallel: layer 0 is the block's record,
 // whose flags carry the point's history switch and whose dL slot its dL/dphi (both
 // from the total psi^+); layer 1 + j that of extra branch j, or flags REC_EMPTY where
-// the point's phase has no branch in slot j. Layer l of a record array sits at
-// rec + l * REC_N * n_q and flags + l * n_q.
+// the point's phase has no branch in slot j. Layer l of the records holds elements
+// l * n_elem on (rec_at), its flags sit at flags + l * n_q.
 constexpr uint8_t REC_EMPTY = 0x80;
 
 struct LinArgs {
@@ -129,7 +139,8 @@ struct LinArgs {
   int nph;
   FracParams<double> fr;
   RecordSoA rec;
-  double* rec64;         // MODE 0: the same record in FP64 [REC_N][n_q] (flags shared), or null
+  float* frame;          // MODE 0, 2: see MGState
+  double* rec64;         // MODE 0: the same record in FP64 (flags shared), or null
   double* state_out;
   int* flag;
   const XBranch* xb;     // extra branches [nph][n_extra] and their states [7*n_extra][n_q]
@@ -169,6 +180,7 @@ __global__ __launch_bounds__(NT) void k_linearize(LinArgs a, DevTables* __restri
   const int t = threadIdx.x;
   const int el = t / Q3, ql = t % Q3;
   const int qx = ql % Q, qy = (ql / Q) % Q, qz = ql / (Q * Q);
+  const int64_t n_elem = (int64_t)a.m.nx * a.m.ny * a.m.nz;
   bool any_bad = false, bad_pid = false;
   for (int r = 0; r < S::ROUNDS; ++r) {
     const int slot0 = r * ER, slot = slot0 + el;
@@ -233,16 +245,17 @@ __global__ __launch_bounds__(NT) void k_linearize(LinArgs a, DevTables* __restri
           qp_state<true, true>(b.m, a.fr, G, phi, 0.0, xs, sj);
           any_bad |= sj.bad;
           psi += sj.psi;
+          const int64_t ro = rec_at<Q3, REC_N>(lj * n_elem + e, ql);
           LinRecord rj;
           record_from_state(sj, rj);
 #pragma unroll
-          for (int k = 0; k < REC_N; ++k) a.rec.rec[(lj * REC_N + k) * a.n_q + gq] = rj.v[k];
+          for (int k = 0; k < REC_N; ++k) a.rec.rec[ro + k * rec_pad(Q3)] = rj.v[k];
           a.rec.flags[lj * a.n_q + gq] = rj.flags;
           if (a.rec64) {
             LinRecordT<double> r64;
             record_from_state(sj, r64);
 #pragma unroll
-            for (int k = 0; k < REC_N; ++k) a.rec64[(lj * REC_N + k) * a.n_q + gq] = r64.v[k];
+            for (int k = 0; k < REC_N; ++k) a.rec64[ro + k * rec_pad(Q3)] = r64.v[k];
           }
         }
         s.hactive = psi > st[7];
@@ -287,16 +300,21 @@ __global__ __launch_bounds__(NT) void k_linearize(LinArgs a, DevTables* __restri
         s.H = s.hactive ? psi : st[7];
       }
       if (MODE == 0 || MODE == 2) {
+        const int64_t ro = rec_at<Q3, REC_N>(e, ql);
         LinRecord rc;
-        record_from_state(s, rc);
+        double N[9], R[9];
+        record_from_state(s, rc, N);
+        frame_product<double>(s.Fi, N, GEO ? nullptr : ih, R);
 #pragma unroll
-        for (int k = 0; k < REC_N; ++k) a.rec.rec[k * a.n_q + gq] = rc.v[k];
+        for (int k = 0; k < 9; ++k) a.frame[rec_at<Q3, 9>(e, ql) + k * rec_pad(Q3)] = (float)R[k];
+#pragma unroll
+        for (int k = 0; k < REC_N; ++k) a.rec.rec[ro + k * rec_pad(Q3)] = rc.v[k];
         a.rec.flags[gq] = rc.flags;
         if (a.rec64) {
           LinRecordT<double> r64;
           record_from_state(s, r64);
 #pragma unroll
-          for (int k = 0; k < REC_N; ++k) a.rec64[k * a.n_q + gq] = r64.v[k];
+          for (int k = 0; k < REC_N; ++k) a.rec64[ro + k * rec_pad(Q3)] = r64.v[k];
         }
       } else {
         double ns[8];
@@ -320,7 +338,8 @@ template <typename V> struct LinApplyArgs {
   MeshDev m;
   LevelDev fine, lev;
   int64_t n_q;
-  const V* z32;          // fine u at the linearisation point [3][n_fine]
+  const V* frame;        // V = float: F^-1 N of the block (see MGState)
+  const V* u;            // V = double: fine u at the linearisation point [3][n_fine]
   const V* dz;           // level vector [4][n_lev]
   RecordSoAT<V> rec;
   const uint8_t* phase;
@@ -343,32 +362,42 @@ __device__ inline void map_grad(double d0, double d1, double d2, const double* A
   for (int J = 0; J < 3; ++J) out[J] = (V)(d0 * A[J] + d1 * A[3 + J] + d2 * A[6 + J]);
 }
 
+// The level applies' QPState::R. V = float reads it: recomputing F^-1 from u at every apply costs a
+// sum factorisation of three fields, an inverse and a product (of 1226 vector instructions per
+// wave 250, order 3) against 36 bytes per point.
+// V = double (the stored linearisation) recomputes it from u.
+template <typename V> constexpr bool FRAME_FROM_U = sizeof(V) == 8;
+
 // Record-based tangent of one point: the block's layer, plus (n_extra > 0) the extra
 // branches' layers, their dP and dpsi^+ summed and the switch applied to the total.
 // valid = false (a lane without a point) reads no layer.
 // MB = false compiles the block's tangent only (kernels launched without branches).
-template <typename V, bool MB>
-__device__ inline void lin_tangent(const RecordSoAT<V>& rec, int64_t n_q, const MatParams<V>* xmats, int n_extra,
-                                   const MatParams<V>& mp, const QPState<V>& s, int pid, int64_t gq, bool valid,
-                                   const V* G, const V* dG, V dphi, V* dP, V& dL) {
+template <typename V, int Q3, bool MB>
+__device__ inline void lin_tangent(const RecordSoAT<V>& rec, int64_t n_elem, const MatParams<V>* xmats, int n_extra,
+                                   const MatParams<V>& mp, const QPState<V>& s, int pid, int64_t e, int ql, bool valid,
+                                   const V* dG, V dphi, V* dP, V& dL) {
   if (!MB || n_extra == 0) {
     qp_tangent<V>(mp, s, dG, dphi, dP, dL);
     return;
   }
   V dpsi;
   qp_tangent_psi<V>(mp, s, dG, dphi, dP, dpsi, true);
+  V Fi[9];  // F^-1 in the directions of R's rows
+  frame_times<V>(s.R, s.N, Fi);
 #pragma unroll 1
   for (int j = 0; j < n_extra; ++j) {
     const int64_t lj = 1 + j;
-    const uint8_t fl = valid ? rec.flags[lj * n_q + gq] : REC_EMPTY;
+    const uint8_t fl = valid ? rec.flags[(lj * n_elem + e) * Q3 + ql] : REC_EMPTY;
     if (fl & REC_EMPTY) continue;
+    const V* rr = rec.rec + rec_at<Q3, REC_N>(lj * n_elem + e, ql);
     LinRecordT<V> r;
 #pragma unroll
-    for (int k = 0; k < REC_N; ++k) r.v[k] = rec.rec[(lj * REC_N + k) * n_q + gq];
+    for (int k = 0; k < REC_N; ++k) r.v[k] = rr[k * rec_pad(Q3)];
     r.flags = fl;
     const MatParams<V>& bm = xmats[pid * n_extra + j];
     QPState<V> sj;
-    qp_state_lin<V>(bm, G, r, sj);
+    qp_state_lin<V>(r, sj);
+    frame_product<V>(Fi, sj.N, nullptr, sj.R);
     V dPj[9], dpj;
     qp_tangent_psi<V>(bm, sj, dG, dphi, dPj, dpj, true);
 #pragma unroll
@@ -561,12 +590,6 @@ static __global__ void k_sumsq(const float* __restrict__ x, int64_t n, double* _
 static __global__ void k_to_f32(const double* __restrict__ x, float* __restrict__ y, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     y[i] = (float)x[i];
-}
-
-static __global__ void k_mirror_u(const double* __restrict__ z, float* __restrict__ z32, int64_t n_nodes) {
-  const int64_t n = 3 * n_nodes;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    z32[i] = (float)z[i];
 }
 
 }  // namespace pfmf

@@ -93,6 +93,12 @@ pf_status upload(T** dst, const std::vector<T>& v) {
 
 pf_status mg_alloc_levels(pf_ctx* c, const int* orders, int nl);
 
+// Values of one record slot over the mesh (one layer), see rec_at.
+size_t rec_points(const pf_ctx* c) {
+  const size_t n_elem = (size_t)c->mesh.nx * c->mesh.ny * c->mesh.nz;
+  return n_elem * rec_pad((int)(c->n_q / n_elem));
+}
+
 pf_status mg_alloc(pf_ctx* c) {
   MGState& mg = c->mg;
   if (mg.n_levels > 0) return PF_OK;
@@ -163,7 +169,7 @@ pf_status mg_alloc_levels(pf_ctx* c, const int* orders, int nl) {
        hipMalloc(&mg.stencil, (size_t)27 * 16 * mg.lv[mg.ebe_level].n_nodes * sizeof(float)) != hipSuccess))
     return fail(PF_ENOMEM, "coarse element matrices: allocation failed");
   const size_t nfine = 4 * mg.lv[0].n_nodes * sizeof(float);
-  if (hipMalloc(&mg.z32, 3 * c->n_nodes * sizeof(float)) != hipSuccess ||
+  if (hipMalloc(&mg.frame, 9 * rec_points(c) * sizeof(float)) != hipSuccess ||
       hipMalloc(&mg.tmpA, nfine) != hipSuccess || hipMalloc(&mg.tmpB, nfine) != hipSuccess ||
       hipMalloc(&mg.red, (RED_PARTS + 16) * sizeof(double)) != hipSuccess)
     return fail(PF_ENOMEM, "multigrid allocation failed");
@@ -182,7 +188,7 @@ pf_status ensure_records(pf_ctx* c) {
   mg.rec = RecordSoA{nullptr, nullptr};
   mg.rec64 = nullptr;
   mg.rec_layers = 0;
-  if (hipMalloc(&mg.rec.rec, (size_t)layers * REC_N * c->n_q * sizeof(float)) != hipSuccess ||
+  if (hipMalloc(&mg.rec.rec, layers * REC_N * rec_points(c) * sizeof(float)) != hipSuccess ||
       hipMalloc(&mg.rec.flags, (size_t)layers * c->n_q) != hipSuccess)
     return fail(PF_ENOMEM, "linearisation record: allocation failed");
   mg.rec_layers = layers;
@@ -213,7 +219,8 @@ A32Args a32_args(pf_ctx* c, int level, const float* dz) {
   a.fine = LevelDev{F.P, F.nx1, F.ny1, F.n_nodes};
   a.lev = LevelDev{L.P, L.nx1, L.ny1, L.n_nodes};
   a.n_q = c->n_q;
-  a.z32 = c->mg.z32;
+  a.frame = c->mg.frame;
+  a.u = nullptr;
   a.dz = dz;
   a.rec = c->mg.rec;
   a.phase = c->qp_phase;
@@ -366,7 +373,7 @@ EbeArgs ebe_args(pf_ctx* c) {
   const MGLevel& F = c->mg.lv[0];
   a.fine = LevelDev{F.P, F.nx1, F.ny1, F.n_nodes};
   a.n_q = c->n_q;
-  a.z32 = c->mg.z32;
+  a.frame = c->mg.frame;
   a.rec = c->mg.rec;
   a.phase = c->qp_phase;
   a.mats = c->d_matsf;
@@ -678,10 +685,8 @@ pf_status pf_linearize(pf_ctx* c, const double* z, void* stream) {
   c->last_stream = s;
   if ((st = mg_alloc(c)) || (st = ensure_records(c))) return st;
   MGState& mg = c->mg;
-  hipLaunchKernelGGL(k_mirror_u, dim3(vec_grid(3 * c->n_nodes)), dim3(NT), 0, s, z, mg.z32, c->n_nodes);
-  HIPCHK(hipGetLastError());
   if (c->store_lin64) {
-    if ((!mg.rec64 && hipMalloc(&mg.rec64, (size_t)mg.rec_layers * REC_N * c->n_q * sizeof(double)) != hipSuccess) ||
+    if ((!mg.rec64 && hipMalloc(&mg.rec64, mg.rec_layers * REC_N * rec_points(c) * sizeof(double)) != hipSuccess) ||
         (!mg.u64 && hipMalloc(&mg.u64, (size_t)3 * c->n_nodes * sizeof(double)) != hipSuccess))
       return fail(PF_ENOMEM, "stored linearisation: allocation failed");
     HIPCHK(hipMemcpyAsync(mg.u64, z, (size_t)3 * c->n_nodes * sizeof(double), hipMemcpyDeviceToDevice, s));
@@ -700,6 +705,7 @@ pf_status pf_linearize(pf_ctx* c, const double* z, void* stream) {
   a.nph = (int)c->phases.size();
   a.fr = frac_params<double>(c->fr);
   a.rec = mg.rec;
+  a.frame = mg.frame;
   a.rec64 = c->store_lin64 ? mg.rec64 : nullptr;
   a.state_out = nullptr;
   a.flag = c->d_flag;
@@ -806,6 +812,7 @@ pf_status commit_state(pf_ctx* c, const double* z, double* state_out, double* xs
   a.nph = (int)c->phases.size();
   a.fr = frac_params<double>(c->fr);
   a.rec = RecordSoA{nullptr, nullptr};
+  a.frame = nullptr;
   a.rec64 = nullptr;
   a.state_out = state_out;
   a.flag = c->d_flag;
@@ -937,7 +944,8 @@ pf_status pf_apply_jacobian_lin(pf_ctx* c, const double* dz, double* y, void* st
   a.fine = LevelDev{F.P, F.nx1, F.ny1, F.n_nodes};
   a.lev = a.fine;
   a.n_q = c->n_q;
-  a.z32 = c->mg.u64;
+  a.frame = nullptr;
+  a.u = c->mg.u64;
   a.dz = dz;
   a.rec = RecordSoAT<double>{c->mg.rec64, c->mg.rec.flags};
   a.phase = c->qp_phase;

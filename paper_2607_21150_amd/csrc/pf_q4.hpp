@@ -631,8 +631,13 @@ __global__ __launch_bounds__(NT5, 2) void k_a32_q4(LinApplyArgs<V> a, int colour
   const int64_t gq = e * Q3 + ql;
   LinRecordT<V> rc;
 #pragma unroll
-  for (int k = 0; k < REC_N; ++k) rc.v[k] = pt ? a.rec.rec[k * a.n_q + gq] : V(0);
+  for (int k = 0; k < REC_N; ++k) rc.v[k] = pt ? a.rec.rec[rec_at<Q3, REC_N>(e, ql) + k * rec_pad(Q3)] : V(0);
   rc.flags = pt ? a.rec.flags[gq] : 0;
+  QPState<V> s;
+  if (!FRAME_FROM_U<V>) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) s.R[k] = pt ? a.frame[rec_at<Q3, 9>(e, ql) + k * rec_pad(Q3)] : V(0);
+  }
   const int pid = pt ? a.phase[gq] : 0;
   const V ih[3] = {(V)a.m.ih[0], (V)a.m.ih[1], (V)a.m.ih[2]};
   V wdet = tabs->w[Q][qx] * tabs->w[Q][qy] * tabs->w[Q][qz] * (V)a.m.jdet;
@@ -643,20 +648,22 @@ __global__ __launch_bounds__(NT5, 2) void k_a32_q4(LinApplyArgs<V> a, int colour
     for (int k = 0; k < 9; ++k) gA[k] = pt ? a.qd[k * a.n_q + gq] : 0.0;
     wdet = pt ? (V)a.qd[9 * a.n_q + gq] : V(0);
   }
-  gather_nodes<V, V, PF, 3>(a.z32, a.fine.n_nodes, elem_node<PF>(a.fine.nx1, a.fine.ny1, g), bufA);
-  __syncthreads();
-  sf5_fwd<V, Tab, PF, Q, 3>(bufA, bufB, tabs);
-  V G[9];
+  V G[FRAME_FROM_U<V> ? 9 : 1];
+  if constexpr (FRAME_FROM_U<V>) {
+    gather_nodes<V, V, PF, 3>(a.u, a.fine.n_nodes, elem_node<PF>(a.fine.nx1, a.fine.ny1, g), bufA);
+    __syncthreads();
+    sf5_fwd<V, Tab, PF, Q, 3>(bufA, bufB, tabs);
 #pragma unroll
-  for (int f = 0; f < 3; ++f) {
-    if (GEO)
-      map_grad<V>((double)bufB[(4 * f + 1) * Q3 + ql], (double)bufB[(4 * f + 2) * Q3 + ql],
-                  (double)bufB[(4 * f + 3) * Q3 + ql], gA, G + 3 * f);
-    else
+    for (int f = 0; f < 3; ++f) {
+      if (GEO)
+        map_grad<V>((double)bufB[(4 * f + 1) * Q3 + ql], (double)bufB[(4 * f + 2) * Q3 + ql],
+                    (double)bufB[(4 * f + 3) * Q3 + ql], gA, G + 3 * f);
+      else
 #pragma unroll
-      for (int J = 0; J < 3; ++J) G[3 * f + J] = bufB[(4 * f + 1 + J) * Q3 + ql] * ih[J];
+        for (int J = 0; J < 3; ++J) G[3 * f + J] = bufB[(4 * f + 1 + J) * Q3 + ql] * ih[J];
+    }
+    __syncthreads();
   }
-  __syncthreads();
   gather_nodes<V, V, PC, 4>(a.dz, a.lev.n_nodes, elem_node<PC>(a.lev.nx1, a.lev.ny1, g), bufA);
   __syncthreads();
   sf5_fwd<V, Tab, PC, Q, 4, true>(bufA, bufB, tabs);
@@ -669,16 +676,16 @@ __global__ __launch_bounds__(NT5, 2) void k_a32_q4(LinApplyArgs<V> a, int colour
                   (double)bufB[qslot<true>(f, 3) * Q3 + ql], gA, out);
     else
 #pragma unroll
-      for (int J = 0; J < 3; ++J) out[J] = bufB[qslot<true>(f, 1 + J) * Q3 + ql] * ih[J];
+      for (int J = 0; J < 3; ++J) out[J] = bufB[qslot<true>(f, 1 + J) * Q3 + ql];  // reference directions
   }
   wphi = bufB[qslot<true>(3, 0) * Q3 + ql];
   __syncthreads();
   const int pidc = pid < a.nph ? pid : 0;
   const MatParams<V> mp = a.mats[pidc];
-  QPState<V> s;
-  qp_state_lin<V>(mp, G, rc, s);
+  qp_state_lin<V>(rc, s);
+  if constexpr (FRAME_FROM_U<V>) frame_from_gradient<V>(G, s.N, GEO ? nullptr : ih, s.R);
   V Fu[9], dL;
-  lin_tangent<V, MB>(a.rec, a.n_q, a.xmats, a.n_extra, mp, s, pidc, gq, pt, G, W, wphi, Fu, dL);
+  lin_tangent<V, Q3, MB>(a.rec, (int64_t)a.m.nx * a.m.ny * a.m.nz, a.xmats, a.n_extra, mp, s, pidc, e, ql, pt, W, wphi, Fu, dL);
   const V kfg = a.fr.kf * mp.Gc;
   if (pt && GEO) {
 #pragma unroll
@@ -692,14 +699,13 @@ __global__ __launch_bounds__(NT5, 2) void k_a32_q4(LinApplyArgs<V> a, int colour
     }
     bufB[qslot<true>(3, 0) * Q3 + ql] = wdet * a.fr.s_phi * dL;
   } else if (pt) {
-    const V wih[3] = {wdet * ih[0], wdet * ih[1], wdet * ih[2]};
 #pragma unroll
     for (int f = 0; f < 3; ++f)
 #pragma unroll
-      for (int J = 0; J < 3; ++J) bufB[qslot<true>(f, 1 + J) * Q3 + ql] = Fu[3 * f + J] * wih[J];
+      for (int J = 0; J < 3; ++J) bufB[qslot<true>(f, 1 + J) * Q3 + ql] = wdet * Fu[3 * f + J];
     bufB[qslot<true>(3, 0) * Q3 + ql] = wdet * a.fr.s_phi * dL;
 #pragma unroll
-    for (int J = 0; J < 3; ++J) bufB[qslot<true>(3, 1 + J) * Q3 + ql] = kfg * gw[J] * wih[J];
+    for (int J = 0; J < 3; ++J) bufB[qslot<true>(3, 1 + J) * Q3 + ql] = wdet * kfg * (ih[J] * ih[J]) * gw[J];
   }
   __syncthreads();
   sf5_bwd<V, Tab, PC, Q, 4, true>(bufB, bufA, tabs);
@@ -743,28 +749,35 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2r(LinApplyArgs<V> a, const type
   V* B = bufB + slot * L::B;
   LinRecordT<V> rc;
 #pragma unroll
-  for (int k = 0; k < REC_N; ++k) rc.v[k] = pt ? a.rec.rec[k * a.n_q + gq] : V(0);
+  for (int k = 0; k < REC_N; ++k) rc.v[k] = pt ? a.rec.rec[rec_at<Q3, REC_N>(e, ql) + k * rec_pad(Q3)] : V(0);
   rc.flags = pt ? a.rec.flags[gq] : 0;
+  QPState<V> s;
+  if (!FRAME_FROM_U<V>) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) s.R[k] = pt ? a.frame[rec_at<Q3, 9>(e, ql) + k * rec_pad(Q3)] : V(0);
+  }
   const int pid = pt ? a.phase[gq] : 0;
   const V ih[3] = {(V)a.m.ih[0], (V)a.m.ih[1], (V)a.m.ih[2]};
   const V wdet = tabs->w[Q][qx] * tabs->w[Q][qy] * tabs->w[Q][qz] * (V)a.m.jdet;
-  // the fine displacement mirror at the element's 27 nodes (thread n owns node n)
-  if (ein && n < PF * PF * PF) {
-    const int64_t gn = lattice_node<PF>(a.fine.nx1, a.fine.ny1, g, n);
-    V v[3];
+  V G[FRAME_FROM_U<V> ? 9 : 1];
+  if constexpr (FRAME_FROM_U<V>) {
+    // the fine displacement at the element's 27 nodes (thread n owns node n)
+    if (ein && n < PF * PF * PF) {
+      const int64_t gn = lattice_node<PF>(a.fine.nx1, a.fine.ny1, g, n);
+      V v[3];
 #pragma unroll
-    for (int f = 0; f < 3; ++f) v[f] = a.z32[f * a.fine.n_nodes + gn];
+      for (int f = 0; f < 3; ++f) v[f] = a.u[f * a.fine.n_nodes + gn];
 #pragma unroll
-    for (int f = 0; f < 3; ++f) A[f * PF * PF * PF + n] = v[f];
+      for (int f = 0; f < 3; ++f) A[f * PF * PF * PF + n] = v[f];
+    }
+    __syncthreads();
+    sf5_fwd<V, Tab, PF, Q, 3, false, true, NE, NT>(bufA, bufB, tabs, L::A, L::B);
+#pragma unroll
+    for (int f = 0; f < 3; ++f)
+#pragma unroll
+      for (int J = 0; J < 3; ++J) G[3 * f + J] = B[(4 * f + 1 + J) * Q3 + ql] * ih[J];
+    __syncthreads();
   }
-  __syncthreads();
-  sf5_fwd<V, Tab, PF, Q, 3, false, true, NE, NT>(bufA, bufB, tabs, L::A, L::B);
-  V G[9];
-#pragma unroll
-  for (int f = 0; f < 3; ++f)
-#pragma unroll
-    for (int J = 0; J < 3; ++J) G[3 * f + J] = B[(4 * f + 1 + J) * Q3 + ql] * ih[J];
-  __syncthreads();
   // the level direction at the element's PC^3 nodes
   if (ein && n < PC3) {
     const int64_t gn = lattice_node<PC>(a.lev.nx1, a.lev.ny1, g, n);
@@ -781,26 +794,25 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2r(LinApplyArgs<V> a, const type
   for (int f = 0; f < 4; ++f) {
     V* out = f < 3 ? W + 3 * f : gw;
 #pragma unroll
-    for (int J = 0; J < 3; ++J) out[J] = B[qslot<true>(f, 1 + J) * Q3 + ql] * ih[J];
+    for (int J = 0; J < 3; ++J) out[J] = B[qslot<true>(f, 1 + J) * Q3 + ql];  // reference directions
   }
   wphi = B[qslot<true>(3, 0) * Q3 + ql];
   __syncthreads();
   const int pidc = pid < a.nph ? pid : 0;
   const MatParams<V> mp = a.mats[pidc];
-  QPState<V> s;
-  qp_state_lin<V>(mp, G, rc, s);
+  qp_state_lin<V>(rc, s);
+  if constexpr (FRAME_FROM_U<V>) frame_from_gradient<V>(G, s.N, ih, s.R);
   V Fu[9], dL;
-  lin_tangent<V, false>(a.rec, a.n_q, a.xmats, a.n_extra, mp, s, pidc, gq, pt, G, W, wphi, Fu, dL);
+  lin_tangent<V, Q3, false>(a.rec, 0, a.xmats, a.n_extra, mp, s, pidc, e, ql, pt, W, wphi, Fu, dL);
   const V kfg = a.fr.kf * mp.Gc;
   if (pt) {
-    const V wih[3] = {wdet * ih[0], wdet * ih[1], wdet * ih[2]};
 #pragma unroll
     for (int f = 0; f < 3; ++f)
 #pragma unroll
-      for (int J = 0; J < 3; ++J) B[qslot<true>(f, 1 + J) * Q3 + ql] = Fu[3 * f + J] * wih[J];
+      for (int J = 0; J < 3; ++J) B[qslot<true>(f, 1 + J) * Q3 + ql] = wdet * Fu[3 * f + J];
     B[qslot<true>(3, 0) * Q3 + ql] = wdet * a.fr.s_phi * dL;
 #pragma unroll
-    for (int J = 0; J < 3; ++J) B[qslot<true>(3, 1 + J) * Q3 + ql] = kfg * gw[J] * wih[J];
+    for (int J = 0; J < 3; ++J) B[qslot<true>(3, 1 + J) * Q3 + ql] = wdet * kfg * (ih[J] * ih[J]) * gw[J];
   }
   __syncthreads();
   sf5_bwd<V, Tab, PC, Q, 4, true, NE, NT>(bufB, bufA, tabs, L::B, L::A);

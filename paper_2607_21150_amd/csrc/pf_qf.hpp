@@ -333,6 +333,7 @@ __device__ inline T log_divdiff(T beta_i, T beta_j, T eps_i, T eps_j, T ib_j) {
 template <typename T> struct QPState {
   T Fi[9];      // F^-1
   T N[9];       // eigenvectors of b_tr (columns)
+  T R[9];       // the linearised applies: F^-1 N, its rows in the applies' directions
   T bd[3];      // principal values b_i of b_tr
   T e[3];       // deviatoric principal trial log strain
   T theta;      // tr eps
@@ -535,8 +536,8 @@ __device__ inline void qp_state(const MatParams<double>& m, const FracParams<dou
 // stored in FP32 (19 values + a flag byte): the return-mapping factor and its
 // tangent coefficients, the degradation and the local phase-field coefficient,
 // the principal frame of b_tr as a unit quaternion, the principal values b_i,
-// the principal log strains and the off-diagonal tangent factors. The FP32
-// applies recompute only F^-1 from the FP32 displacement mirror.
+// the principal log strains and the off-diagonal tangent factors. F^-1 N of the point's
+// block goes with it in an array of its own (QPState::R).
 // Record slots: return factor, tangent scalars, degradation and its derivative, the
 // history term's coefficient, the frame of b_tr as the three smallest components of a
 // unit quaternion (the largest, made positive, is recovered from the norm; its index is
@@ -581,8 +582,32 @@ __device__ inline void quat_to_rot(const T* q, T* R) {
   R[6] = T(2) * (xz - wy);          R[7] = T(2) * (yz + wx);          R[8] = T(1) - T(2) * (xx + yy);
 }
 
+// R = F^-1 N with row k times dir[k] (box elements: 2 / h of the axis, so that R takes
+// reference derivatives; null: physical directions).
+template <typename T>
+__device__ inline void frame_product(const T* Fi, const T* N, const T* dir, T* R) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const T v = Fi[3 * i] * N[j] + Fi[3 * i + 1] * N[3 + j] + Fi[3 * i + 2] * N[6 + j];
+      R[3 * i + j] = dir ? dir[i] * v : v;
+    }
+}
+
+// Fi = R N^T: F^-1 back from R = F^-1 N.
+template <typename T>
+__device__ inline void frame_times(const T* R, const T* N, T* Fi) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+      Fi[3 * i + j] = R[3 * i] * N[3 * j] + R[3 * i + 1] * N[3 * j + 1] + R[3 * i + 2] * N[3 * j + 2];
+}
+
+// frame (unless null): the rotation that the record holds.
 template <typename V>
-__device__ inline void record_from_state(const QPState<double>& s, LinRecordT<V>& r) {
+__device__ inline void record_from_state(const QPState<double>& s, LinRecordT<V>& r, double* frame = nullptr) {
   r.v[R_C] = (V)s.c;
   r.v[R_KQ] = (V)s.kq;
   r.v[R_KPHI] = (V)s.kphi;
@@ -595,6 +620,8 @@ __device__ inline void record_from_state(const QPState<double>& s, LinRecordT<V>
   const double det = R[0] * (R[4] * R[8] - R[5] * R[7]) - R[1] * (R[3] * R[8] - R[5] * R[6]) +
                      R[2] * (R[3] * R[7] - R[4] * R[6]);
   if (det < 0.0) R[0] = -R[0], R[3] = -R[3], R[6] = -R[6];
+  if (frame)
+    for (int k = 0; k < 9; ++k) frame[k] = R[k];
   double q[4];
   rot_to_quat(R, q);
   // q and -q are the same rotation: keep the largest component positive and drop it
@@ -648,14 +675,20 @@ __device__ inline void commit_from_state(const QPState<double>& s, const double*
   out[7] = s.H;
 }
 
-// State for the linearised FP32 apply: F^-1 from the FP32 displacement mirror,
-// everything else (frame, principal values, decisions, coefficients) from the record.
+// R of a point from its physical displacement gradient (the FP64 record apply).
 template <typename T>
-__device__ inline void qp_state_lin(const MatParams<T>& m, const T* G, const LinRecordT<T>& r, QPState<T>& s) {
-  T F[9];
+__device__ inline void frame_from_gradient(const T* G, const T* N, const T* dir, T* R) {
+  T F[9], Fi[9];
 #pragma unroll
   for (int k = 0; k < 9; ++k) F[k] = G[k] + ((k % 4 == 0) ? T(1) : T(0));
-  inverse33<T>(F, s.Fi);
+  inverse33<T>(F, Fi);
+  frame_product<T>(Fi, N, dir, R);
+}
+
+// State for the linearised applies from the record (frame, principal values, decisions,
+// coefficients); s.R is the caller's.
+template <typename T>
+__device__ inline void qp_state_lin(const LinRecordT<T>& r, QPState<T>& s) {
   {
     const int m = (r.flags >> 3) & 3;
     const T a0 = (T)r.v[R_Q0], a1 = (T)r.v[R_Q0 + 1], a2 = (T)r.v[R_Q0 + 2];
@@ -688,7 +721,8 @@ __device__ inline void qp_state_lin(const MatParams<T>& m, const T* G, const Lin
 }
 
 // Directional derivative (Appendices B-C): (dG, dphi) -> (dP, dL).
-// Evaluated in the principal frame of b_tr: with dl = dG F^-1 and Lt = N^T dl N,
+// Evaluated in the principal frame of b_tr: with dl = dG F^-1 and Lt = N^T dl N = N^T dG R
+// (dG and dP in the directions of R's rows),
 // the rotated perturbation N^T (dl b + b dl^T) N is Lt diag(b) + diag(b) Lt^T, and
 // dP = N (dtau_rot - diag(tau_d) Lt^T) N^T F^-T, where dtau_rot carries the principal
 // increments on the diagonal and the divided-difference terms off it, and the second
@@ -699,13 +733,7 @@ template <typename T>
 __device__ inline void qp_tangent_psi(const MatParams<T>& m, const QPState<T>& s, const T* dG, T dphi,
                                       T* dP, T& dpsi, bool want = true) {
   const T* N = s.N;
-  // FiN = F^-1 N serves both ends: dl N = dG FiN and F^-T at the output
-  T FiN[9];
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      FiN[3 * i + j] = s.Fi[3 * i] * N[j] + s.Fi[3 * i + 1] * N[3 + j] + s.Fi[3 * i + 2] * N[6 + j];
+  const T* FiN = s.R;  // serves both ends: dl N = dG F^-1 N and F^-T at the output
   // Lt = N^T (dl N), dl = dG F^-1
   T dN[9], Lt[9];
 #pragma unroll
