@@ -43,6 +43,13 @@ struct LevelDev {
   int64_t n_nodes;
 };
 
+// Block stencil of an order-1 level, [blocks of 64 nodes][4 rows f][27 offsets][4 columns g][64]: a
+// wavefront reads the 108 entries of its row as one run of memory. Entry (o, g) of row f of node i is
+// at stencil_at(i, f) + (4 o + g) * 64 + i % 64; entries towards nodes outside the lattice are 0, and
+// the last block is padded.
+__host__ __device__ constexpr int64_t stencil_at(int64_t i, int f) { return (i / 64 * 4 + f) * (108 * 64); }
+__host__ __device__ constexpr int64_t stencil_size(int64_t n) { return stencil_at(n + 63, 0); }
+
 constexpr int MG_MAX_LEVELS = 8;
 
 struct MGLevel {
@@ -54,7 +61,7 @@ struct MGLevel {
   int ne[3] = {0, 0, 0};  // elements per direction of this level's lattice
   int nx1 = 0, ny1 = 0, nz1 = 0;
   int64_t n_nodes = 0;
-  float* S = nullptr;  // h > 0: block stencil [27][4][4][n_nodes]
+  float* S = nullptr;  // h > 0: block stencil (stencil_at)
   float *x = nullptr, *r = nullptr, *d = nullptr, *t = nullptr, *b = nullptr;
   float *diag = nullptr, *dinv = nullptr;
   double lmax = 0.0;
@@ -77,7 +84,7 @@ struct MGState {
   double* red = nullptr;  // reduction scratch
   float* ebe = nullptr;    // element matrices of the order-1 level on the mesh [n_elem][32][32], and the
                            // levels' element diagonals (both per linearisation)
-  float* stencil = nullptr;  // the same level as a block stencil [27][4][4][n_nodes]
+  float* stencil = nullptr;  // the same level as a block stencil (stencil_at)
   float* ebuf32 = nullptr;   // brick-buffer scatter of the FP32 level applies
   double* rec64 = nullptr;   // stored FP64 linearisation, laid out as rec (flags in rec.flags)
   double* u64 = nullptr;     // u at the linearisation point [3][n_nodes]

@@ -141,7 +141,7 @@ pf_status mg_alloc_levels(pf_ctx* c, const int* orders, int nl) {
     float** bufs[] = {&L.x, &L.r, &L.d, &L.t, &L.b, &L.diag, &L.dinv};
     for (float** b : bufs)
       if (hipMalloc(b, nb) != hipSuccess) return fail(PF_ENOMEM, "multigrid level allocation failed");
-    if (L.h > 0 && hipMalloc(&L.S, (size_t)27 * 16 * L.n_nodes * sizeof(float)) != hipSuccess)
+    if (L.h > 0 && hipMalloc(&L.S, (size_t)stencil_size(L.n_nodes) * sizeof(float)) != hipSuccess)
       return fail(PF_ENOMEM, "coarse stencil: allocation failed");
     if (l + 1 < nl) {
       const bool hnext = L.p == 1 && orders[l + 1] == 1;
@@ -166,7 +166,7 @@ pf_status mg_alloc_levels(pf_ctx* c, const int* orders, int nl) {
   const int64_t n_elem = (int64_t)N[0] * N[1] * N[2];
   if (hipMalloc(&mg.ebe, (size_t)n_elem * 1024 * sizeof(float)) != hipSuccess ||
       (mg.ebe_level >= 0 &&
-       hipMalloc(&mg.stencil, (size_t)27 * 16 * mg.lv[mg.ebe_level].n_nodes * sizeof(float)) != hipSuccess))
+       hipMalloc(&mg.stencil, (size_t)stencil_size(mg.lv[mg.ebe_level].n_nodes) * sizeof(float)) != hipSuccess))
     return fail(PF_ENOMEM, "coarse element matrices: allocation failed");
   const size_t nfine = 4 * mg.lv[0].n_nodes * sizeof(float);
   if (hipMalloc(&mg.frame, 9 * rec_points(c) * sizeof(float)) != hipSuccess ||
