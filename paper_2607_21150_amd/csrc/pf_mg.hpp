@@ -11,6 +11,7 @@
 // (F^-1 N, frame, log strains, the yield, split and history decisions, the
 // return-mapping scalars) comes from the record taken in FP64 by the linearisation.
 #pragma once
+#include <climits>
 #include <hip/hip_runtime.h>
 
 #include "pf_brick.hpp"
@@ -549,6 +550,72 @@ static __global__ void k_transfer_1d(const float* __restrict__ in, float* __rest
       const float v = (bits >> f) & 1u ? 0.f : acc[f];
       out[f * no + o] = add ? out[f * no + o] + v : v;
     }
+  }
+}
+
+// The three directions in one launch: NW weights per direction (NW^3 inputs per output). One thread
+// per (i0, i1) and field (blockIdx.y) for zb outputs along direction 2 (blockIdx.z), which keep the
+// NW interpolated planes of the inputs while their base stays the same. add, has_dir: see above.
+struct TransferAxes {
+  const int* base[3];
+  const float* w[3];
+};
+template <int NW>
+static __global__ __launch_bounds__(NT) void k_transfer(const float* __restrict__ in, float* __restrict__ out, int n0o,
+                                                        int n1o, int n2o, int n0i, int n1i, int n2i, TransferAxes ax,
+                                                        int zb, int add, DirMask dir, int has_dir) {
+  const int t = blockIdx.x * NT + threadIdx.x;
+  if (t >= n0o * n1o) return;
+  const int i1 = t / n0o, i0 = t - i1 * n0o, f = blockIdx.y;
+  const float* src = in + (int64_t)f * n0i * n1i * n2i;
+  float* dst = out + (int64_t)f * n0o * n1o * n2o;
+  int j0[NW], j1[NW];
+  float w0[NW], w1[NW];
+#pragma unroll
+  for (int k = 0; k < NW; ++k) {
+    // a weight outside the lattice counts as 0; an input with weight 0 is taken as 0
+    const int a = ax.base[0][i0] + k, b = ax.base[1][i1] + k;
+    w0[k] = a >= 0 && a < n0i ? ax.w[0][i0 * NW + k] : 0.f;
+    w1[k] = b >= 0 && b < n1i ? ax.w[1][i1 * NW + k] : 0.f;
+    j0[k] = w0[k] != 0.f ? a : 0;
+    j1[k] = w1[k] != 0.f ? b * n0i : 0;
+  }
+  float plane[NW];
+  int have = INT_MIN;  // base of the planes held
+  const int z1 = (int)min((int64_t)n2o, (int64_t)(blockIdx.z + 1) * zb);
+  for (int i2 = blockIdx.z * zb; i2 < z1; ++i2) {
+    const int b2 = ax.base[2][i2];
+    if (b2 != have) {  // uniform
+      have = b2;
+#pragma unroll
+      for (int k2 = 0; k2 < NW; ++k2) {
+        const int c = b2 + k2;
+        plane[k2] = 0.f;
+        if (c < 0 || c >= n2i) continue;  // uniform
+        const float* s2 = src + (int64_t)c * n0i * n1i;
+        float v[NW][NW];
+#pragma unroll
+        for (int k1 = 0; k1 < NW; ++k1)
+#pragma unroll
+          for (int k0 = 0; k0 < NW; ++k0) v[k1][k0] = s2[j1[k1] + j0[k0]];
+#pragma unroll
+        for (int k1 = 0; k1 < NW; ++k1) {
+          float r = 0.f;
+#pragma unroll
+          for (int k0 = 0; k0 < NW; ++k0) r += w0[k0] != 0.f ? w0[k0] * v[k1][k0] : 0.f;
+          plane[k2] += w1[k1] != 0.f ? w1[k1] * r : 0.f;
+        }
+      }
+    }
+    float acc = 0.f;
+#pragma unroll
+    for (int k2 = 0; k2 < NW; ++k2) {
+      const float wk = ax.w[2][(int64_t)i2 * NW + k2];
+      acc += wk != 0.f ? wk * plane[k2] : 0.f;
+    }
+    if (has_dir && ((dir_bits(dir, i0, i1, i2, n0o, n1o, n2o) >> f) & 1u)) acc = 0.f;
+    float* o = dst + ((int64_t)i2 * n1o + i1) * n0o + i0;
+    *o = add ? *o + acc : acc;
   }
 }
 

@@ -552,45 +552,61 @@ pf_status launch_linearize(pf_ctx* c, const LinArgs& a, hipStream_t s) {
   return PF_OK;
 }
 
-// y = P x (coarse level l+1 -> level l) or y += P x, separable passes x, y, z; masked.
+// One launch for the three directions up to 4^3 inputs per node: every prolongation, and the
+// restriction between order-1 lattices. The small levels pay the launches, the large ones the passes
+// over intermediate lattices: 17^3 nodes from 2^3 inputs 12 -> 5 us, 97^3 from 3^3 34 -> 31, 161^3 from
+// 3^3 125 -> 92, order 3 to 4 on 32^3 elements 71 -> 66. The 5^3 inputs of the restriction from order 2
+// took 25 us on 41^3 nodes against 19 in three passes, so it and the wider ones stay there.
+template <int NW>
+pf_status transfer_nw(pf_ctx* c, const float* in, const MGLevel& I, float* out, const MGLevel& O, const TransferAxes& ax,
+                      bool add, hipStream_t s) {
+  const unsigned nb = (unsigned)(((int64_t)O.nx1 * O.ny1 + NT - 1) / NT);
+  // outputs per thread: as many as an element's nodes share planes, where the rest fills the chip
+  // (256 CUs, 8 workgroups each); at most 65535 groups
+  int zb = (int64_t)nb * 4 * O.nz1 >= 4 * 2048 ? 4 : 1;
+  zb = std::max(zb, (O.nz1 + 65534) / 65535);
+  hipLaunchKernelGGL(k_transfer<NW>, dim3(nb, 4, (O.nz1 + zb - 1) / zb), dim3(NT), 0, s, in, out, O.nx1, O.ny1, O.nz1,
+                     I.nx1, I.ny1, I.nz1, ax, zb, add ? 1 : 0, c->dir, c->has_dir ? 1 : 0);
+  HIPCHK(hipGetLastError());
+  return PF_OK;
+}
+
+pf_status transfer(pf_ctx* c, const float* in, const MGLevel& I, float* out, const MGLevel& O, int* const* base,
+                   float* const* w, int nw, bool add, hipStream_t s) {
+  const TransferAxes ax{{base[0], base[1], base[2]}, {w[0], w[1], w[2]}};
+  switch (nw) {
+    case 2: return transfer_nw<2>(c, in, I, out, O, ax, add, s);
+    case 3: return transfer_nw<3>(c, in, I, out, O, ax, add, s);
+    case 4: return transfer_nw<4>(c, in, I, out, O, ax, add, s);
+    default: break;
+  }
+  float* A = c->mg.tmpA;
+  float* B = c->mg.tmpB;
+  int64_t n = (int64_t)O.nx1 * I.ny1 * I.nz1;
+  hipLaunchKernelGGL(k_transfer_1d, dim3(vec_grid(n)), dim3(NT), 0, s, in, A, O.nx1, I.ny1, I.nz1, I.nx1, I.ny1, I.nz1,
+                     0, base[0], w[0], nw, 0, c->dir, 0);
+  n = (int64_t)O.nx1 * O.ny1 * I.nz1;
+  hipLaunchKernelGGL(k_transfer_1d, dim3(vec_grid(n)), dim3(NT), 0, s, A, B, O.nx1, O.ny1, I.nz1, O.nx1, I.ny1, I.nz1,
+                     1, base[1], w[1], nw, 0, c->dir, 0);
+  n = O.n_nodes;
+  hipLaunchKernelGGL(k_transfer_1d, dim3(vec_grid(n)), dim3(NT), 0, s, B, out, O.nx1, O.ny1, O.nz1, O.nx1, O.ny1, I.nz1,
+                     2, base[2], w[2], nw, add ? 1 : 0, c->dir, c->has_dir ? 1 : 0);
+  HIPCHK(hipGetLastError());
+  return PF_OK;
+}
+
+// xf (+)= P xc (coarse level l+1 -> level l), masked.
 pf_status prolong(pf_ctx* c, int l, const float* xc, float* xf, bool add, hipStream_t s) {
   const MGLevel& F = c->mg.lv[l];
   const MGLevel& C = c->mg.lv[l + 1];
-  float* A = c->mg.tmpA;
-  float* B = c->mg.tmpB;
-  int64_t n;
-  n = (int64_t)F.nx1 * C.ny1 * C.nz1;
-  hipLaunchKernelGGL(k_transfer_1d, dim3(vec_grid(n)), dim3(NT), 0, s, xc, A, F.nx1, C.ny1, C.nz1, C.nx1, C.ny1,
-                     C.nz1, 0, F.pbase[0], F.pw[0], C.P, 0, c->dir, 0);
-  n = (int64_t)F.nx1 * F.ny1 * C.nz1;
-  hipLaunchKernelGGL(k_transfer_1d, dim3(vec_grid(n)), dim3(NT), 0, s, A, B, F.nx1, F.ny1, C.nz1, F.nx1, C.ny1,
-                     C.nz1, 1, F.pbase[1], F.pw[1], C.P, 0, c->dir, 0);
-  n = F.n_nodes;
-  hipLaunchKernelGGL(k_transfer_1d, dim3(vec_grid(n)), dim3(NT), 0, s, B, xf, F.nx1, F.ny1, F.nz1, F.nx1, F.ny1,
-                     C.nz1, 2, F.pbase[2], F.pw[2], C.P, add ? 1 : 0, c->dir, c->has_dir ? 1 : 0);
-  HIPCHK(hipGetLastError());
-  return PF_OK;
+  return transfer(c, xc, C, xf, F, F.pbase, F.pw, C.P, add, s);
 }
 
 // rc = P^T rf (level l -> coarse level l+1), masked.
 pf_status restrict_(pf_ctx* c, int l, const float* rf, float* rc, hipStream_t s) {
   const MGLevel& F = c->mg.lv[l];
   const MGLevel& C = c->mg.lv[l + 1];
-  float* A = c->mg.tmpA;
-  float* B = c->mg.tmpB;
-  const int nw = 2 * F.p + 1;
-  int64_t n;
-  n = (int64_t)C.nx1 * F.ny1 * F.nz1;
-  hipLaunchKernelGGL(k_transfer_1d, dim3(vec_grid(n)), dim3(NT), 0, s, rf, A, C.nx1, F.ny1, F.nz1, F.nx1, F.ny1,
-                     F.nz1, 0, F.rbase[0], F.rw[0], nw, 0, c->dir, 0);
-  n = (int64_t)C.nx1 * C.ny1 * F.nz1;
-  hipLaunchKernelGGL(k_transfer_1d, dim3(vec_grid(n)), dim3(NT), 0, s, A, B, C.nx1, C.ny1, F.nz1, C.nx1, F.ny1,
-                     F.nz1, 1, F.rbase[1], F.rw[1], nw, 0, c->dir, 0);
-  n = C.n_nodes;
-  hipLaunchKernelGGL(k_transfer_1d, dim3(vec_grid(n)), dim3(NT), 0, s, B, rc, C.nx1, C.ny1, C.nz1, C.nx1, C.ny1,
-                     F.nz1, 2, F.rbase[2], F.rw[2], nw, 0, c->dir, c->has_dir ? 1 : 0);
-  HIPCHK(hipGetLastError());
-  return PF_OK;
+  return transfer(c, rf, F, rc, C, F.rbase, F.rw, 2 * F.p + 1, false, s);
 }
 
 // Chebyshev(k) with point Jacobi on level l for A x = b, bounds [0.1, 1.1] * lmax; x_zero: from

@@ -153,3 +153,47 @@ def test_level_diagonals_match_the_level_applies(pf, p, n, levels, variant):
         for f in range(4):
             err = float(torch.linalg.norm(got[f] - ref[f]) / torch.linalg.norm(ref[f]))
             assert err <= 2e-5, (l, f, err)
+
+
+def lagrange(xc, xf):
+    B = np.ones((len(xf), len(xc)))
+    for j in range(len(xc)):
+        for k in range(len(xc)):
+            if k != j:
+                B[:, j] *= (xf - xc[k]) / (xc[j] - xc[k])
+    return B
+
+
+@pytest.mark.parametrize("p,n,levels", [(4, 20, [4, 3]), (3, 32, [3, 2]), (2, 44, [2, 1, 1]), (4, 2, [4, 3]), (3, 1, [3, 1])])
+def test_transfers_match_dense_rows(pf, p, n, levels):
+    """Sizes on both sides of the rule for the outputs per thread, masked faces. Three nested sums of
+    at most 9 terms in FP32 with weights up to 1.2: 27 * 6e-8 * 1.2^3 = 2.8e-6, taken as 3e-6."""
+    d = I.make_inputs("C1", "base", p=p, n=n)
+    ctx = make_ctx(pf, d, levels, "brick_buffer", FACES)
+    torch.manual_seed(3)
+    ne = n
+    for l, (q, r) in enumerate(zip(levels[:-1], levels[1:])):
+        nc = ne // 2 if q == 1 else ne
+        P = np.zeros((q * ne + 1, r * nc + 1))
+        if q == 1:
+            for i in range(ne + 1):
+                P[i, i // 2] += 0.5
+                P[i, (i + 1) // 2] += 0.5
+        else:
+            B = lagrange(np.asarray(I.gll_points(r)), np.asarray(I.gll_points(q)))
+            for e in range(ne):
+                P[q * e:q * e + q + 1, r * e:r * e + r + 1] = B
+        P = torch.as_tensor(P).cuda()
+        kf, kc = P.shape
+        mf, mc = free_mask(kf ** 3, FACES), free_mask(kc ** 3, FACES)
+        ap = lambda M, x: torch.stack([torch.tensordot(M, torch.tensordot(M, torch.tensordot(M, x[f], ([1], [2])), ([1], [2])),
+                                                       ([1], [2])) for f in range(4)])
+        x = torch.randn(4, kc ** 3, device="cuda")
+        ref = ap(P, x.double().reshape(4, kc, kc, kc)).reshape(4, -1) * mf
+        err = float(torch.linalg.norm(ctx.prolong(l, x).double() - ref) / torch.linalg.norm(ref))
+        assert err <= 3e-6, ("prolong", l, err)
+        y = torch.randn(4, kf ** 3, device="cuda")
+        ref = ap(P.T.contiguous(), y.double().reshape(4, kf, kf, kf)).reshape(4, -1) * mc
+        err = float(torch.linalg.norm(ctx.restrict(l, y).double() - ref) / torch.linalg.norm(ref))
+        assert err <= 3e-6, ("restrict", l, err)
+        ne = nc
