@@ -669,6 +669,71 @@ __global__ __launch_bounds__(NT) void k_stencil_apply(const float* __restrict__ 
   if (OP == E_POWER) epi_sum(sq, ep.part, (int)(blockIdx.x + gridDim.x * f));
 }
 
+// The coarsest level's solve, all sweeps of the Chebyshev smoother in one workgroup of 8 waves (a
+// wave holds 64 nodes of one field, a thread its row's 108 entries, b, r, d and x): a launch per
+// apply of a few hundred rows is all latency. 125 nodes, 8 sweeps of degree 3 (23 applies): 37 us,
+// 23 launches of 4.3 us and their gaps before. At most COARSE_SOLVE_NODES nodes: beyond them a
+// thread's registers do not hold a row, and reading the rows from L2 took 24 us per apply at 216
+// nodes against 5.3 us for a launch.
+constexpr int COARSE_SOLVE_NODES = 128;
+struct ChebCoefs {
+  float c0, a[32], c[32];  // start, and steps 1 to degree - 1
+};
+static __global__ __launch_bounds__(4 * COARSE_SOLVE_NODES) void k_coarse_solve(const float* __restrict__ S, int nx1, int ny1, int nz1,
+                                                             int n, const float* __restrict__ b,
+                                                             const float* __restrict__ dinv, float* __restrict__ x,
+                                                             int degree, int sweeps, ChebCoefs co, DirMask dir,
+                                                             int has_dir) {
+  constexpr int NV = COARSE_SOLVE_NODES, LD = NV + 1;  // slot NV: the value 0 of a neighbour outside
+  __shared__ float vec[2][4 * LD];
+  const int w = wave_id(), f = w & 3, blk = w >> 2;
+  const int slot = blk * 64 + (threadIdx.x & 63);
+  const bool node = slot < n;
+  const int i = node ? slot : n - 1;
+  const int ix = i % nx1, iyz = i / nx1, iy = iyz % ny1, iz = iyz / ny1;
+  // a wave without a block of nodes (n <= 64 blk) reads the last one
+  const float* So = S + stencil_at(min(blk * 64, (n - 1) / 64 * 64), f) + (threadIdx.x & 63);
+  float row[108];
+#pragma unroll
+  for (int k = 0; k < 108; ++k) row[k] = So[k * 64];
+  const bool fixed = has_dir && ((dir_bits(dir, ix, iy, iz, nx1, ny1, nz1) >> f) & 1u);
+  const float bi = b[f * n + i], di = dinv[f * n + i];
+  if (threadIdx.x < 8) vec[threadIdx.x >> 2][(threadIdx.x & 3) * LD + NV] = 0.f;
+  const int sx[3] = {ix > 0 ? -1 : 0, 0, ix + 1 < nx1 ? 1 : 0};
+  const int sy[3] = {iy > 0 ? -nx1 : 0, 0, iy + 1 < ny1 ? nx1 : 0};
+  const int sz[3] = {iz > 0 ? -nx1 * ny1 : 0, 0, iz + 1 < nz1 ? nx1 * ny1 : 0};
+  int turn = 0;
+  // A v of this row, v_i this thread's entry
+  auto apply = [&](float vi) {
+    float* v = vec[turn];
+    turn ^= 1;
+    v[f * LD + slot] = vi;
+    __syncthreads();
+    float acc = 0.f;
+#pragma unroll
+    for (int o = 0; o < 27; ++o) {
+      const int ax = o % 3, ay = (o / 3) % 3, az = o / 9;
+      const bool inside = (ax == 1 || sx[ax] != 0) && (ay == 1 || sy[ay] != 0) && (az == 1 || sz[az] != 0);
+      const int j = inside ? i + sx[ax] + sy[ay] + sz[az] : NV;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) acc += row[4 * o + g] * v[g * LD + j];
+    }
+    return fixed ? 0.f : acc;
+  };
+  float xi = 0.f;
+  for (int s = 0; s < sweeps; ++s) {
+    float r = s == 0 ? bi : bi - apply(xi);
+    float d = co.c0 * di * r;
+    xi += d;
+    for (int it = 1; it < degree; ++it) {
+      r -= apply(d);
+      d = co.a[it - 1] * d + co.c[it - 1] * di * r;
+      xi += d;
+    }
+  }
+  if (node) x[f * n + i] = xi;
+}
+
 // Galerkin product of a block stencil on a coarser order-1 lattice: Sc = P^T Sf P with P
 // the trilinear interpolation from the coarse lattice (every second fine node per
 // direction, fine n = 2 nc - 1 nodes) to the fine one; fine node 2I + a (a = -1, 0, 1)

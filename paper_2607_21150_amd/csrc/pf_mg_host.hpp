@@ -658,11 +658,34 @@ pf_status chebyshev(pf_ctx* c, int l, const float* b, float* x, int k, bool x_ze
   return PF_OK;
 }
 
+// The sweeps of the coarsest level in one workgroup (n_nodes <= COARSE_SOLVE_NODES, degree <= 32).
+pf_status coarse_solve(pf_ctx* c, int l, const float* b, float* x, int degree, int sweeps, hipStream_t s) {
+  const MGLevel& L = c->mg.lv[l];
+  const double lmin = 0.1 * L.lmax, lhi = 1.1 * L.lmax;
+  const double theta = 0.5 * (lhi + lmin), delta = 0.5 * (lhi - lmin), sigma = theta / delta;
+  double rho = 1.0 / sigma;
+  ChebCoefs co{};
+  co.c0 = (float)(1.0 / theta);
+  for (int it = 1; it < degree; ++it) {
+    const double rn = 1.0 / (2.0 * sigma - rho);
+    co.a[it - 1] = (float)(rn * rho);
+    co.c[it - 1] = (float)(2.0 * rn / delta);
+    rho = rn;
+  }
+  const int n = (int)L.n_nodes;
+  hipLaunchKernelGGL(k_coarse_solve, dim3(1), dim3(4 * COARSE_SOLVE_NODES), 0, s, level_stencil(c, l), L.nx1, L.ny1,
+                     L.nz1, n, b, L.dinv, x, degree, sweeps, co, c->dir, c->has_dir ? 1 : 0);
+  HIPCHK(hipGetLastError());
+  return PF_OK;
+}
+
 pf_status vcycle(pf_ctx* c, int l, const float* b, float* x, const pf_pmg_opts& o, hipStream_t s) {
   MGState& mg = c->mg;
   MGLevel& L = mg.lv[l];
   pf_status st;
   if (l == mg.n_levels - 1) {
+    if (is_stencil(c, l) && L.n_nodes <= COARSE_SOLVE_NODES)
+      return coarse_solve(c, l, b, x, o.cheb_degree, o.coarse_sweeps, s);
     for (int sw = 0; sw < o.coarse_sweeps; ++sw)
       if ((st = chebyshev(c, l, b, x, o.cheb_degree, sw == 0, s))) return st;
     return PF_OK;

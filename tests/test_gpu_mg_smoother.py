@@ -112,6 +112,7 @@ def dnorm(x, dinv):
     (4, 3, [4, 2, 1], "brick_buffer", FACES), (4, 3, [4, 2], "colour", FACES), (4, 17, [4, 2], "brick_buffer", None),
     (3, 5, [3, 2], "brick_buffer", FACES), (3, 4, [3, 2, 1, 1], "colour", FACES),
     (3, 22, [3, 1], "brick_buffer", FACES), (3, 43, [3, 2], "brick_buffer", FACES),
+    (2, 4, [2, 1], "brick_buffer", FACES), (3, 5, [3, 1], "brick_buffer", FACES),  # 125 and 216 coarsest nodes
     (2, 1, [2, 1], "brick_buffer", None), (2, 4, [2, 1, 1], "brick_buffer", FACES), (2, 33, [2, 1], "brick_buffer", None)])
 def test_cycle_matches_its_definition(pf, p, n, levels, scatter, faces):
     print(f"case p={p} n={n} {levels} {scatter} faces={bool(faces)}", flush=True)
