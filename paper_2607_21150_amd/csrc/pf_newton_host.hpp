@@ -10,41 +10,36 @@
 
 namespace {
 
-// Deterministic dot products <V_j, w>, j = 0..k-1, summed on the host in block order.
+// The k rows of g block partials in kpart, summed on the device: k values come to the host.
+pf_status sum_partials(pf_ctx* c, int g, int k, hipStream_t s, double* out) {
+  double* sums = c->kcoef + 64;
+  hipLaunchKernelGGL(k_sum_parts, dim3(k), dim3(NT), 0, s, c->kpart, g, sums);
+  HIPCHK(hipGetLastError());
+  HIPCHK(hipMemcpyAsync(out, sums, k * sizeof(double), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  return PF_OK;
+}
+
+// Deterministic dot products <V_j, w>, j = 0..k-1.
 pf_status mdot(pf_ctx* c, const double* V, int64_t ld, int k, const double* w, int64_t n, hipStream_t s,
                double* out) {
   const int g = vec_grid(n);
   hipLaunchKernelGGL(k_mdot, dim3(g, k), dim3(NT), 0, s, V, ld, k, w, n, c->kpart);
   HIPCHK(hipGetLastError());
-  std::vector<double> h((size_t)g * k);
-  HIPCHK(hipMemcpyAsync(h.data(), c->kpart, h.size() * sizeof(double), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
-  for (int j = 0; j < k; ++j) {
-    double acc = 0.0;
-    for (int b = 0; b < g; ++b) acc += h[(size_t)j * g + b];
-    out[j] = acc;
-  }
-  return PF_OK;
-}
-
-// The k block-partial rows of part summed on the host in block order.
-pf_status sum_partials(pf_ctx* c, int g, int k, hipStream_t s, double* out) {
-  std::vector<double> h((size_t)g * k);
-  HIPCHK(hipMemcpyAsync(h.data(), c->kpart, h.size() * sizeof(double), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
-  for (int j = 0; j < k; ++j) {
-    double acc = 0.0;
-    for (int b = 0; b < g; ++b) acc += h[(size_t)j * g + b];
-    out[j] = acc;
-  }
-  return PF_OK;
+  return sum_partials(c, g, k, s, out);
 }
 
 // <V_j, w>, j < k <= GS_MAX, reading w once.
 pf_status mdot_multi(pf_ctx* c, const double* V, int64_t ld, int k, const double* w, int64_t n, hipStream_t s,
                      double* out) {
   const int g = vec_grid(n);
-  hipLaunchKernelGGL(k_mdot_multi, dim3(g), dim3(NT), 0, s, V, ld, k, w, n, c->kpart);
+  auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(g), dim3(NT), 0, s, V, ld, k, w, n, c->kpart); };
+  switch ((k + 7) / 8) {
+    case 1: run(k_mdot_multi<8>); break;
+    case 2: run(k_mdot_multi<16>); break;
+    case 3: run(k_mdot_multi<24>); break;
+    default: run(k_mdot_multi<32>); break;
+  }
   HIPCHK(hipGetLastError());
   return sum_partials(c, g, k, s, out);
 }
@@ -56,10 +51,15 @@ pf_status gs_correct(pf_ctx* c, const double* V, int64_t ld, int k, const double
   HIPCHK(hipMemcpyAsync(c->kcoef, coef, k * sizeof(double), hipMemcpyHostToDevice, s));
   HIPCHK(hipStreamSynchronize(s));  // coef is host memory
   const int g = vec_grid(n);
-  if (dots)
-    hipLaunchKernelGGL(k_maxpy_fused<true>, dim3(g), dim3(NT), 0, s, V, ld, k, c->kcoef, w, n, c->kpart);
-  else
-    hipLaunchKernelGGL(k_maxpy_fused<false>, dim3(g), dim3(NT), 0, s, V, ld, k, c->kcoef, w, n, c->kpart);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(g), dim3(NT), 0, s, V, ld, k, c->kcoef, w, n, c->kpart);
+  };
+  switch ((k + 7) / 8) {
+    case 1: dots ? run(k_maxpy_fused<8, true>) : run(k_maxpy_fused<8, false>); break;
+    case 2: dots ? run(k_maxpy_fused<16, true>) : run(k_maxpy_fused<16, false>); break;
+    case 3: dots ? run(k_maxpy_fused<24, true>) : run(k_maxpy_fused<24, false>); break;
+    default: dots ? run(k_maxpy_fused<32, true>) : run(k_maxpy_fused<32, false>); break;
+  }
   HIPCHK(hipGetLastError());
   return sum_partials(c, g, dots ? k : 1, s, out);
 }
@@ -89,7 +89,7 @@ pf_status newton_alloc(pf_ctx* c, int m) {
   // V[m+1], Z[m], r, dz, w-spare
   if (hipMalloc(&c->kry, (size_t)(2 * m + 4) * n * sizeof(double)) != hipSuccess ||
       hipMalloc(&c->kpart, (size_t)(m + 2) * VEC_BLOCKS * sizeof(double)) != hipSuccess ||
-      hipMalloc(&c->kcoef, 64 * sizeof(double)) != hipSuccess ||
+      hipMalloc(&c->kcoef, (64 + m + 2) * sizeof(double)) != hipSuccess ||
       hipMalloc(&c->k32, (size_t)2 * n * sizeof(float)) != hipSuccess)
     return fail(PF_ENOMEM, "Newton workspace allocation failed (restart %d)", m);
   c->kry_m = m;
