@@ -198,3 +198,28 @@ def test_transfers_match_dense_rows(pf, p, n, levels):
         err = float(torch.linalg.norm(ctx.restrict(l, y).double() - ref) / torch.linalg.norm(ref))
         assert err <= 3e-6, ("restrict", l, err)
         ne = nc
+
+
+@pytest.mark.parametrize("p", [2, 3, 4])
+@pytest.mark.parametrize("stretch", [0.0, 0.25, 0.6, 1.5])
+def test_level_apply_at_large_strain_differences(pf, p, stretch):
+    """The FP32 record forms the off-diagonal tangent factors from the differences of the principal
+    log strains, by a series up to 1/2 and by exponentials above: differences about 0, on both sides
+    of the limit and up to 1.3. Bar of the FP32 applies: 1e-5 of FP64."""
+    d = I.make_inputs("C1", "base", p=p, n=3)
+    m = d["mesh"]
+    gll = np.asarray(I.gll_points(p))
+    x = I._coords_1d(m.nx, p, m.lx, gll)
+    z = np.array(d["z"], copy=True)
+    n1 = len(x)
+    z[0] += stretch * np.tile(x, n1 * n1)
+    z[1] -= 0.25 * stretch * np.tile(np.repeat(x, n1), n1)
+    z = torch.as_tensor(z).to("cuda", torch.float64)
+    ctx = pf.Context.from_inputs(d)
+    ctx.linearize(z)
+    ctx.check()
+    torch.manual_seed(4)
+    v = torch.randn(4, m.n_nodes, device="cuda")
+    y, ref = ctx.apply_jacobian_f32(0, v).double(), ctx.apply_jacobian(z, v.double())
+    err = float(torch.linalg.norm(y - ref) / torch.linalg.norm(ref))
+    assert err <= 1e-5, err
