@@ -424,13 +424,15 @@ using A32Args = LinApplyArgs<float>;
 // read back (a Chebyshev step on n entries moves 28 n bytes beside the apply instead of 40 n, in
 // one launch less, and the Dirichlet mask needs no launch of its own). Order 4 on 40^3 elements:
 // gather 77 us and step up to 94 us -> 102 us in one launch, the Newton step on the order-3 32^3 mesh
-// 70.0 -> 60.7 ms.
+// 70.0 -> 60.7 ms. The last step of a smoother stores x alone: 80 us.
 // ---------------------------------------------------------------------------
 enum EpiOp {
   E_STORE,  // out = v
   E_RESID,  // r = b - v
   E_FIRST,  // r = b - v, d = c dinv r (the Chebyshev start; x takes d in the first step)
   E_STEP,   // r = r_in - v, d = a d_in + c dinv r, x = x_in + [d_in] + d
+  E_LAST,   // the same where r and d are not needed after it
+  E_SCALE,  // out = dinv v inv[0]
   E_POWER   // out = dinv v inv[0], and the sum of its squares
 };
 
@@ -439,7 +441,7 @@ template <typename T> struct Epilogue {
   const T *b, *r_in, *d_in, *x_in, *dinv;  // x_in null: x starts from zero
   T a, c;
   int x_first;          // E_STEP: the first one, x takes d_in too
-  const float* inv;     // E_POWER: 1 / norm of the vector applied
+  const float* inv;     // E_SCALE, E_POWER: 1 / norm of the vector applied, or null
   double* part;         // E_POWER: one partial sum per workgroup
   DirMask dir;          // constrained entries: v = 0
   int has_dir, nz1;
@@ -453,12 +455,12 @@ template <int OP, typename T>
 __device__ inline EpiIn<T> epi_load(const Epilogue<T>& e, int64_t i) {
   EpiIn<T> v{T(0), T(0), T(0), T(0)};
   if (OP == E_RESID || OP == E_FIRST) v.r = e.b[i];
-  if (OP == E_STEP) {
+  if (OP == E_STEP || OP == E_LAST) {
     v.r = e.r_in[i];
     v.d = e.d_in[i];
     if (e.x_in) v.x = e.x_in[i];
   }
-  if (OP == E_FIRST || OP == E_STEP || OP == E_POWER) v.dinv = e.dinv[i];
+  if (OP != E_STORE && OP != E_RESID) v.dinv = e.dinv[i];
   return v;
 }
 
@@ -473,13 +475,15 @@ __device__ inline T epi_apply(const Epilogue<T>& e, const EpiIn<T>& in, int64_t 
     const T r = in.r - v;
     e.r[i] = r;
     e.d[i] = e.c * in.dinv * r;
-  } else if (OP == E_STEP) {
+  } else if (OP == E_STEP || OP == E_LAST) {
     const T r = in.r - v, d = e.a * in.d + e.c * in.dinv * r;
-    e.r[i] = r;
-    e.d[i] = d;
+    if (OP == E_STEP) {
+      e.r[i] = r;
+      e.d[i] = d;
+    }
     e.x[i] = (e.x_first ? in.x + in.d : in.x) + d;
   } else {
-    const T y = (in.dinv * v) * (T)e.inv[0];
+    const T y = e.inv ? (in.dinv * v) * (T)e.inv[0] : in.dinv * v;
     e.out[i] = y;
     return y;
   }
@@ -643,23 +647,6 @@ static __global__ void k_cheb_start(const float* __restrict__ b, const float* __
 static __global__ void k_vec_inv(const float* __restrict__ a, float* __restrict__ b, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     b[i] = a[i] != 0.f ? 1.f / a[i] : 0.f;
-}
-
-// double-precision sum of squares, per-block partials (deterministic)
-static __global__ void k_sumsq(const float* __restrict__ x, int64_t n, double* __restrict__ part) {
-  __shared__ double red[NT];
-  double s = 0.0;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const double v = x[i];
-    s += v * v;
-  }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int st = NT / 2; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
 // FP64 -> FP32 copy
