@@ -419,9 +419,7 @@ pf_status ebe_assemble(pf_ctx* c, hipStream_t s) {
   }
   if (st) return st;
   const MGLevel& L = c->mg.lv[c->mg.ebe_level];
-  const int64_t nall = 27 * L.n_nodes;
-  const int nb = (int)std::min<int64_t>((nall + NT - 1) / NT, 65536);
-  hipLaunchKernelGGL(k_stencil_from_ebe, dim3(nb), dim3(NT), 0, s, c->mg.ebe, c->mesh.nx, c->mesh.ny, c->mesh.nz,
+  hipLaunchKernelGGL(k_stencil_from_ebe, dim3((unsigned)((L.n_nodes + 63) / 64), 4), dim3(NT), 0, s, c->mg.ebe, c->mesh.nx, c->mesh.ny, c->mesh.nz,
                      L.n_nodes, c->mg.stencil);
   HIPCHK(hipGetLastError());
   return PF_OK;
