@@ -448,9 +448,8 @@ pf_status build_h_levels(pf_ctx* c, hipStream_t s) {
     if (L.h == 0) continue;
     const MGLevel& F = mg.lv[l - 1];
     const float* Sf = F.h > 0 ? F.S : mg.stencil;
-    const int64_t nall = 27 * 16 * L.n_nodes;
-    const int nb = (int)std::min<int64_t>((nall + NT - 1) / NT, 65536);
-    hipLaunchKernelGGL(k_stencil_rap, dim3(nb), dim3(NT), 0, s, Sf, F.nx1, F.ny1, F.nz1, L.S, L.nx1, L.ny1, L.nz1);
+    const int nb = (int)std::min<int64_t>((L.n_nodes + NT - 1) / NT, 65536);
+    hipLaunchKernelGGL(k_stencil_rap, dim3(nb, 27, 4), dim3(NT), 0, s, Sf, F.nx1, F.ny1, F.nz1, L.S, L.nx1, L.ny1, L.nz1);
     HIPCHK(hipGetLastError());
   }
   return PF_OK;
