@@ -19,7 +19,6 @@ namespace pfmf {
 
 struct EbeArgs {
   MeshDev m;
-  LevelDev fine;        // fine level (kinematics)
   int64_t n_q;
   const float* frame;   // F^-1 N of the block (see MGState)
   RecordSoA rec;

@@ -370,8 +370,6 @@ pf_status launch_lin_q4(pf_ctx* c, const LinApplyArgs<V>& a, const Epilogue<V>& 
 EbeArgs ebe_args(pf_ctx* c) {
   EbeArgs a;
   a.m = mesh_dev(c);
-  const MGLevel& F = c->mg.lv[0];
-  a.fine = LevelDev{F.P, F.nx1, F.ny1, F.n_nodes};
   a.n_q = c->n_q;
   a.frame = c->mg.frame;
   a.rec = c->mg.rec;

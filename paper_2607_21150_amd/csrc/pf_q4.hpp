@@ -833,8 +833,11 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2r(LinApplyArgs<V> a, const type
 // tasks spread over the workgroup through LDS (no contraction padded from 3 to 4 points).
 // Brick sums to the brick buffer (store_brick4), then k_gather_ext<double, 5>; the
 // adjoint's per-phase parameter partials are summed per brick in a fixed order.
+// Waves per SIMD: the residual's 144 registers make 3, forced to 128 (16 spilled) it runs 4, which the
+// 36 KB of LDS allow: 211 -> 196 us on 48^3 elements. The adjoint's 172 make 2, at 168 (8 spilled) it runs
+// 3: 438 -> 346 us. The Jacobian takes 158.
 template <int MODE, bool VOCE>
-__global__ __launch_bounds__(NT, 2) void k_op64_q2r(OpArgs a, DevTables* __restrict__ tabs) {
+__global__ __launch_bounds__(NT, MODE == M_RES ? 4 : 3) void k_op64_q2r(OpArgs a, DevTables* __restrict__ tabs) {
   constexpr int P = 3, Q = 3, Q3 = 27, NE = 8;
   static_assert(NE * 32 == NT, "eight elements of 32 threads");
   using L = Q5Lds<P, Q, true>;
@@ -865,10 +868,12 @@ __global__ __launch_bounds__(NT, 2) void k_op64_q2r(OpArgs a, DevTables* __restr
   const int pid = pt ? a.phase[gq] : 0;
   const double ih[3] = {a.m.ih[0], a.m.ih[1], a.m.ih[2]};
   const double wdet = tabs->w[Q][qx] * tabs->w[Q][qy] * tabs->w[Q][qz] * a.m.jdet;
-  if (gn >= 0) {
+  // a slot without an element takes the undeformed state: on whatever was in LDS the point function
+  // would run its longest path and the wave wait (17^3 elements: adjoint 79 us against 36.5)
+  if (n < Q3) {
     double v[4];
 #pragma unroll
-    for (int f = 0; f < 4; ++f) v[f] = a.z[f * a.n_nodes + gn];
+    for (int f = 0; f < 4; ++f) v[f] = ein ? a.z[f * a.n_nodes + gn] : 0.0;
 #pragma unroll
     for (int f = 0; f < 4; ++f) A[f * Q3 + n] = v[f];
   }
@@ -878,7 +883,8 @@ __global__ __launch_bounds__(NT, 2) void k_op64_q2r(OpArgs a, DevTables* __restr
 #pragma unroll
   for (int f = 0; f < 4; ++f)
 #pragma unroll
-    for (int J = 0; J < 3; ++J) (f < 3 ? G + 3 * f : gphi)[J] = B[qslot<true>(f, 1 + J) * Q3 + ql] * ih[J];
+    for (int J = 0; J < 3; ++J)
+      (f < 3 ? G + 3 * f : gphi)[J] = B[qslot<true>(f, 1 + J) * Q3 + ql] * ih[J];
   phi = B[qslot<true>(3, 0) * Q3 + ql];
   double phin = 0.0;
   __syncthreads();
