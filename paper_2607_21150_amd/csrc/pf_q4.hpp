@@ -420,7 +420,7 @@ template <int P, int Q, bool CV = false> struct Q5Lds {
 // GEO): table restriction, element e = workgroup (XCD-aware order), nodes from a.conn,
 // the element vector stored node-major to a.evec (summed per node by k_gather_csr).
 template <int MODE, bool VOCE, bool MB, bool GEO, bool EV = false, bool TAB = false>
-__global__ __launch_bounds__(NT5, MB || GEO ? 2 : 3) void k_op64_q4(OpArgs a, int colour, DevTables* __restrict__ tabs) {
+__global__ __launch_bounds__(NT5, MB || (GEO && MODE == M_ADJ) ? 2 : 3) void k_op64_q4(OpArgs a, int colour, DevTables* __restrict__ tabs) {
   static_assert(!TAB || (GEO && !MB), "the table restriction runs on mapped elements without branches");
   constexpr int P = 5, Q = 5, Q3 = 125;
   // compact point arrays (13 of 125 values each): 25 KB of LDS per element instead of 28,

@@ -90,47 +90,171 @@ __device__ inline void log_series(double J2, double J3, TState& s) {
   }
 }
 
-// The same for any positive definite I + S, I2 = 3 - J2 > 0 and I3 = det(I + S) > 0 given:
-// f(s) = (1/2) int_0^1 s / (1 + t s) dt, so with D(t) = det(I + t S) the sums are integrals of
-// (1, -t) / D and (t^2, -t^3, t^4) / D^2, taken by 12-point Gauss rules on panels that halve
-// towards t = 1, the last one no longer than the distance of the pole beyond it (the error of
-// the rule is then below 1e-17). D in powers of t and 1 - t has positive terms only. About 20
-// instructions per node, 12 nodes up to |s_i| = 0.5 and 12 more for every halving of the
-// smallest 1 + s_i: at most the cost of a principal frame up to stretches of 2 : 1.
+// The same for any positive definite I + S, I2 = 3 - J2 > 0 and I3 = det(I + S) > 0 given. As
+// log x is an integral of 1 / (1 + T) - 1 / (x + T), the coefficients are moments over T > 0,
+//     c1 = (1/2) int (1 + T) / D,  c2 = -(1/2) int T / D,
+//     g3 = (1/2) int (1 + T)^2 T^2 / D^2,  g4 = -(1/2) int (1 + T) T^3 / D^2,
+//     g5 = (1/2) int T^4 / D^2,     D(T) = det(I + T (I + S)) = 1 + 3 T + I2 T^2 + I3 T^3,
+// all of one sign. With the eigenvalues in [l, u] and T = t / sqrt(l u) the integrand depends on
+// the ratio u / l alone, for which a rule of n nodes is enough up to a limit: Gauss-Legendre nodes
+// v mapped by t / (1 + t) = (1 + tanh(c v) / tanh(c)) / 2, c (0.096, 0.355, 0.683, 1.207, 1.673) chosen
+// per rule for the widest range in which the moments of D^-2 are exact to 1.5e-16 over all triples
+// of eigenvalues. The moments of D^-1 (all that the residual takes) converge faster and have wider
+// limits, to 2e-17; the tangent takes them from those of D^-2, by the integrals of (T / D)' and
+// (T^2 / D)'. A rule is symmetric under t -> 1 / t: half of its nodes {t, weight} are listed.
+constexpr int LOG_RULES = 5;
+constexpr int LOG_FIRST[LOG_RULES + 1] = {0, 4, 10, 18, 30, 46};  // node pairs of a rule: 8, 12, 16, 24, 32 nodes
+constexpr float LOG_RATIO[2][LOG_RULES] = {{1.72f, 5.4f, 21.9f, 245.f, 2180.f}, {1.45f, 4.2f, 16.f, 155.f, 1250.f}};
+constexpr double LOG_HALF[LOG_FIRST[LOG_RULES]][2] = {
+    {0.020138255037087625, 0.026194290990111748},
+    {0.11262061675326468, 0.068631810355546441},
+    {0.31001587292394411, 0.1346614192413006},
+    {0.68921944851820094, 0.25943998725634648},
+    {0.0085801794734985393, 0.011094388123626248},
+    {0.046724746578257009, 0.02757252205050631},
+    {0.12196543372248697, 0.048742857328326138},
+    {0.24760474821808001, 0.078873258746406619},
+    {0.44823409766569228, 0.12538109951720797},
+    {0.76934045848401589, 0.20271518284789292},
+    {0.0039837365284311017, 0.0051449781680020573},
+    {0.021580838737189138, 0.012653711885053317},
+    {0.055761410978053615, 0.021919730069819433},
+    {0.11133128832960038, 0.034312758758648754},
+    {0.19639815617166972, 0.051818402015395872},
+    {0.3240045946317136, 0.077483291115063205},
+    {0.51497953928343465, 0.11623031597206854},
+    {0.80311204340820996, 0.17647310117814724},
+    {0.0010539063871771242, 0.0013592389093590852},
+    {0.0056755085344818799, 0.0033042116564926021},
+    {0.014508587549275018, 0.0056082977409746028},
+    {0.028521034340004813, 0.0085339071464631093},
+    {0.049292778730376657, 0.012437077600069967},
+    {0.07924964199509639, 0.017817795215835586},
+    {0.12201967756557056, 0.025392550189777496},
+    {0.18296259353024077, 0.036196664998377134},
+    {0.26994438624939032, 0.051729979807706973},
+    {0.39446411585716096, 0.074168108560173113},
+    {0.57330003875899016, 0.10667963281595669},
+    {0.83095723934735877, 0.15392875119826072},
+    {0.00032437570271627521, 0.0004179485900133064},
+    {0.0017396178062583591, 0.0010077492945685673},
+    {0.0044141370533642829, 0.0016862601896185246},
+    {0.0085850190398862984, 0.0025159539434861707},
+    {0.014633079476964949, 0.0035793332063693071},
+    {0.02313240282327499, 0.0049892846701197766},
+    {0.034925461200309961, 0.0069043034428476983},
+    {0.051234607367938452, 0.0095500114878653997},
+    {0.07382500316861039, 0.013249574111753834},
+    {0.10524005999030583, 0.018466441295668542},
+    {0.14913824556346861, 0.025863788477475346},
+    {0.21076993860200688, 0.036386142154583558},
+    {0.29764531999690569, 0.051370086030583802},
+    {0.42046005948396731, 0.072693119112912305},
+    {0.59436735518174, 0.10297388358530327},
+    {0.84071897169437415, 0.14584573103004089},
+};
+// A pair of nodes t and 1 / t, each with its weight times t^0, ..., t^4.
+struct LogPair {
+  double t[2], w[2][5];
+};
+struct LogPairs {
+  LogPair p[LOG_FIRST[LOG_RULES]];
+};
+constexpr LogPairs log_pairs() {
+  LogPairs r{};
+  for (int k = 0; k < LOG_FIRST[LOG_RULES]; ++k)
+    for (int h = 0; h < 2; ++h) {
+      const double t = LOG_HALF[k][0];
+      r.p[k].t[h] = h ? 1.0 / t : t;
+      double w = h ? LOG_HALF[k][1] / (t * t) : LOG_HALF[k][1];
+      for (int j = 0; j < 5; ++j, w *= r.p[k].t[h]) r.p[k].w[h][j] = w;
+    }
+  return r;
+}
+
+// Bounds of the eigenvalues from the invariants by a step of Laguerre's iteration from 0 and from
+// infinity, which stays outside the roots of a cubic with real roots (l is at least 3/4 of the smallest).
+// The wave takes one rule, the shortest that serves all its lanes here, so that its nodes are in scalar
+// registers: 24 vector instructions per pair of nodes with the tangent, 18 without. Order-3 Jacobian on 24^3
+// elements (0.061 ms at strains of 1 %) at isochoric stretches of 1.5, 2, 3 and 5: 0.060, 0.060, 0.064 and
+// 0.068 ms; with a principal frame 0.072 to 0.073, and with 12 Gauss nodes in t / (1 + t) on panels that
+// halve towards 1 (one per factor 2 of a loose lower bound) 0.083, 0.104, 0.135 and 0.178.
 template <bool TAN>
 __device__ inline void log_quadrature(double I2, double I3, TState& s) {
-  constexpr int NG = 12;
-  static constexpr double xg[NG] = {0.009219682876640375, 0.04794137181476257, 0.11504866290284765, 0.2063410228566913,
-                                    0.3160842505009099,   0.43738329574426554, 0.5626167042557345,  0.6839157494990901,
-                                    0.7936589771433087,   0.8849513370971523,  0.9520586281852375,  0.9907803171233597};
-  static constexpr double wg[NG] = {0.023587668193255914, 0.05346966299765921, 0.08003916427167311, 0.10158371336153296,
-                                    0.1167462682691774,   0.12457352290670139, 0.12457352290670139, 0.1167462682691774,
-                                    0.10158371336153296,  0.08003916427167311, 0.05346966299765921, 0.023587668193255914};
-  // a lower bound of the smallest eigenvalue: the other two have at most the mean (3 - l) / 2,
-  // and |s_i| <= 2 sqrt(J2 / 3)
-  const double J = (kst(3.0) - I2) * kst(1.0 / 3.0);
-  const double lam = fmax(kst(4.0 / 9.0) * I3, 1.0 - 2.0 * J * frsqrt(J));
-  double t0 = 0.0, h = 1.0, c1 = 0.0, c2 = 0.0, g3 = 0.0, g4 = 0.0, g5 = 0.0;
-  for (int panel = 0; panel < 64; ++panel) {
-    const bool last = h * (1.0 - lam) <= lam || panel == 63;
-    const double hp = last ? h : 0.5 * h;
+  const float i2 = (float)I2, i3 = (float)I3;
+  const float il = (i2 + 2.f * __builtin_amdgcn_sqrtf(fmaxf(i2 * i2 - 9.f * i3, 0.f))) * frcp(3.f * i3);
+  const float u = 1.f + 2.f * __builtin_amdgcn_sqrtf(fmaxf(1.f - i2 * (1.f / 3.f), 0.f)), ratio = u * il;
+  double c1 = 0.0, c2 = 0.0, g3 = 0.0, g4 = 0.0, g5 = 0.0;
+  if (ratio <= LOG_RATIO[TAN][LOG_RULES - 1]) {
+    static constexpr LogPairs pairs = log_pairs();
+    int rule = 0;
+    while (rule < LOG_RULES - 1 && __ballot(ratio > LOG_RATIO[TAN][rule])) ++rule;  // uniform
+    const double ia = (double)frsqrt(u * frcp(il)), ia2 = ia * ia;
+    const double a1 = 3.0 * ia, a2 = I2 * ia2, a3 = I3 * ia2 * ia;  // D = 1 + a1 t + a2 t^2 + a3 t^3
+    double m0 = 0.0, m1 = 0.0, m2 = 0.0, m3 = 0.0;  // moments t^k / D, or t^(k + 1) / D^2 with TAN
 #pragma unroll 1
-    for (int k = 0; k < NG; ++k) {
-      const double t = fma(hp, xg[k], t0), r = 1.0 - t;
-      const double iD = frcp(fma(t * t, fma(t, I3, r * I2), r * r * fma(2.0, t, 1.0)));
-      const double w = 0.5 * hp * wg[k] * iD, wt = w * t;
-      c1 += w;
-      c2 -= wt;
+    for (int k = LOG_FIRST[rule]; k < LOG_FIRST[rule + 1]; ++k) {
+      const LogPair& p = pairs.p[k];
+      const double d0 = fma(p.t[0], fma(p.t[0], fma(p.t[0], a3, a2), a1), 1.0);
+      const double d1 = fma(p.t[1], fma(p.t[1], fma(p.t[1], a3, a2), a1), 1.0);
+      const double r = frcp(d0 * d1);
+      const double i0 = r * d1, i1 = r * d0;
       if (TAN) {
-        const double u = wt * t * iD, ut = u * t;
-        g3 += u;
-        g4 -= ut;
-        g5 = fma(ut, t, g5);
+        const double q0 = i0 * i0, q1 = i1 * i1;
+        m0 = fma(p.w[1][1], q1, fma(p.w[0][1], q0, m0));
+        m1 = fma(p.w[1][2], q1, fma(p.w[0][2], q0, m1));
+        m2 = fma(p.w[1][3], q1, fma(p.w[0][3], q0, m2));
+        m3 = fma(p.w[1][4], q1, fma(p.w[0][4], q0, m3));
+      } else {
+        m0 = fma(p.w[1][0], i1, fma(p.w[0][0], i0, m0));
+        m1 = fma(p.w[1][1], i1, fma(p.w[0][1], i0, m1));
       }
     }
-    if (last) break;
-    t0 += hp;
-    h = hp;
+    if (TAN) {
+      const double ia3 = ia2 * ia;
+      g3 = ia3 * fma(ia, fma(ia, m3, 2.0 * m2), m1);
+      g4 = -ia3 * ia * fma(ia, m3, m2);
+      g5 = ia3 * ia2 * m3;
+      m0 = fma(a1, m0, fma(2.0 * a2, m1, 3.0 * a3 * m2));
+      m1 = 0.5 * fma(a1, m1, fma(2.0 * a2, m2, 3.0 * a3 * m3));
+    }
+    c1 = ia * fma(ia, m1, m0);
+    c2 = -ia2 * m1;
+  } else {
+    // wider still: c1 = int 1 / (2 D), c2 = -int t / (2 D), ... over t in [0, 1] with D = det(I + t S),
+    // 12 nodes on panels that halve towards t = 1, the last one no longer than the distance of the
+    // pole beyond it (the error of the rule is then below 1e-17); D in powers of t and 1 - t
+    constexpr int NG = 12;
+    static constexpr double xg[NG / 2] = {0.009219682876640375, 0.04794137181476257, 0.11504866290284765,
+                                          0.2063410228566913,   0.3160842505009099,  0.43738329574426554};
+    static constexpr double wg[NG / 2] = {0.023587668193255914, 0.05346966299765921, 0.08003916427167311,
+                                          0.10158371336153296,  0.1167462682691774,  0.12457352290670139};
+    // l with a margin for its rounding, or where FP32 does not reach it, that the other two have at
+    // most the mean (3 - l) / 2
+    const double lam = fmax(kst(4.0 / 9.0) * I3, (double)(0.999f * frcp(il)));
+    double t0 = 0.0, h = 1.0;
+    for (int panel = 0; panel < 64; ++panel) {
+      const bool last = h * (1.0 - lam) <= lam || panel == 63;
+      const double hp = last ? h : 0.5 * h;
+#pragma unroll 1
+      for (int k = 0; k < NG; ++k) {
+        const double x = k < NG / 2 ? xg[k] : 1.0 - xg[NG - 1 - k], wk = wg[k < NG / 2 ? k : NG - 1 - k];
+        const double t = fma(hp, x, t0), r = 1.0 - t;
+        const double iD = frcp(fma(t * t, fma(t, I3, r * I2), r * r * fma(2.0, t, 1.0)));
+        const double w = 0.5 * hp * wk * iD, wt = w * t;
+        c1 += w;
+        c2 -= wt;
+        if (TAN) {
+          const double v = wt * t * iD, vt = v * t;
+          g3 += v;
+          g4 -= vt;
+          g5 = fma(vt, t, g5);
+        }
+      }
+      if (last) break;
+      t0 += hp;
+      h = hp;
+    }
   }
   s.c1 = c1;
   s.c2 = c2;
@@ -211,8 +335,8 @@ __device__ inline void mul33t(const double* A, const double* B, double* M) {
 }
 
 // log(x) / 2 for x > 0 (not a number otherwise): x = 2^n y, y in [sqrt(1/2), sqrt(2)), and
-// 2 atanh((y - 1) / (y + 1)) by its series, whose coefficients are formed in the loop. For the
-// points whose volume changes by more than a quarter; no constants for the common path to hold.
+// 2 atanh((y - 1) / (y + 1)) by 12 terms of its series (squared argument up to 0.0295, truncation
+// below 1e-18). For the points whose volume changes by more than a quarter.
 __device__ inline double half_log(double x) {
   double y = __builtin_amdgcn_frexp_mant(x);
   int n = __builtin_amdgcn_frexp_exp(x);
@@ -221,10 +345,11 @@ __device__ inline double half_log(double x) {
     --n;
   }
   const double z = (y - 1.0) * frcp(y + 1.0), z2 = z * z;
-  double r = 0.0;
-#pragma unroll 1
-  for (int k = 12; k >= 0; --k) r = fma(r, z2, frcp((double)(2 * k + 1)));
-  r = fma(z, r, (double)n * kst(0.34657359027997265471));
+  double r = kst(1.0 / 23.0);
+#pragma unroll
+  for (int k = 10; k >= 1; --k) r = fma(r, z2, kst(1.0 / (2 * k + 1)));
+  r = fma(z * z2, r, z);
+  r = fma((double)n, kst(0.34657359027997265471), r);
   return x > 0.0 ? r : __builtin_nan("");
 }
 
