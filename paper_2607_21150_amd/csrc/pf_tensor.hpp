@@ -2,18 +2,23 @@
 // mapping, tangent and its transpose without a principal frame.
 //
 // With b_tr = m (I + S), m = tr b_tr / 3 and S traceless, the deviatoric trial log strain
-// is an isotropic function of S,
-//     e = c1 S + c2 Q,    Q = S^2 - (2/3) J2 I,   J2 = tr S^2 / 2,   J3 = det S,
-// whose coefficients depend on (J2, J3) only. For f(s) = log(1 + s) / 2 = sum_n f_n s^n
-// the Cayley-Hamilton theorem gives S^n = h_{n-2} S^2 + h_{n-1} S + ..., h_n = J2 h_{n-2} +
-// J3 h_{n-3}, so c1 = sum f_n h_{n-1} and c2 = sum f_n h_{n-2}; their derivatives
-//     g3 = dc1/dJ2,   g4 = dc1/dJ3 = dc2/dJ2,   g5 = dc2/dJ3
-// are the same sums over the coefficients of 1 / (1 - J2 t^2 - J3 t^3)^2. Nothing is divided
-// by a difference of eigenvalues, so repeated eigenvalues need no case of their own, and the
-// strain's derivative (Appendices A-B) is
-//     de = c1 dS + c2 dev(S dS + dS S) + (g3 dJ2 + g4 dJ3) S + (g4 dJ2 + g5 dJ3) Q,
-// dJ2 = S:dS, dJ3 = Q:dS, a self-adjoint map of dS (the transpose uses it again). The products
-// of e come from the invariants as well: S:S = 2 J2, S:Q = 3 J3, Q:Q = (2/3) J2^2.
+// is an isotropic function of S. As log x is an integral of 1 / (1 + T) - 1 / (x + T) over T > 0,
+//     e = p0 S - p1 M,    M = dev K,    K = adj(I + S),
+//     p0 = (1/2) int 1 / D,   p1 = (1/2) int T / D,   n_k = (1/2) int T^k / D^2  (k = 2, 3, 4),
+//     D(T) = det(I + T (I + S)) = 1 + 3 T + I2 T^2 + I3 T^3,
+// moments of one sign that depend on the invariants I2 = 3 - J2 and I3 = 1 - J2 + J3 of I + S only (J2 =
+// tr S^2 / 2, J3 = det S). Nothing is divided by a difference of eigenvalues, so repeated eigenvalues
+// need no case of their own. With dK = S dS + dS S - dS up to a multiple of I and D's derivatives,
+// the strain's derivative (Appendices A-B) is
+//     de = (p0 + p1) dS - p1 dev(S dS + dS S) + (n2 a - n3 b) S + (n4 b - n3 a) M,
+// a = S:dS, b = M:dS, a self-adjoint map of dS (the transpose uses it again). The products of e come from
+// S:S = 2 J2, S:M = 3 J3 - 2 J2 = 3 I3 - I2 and M:M = (2/3) I2^2 - 6 I3, and M S = -M - (I2 / 3) S + ... I.
+//
+// S resolves the large eigenvalues and M the small ones, and their terms don't cancel; with S and
+// dev S^2 = M + S instead, coefficients that grow as 1 / x to 1 / x^3 cancel where two eigenvalues of I + S are of
+// the order of x, at the ratio of the eigenvalues squared times the rounding: the Jacobian was off by 4e-11 at
+// an isochoric stretch of 9 and by 6e-9 at 20, now by 3e-14 and 3e-13 (2e-14 to 4e-13 with a principal frame,
+// by the orientation of the stretch).
 //
 // The FP64 applies are bound by VALU issue. The principal form (eigenvalues, an orthonormal
 // frame with polish rotations, three logarithms, divided differences, the tangent rotated
@@ -34,9 +39,9 @@ namespace pfmf {
 // {xx, yy, zz, yz, xz, xy}.
 struct TState {
   double Fi[9];               // F^-1
-  double S[6], Q[6];          // b_tr / m - I and dev(S^2)
-  double J2, J3;              // invariants of S
-  double c1, c2, g3, g4, g5;  // log coefficients and their derivatives
+  double S[6], M[6];          // b_tr / m - I and dev adj(b_tr / m)
+  double ss, sm, mm;          // S:S, S:M, M:M
+  double p0, p1, n2, n3, n4;  // moments of the header comment
   double ee, theta;           // e:e and tr eps
   double g, gp, c, kq, kphi;  // degradation, return factor and its tangent (as in QPState)
   double psi, H, L, dLcoef, ddg_s0, ddg_visc, dg;
@@ -47,7 +52,10 @@ struct TState {
 // of their mean): the coefficients are sums of 13 terms there, 46 multiply-adds in all.
 constexpr double LOG_SERIES_J2 = 0.0075;
 
-// c1, c2 (and, with TAN, g3, g4, g5) of log(1 + s) / 2 for J2 <= LOG_SERIES_J2: f' = 1 / (2 (1 + s))
+// The moments for J2 <= LOG_SERIES_J2. With f(s) = log(1 + s) / 2 = sum_n f_n s^n, the Cayley-Hamilton theorem
+// (S^n = h_{n-2} S^2 + h_{n-1} S + ..., h_n = J2 h_{n-2} + J3 h_{n-3}) gives e = c1 S + c2 dev S^2 with c1 = sum f_n
+// h_{n-1} = p0 + p1 and c2 = sum f_n h_{n-2} = -p1, and the derivatives g3 = dc1/dJ2 = n2 + 2 n3 + n4, g4 = dc1/dJ3 =
+// dc2/dJ2 = -(n3 + n4) and g5 = dc2/dJ3 = n4. f' = 1 / (2 (1 + s)) is
 // interpolated at 13 Chebyshev nodes of [-0.1, 0.1] and integrated (relative error of f and of
 // f' below 4e-17), summed downwards: b_k = sum_n f_n h_{n-k} and q_k = sum_n f_n d_{n-k}, h_n and
 // d_n the coefficients of 1 / (1 - J2 t^2 - J3 t^3) and of its square.
@@ -81,30 +89,30 @@ __device__ inline void log_series(double J2, double J3, TState& s) {
       if (k + 3 <= N) q[k] = fma(J3, q[k + 3], q[k]);
     }
   }
-  s.c1 = b[1];
-  s.c2 = b[2];
+  s.p0 = b[1] + b[2];
+  s.p1 = -b[2];
   if (TAN) {
-    s.g3 = q[3];
-    s.g4 = q[4];
-    s.g5 = q[5];
+    s.n2 = q[3] + 2.0 * q[4] + q[5];
+    s.n3 = -(q[4] + q[5]);
+    s.n4 = q[5];
   }
 }
 
-// The same for any positive definite I + S, I2 = 3 - J2 > 0 and I3 = det(I + S) > 0 given. As
-// log x is an integral of 1 / (1 + T) - 1 / (x + T), the coefficients are moments over T > 0,
-//     c1 = (1/2) int (1 + T) / D,  c2 = -(1/2) int T / D,
-//     g3 = (1/2) int (1 + T)^2 T^2 / D^2,  g4 = -(1/2) int (1 + T) T^3 / D^2,
-//     g5 = (1/2) int T^4 / D^2,     D(T) = det(I + T (I + S)) = 1 + 3 T + I2 T^2 + I3 T^3,
-// all of one sign. With the eigenvalues in [l, u] and T = t / sqrt(l u) the integrand depends on
+// The same for any positive definite I + S, I2 and I3 given.
+// With the eigenvalues in [l, u] and T = t / sqrt(l u) the integrands depend on
 // the ratio u / l alone, for which a rule of n nodes is enough up to a limit: Gauss-Legendre nodes
-// v mapped by t / (1 + t) = (1 + tanh(c v) / tanh(c)) / 2, c (0.096, 0.355, 0.683, 1.207, 1.673) chosen
+// v mapped by t / (1 + t) = (1 + tanh(c v) / tanh(c)) / 2, c (0.096, 0.355, 0.683, 0.947, 1.207, 1.673) chosen
 // per rule for the widest range in which the moments of D^-2 are exact to 1.5e-16 over all triples
 // of eigenvalues. The moments of D^-1 (all that the residual takes) converge faster and have wider
 // limits, to 2e-17; the tangent takes them from those of D^-2, by the integrals of (T / D)' and
 // (T^2 / D)'. A rule is symmetric under t -> 1 / t: half of its nodes {t, weight} are listed.
-constexpr int LOG_RULES = 5;
-constexpr int LOG_FIRST[LOG_RULES + 1] = {0, 4, 10, 18, 30, 46};  // node pairs of a rule: 8, 12, 16, 24, 32 nodes
-constexpr float LOG_RATIO[2][LOG_RULES] = {{1.72f, 5.4f, 21.9f, 245.f, 2180.f}, {1.45f, 4.2f, 16.f, 155.f, 1250.f}};
+constexpr int LOG_RULES = 6;
+constexpr int LOG_FIRST[LOG_RULES + 1] = {0, 4, 10, 18, 28, 40, 56};  // node pairs of a rule: 8, 12, 16, 20, 24, 32 nodes
+constexpr float LOG_RATIO[2][LOG_RULES] = {{1.72f, 5.4f, 21.9f, 74.f, 245.f, 2180.f},
+                                           {1.45f, 4.2f, 16.f, 53.f, 155.f, 1250.f}};
+// Ratio beyond which K is taken from F^-1 and I + D: adj(I + S) from S holds K's small entries with the rounding
+// of its large terms, which p1 multiplies by the ratio.
+constexpr float LOG_WIDE = 4.2f;
 constexpr double LOG_HALF[LOG_FIRST[LOG_RULES]][2] = {
     {0.020138255037087625, 0.026194290990111748},
     {0.11262061675326468, 0.068631810355546441},
@@ -124,6 +132,16 @@ constexpr double LOG_HALF[LOG_FIRST[LOG_RULES]][2] = {
     {0.3240045946317136, 0.077483291115063205},
     {0.51497953928343465, 0.11623031597206854},
     {0.80311204340820996, 0.17647310117814724},
+    {0.0020173360113880105, 0.0026032502760562461},
+    {0.010889950058838437, 0.0063582924339478063},
+    {0.027958590317377068, 0.010880634648877729},
+    {0.055300289937880713, 0.016741651505975882},
+    {0.096335153581969285, 0.024728649914141598},
+    {0.15637114777502886, 0.035967074411776198},
+    {0.24345216595420965, 0.052104796077011059},
+    {0.36966563675320629, 0.075596627074520695},
+    {0.55318213433546937, 0.11017080684629943},
+    {0.82154155346127311, 0.16164993502753211},
     {0.0010539063871771242, 0.0013592389093590852},
     {0.0056755085344818799, 0.0033042116564926021},
     {0.014508587549275018, 0.0056082977409746028},
@@ -172,24 +190,35 @@ constexpr LogPairs log_pairs() {
   return r;
 }
 
-// Bounds of the eigenvalues from the invariants by a step of Laguerre's iteration from 0 and from
-// infinity, which stays outside the roots of a cubic with real roots (l is at least 3/4 of the smallest).
+// Bounds u and 1 / l of the eigenvalues from the invariants by a step of Laguerre's iteration from infinity
+// and from 0, which stays outside the roots of a cubic with real roots (l is at least 3/4 of the smallest).
+struct LogBounds {
+  float u, il;
+};
+__device__ inline LogBounds log_bounds(double I2, double I3) {
+  const float i2 = (float)I2, i3 = (float)I3;
+  return LogBounds{1.f + 2.f * __builtin_amdgcn_sqrtf(fmaxf(1.f - i2 * (1.f / 3.f), 0.f)),
+                   (i2 + 2.f * __builtin_amdgcn_sqrtf(fmaxf(i2 * i2 - 9.f * i3, 0.f))) * frcp(3.f * i3)};
+}
+
+struct LogMoments {
+  double p0, p1, n2, n3, n4;
+};
+
 // The wave takes one rule, the shortest that serves all its lanes here, so that its nodes are in scalar
 // registers: 24 vector instructions per pair of nodes with the tangent, 18 without. Order-3 Jacobian on 24^3
-// elements (0.061 ms at strains of 1 %) at isochoric stretches of 1.5, 2, 3 and 5: 0.060, 0.060, 0.064 and
+// elements (0.059 ms at strains of 1 %) at isochoric stretches of 1.5, 2, 3 and 5: 0.060, 0.060, 0.061 and
 // 0.068 ms; with a principal frame 0.072 to 0.073, and with 12 Gauss nodes in t / (1 + t) on panels that
 // halve towards 1 (one per factor 2 of a loose lower bound) 0.083, 0.104, 0.135 and 0.178.
 template <bool TAN>
-__device__ inline void log_quadrature(double I2, double I3, TState& s) {
-  const float i2 = (float)I2, i3 = (float)I3;
-  const float il = (i2 + 2.f * __builtin_amdgcn_sqrtf(fmaxf(i2 * i2 - 9.f * i3, 0.f))) * frcp(3.f * i3);
-  const float u = 1.f + 2.f * __builtin_amdgcn_sqrtf(fmaxf(1.f - i2 * (1.f / 3.f), 0.f)), ratio = u * il;
-  double c1 = 0.0, c2 = 0.0, g3 = 0.0, g4 = 0.0, g5 = 0.0;
+__device__ inline LogMoments log_moments(double I2, double I3, const LogBounds& bd) {
+  const float ratio = bd.u * bd.il;
+  LogMoments m{0.0, 0.0, 0.0, 0.0, 0.0};
   if (ratio <= LOG_RATIO[TAN][LOG_RULES - 1]) {
     static constexpr LogPairs pairs = log_pairs();
     int rule = 0;
     while (rule < LOG_RULES - 1 && __ballot(ratio > LOG_RATIO[TAN][rule])) ++rule;  // uniform
-    const double ia = (double)frsqrt(u * frcp(il)), ia2 = ia * ia;
+    const double ia = (double)frsqrt(bd.u * frcp(bd.il)), ia2 = ia * ia;
     const double a1 = 3.0 * ia, a2 = I2 * ia2, a3 = I3 * ia2 * ia;  // D = 1 + a1 t + a2 t^2 + a3 t^3
     double m0 = 0.0, m1 = 0.0, m2 = 0.0, m3 = 0.0;  // moments t^k / D, or t^(k + 1) / D^2 with TAN
 #pragma unroll 1
@@ -212,18 +241,18 @@ __device__ inline void log_quadrature(double I2, double I3, TState& s) {
     }
     if (TAN) {
       const double ia3 = ia2 * ia;
-      g3 = ia3 * fma(ia, fma(ia, m3, 2.0 * m2), m1);
-      g4 = -ia3 * ia * fma(ia, m3, m2);
-      g5 = ia3 * ia2 * m3;
+      m.n2 = ia3 * m1;
+      m.n3 = ia3 * ia * m2;
+      m.n4 = ia3 * ia2 * m3;
       m0 = fma(a1, m0, fma(2.0 * a2, m1, 3.0 * a3 * m2));
       m1 = 0.5 * fma(a1, m1, fma(2.0 * a2, m2, 3.0 * a3 * m3));
     }
-    c1 = ia * fma(ia, m1, m0);
-    c2 = -ia2 * m1;
+    m.p0 = ia * m0;
+    m.p1 = ia2 * m1;
   } else {
-    // wider still: c1 = int 1 / (2 D), c2 = -int t / (2 D), ... over t in [0, 1] with D = det(I + t S),
-    // 12 nodes on panels that halve towards t = 1, the last one no longer than the distance of the
-    // pole beyond it (the error of the rule is then below 1e-17); D in powers of t and 1 - t
+    // wider still: over t = T / (1 + T) in [0, 1], 12 Gauss nodes on panels that halve towards t = 1, the last
+    // one no longer than the distance of the pole beyond it (the error of the rule is then below
+    // 1e-17), E(t) = (1 - t)^3 D in powers of t and 1 - t
     constexpr int NG = 12;
     static constexpr double xg[NG / 2] = {0.009219682876640375, 0.04794137181476257, 0.11504866290284765,
                                           0.2063410228566913,   0.3160842505009099,  0.43738329574426554};
@@ -231,7 +260,7 @@ __device__ inline void log_quadrature(double I2, double I3, TState& s) {
                                           0.10158371336153296,  0.1167462682691774,  0.12457352290670139};
     // l with a margin for its rounding, or where FP32 does not reach it, that the other two have at
     // most the mean (3 - l) / 2
-    const double lam = fmax(kst(4.0 / 9.0) * I3, (double)(0.999f * frcp(il)));
+    const double lam = fmax(kst(4.0 / 9.0) * I3, (double)(0.999f * frcp(bd.il)));
     double t0 = 0.0, h = 1.0;
     for (int panel = 0; panel < 64; ++panel) {
       const bool last = h * (1.0 - lam) <= lam || panel == 63;
@@ -239,16 +268,16 @@ __device__ inline void log_quadrature(double I2, double I3, TState& s) {
 #pragma unroll 1
       for (int k = 0; k < NG; ++k) {
         const double x = k < NG / 2 ? xg[k] : 1.0 - xg[NG - 1 - k], wk = wg[k < NG / 2 ? k : NG - 1 - k];
-        const double t = fma(hp, x, t0), r = 1.0 - t;
-        const double iD = frcp(fma(t * t, fma(t, I3, r * I2), r * r * fma(2.0, t, 1.0)));
-        const double w = 0.5 * hp * wk * iD, wt = w * t;
-        c1 += w;
-        c2 -= wt;
+        const double t = fma(hp, x, t0), r = (1.0 - t0) - hp * x;
+        const double iE = frcp(fma(t * t, fma(t, I3, r * I2), r * r * fma(2.0, t, 1.0)));
+        const double w = 0.5 * hp * wk * iE;
+        m.p0 = fma(w, r, m.p0);
+        m.p1 = fma(w, t, m.p1);
         if (TAN) {
-          const double v = wt * t * iD, vt = v * t;
-          g3 += v;
-          g4 -= vt;
-          g5 = fma(vt, t, g5);
+          const double v = w * iE * t * t;
+          m.n2 = fma(v * r, r, m.n2);
+          m.n3 = fma(v * r, t, m.n3);
+          m.n4 = fma(v * t, t, m.n4);
         }
       }
       if (last) break;
@@ -256,13 +285,7 @@ __device__ inline void log_quadrature(double I2, double I3, TState& s) {
       h = hp;
     }
   }
-  s.c1 = c1;
-  s.c2 = c2;
-  if (TAN) {
-    s.g3 = g3;
-    s.g4 = g4;
-    s.g5 = g5;
-  }
+  return m;
 }
 
 // Y = S D + D S of symmetric traceless S and D: with a zero trace S_ii + S_jj = -S_kk.
@@ -280,18 +303,20 @@ __device__ inline double sym_dot(const double* a, const double* b) {
   return a[0] * b[0] + a[1] * b[1] + a[2] * b[2] + 2.0 * (a[3] * b[3] + a[4] * b[4] + a[5] * b[5]);
 }
 
-// A tensor as c1 D + c2 dev(S D + D S) + a S + b Q of the point's S and Q and a traceless D.
+// A tensor as c1 D + c2 dev(S D + D S) + a S + b M of the point's S and M and a traceless D.
 struct LogMap {
   double c1, c2, a, b;
 };
 
-// L(dS) of the header comment, its inner products dJ2 = S:dS and dJ3 = Q:dS given; ede = e:de.
-__device__ inline LogMap log_tangent(const TState& s, double dJ2, double dJ3, double& ede) {
-  const LogMap m{s.c1, s.c2, s.g3 * dJ2 + s.g4 * dJ3, s.g4 * dJ2 + s.g5 * dJ3};
-  const double j2 = kst(2.0 / 3.0) * s.J2 * s.c2, j3 = 3.0 * s.J3;
-  // e:dS = c1 dJ2 + c2 dJ3, e:(S dS + dS S) = 2 c1 dJ3 + (2/3) c2 J2 dJ2
-  ede = m.c1 * (m.c1 * dJ2 + m.c2 * dJ3) + m.c2 * (2.0 * m.c1 * dJ3 + j2 * dJ2) +
-        m.a * (2.0 * m.c1 * s.J2 + m.c2 * j3) + m.b * (m.c1 * j3 + j2 * s.J2);
+// The S coefficient of (p0 + p1) e - p1 dev(S e + e S), p0^2 - p0 p1 - (2/3) I2 p1^2; that of M is -3 p1 (p0 + p1).
+__device__ inline double log_eS(const TState& s) {
+  return s.p0 * (s.p0 - s.p1) - s.p1 * s.p1 * fma(kst(-1.0 / 3.0), s.ss, 2.0);
+}
+
+// L(dS) of the header comment, a = S:dS and b = M:dS given; ede = e:de.
+__device__ inline LogMap log_tangent(const TState& s, double a, double b, double& ede) {
+  const LogMap m{s.p0 + s.p1, -s.p1, s.n2 * a - s.n3 * b, s.n4 * b - s.n3 * a};
+  ede = log_eS(s) * a - 3.0 * s.p1 * m.c1 * b + m.a * (s.p0 * s.ss - s.p1 * s.sm) + m.b * (s.p0 * s.sm - s.p1 * s.mm);
   return m;
 }
 
@@ -302,7 +327,7 @@ __device__ inline void log_expand(const TState& s, const LogMap& m, const double
   const double tr = kst(2.0 / 3.0) * m.c2 * SD;
 #pragma unroll
   for (int k = 0; k < 6; ++k) {
-    double v = m.c1 * D[k] + m.c2 * Y[k] + m.a * s.S[k] + m.b * s.Q[k];
+    double v = m.c1 * D[k] + m.c2 * Y[k] + m.a * s.S[k] + m.b * s.M[k];
     if (k < 3) v -= tr;
     out[k] = v;
   }
@@ -376,6 +401,25 @@ __device__ inline double det_plus_one(const double* st) {
   return a * (b * c - st[3] * st[3]) - st[5] * (st[5] * c - st[3] * st[4]) + st[4] * (st[5] * st[3] - b * st[4]);
 }
 
+// M = dev K and I2 = tr K of K = adj(b_tr / m) = (det F / m)^2 F^-T adj(I + D) F^-1, dm = det F / m: the
+// products keep the small entries that adj(I + S) = Q - S + I2 / 3 loses.
+__device__ inline void dev_adjugate(const double* Fi, const double* st, double dm, double* M, double& I2) {
+  const double a = 1.0 + st[0], b = 1.0 + st[1], c = 1.0 + st[2], f = st[3], g = st[4], h = st[5];
+  const double A[6] = {b * c - f * f, a * c - g * g, a * b - h * h, h * g - f * a, h * f - g * b, g * f - h * c};
+  const double s = dm * dm;
+  const int at[3][3] = {{0, 5, 4}, {5, 1, 3}, {4, 3, 2}};
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    const double x = s * Fi[j], y = s * Fi[3 + j], z = s * Fi[6 + j];
+    const double t[3] = {A[0] * x + A[5] * y + A[4] * z, A[5] * x + A[1] * y + A[3] * z, A[4] * x + A[3] * y + A[2] * z};
+#pragma unroll
+    for (int i = 0; i <= j; ++i) M[at[i][j]] = Fi[i] * t[0] + Fi[3 + i] * t[1] + Fi[6 + i] * t[2];
+  }
+  I2 = M[0] + M[1] + M[2];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) M[k] -= I2 * kst(1.0 / 3.0);
+}
+
 // Residual state at one point (Box 1 / Box 2 and Section 3); arguments as for qp_state.
 // TAN: also the derivatives of the log coefficients (the tangent and its transpose).
 template <bool TAN, bool VOCE, bool MAXW = false>
@@ -396,25 +440,46 @@ __device__ inline void ts_state(const MatParams<double>& m, const FracParams<dou
   SS[3] = S[5] * S[4] - S[0] * S[3];
   SS[4] = S[5] * S[3] - S[1] * S[4];
   SS[5] = S[4] * S[3] - S[2] * S[5];
-  s.J2 = 0.5 * (SS[0] + SS[1] + SS[2]);
-  s.J3 = third * sym_dot(S, SS);
+  s.ss = SS[0] + SS[1] + SS[2];
+  const double J2 = 0.5 * s.ss, J3 = third * sym_dot(S, SS);
+  s.sm = 3.0 * J3 - s.ss;
+  s.mm = kst(2.0 / 3.0) * J2 * J2 - 2.0 * s.sm - s.ss;
 #pragma unroll
-  for (int k = 0; k < 6; ++k) s.Q[k] = k < 3 ? fma(-2.0 * third, s.J2, SS[k]) : SS[k];
+  for (int k = 0; k < 6; ++k) s.M[k] = (k < 3 ? fma(-third, s.ss, SS[k]) : SS[k]) - S[k];
   // det F <= 0 or an eigenvalue of b_tr <= 0 (trace, second invariant or determinant <= 0):
   // not physical, the point's values are NaN
   s.bad = !(det > 0.0) || !(t > -1.0);
-  if (s.J2 <= kst(LOG_SERIES_J2)) {
-    log_series<TAN>(s.J2, s.J3, s);
+  bool wide = false;
+  if (J2 <= kst(LOG_SERIES_J2)) {
+    log_series<TAN>(J2, J3, s);
   } else {
-    const double I2 = 3.0 - s.J2, I3 = det * det * det_plus_one(st) * (im * im * im);
+    double I2 = 3.0 - J2;
+    const double I3 = det * det * det_plus_one(st) * (im * im * im);
     s.bad |= !(I2 > 0.0) || !(I3 > 0.0);
-    if (!s.bad) log_quadrature<TAN>(I2, I3, s);
+    if (!s.bad) {
+      const LogBounds bd = log_bounds(I2, I3);
+      wide = bd.u * bd.il > LOG_WIDE;
+      if (wide) {
+        dev_adjugate(s.Fi, st, det * im, s.M, I2);
+        s.sm = 3.0 * I3 - I2;
+        s.mm = kst(2.0 / 3.0) * I2 * I2 - 6.0 * I3;
+      }
+      const LogMoments m = log_moments<TAN>(I2, I3, bd);
+      s.p0 = m.p0;
+      s.p1 = m.p1;
+      if (TAN) {
+        s.n2 = m.n2;
+        s.n3 = m.n3;
+        s.n4 = m.n4;
+      }
+    }
   }
-  if (s.bad) s.c1 = s.c2 = __builtin_nan("");
-  s.ee = 2.0 * s.c1 * (s.c1 * s.J2 + 3.0 * s.c2 * s.J3) + kst(2.0 / 3.0) * (s.c2 * s.J2) * (s.c2 * s.J2);
+  if (s.bad) s.p0 = s.p1 = __builtin_nan("");
+  s.ee = s.p0 * (s.p0 * s.ss - 2.0 * s.p1 * s.sm) + s.p1 * s.p1 * s.mm;
   // tr eps = log(det b_tr) / 2: det b_tr = m^3 (1 - J2 + J3) formed about 1 where it is near 1,
-  // else det F^2 det(I + D)
-  const double v = t * fma(t, kst(3.0) + t, kst(3.0)), w = s.J3 - s.J2, x = v + w + v * w;
+  // else, and where the eigenvalues differ widely (J3 - J2 then holds few digits of I3), det F^2 det(I + D)
+  const double v = t * fma(t, kst(3.0) + t, kst(3.0)), w = J3 - J2;
+  const double x = wide ? fma(det * det, det_plus_one(st), -1.0) : v + w + v * w;
   if (fabs(x) <= 0.25)
     s.theta = half_log1p_near(x);
   else
@@ -425,9 +490,9 @@ __device__ inline void ts_state(const MatParams<double>& m, const FracParams<dou
 // Degraded Kirchhoff stress tau_degr (symmetric).
 __device__ inline void ts_stress(const MatParams<double>& m, const TState& s, double* tau) {
   const double a = 2.0 * m.mu * s.c * s.g, kt = m.kappa * s.theta, vol = s.tension ? s.g * kt : kt;
-  const double a1 = a * s.c1, a2 = a * s.c2;
+  const double a0 = a * s.p0, a1 = -a * s.p1;
 #pragma unroll
-  for (int k = 0; k < 6; ++k) tau[k] = fma(a1, s.S[k], k < 3 ? fma(a2, s.Q[k], vol) : a2 * s.Q[k]);
+  for (int k = 0; k < 6; ++k) tau[k] = fma(a0, s.S[k], k < 3 ? fma(a1, s.M[k], vol) : a1 * s.M[k]);
 }
 
 // First Piola stress P = tau_degr F^-T (eq:mechanical-gradient-transformation).
@@ -453,19 +518,19 @@ __device__ inline void ts_tangent_psi(const MatParams<double>& m, const TState& 
 #pragma unroll
   for (int k = 0; k < 3; ++k) X[k] -= t3;  // dev X: dS = dev X - t3 S
   const double SX = sym_dot(s.S, X);
-  const double dJ2 = SX - 2.0 * t3 * s.J2, dJ3 = sym_dot(s.Q, X) - 3.0 * t3 * s.J3;
+  const double aS = SX - t3 * s.ss, aM = sym_dot(s.M, X) - t3 * s.sm;  // S:dS, M:dS
   double ede;
-  LogMap de = log_tangent(s, dJ2, dJ3, ede);
+  LogMap de = log_tangent(s, aS, aM, ede);
   const double dth = dl[0] + dl[4] + dl[8];
   // linearised return: d(c e) = c de + e (kq e:de + kphi dphi)
   const double kk = s.kq * ede + s.kphi * dphi;
   // degraded stress increment (eq:linear-degraded-stress-linearization) a de + b e + vol I, in
-  // terms of dev X: dev(S dS + dS S) = dev(S X + X S) - 2 t3 Q
+  // terms of dev X: dev(S dS + dS S) = dev(S X + X S) - 2 t3 (M + S)
   const double tm2 = 2.0 * m.mu, kt = m.kappa * s.theta, kdt = m.kappa * dth;
   const double a = s.g * tm2 * s.c, b = tm2 * (s.g * kk + s.gp * dphi * s.c);
   const double vol = s.tension ? s.g * kdt + s.gp * dphi * kt : kdt;
-  de.a = a * (de.a - t3 * de.c1) + b * s.c1;
-  de.b = a * (de.b - 2.0 * t3 * de.c2) + b * s.c2;
+  de.a = a * (de.a - t3 * (s.p0 - s.p1)) + b * s.p0;
+  de.b = a * (de.b + 2.0 * t3 * s.p1) - b * s.p1;
   de.c1 *= a;
   de.c2 *= a;
   double dt[6], tau[6];
@@ -505,8 +570,8 @@ __device__ inline void ts_tangent_T_psi(const MatParams<double>& m, const TState
   mul33(Pb, s.Fi, Zb);
   ts_stress(m, s, tau);
   double E[6] = {Zb[0], Zb[4], Zb[8], 0.5 * (Zb[5] + Zb[7]), 0.5 * (Zb[2] + Zb[6]), 0.5 * (Zb[1] + Zb[3])};
-  const double eS0 = sym_dot(s.S, E), eQ0 = sym_dot(s.Q, E);
-  xe = s.c1 * eS0 + s.c2 * eQ0;
+  const double eS0 = sym_dot(s.S, E), eM0 = sym_dot(s.M, E);
+  xe = s.p0 * eS0 - s.p1 * eM0;
   const double tz = Zb[0] + Zb[4] + Zb[8];
   // dtau = a de + b e + vol I
   phib = phib0 + tm2 * s.gp * s.c * xe + (s.tension ? s.gp * kt * tz : 0.0);
@@ -517,13 +582,10 @@ __device__ inline void ts_tangent_T_psi(const MatParams<double>& m, const TState
   const double a = s.g * tm2 * s.c, tz3 = tz * kst(1.0 / 3.0);
 #pragma unroll
   for (int k = 0; k < 3; ++k) E[k] -= tz3;  // the stress cotangent's deviator; de's is a E + edeb e
-  // L of it: L(E) by the map, L(e) = the tensor of (c1 e + c2 dev(S e + e S) + ...), with
-  // dev(S S + S S) = 2 Q and dev(S Q + Q S) = (2/3) J2 S
-  const double j2 = kst(2.0 / 3.0) * s.J2, j3 = 3.0 * s.J3;
-  const double eS = a * eS0 + edeb * (2.0 * s.c1 * s.J2 + s.c2 * j3);
-  const double eQ = a * eQ0 + edeb * (s.c1 * j3 + s.c2 * j2 * s.J2);
-  const LogMap lm{a * s.c1, a * s.c2, s.g3 * eS + s.g4 * eQ + edeb * (s.c1 * s.c1 + j2 * s.c2 * s.c2),
-                  s.g4 * eS + s.g5 * eQ + 3.0 * edeb * s.c1 * s.c2};
+  // L of it: L(E) by the map, L(e) in S and M alone (log_eS and the rank-2 part)
+  const double c1 = s.p0 + s.p1;
+  const double eS = a * eS0 + edeb * (s.p0 * s.ss - s.p1 * s.sm), eM = a * eM0 + edeb * (s.p0 * s.sm - s.p1 * s.mm);
+  const LogMap lm{a * c1, -a * s.p1, s.n2 * eS - s.n3 * eM + edeb * log_eS(s), s.n4 * eM - s.n3 * eS - 3.0 * edeb * s.p1 * c1};
   double Xb[6];
   log_expand(s, lm, E, eS0, Xb);
   // dS = dev X - (tr X / 3) S
