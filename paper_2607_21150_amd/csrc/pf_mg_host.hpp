@@ -569,7 +569,9 @@ pf_status transfer_nw(pf_ctx* c, const float* in, const MGLevel& I, float* out, 
 pf_status transfer(pf_ctx* c, const float* in, const MGLevel& I, float* out, const MGLevel& O, int* const* base,
                    float* const* w, int nw, bool add, hipStream_t s) {
   const TransferAxes ax{{base[0], base[1], base[2]}, {w[0], w[1], w[2]}};
-  switch (nw) {
+  // vectors that overlap go through the intermediate lattices: one launch would read what it has written
+  const bool apart = !overlaps(in, 4 * I.n_nodes * sizeof(float), out, 4 * O.n_nodes * sizeof(float));
+  switch (apart ? nw : 0) {
     case 2: return transfer_nw<2>(c, in, I, out, O, ax, add, s);
     case 3: return transfer_nw<3>(c, in, I, out, O, ax, add, s);
     case 4: return transfer_nw<4>(c, in, I, out, O, ax, add, s);
