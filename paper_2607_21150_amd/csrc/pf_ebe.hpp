@@ -752,8 +752,8 @@ static __global__ __launch_bounds__(4 * COARSE_SOLVE_NODES) void k_coarse_solve(
 // node I: sum over fine i = 2I + a and j = 2(I + O) + b with |j - i| <= 1 per direction
 // of w(a) w(b) Sf[j - i][f][g][i] (accumulated in double, fixed order: deterministic).
 // One thread per coarse node and row f (4 columns g), blockIdx.y = offset O, so that the bounds of
-// a and b are uniform; fine nodes outside the lattice take weight 0, and entries of Sf towards
-// nodes outside are 0. 33^3 to 17^3 nodes 529 -> 285 us, 41^3 to
+// a and b are uniform; fine nodes outside the lattice take weight 0 and node 0's entry (-1, -1, -1), and entries
+// of Sf towards nodes outside are 0. 33^3 to 17^3 nodes 529 -> 285 us, 41^3 to
 // 21^3 1048 -> 601 (a thread per entry, its bounds and index lists formed per lane, before).
 static __global__ __launch_bounds__(NT) void k_stencil_rap(const float* __restrict__ Sf, int fx1, int fy1, int fz1,
                                                     float* __restrict__ Sc, int cx1, int cy1, int cz1) {
@@ -771,7 +771,9 @@ static __global__ __launch_bounds__(NT) void k_stencil_rap(const float* __restri
           const bool in = x >= 0 && x < fx1 && y >= 0 && y < fy1 && z >= 0 && z < fz1;
           const int64_t i = in ? x + (int64_t)fx1 * (y + (int64_t)fy1 * z) : 0;
           const float wa = in ? (ax ? 0.5f : 1.f) * (ay ? 0.5f : 1.f) * (az ? 0.5f : 1.f) : 0.f;
+          // (a NaN or infinity of node 0 does not count: the entry towards a node outside is read, a 0)
           const float* Si = Sf + stencil_at(i, f) + (i & 63);
+          const int so = in ? 4 * 64 : 0;
           for (int oz = max(-1, 2 * dO[2] - az - 1); oz <= min(1, 2 * dO[2] - az + 1); ++oz)
             for (int oy = max(-1, 2 * dO[1] - ay - 1); oy <= min(1, 2 * dO[1] - ay + 1); ++oy) {
               const float wy = wa * (oz - 2 * dO[2] + az ? 0.5f : 1.f) * (oy - 2 * dO[1] + ay ? 0.5f : 1.f);
@@ -780,7 +782,7 @@ static __global__ __launch_bounds__(NT) void k_stencil_rap(const float* __restri
                 const int bx = ox - 2 * dO[0] + ax;
                 if (bx < -1 || bx > 1) continue;  // uniform
                 const double w = wy * (bx ? 0.5f : 1.f);
-                const float* Se = Si + 4 * ((ox + 1) + 3 * (oy + 1) + 9 * (oz + 1)) * 64;
+                const float* Se = Si + so * ((ox + 1) + 3 * (oy + 1) + 9 * (oz + 1));
 #pragma unroll
                 for (int g = 0; g < 4; ++g) acc[g] += w * (double)Se[g * 64];
               }
