@@ -121,10 +121,10 @@ def alg_bytes(mesh, kind):
 def stored_bytes(mesh, kind):
     """Bytes the record applies actually read and write (larger than the algorithmic bytes,
     which do not grow with what is stored): FP32 apply: dz (16), y (16) per
-    node, record 48 + F^-1 N 36 + flags 1 + phase 1 per point; stored FP64 Jacobian: u copy (24), dz (32),
+    node, record 60 + F^-1 N 36 + flags 1 + phase 1 per point; stored FP64 Jacobian: u copy (24), dz (32),
     y (32) per node, record 120 + flags 1 + phase 1 per point."""
     if kind == "fp32_apply":
-        return 32 * mesh.n_nodes + 86 * mesh.n_q
+        return 32 * mesh.n_nodes + 98 * mesh.n_q
     if kind == "jacobian_stored":
         return 88 * mesh.n_nodes + 122 * mesh.n_q
     raise ValueError(kind)

@@ -238,9 +238,9 @@ pf_status pf_apply_adjoint_noalloc(pf_ctx* ctx, const double* z, const double* v
 
 /* Linearise at z for the FP32 multigrid: the return-mapping, split and history
  * decisions, their scalars, the principal frame of b_tr (a unit quaternion, its three
- * smallest components) and the principal trial log strains
- * are taken in FP64 and stored per point (and per branch, see pf_set_branches)
- * as an FP32 record of 12 values and a
+ * smallest components), the principal trial log strains and the off-diagonal tangent
+ * factors are taken in FP64 and stored per point (and per branch, see pf_set_branches)
+ * as an FP32 record of 15 values and a
  * flag byte (Appendices A-C evaluated once), with F^-1 in that frame (9 values); assembles an
  * order-1 level into a block stencil and the Galerkin stencils of any coarser order-1
  * lattices below it; builds every level's point-Jacobi

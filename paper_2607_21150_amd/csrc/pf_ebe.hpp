@@ -57,16 +57,15 @@ __device__ inline void tangent_factors(const MatParams<float>& m, const QPState<
     t.h[i] = tmc * (s.c + ee * s.kq) * s.e[i] + (s.tension ? kt : 0.f);
   }
   t.hphi = tmc * ee * s.kphi;
-  // factors of Lt_ij and Lt_ji in the off-diagonal increment of (i, j)
-  const float pj[9] = {0.f, s.offj[2], s.offj[1], s.offi[2], 0.f, s.offj[0], s.offi[1], s.offi[0], 0.f};
+  const float co[9] = {0.f, s.coef[2], s.coef[1], s.coef[2], 0.f, s.coef[0], s.coef[1], s.coef[0], 0.f};
 #pragma unroll
   for (int i = 0; i < 3; ++i)
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
       t.M[3 * i + j] = s.g * (tmc * ((i == j ? 1.f : 0.f) - 1.f / 3.f) + tm2 * s.kq * s.e[i] * s.e[j]) + kap -
                        (i == j ? td[i] : 0.f);
-      t.p[3 * i + j] = pj[3 * i + j];
-      t.q[3 * i + j] = pj[3 * j + i] - td[i];
+      t.p[3 * i + j] = co[3 * i + j] * s.bd[j];
+      t.q[3 * i + j] = co[3 * i + j] * s.bd[i] - td[i];
     }
 #pragma unroll
   for (int k = 0; k < 9; ++k) t.N[k] = s.N[k], t.R[k] = s.R[k];
@@ -176,12 +175,12 @@ __device__ inline bool ebe_layer(const EbeArgs& a, EbePoint& p, int j, TangentFa
   if (j > 0 && (!p.pt || (rc.flags & REC_EMPTY))) return false;
   constexpr int Q3 = PF * PF * PF;
   const int64_t n_elem = (int64_t)a.m.nx * a.m.ny * a.m.nz;
-  const float* rr = a.rec.rec + rec_at<Q3, REC_N<float>>(j * n_elem + p.e, (int)(p.gq - p.e * Q3));
+  const float* rr = a.rec.rec + rec_at<Q3, REC_N>(j * n_elem + p.e, (int)(p.gq - p.e * Q3));
 #pragma unroll
-  for (int k = 0; k < REC_N<float>; ++k) rc.v[k] = p.pt ? rr[k * rec_pad(Q3)] : 0.f;
+  for (int k = 0; k < REC_N; ++k) rc.v[k] = p.pt ? rr[k * rec_pad(Q3)] : 0.f;
   const MatParams<float> m = j == 0 ? a.mats[p.pidc] : a.xmats[p.pidc * a.n_extra + j - 1];
   QPState<float> s;
-  qp_state_lin<float>(m, rc, s);
+  qp_state_lin<float>(rc, s);
   if (j == 0) {
 #pragma unroll
     for (int k = 0; k < 9; ++k) s.R[k] = p.R[k];

@@ -1014,13 +1014,13 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2(LinApplyArgs<V> a, int colour,
     }
     LinRecordT<V> rc;
 #pragma unroll
-    for (int k = 0; k < REC_N<V>; ++k) rc.v[k] = valid ? a.rec.rec[rec_at<27, REC_N<V>>(e, q) + k * rec_pad(27)] : V(0);
+    for (int k = 0; k < REC_N; ++k) rc.v[k] = valid ? a.rec.rec[rec_at<27, REC_N>(e, q) + k * rec_pad(27)] : V(0);
     rc.flags = valid ? a.rec.flags[gq] : 0;
     const int pid = valid ? a.phase[gq] : 0;
     const int pidc = pid < a.nph ? pid : 0;
     const MatParams<V> mp = a.mats[pidc];
     QPState<V> s;
-    qp_state_lin<V>(mp, rc, s);
+    qp_state_lin<V>(rc, s);
     if constexpr (FRAME_FROM_U<V>) {
       frame_from_gradient<V>(G, s.N, GEO ? nullptr : ih, s.R);
     } else {
@@ -1119,7 +1119,7 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q3(LinApplyArgs<V> a, int colour,
     const int64_t gq = e * 64 + ql;
     LinRecordT<V> rc;
 #pragma unroll
-    for (int k = 0; k < REC_N<V>; ++k) rc.v[k] = (a.rec.rec + (e * REC_N<V> + k) * 64)[ql];
+    for (int k = 0; k < REC_N; ++k) rc.v[k] = (a.rec.rec + (e * REC_N + k) * 64)[ql];
     rc.flags = (a.rec.flags + e * 64)[ql];
     QPState<V> s;
     if constexpr (!FRAME_FROM_U<V>) {
@@ -1168,7 +1168,7 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q3(LinApplyArgs<V> a, int colour,
     }
     const int pidc = pid < a.nph ? pid : 0;
     const MatParams<V> mp = a.mats[pidc];
-    qp_state_lin<V>(mp, rc, s);
+    qp_state_lin<V>(rc, s);
     if constexpr (FRAME_FROM_U<V>) frame_from_gradient<V>(G, s.N, GEO ? nullptr : ih, s.R);
     V Fu[9], dL;
     lin_tangent<V, 64, MB>(a.rec, n_elem, a.xmats, a.n_extra, mp, s, pidc, e, ql, true, W, wphi, Fu, dL);

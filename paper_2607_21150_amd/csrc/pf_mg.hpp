@@ -253,18 +253,17 @@ __global__ __launch_bounds__(NT) void k_linearize(LinArgs a, DevTables* __restri
           qp_state<true, true>(b.m, a.fr, G, phi, 0.0, xs, sj);
           any_bad |= sj.bad;
           psi += sj.psi;
-          const int64_t ro = rec_at<Q3, REC_N<float>>(lj * n_elem + e, ql);
+          const int64_t ro = rec_at<Q3, REC_N>(lj * n_elem + e, ql);
           LinRecord rj;
           record_from_state(sj, rj);
 #pragma unroll
-          for (int k = 0; k < REC_N<float>; ++k) a.rec.rec[ro + k * rec_pad(Q3)] = rj.v[k];
+          for (int k = 0; k < REC_N; ++k) a.rec.rec[ro + k * rec_pad(Q3)] = rj.v[k];
           a.rec.flags[lj * a.n_q + gq] = rj.flags;
           if (a.rec64) {
             LinRecordT<double> r64;
             record_from_state(sj, r64);
 #pragma unroll
-            for (int k = 0; k < REC_N<double>; ++k)
-              a.rec64[rec_at<Q3, REC_N<double>>(lj * n_elem + e, ql) + k * rec_pad(Q3)] = r64.v[k];
+            for (int k = 0; k < REC_N; ++k) a.rec64[ro + k * rec_pad(Q3)] = r64.v[k];
           }
         }
         s.hactive = psi > st[7];
@@ -309,7 +308,7 @@ __global__ __launch_bounds__(NT) void k_linearize(LinArgs a, DevTables* __restri
         s.H = s.hactive ? psi : st[7];
       }
       if (MODE == 0 || MODE == 2) {
-        const int64_t ro = rec_at<Q3, REC_N<float>>(e, ql);
+        const int64_t ro = rec_at<Q3, REC_N>(e, ql);
         LinRecord rc;
         double N[9], R[9];
         record_from_state(s, rc, N);
@@ -317,14 +316,13 @@ __global__ __launch_bounds__(NT) void k_linearize(LinArgs a, DevTables* __restri
 #pragma unroll
         for (int k = 0; k < 9; ++k) a.frame[rec_at<Q3, 9>(e, ql) + k * rec_pad(Q3)] = (float)R[k];
 #pragma unroll
-        for (int k = 0; k < REC_N<float>; ++k) a.rec.rec[ro + k * rec_pad(Q3)] = rc.v[k];
+        for (int k = 0; k < REC_N; ++k) a.rec.rec[ro + k * rec_pad(Q3)] = rc.v[k];
         a.rec.flags[gq] = rc.flags;
         if (a.rec64) {
           LinRecordT<double> r64;
           record_from_state(s, r64);
 #pragma unroll
-          for (int k = 0; k < REC_N<double>; ++k)
-            a.rec64[rec_at<Q3, REC_N<double>>(e, ql) + k * rec_pad(Q3)] = r64.v[k];
+          for (int k = 0; k < REC_N; ++k) a.rec64[ro + k * rec_pad(Q3)] = r64.v[k];
         }
       } else {
         double ns[8];
@@ -399,14 +397,14 @@ __device__ inline void lin_tangent(const RecordSoAT<V>& rec, int64_t n_elem, con
     const int64_t lj = 1 + j;
     const uint8_t fl = valid ? rec.flags[(lj * n_elem + e) * Q3 + ql] : REC_EMPTY;
     if (fl & REC_EMPTY) continue;
-    const V* rr = rec.rec + rec_at<Q3, REC_N<V>>(lj * n_elem + e, ql);
+    const V* rr = rec.rec + rec_at<Q3, REC_N>(lj * n_elem + e, ql);
     LinRecordT<V> r;
 #pragma unroll
-    for (int k = 0; k < REC_N<V>; ++k) r.v[k] = rr[k * rec_pad(Q3)];
+    for (int k = 0; k < REC_N; ++k) r.v[k] = rr[k * rec_pad(Q3)];
     r.flags = fl;
     const MatParams<V>& bm = xmats[pid * n_extra + j];
     QPState<V> sj;
-    qp_state_lin<V>(bm, r, sj);
+    qp_state_lin<V>(r, sj);
     frame_product<V>(Fi, sj.N, nullptr, sj.R);
     V dPj[9], dpj;
     qp_tangent_psi<V>(bm, sj, dG, dphi, dPj, dpj, true);

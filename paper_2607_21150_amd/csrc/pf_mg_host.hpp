@@ -188,7 +188,7 @@ pf_status ensure_records(pf_ctx* c) {
   mg.rec = RecordSoA{nullptr, nullptr};
   mg.rec64 = nullptr;
   mg.rec_layers = 0;
-  if (hipMalloc(&mg.rec.rec, layers * REC_N<float> * rec_points(c) * sizeof(float)) != hipSuccess ||
+  if (hipMalloc(&mg.rec.rec, layers * REC_N * rec_points(c) * sizeof(float)) != hipSuccess ||
       hipMalloc(&mg.rec.flags, (size_t)layers * c->n_q) != hipSuccess)
     return fail(PF_ENOMEM, "linearisation record: allocation failed");
   mg.rec_layers = layers;
@@ -722,7 +722,7 @@ pf_status pf_linearize(pf_ctx* c, const double* z, void* stream) {
   if ((st = mg_alloc(c)) || (st = ensure_records(c))) return st;
   MGState& mg = c->mg;
   if (c->store_lin64) {
-    if ((!mg.rec64 && hipMalloc(&mg.rec64, mg.rec_layers * REC_N<double> * rec_points(c) * sizeof(double)) != hipSuccess) ||
+    if ((!mg.rec64 && hipMalloc(&mg.rec64, mg.rec_layers * REC_N * rec_points(c) * sizeof(double)) != hipSuccess) ||
         (!mg.u64 && hipMalloc(&mg.u64, (size_t)3 * c->n_nodes * sizeof(double)) != hipSuccess))
       return fail(PF_ENOMEM, "stored linearisation: allocation failed");
     HIPCHK(hipMemcpyAsync(mg.u64, z, (size_t)3 * c->n_nodes * sizeof(double), hipMemcpyDeviceToDevice, s));

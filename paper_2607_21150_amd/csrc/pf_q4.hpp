@@ -631,7 +631,7 @@ __global__ __launch_bounds__(NT5, 2) void k_a32_q4(LinApplyArgs<V> a, int colour
   const int64_t gq = e * Q3 + ql;
   LinRecordT<V> rc;
 #pragma unroll
-  for (int k = 0; k < REC_N<V>; ++k) rc.v[k] = pt ? a.rec.rec[rec_at<Q3, REC_N<V>>(e, ql) + k * rec_pad(Q3)] : V(0);
+  for (int k = 0; k < REC_N; ++k) rc.v[k] = pt ? a.rec.rec[rec_at<Q3, REC_N>(e, ql) + k * rec_pad(Q3)] : V(0);
   rc.flags = pt ? a.rec.flags[gq] : 0;
   QPState<V> s;
   if (!FRAME_FROM_U<V>) {
@@ -682,7 +682,7 @@ __global__ __launch_bounds__(NT5, 2) void k_a32_q4(LinApplyArgs<V> a, int colour
   __syncthreads();
   const int pidc = pid < a.nph ? pid : 0;
   const MatParams<V> mp = a.mats[pidc];
-  qp_state_lin<V>(mp, rc, s);
+  qp_state_lin<V>(rc, s);
   if constexpr (FRAME_FROM_U<V>) frame_from_gradient<V>(G, s.N, GEO ? nullptr : ih, s.R);
   V Fu[9], dL;
   lin_tangent<V, Q3, MB>(a.rec, (int64_t)a.m.nx * a.m.ny * a.m.nz, a.xmats, a.n_extra, mp, s, pidc, e, ql, pt, W, wphi, Fu, dL);
@@ -749,7 +749,7 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2r(LinApplyArgs<V> a, const type
   V* B = bufB + slot * L::B;
   LinRecordT<V> rc;
 #pragma unroll
-  for (int k = 0; k < REC_N<V>; ++k) rc.v[k] = pt ? a.rec.rec[rec_at<Q3, REC_N<V>>(e, ql) + k * rec_pad(Q3)] : V(0);
+  for (int k = 0; k < REC_N; ++k) rc.v[k] = pt ? a.rec.rec[rec_at<Q3, REC_N>(e, ql) + k * rec_pad(Q3)] : V(0);
   rc.flags = pt ? a.rec.flags[gq] : 0;
   QPState<V> s;
   if (!FRAME_FROM_U<V>) {
@@ -800,7 +800,7 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2r(LinApplyArgs<V> a, const type
   __syncthreads();
   const int pidc = pid < a.nph ? pid : 0;
   const MatParams<V> mp = a.mats[pidc];
-  qp_state_lin<V>(mp, rc, s);
+  qp_state_lin<V>(rc, s);
   if constexpr (FRAME_FROM_U<V>) frame_from_gradient<V>(G, s.N, ih, s.R);
   V Fu[9], dL;
   lin_tangent<V, Q3, false>(a.rec, 0, a.xmats, a.n_extra, mp, s, pidc, e, ql, pt, W, wphi, Fu, dL);

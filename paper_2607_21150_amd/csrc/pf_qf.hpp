@@ -341,7 +341,6 @@ template <typename T> struct QPState {
   T c;          // radial-return factor
   T kq, kphi;   // plastic tangent: d(c e)_i = c de_i + e_i (kq e.de + kphi dphi)
   T coef[3];    // off-diagonal tangent factors for pairs (1,2), (0,2), (0,1)
-  T offj[3], offi[3];  // the linearised applies: coef b_j and coef b_i of pair (i, j)
   T psi, H, L;  // psi^+, max(H_n, psi^+), local phase-field residual
   T dLcoef;     // dL / dphi at fixed history
   T ddg_s0, ddg_visc;  // d dgamma / d sigma0, d dgamma / d visc (0 when elastic)
@@ -534,22 +533,21 @@ __device__ inline void qp_state(const MatParams<double>& m, const FracParams<dou
 }
 
 // Linearisation record of one point, taken in FP64 once per linearisation and
-// stored in FP32 (12 values + a flag byte) or FP64 (15): the return-mapping factor and its
+// stored in FP32 (19 values + a flag byte): the return-mapping factor and its
 // tangent coefficients, the degradation and the local phase-field coefficient,
-// the principal frame of b_tr as a unit quaternion, the principal log strains and (FP64)
-// the off-diagonal tangent factors. F^-1 N of the point's block goes with the FP32 record
-// in an array of its own (QPState::R).
+// the principal frame of b_tr as a unit quaternion, the principal values b_i,
+// the principal log strains and the off-diagonal tangent factors. F^-1 N of the point's
+// block goes with it in an array of its own (QPState::R).
 // Record slots: return factor, tangent scalars, degradation and its derivative, the
 // history term's coefficient, the frame of b_tr as the three smallest components of a
 // unit quaternion (the largest, made positive, is recovered from the norm; its index is
-// in the flags), the principal trial log strains (b_i = exp(2 eps_i) is recomputed) and,
-// in FP64, the off-diagonal divided-difference coefficients. The FP32 applies are bound by
-// the record's bytes and form those from the log strains (offdiagonal_pair).
-template <typename V> constexpr int REC_N = sizeof(V) == 8 ? 15 : 12;
+// in the flags), the principal trial log strains (b_i = exp(2 eps_i) is recomputed) and
+// the off-diagonal divided-difference coefficients.
+constexpr int REC_N = 15;
 enum RecSlot { R_C = 0, R_KQ, R_KPHI, R_G, R_GP, R_DL, R_Q0, R_E0 = R_Q0 + 3, R_O0 = R_E0 + 3 };
 // V = float: the FP32 multigrid record; V = double: the stored FP64 linearisation.
 template <typename V> struct LinRecordT {
-  V v[REC_N<V>];
+  V v[REC_N];
   uint8_t flags;  // bit0 tension, bit1 history active, bit2 plastic, bits 3-4 dropped quaternion index
 };
 using LinRecord = LinRecordT<float>;
@@ -636,7 +634,7 @@ __device__ inline void record_from_state(const QPState<double>& s, LinRecordT<V>
   const double th3 = s.theta * (1.0 / 3.0);
   for (int i = 0; i < 3; ++i) {
     r.v[R_E0 + i] = (V)(s.e[i] + th3);
-    if (sizeof(V) == 8) r.v[(R_O0 + i) % REC_N<V>] = (V)s.coef[i];
+    r.v[R_O0 + i] = (V)s.coef[i];
   }
   r.flags = (s.tension ? 1 : 0) | (s.hactive ? 2 : 0) | (s.plastic ? 4 : 0) | (m << 3);
 }
@@ -687,38 +685,17 @@ __device__ inline void frame_from_gradient(const T* G, const T* N, const T* dir,
   frame_product<T>(Fi, N, dir, R);
 }
 
-// g mu c (ln b_i - ln b_j) / (b_i - b_j) times b_j and b_i by the difference d of the log strains:
-// 2 d / (exp(2 d) - 1) = d coth d - d and d coth d + d. The series of d coth d holds to FP32 for
-// |d| <= 1/2 (next term 2e-6 d^12). Read from the record as 3 of its 15 values before, an eighth of an
-// apply's bytes: order-4 V-cycle on 40^3 elements 3.64 -> 3.56 ms, Newton step on 32^3 of order 3 47.1
-// -> 46.0; the apply's error against FP64 is the same on average over orders 2 to 4 (1e-7 to 2.2e-7).
-__device__ inline void offdiagonal_pair(float gmc, float d, float& offj, float& offi) {
-  const float x = d * d;
-  float bj, bi;
-  if (fabsf(d) <= 0.5f) {
-    const float dc = 1.f + x * (1.f / 3.f + x * (-1.f / 45.f + x * (2.f / 945.f + x * (-1.f / 4725.f + x * (2.f / 93555.f)))));
-    bj = dc - d;
-    bi = dc + d;
-  } else {
-    const float a = 2.f * fabsf(d), s = a / (fexp(a) - 1.f);
-    bj = d > 0.f ? s : s + a;
-    bi = d > 0.f ? s + a : s;
-  }
-  offj = gmc * bj;
-  offi = gmc * bi;
-}
-
 // State for the linearised applies from the record (frame, principal values, decisions,
 // coefficients); s.R is the caller's.
 template <typename T>
-__device__ inline void qp_state_lin(const MatParams<T>& m, const LinRecordT<T>& r, QPState<T>& s) {
+__device__ inline void qp_state_lin(const LinRecordT<T>& r, QPState<T>& s) {
   {
-    const int dropped = (r.flags >> 3) & 3;
+    const int m = (r.flags >> 3) & 3;
     const T a0 = (T)r.v[R_Q0], a1 = (T)r.v[R_Q0 + 1], a2 = (T)r.v[R_Q0 + 2];
     const T rest = T(1) - (a0 * a0 + a1 * a1 + a2 * a2);
-    const T qm = sqrt(rest > T(0) ? rest : T(0));  // >= 1/2 by the choice of dropped
-    const T q[4] = {dropped == 0 ? qm : a0, dropped == 1 ? qm : (dropped == 0 ? a0 : a1),
-                    dropped == 2 ? qm : (dropped <= 1 ? a1 : a2), dropped == 3 ? qm : a2};
+    const T qm = sqrt(rest > T(0) ? rest : T(0));  // >= 1/2 by the choice of m
+    const T q[4] = {m == 0 ? qm : a0, m == 1 ? qm : (m == 0 ? a0 : a1), m == 2 ? qm : (m <= 1 ? a1 : a2),
+                    m == 3 ? qm : a2};
     quat_to_rot<T>(q, s.N);
   }
   s.c = (T)r.v[R_C];
@@ -734,18 +711,9 @@ __device__ inline void qp_state_lin(const MatParams<T>& m, const LinRecordT<T>& 
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     const T E = (T)r.v[R_E0 + i];  // principal trial log strain: b_i = exp(2 E)
+    s.bd[i] = fexp(T(2) * E);
     s.theta += E;
-    if constexpr (sizeof(T) == 8) s.bd[i] = fexp(T(2) * E);
-  }
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const int i = k == 0 ? 1 : 0, j = k == 2 ? 1 : 2;
-    if constexpr (sizeof(T) == 8) {
-      s.offj[k] = r.v[R_O0 + k] * s.bd[j];
-      s.offi[k] = r.v[R_O0 + k] * s.bd[i];
-    } else {
-      offdiagonal_pair(s.g * m.mu * s.c, r.v[R_E0 + i] - r.v[R_E0 + j], s.offj[k], s.offi[k]);
-    }
+    s.coef[i] = (T)r.v[R_O0 + i];
   }
   const T th3 = s.theta * (T(1) / T(3));
 #pragma unroll
@@ -777,6 +745,7 @@ __device__ inline void qp_tangent_psi(const MatParams<T>& m, const QPState<T>& s
   for (int i = 0; i < 3; ++i)
 #pragma unroll
     for (int j = 0; j < 3; ++j) Lt[3 * i + j] = N[i] * dN[j] + N[3 + i] * dN[3 + j] + N[6 + i] * dN[6 + j];
+  const T* bd = s.bd;
   // principal strain increments from the diagonal (eq:hencky-stress-linearization)
   T deps[3];
   T dth = T(0);
@@ -809,9 +778,9 @@ __device__ inline void qp_tangent_psi(const MatParams<T>& m, const QPState<T>& s
       X[i] = s.g * (tm2 * dce[i]) + kdt + s.gp * dphi * taubd;
   }
   // off-diagonal increments: rotated db_ij times the divided-difference factors
-  const T o12 = Lt[5] * s.offj[0] + Lt[7] * s.offi[0];
-  const T o02 = Lt[2] * s.offj[1] + Lt[6] * s.offi[1];
-  const T o01 = Lt[1] * s.offj[2] + Lt[3] * s.offi[2];
+  const T o12 = (Lt[5] * bd[2] + bd[1] * Lt[7]) * s.coef[0];
+  const T o02 = (Lt[2] * bd[2] + bd[0] * Lt[6]) * s.coef[1];
+  const T o01 = (Lt[1] * bd[1] + bd[0] * Lt[3]) * s.coef[2];
   // Z = dtau_rot - diag(tau_d) Lt^T
   const T Z[9] = {X[0] - td[0] * Lt[0], o01 - td[0] * Lt[3], o02 - td[0] * Lt[6],
                   o01 - td[1] * Lt[1], X[1] - td[1] * Lt[4], o12 - td[1] * Lt[7],
