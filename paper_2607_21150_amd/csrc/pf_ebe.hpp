@@ -10,6 +10,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "pf_brick.hpp"
 #include "pf_mg.hpp"
 #include "pf_q4.hpp"
@@ -123,16 +125,22 @@ template <int PF> struct EbeShape {
 
 // A point of the element matrices' and diagonals' kernels: thread t holds point ql of element
 // el (of the workgroup's NE); the block's F^-1 N, the reference-to-physical factors
-// A[3 K + J] = d xi_K / d x_J and the weight (0 for threads without a point).
-struct EbePoint {
+// A[3 K + J] = d xi_K / d x_J (mapped elements: in FP64, products with them are summed and rounded once) and
+// the weight (0 for threads without a point).
+template <bool GEO> struct EbePoint {
   int64_t e, gq;
   int el, qx, qy, qz, pidc;
   bool pt;
-  float R[9], Fi[9], A[9], w;  // Fi: F^-1 in the directions of R's rows (ebe_layer of the block sets it)
+  float R[9], Fi[9], w;  // Fi: F^-1 in the directions of R's rows (ebe_layer of the block sets it)
+  std::conditional_t<GEO, double, float> A[9];
+  // grad xi_J . grad xi_L
+  __device__ float metric(int J, int L) const {
+    return (float)(A[3 * J] * A[3 * L] + A[3 * J + 1] * A[3 * L + 1] + A[3 * J + 2] * A[3 * L + 2]);
+  }
 };
 
 template <int PF, bool GEO>
-__device__ inline void ebe_point(const EbeArgs& a, const DevTablesF* __restrict__ tabs, EbePoint& p) {
+__device__ inline void ebe_point(const EbeArgs& a, const DevTablesF* __restrict__ tabs, EbePoint<GEO>& p) {
   using S = EbeShape<PF>;
   constexpr int Q = S::Q, Q2 = S::Q2, Q3 = S::Q3, NE = S::NE;
   const int t = threadIdx.x;
@@ -150,7 +158,10 @@ __device__ inline void ebe_point(const EbeArgs& a, const DevTablesF* __restrict_
   const float ih[3] = {(float)a.m.ih[0], (float)a.m.ih[1], (float)a.m.ih[2]};
 #pragma unroll
   for (int k = 0; k < 9; ++k)
-    p.A[k] = GEO ? (p.pt ? (float)a.qd[k * a.n_q + p.gq] : 0.f) : (k % 4 == 0 ? ih[k / 4] : 0.f);
+    if constexpr (GEO)
+      p.A[k] = p.pt ? a.qd[k * a.n_q + p.gq] : 0.0;
+    else
+      p.A[k] = k % 4 == 0 ? ih[k / 4] : 0.f;
   p.w = 0.f;
   if (p.pt)
     p.w = GEO ? (float)a.qd[9 * a.n_q + p.gq]
@@ -166,9 +177,10 @@ struct EbeBlock {
 };
 
 // The tangent's factors of record layer j (0: the block, taken first; 1 + j: extra branch j) of
-// point p; false where the layer is empty.
-template <int PF, bool GEO>
-__device__ inline bool ebe_layer(const EbeArgs& a, EbePoint& p, int j, TangentFactors& tf, EbeBlock& blk) {
+// point p; false where the layer is empty. REF: R in reference directions (mapped elements; the box's
+// record holds them).
+template <int PF, bool GEO, bool REF = GEO>
+__device__ inline bool ebe_layer(const EbeArgs& a, EbePoint<GEO>& p, int j, TangentFactors& tf, EbeBlock& blk) {
   const int64_t o = (int64_t)j * a.n_q + p.gq;
   LinRecord rc;
   rc.flags = p.pt ? a.rec.flags[o] : 0;
@@ -190,13 +202,13 @@ __device__ inline bool ebe_layer(const EbeArgs& a, EbePoint& p, int j, TangentFa
   }
   if (j == 0) blk = EbeBlock{s.hactive, s.gp, s.dLcoef};
   tangent_factors(m, s, tf);
-  if (GEO) {
+  if (REF && GEO) {
     float R[9];
 #pragma unroll
     for (int K = 0; K < 3; ++K)
 #pragma unroll
       for (int b = 0; b < 3; ++b)
-        R[3 * K + b] = p.A[3 * K] * tf.R[b] + p.A[3 * K + 1] * tf.R[3 + b] + p.A[3 * K + 2] * tf.R[6 + b];
+        R[3 * K + b] = (float)(p.A[3 * K] * tf.R[b] + p.A[3 * K + 1] * tf.R[3 + b] + p.A[3 * K + 2] * tf.R[6 + b]);
 #pragma unroll
     for (int k = 0; k < 9; ++k) tf.R[k] = R[k];
   }
@@ -225,11 +237,10 @@ __global__ __launch_bounds__(NT) void k_ebe_assemble(EbeArgs a, const DevTablesF
   const int l = threadIdx.x & 63, wv = wave_id();
   const int64_t n_elem = (int64_t)a.m.nx * a.m.ny * a.m.nz;
   const int64_t e0 = (int64_t)blockIdx.x * NE;
-  EbePoint p;
+  EbePoint<GEO> p;
   ebe_point<PF, GEO>(a, tabs, p);
   const int el = p.el, qx = p.qx, qy = p.qy, qz = p.qz;
   const float w = p.w;
-  const float* A = p.A;
   const MatParams<float> mp = a.mats[p.pidc];
   EbeBlock blk;
   TangentFactors tf0;
@@ -305,7 +316,7 @@ __global__ __launch_bounds__(NT) void k_ebe_assemble(EbeArgs a, const DevTablesF
 #pragma unroll
           for (int L = 0; L < 3; ++L)
             my[(10 + 3 * J + L) * NE * ES] =
-                kfg * (A[3 * J] * A[3 * L] + A[3 * J + 1] * A[3 * L + 1] + A[3 * J + 2] * A[3 * L + 2]);
+                kfg * p.metric(J, L);
       }
     }
     __syncthreads();
@@ -415,9 +426,10 @@ __global__ __launch_bounds__(NT) void k_ebe_assemble(EbeArgs a, const DevTablesF
 }
 
 // The diagonal block of displacement field K: D[0..5] += dP_KJ / dG_KL for (J, L) = xx, yy, zz,
-// xy + yx, xz + zx, yz + zy.
-template <int K>
-__device__ inline void tangent_diagonal(const TangentFactors& t, float* D) {
+// xy + yx, xz + zx, yz + zy. GEO: R in physical directions, the block taken to reference directions
+// as A C A^T.
+template <int K, bool GEO>
+__device__ inline void tangent_diagonal(const TangentFactors& t, const EbePoint<GEO>& p, float* D) {
   const float n[3] = {t.N[3 * K], t.N[3 * K + 1], t.N[3 * K + 2]};
   float X[3][3];  // sum_a N_Ka O_ab(L)
 #pragma unroll
@@ -436,6 +448,18 @@ __device__ inline void tangent_diagonal(const TangentFactors& t, float* D) {
   for (int J = 0; J < 3; ++J)
 #pragma unroll
     for (int L = 0; L < 3; ++L) C[J][L] = t.R[3 * J] * X[0][L] + t.R[3 * J + 1] * X[1][L] + t.R[3 * J + 2] * X[2][L];
+  if constexpr (GEO) {
+    double AC[3][3];
+#pragma unroll
+    for (int J = 0; J < 3; ++J)
+#pragma unroll
+      for (int L = 0; L < 3; ++L) AC[J][L] = p.A[3 * J] * C[0][L] + p.A[3 * J + 1] * C[1][L] + p.A[3 * J + 2] * C[2][L];
+#pragma unroll
+    for (int J = 0; J < 3; ++J)
+#pragma unroll
+      for (int L = 0; L < 3; ++L)
+        C[J][L] = (float)(AC[J][0] * p.A[3 * L] + AC[J][1] * p.A[3 * L + 1] + AC[J][2] * p.A[3 * L + 2]);
+  }
   D[0] += C[0][0];
   D[1] += C[1][1];
   D[2] += C[2][2];
@@ -463,7 +487,7 @@ __global__ __launch_bounds__(NT) void k_level_diag(EbeArgs a, float* __restrict_
   const int l = threadIdx.x & 63, wv = wave_id();
   const int64_t n_elem = (int64_t)a.m.nx * a.m.ny * a.m.nz;
   const int64_t e0 = (int64_t)blockIdx.x * NE;
-  EbePoint p;
+  EbePoint<GEO> p;
   ebe_point<PF, GEO>(a, tabs, p);
   {
     const MatParams<float> mp = a.mats[p.pidc];
@@ -474,10 +498,10 @@ __global__ __launch_bounds__(NT) void k_level_diag(EbeArgs a, float* __restrict_
     float hphi;
     {
       TangentFactors tf;
-      ebe_layer<PF, GEO>(a, p, 0, tf, blk);
-      tangent_diagonal<0>(tf, D);
-      tangent_diagonal<1>(tf, D + 6);
-      tangent_diagonal<2>(tf, D + 12);
+      ebe_layer<PF, GEO, false>(a, p, 0, tf, blk);
+      tangent_diagonal<0>(tf, p, D);
+      tangent_diagonal<1>(tf, p, D + 6);
+      tangent_diagonal<2>(tf, p, D + 12);
       hphi = tf.hphi;
     }
     if (MB) {
@@ -485,10 +509,10 @@ __global__ __launch_bounds__(NT) void k_level_diag(EbeArgs a, float* __restrict_
       for (int j = 0; j < a.n_extra; ++j) {
         TangentFactors tf;
         EbeBlock bj;
-        if (ebe_layer<PF, GEO>(a, p, 1 + j, tf, bj)) {
-          tangent_diagonal<0>(tf, D);
-          tangent_diagonal<1>(tf, D + 6);
-          tangent_diagonal<2>(tf, D + 12);
+        if (ebe_layer<PF, GEO, false>(a, p, 1 + j, tf, bj)) {
+          tangent_diagonal<0>(tf, p, D);
+          tangent_diagonal<1>(tf, p, D + 6);
+          tangent_diagonal<2>(tf, p, D + 12);
           hphi += tf.hphi;
         }
       }
@@ -496,14 +520,13 @@ __global__ __launch_bounds__(NT) void k_level_diag(EbeArgs a, float* __restrict_
     if (p.el < NE) {
       float* my = lds + p.el * ES + (p.qz * Q + p.qy) * Q + p.qx;
       const float kfg = p.w * a.fr.kf * mp.Gc;
-      const float* A = p.A;
 #pragma unroll
       for (int k = 0; k < 18; ++k) my[k * NE * ES] = p.w * D[k];
       my[18 * NE * ES] = p.w * a.fr.s_phi * (blk.dLc + (blk.hact ? blk.gp * hphi : 0.f));
 #pragma unroll
       for (int k = 0; k < NPHI - 1; ++k) {
         const int J = k < 3 ? k : (k == 5 ? 1 : 0), L = k < 3 ? k : (k == 3 ? 1 : 2);
-        my[(19 + k) * NE * ES] = (k < 3 ? kfg : 2.f * kfg) * (A[3 * J] * A[3 * L] + A[3 * J + 1] * A[3 * L + 1] + A[3 * J + 2] * A[3 * L + 2]);
+        my[(19 + k) * NE * ES] = (k < 3 ? kfg : 2.f * kfg) * p.metric(J, L);
       }
     }
   }
