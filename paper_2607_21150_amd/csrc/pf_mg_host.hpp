@@ -159,12 +159,16 @@ pf_status mg_alloc_levels(pf_ctx* c, const int* orders, int nl) {
       }
     }
   }
-  // the order-1 level on the mesh itself: block stencil, from element matrices (the levels'
-  // element diagonals, at most 4 (p + 1)^3 values per element, use the same buffer)
-  for (int l = 0; l < nl && mg.ebe_level < 0; ++l)
-    if (mg.lv[l].p == 1) mg.ebe_level = l;
+  // the order-1 level on the mesh itself: block stencil, from element matrices; the element diagonals of
+  // the levels above it, 4 (order + 1)^3 values, use the same buffer
+  size_t ebe = 0;
+  for (int l = 0; l < nl && mg.ebe_level < 0; ++l) {
+    const MGLevel& L = mg.lv[l];
+    ebe = std::max(ebe, L.p == 1 ? (size_t)1024 : (size_t)4 * L.P * L.P * L.P);
+    if (L.p == 1) mg.ebe_level = l;
+  }
   const int64_t n_elem = (int64_t)N[0] * N[1] * N[2];
-  if (hipMalloc(&mg.ebe, (size_t)n_elem * 1024 * sizeof(float)) != hipSuccess ||
+  if (hipMalloc(&mg.ebe, n_elem * ebe * sizeof(float)) != hipSuccess ||
       (mg.ebe_level >= 0 &&
        hipMalloc(&mg.stencil, (size_t)stencil_size(mg.lv[mg.ebe_level].n_nodes) * sizeof(float)) != hipSuccess))
     return fail(PF_ENOMEM, "coarse element matrices: allocation failed");
