@@ -5,7 +5,8 @@
 namespace {
 
 constexpr int VEC_BLOCKS = 2048;
-constexpr int RED_PARTS = 2048;  // block partials of a reduction (VEC_BLOCKS, or four fields' EPI_BLOCKS)
+constexpr int EPI_BLOCKS = 512;              // workgroups per field of a launch with partial sums (E_POWER)
+constexpr int RED_PARTS = 4 * EPI_BLOCKS;    // their partial sums, one per workgroup and field
 
 inline int vec_grid(int64_t n) {
   const int64_t b = (n + NT - 1) / NT;
@@ -239,9 +240,7 @@ A32Args a32_args(pf_ctx* c, int level, const float* dz) {
   return a;
 }
 
-// Rows of the node gather in flight: E_POWER leaves one partial sum per workgroup, EPI_BLOCKS of
-// them per field.
-constexpr int EPI_BLOCKS = 512;
+// Workgroups of a launch with an epilogue: E_POWER leaves one partial sum per workgroup.
 template <int OP>
 int epi_blocks(int64_t blocks, int most) {
   return (int)std::min<int64_t>(blocks, OP == E_POWER ? EPI_BLOCKS : most);
