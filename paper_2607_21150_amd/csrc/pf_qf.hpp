@@ -75,11 +75,13 @@ __device__ inline double kst(double c) {
 
 // exp(x), the argument reduced by multiples of ln 2 to |r| <= 0.35 and the Taylor sum to r^13
 // (truncation below 1e-17); below exp(-1000) it is 0. One exponential per Voce evaluation.
+// ln 2 in two parts (Cody and Waite's reduction): its first 42 bits, so that the product with n <= 1443
+// is exact, and the rest.
 __device__ inline double exp_taylor(double x) {
   x = fmax(x, kst(-1000.0));
   const double n = rint(x * kst(1.44269504088896340736));
-  double r = fma(n, kst(-6.93147180369123816490e-01), x);
-  r = fma(n, kst(-1.90821492927058770002e-10), r);
+  double r = fma(n, kst(-0x1.62e42fefa3800p-1), x);
+  r = fma(n, kst(-0x1.ef35793c76730p-45), r);
   double p = kst(1.0 / 6227020800.0);
   p = fma(p, r, kst(1.0 / 479001600.0));
   p = fma(p, r, kst(1.0 / 39916800.0));
