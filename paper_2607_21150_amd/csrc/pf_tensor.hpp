@@ -112,7 +112,7 @@ constexpr float LOG_RATIO[2][LOG_RULES] = {{1.72f, 5.4f, 21.9f, 74.f, 245.f, 218
                                            {1.45f, 4.2f, 16.f, 53.f, 155.f, 1250.f}};
 // Ratio beyond which K is taken from F^-1 and I + D: adj(I + S) from S holds K's small entries with the rounding
 // of its large terms, which p1 multiplies by the ratio.
-constexpr float LOG_WIDE = 4.2f;
+constexpr float LOG_WIDE = 8.f;
 constexpr double LOG_HALF[LOG_FIRST[LOG_RULES]][2] = {
     {0.020138255037087625, 0.026194290990111748},
     {0.11262061675326468, 0.068631810355546441},
@@ -449,12 +449,15 @@ __device__ inline void ts_state(const MatParams<double>& m, const FracParams<dou
   // det F <= 0 or an eigenvalue of b_tr <= 0 (trace, second invariant or determinant <= 0):
   // not physical, the point's values are NaN
   s.bad = !(det > 0.0) || !(t > -1.0);
+  const bool far = !(J2 <= kst(LOG_SERIES_J2));
   bool wide = false;
-  if (J2 <= kst(LOG_SERIES_J2)) {
+  double db = 0.0;  // det b_tr, where formed
+  if (!far) {
     log_series<TAN>(J2, J3, s);
   } else {
+    db = det * det * det_plus_one(st);
     double I2 = 3.0 - J2;
-    const double I3 = det * det * det_plus_one(st) * (im * im * im);
+    const double I3 = db * (im * im * im);
     s.bad |= !(I2 > 0.0) || !(I3 > 0.0);
     if (!s.bad) {
       const LogBounds bd = log_bounds(I2, I3);
@@ -479,11 +482,13 @@ __device__ inline void ts_state(const MatParams<double>& m, const FracParams<dou
   // tr eps = log(det b_tr) / 2: det b_tr = m^3 (1 - J2 + J3) formed about 1 where it is near 1,
   // else, and where the eigenvalues differ widely (J3 - J2 then holds few digits of I3), det F^2 det(I + D)
   const double v = t * fma(t, kst(3.0) + t, kst(3.0)), w = J3 - J2;
-  const double x = wide ? fma(det * det, det_plus_one(st), -1.0) : v + w + v * w;
-  if (fabs(x) <= 0.25)
+  const double x = wide ? db - 1.0 : v + w + v * w;
+  if (fabs(x) <= 0.25) {
     s.theta = half_log1p_near(x);
-  else
-    s.theta = half_log(det * det * det_plus_one(st));
+  } else {
+    if (!far) db = det * det * det_plus_one(st);
+    s.theta = half_log(db);
+  }
   return_map<VOCE, MAXW>(m, fr, phi, phin, st, s.ee, s);
 }
 
