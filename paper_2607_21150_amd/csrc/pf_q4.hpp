@@ -833,9 +833,9 @@ __global__ __launch_bounds__(NT, 2) void k_a32_q2r(LinApplyArgs<V> a, const type
 // tasks spread over the workgroup through LDS (no contraction padded from 3 to 4 points).
 // Brick sums to the brick buffer (store_brick4), then k_gather_ext<double, 5>; the
 // adjoint's per-phase parameter partials are summed per brick in a fixed order.
-// Waves per SIMD: the residual's 144 registers make 3, forced to 128 (16 spilled) it runs 4, which the
+// Waves per SIMD: the residual's 144 registers make 3, forced to 128 (8 to 14 spilled) it runs 4, which the
 // 36 KB of LDS allow: 211 -> 196 us on 48^3 elements. The adjoint's 172 make 2, at 168 (8 spilled) it runs
-// 3: 438 -> 346 us. The Jacobian takes 158.
+// 3: 438 -> 346 us. The Jacobian takes 156.
 template <int MODE, bool VOCE>
 __global__ __launch_bounds__(NT, MODE == M_RES ? 4 : 3) void k_op64_q2r(OpArgs a, DevTables* __restrict__ tabs) {
   constexpr int P = 3, Q = 3, Q3 = 27, NE = 8;

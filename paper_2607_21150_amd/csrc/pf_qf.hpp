@@ -8,7 +8,9 @@
 // density, damage viscosity). The Prandtl update uses the degraded trial stress
 // g*q_tr and g*mu (eq:degraded-trial-stress, eq:degraded-yield-condition).
 //
-// Everything is formulated in the principal frame of b_tr (Appendix A): the
+// The FP64 applies take the trial strain and its tangent in tensor form (pf_tensor.hpp) and share
+// the return mapping and the kinematics of this file. The linearisation record, the applies that read
+// it and the state commit work in the principal frame of b_tr (Appendix A): the
 // stress update acts on eigenvalues, and the tangent (Appendices B-C) acts on
 // the rotated perturbation N^T db N, whose off-diagonal part is scaled by the
 // divided difference (tau_i - tau_j)/(b_i - b_j) = g mu c (ln b_i - ln b_j)/(b_i - b_j),

@@ -23,9 +23,9 @@
 // The FP64 applies are bound by VALU issue. The principal form (eigenvalues, an orthonormal
 // frame with polish rotations, three logarithms, divided differences, the tangent rotated
 // there and back) took 1,152 vector instructions per order-3 element in the Jacobian beside its
-// 93 matrix-core ones; this form takes 768, and 168 registers (3 waves per SIMD) instead of
-// 217. Order-3 Jacobian on 48^3 elements 0.465 -> 0.377 ms, with two extra branches on 32^3
-// 0.310 -> 0.237 (18 spilled registers -> none), order 4 on 40^3 0.644 -> 0.576, order 2 on 32^3
+// 93 matrix-core ones; this form takes 721, and 168 registers (3 waves per SIMD, 1 or 2 spilled) instead of
+// 217. Order-3 Jacobian on 48^3 elements 0.465 -> 0.372 ms, with two extra branches on 32^3
+// 0.310 -> 0.237, order 4 on 40^3 0.644 -> 0.560, order 2 on 32^3
 // 0.097 -> 0.088. The linearisation record and the state commit keep the principal form (their
 // data are principal).
 #pragma once
